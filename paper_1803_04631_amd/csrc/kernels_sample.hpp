@@ -5,8 +5,8 @@
 // index trees, was made for NVIDIA warps; measured here, a whole 64-lane wave per token is
 // bound by VALU issue, not by HBM):
 //   - a workgroup owns one tile = up to 1024 (4096 for large K) consecutive tokens of ONE
-//     word and stages that word's p*(k) (Eq. 8) once in LDS as fp32, with fp64 prefix sums
-//     over groups of 4 (or 16) topics (Section 6.1.2: samplers of a block share the word's data);
+//     word and stages that word's p*(k) (Eq. 8, rounded to fp32) once in LDS, widened to fp64 where
+//     K <= 2048, with fp64 prefix sums over groups of 4 (or 16) topics (Section 6.1.2: samplers of a block share the word's data);
 //     for large K, the many words of few tokens are taken in runs by one workgroup, which turns
 //     p* of one word into p* of the next; where K is too large for p* to fit the LDS at all, it
 //     is staged in a strip of device memory that the workgroup owns, and read from there;
@@ -30,10 +30,10 @@
 //     results travel between the per-lane and per-group phases through small per-wave LDS
 //     records;
 //   - a theta row is a run of entries (topic, count) in ascending topic order, 2 bytes each
-//     when K < 1024 (10 bits of topic, 4 of count), else 4 bytes (16 bits of topic, 14 of
-//     count); a count too large for its field is written as several entries of the same
-//     topic, one after the other, which changes no sum.  Only the first entry of the token's
-//     own topic gives up the token itself;
+//     where K <= 2048 (13 bits of topic, 3 of count; 4 bytes for long documents over few topics),
+//     else 4 bytes (16 bits of topic, 14 of count); a count too large for its field is written
+//     as several entries of the same topic, one after the other, which changes no sum.  Only
+//     the first entry of the token's own topic gives up the token itself;
 //   - the row walk is a chain of dependent loads (record, then a random row in HBM), so the
 //     loads of the next pass are issued before the current pass is worked on.
 #pragma once
@@ -100,23 +100,27 @@ struct __align__(16) TokenRec { // per-lane phase -> per-group phase, 32 bytes
     uint32_t off;               // slot offset of the token's theta row, 16-byte units
     int32_t nnz;                // 16-byte units of entries of the row
     int32_t o;                  // current topic
-    float w_o;                  // p*(o) with the token itself removed
+    float w_o;                  // p*(o) with the token itself removed, times kSumScale where p* is fp64
     double u;
-    double Qp;                  // alpha * sum_k p*'(k)
+    double Qp;                  // alpha * sum_k p*'(k), scaled the same
 };
 constexpr int kDrawInUnit = -1; // off = the 16-byte unit of the slot buffer that holds the draw,
                                 // u = what is left of the draw at the unit's start
 constexpr int kDrawDense = -2;  // the draw falls into the dense bucket p2; u = its position there
 constexpr int kDrawTopic = -3;  // off = the new topic itself
 
+// p* of the tile's word is staged as fp64 in the workgroups of four waves (K <= 2048), as fp32 in
+// those of twelve, where fp64 would cost a CU its second workgroup.
+__host__ __device__ constexpr int weight_bytes(int waves) { return waves == 4 ? 8 : 4; }
+
 // LDS bytes of sample_kernel<kWaves> for a given Kpad.
 __host__ __device__ constexpr size_t sample_lds_bytes(int Kpad, int waves) {
-    return (size_t)Kpad * 4 + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 +
+    return (size_t)Kpad * weight_bytes(waves) + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 +
            (size_t)waves * kWave * sizeof(TokenRec);
 }
 // The same when p* stays in device memory: the prefix sums and the waves' records only.
 __host__ __device__ constexpr size_t sample_far_lds_bytes(int Kpad, int waves) {
-    return sample_lds_bytes(Kpad, waves) - (size_t)Kpad * 4;
+    return sample_lds_bytes(Kpad, waves) - (size_t)Kpad * weight_bytes(waves);
 }
 // What runs of small tiles keep in LDS besides: the groups' own sums (the prefix sums are made
 // from them again after every change) and one bit per group for "changed".
@@ -126,11 +130,24 @@ __host__ __device__ constexpr size_t sample_run_lds_bytes(int Kpad, int waves) {
 }
 constexpr int kRunTileTokens = 1024;    // a tile of a run holds a whole word of at most this many tokens
 
+// A count becomes a factor without a conversion: its bits, taken as the upper dword of a double
+// whose lower dword is zero, are the denormal number count * kCountUnit.  The weights staged in
+// LDS carry kWeightScale, so a product (exact, as before) is count * p* * kSumScale: powers of two
+// that change no rounding anywhere.  p* < 1, hence a weight stays finite; p* > 2^-60 or so, hence
+// no product comes near the denormal numbers again.
+constexpr double kWeightScale = 0x1p1000;
+constexpr double kCountUnit = 0x1p-1042;
+constexpr double kSumScale = 0x1p-42;
+
+// A staged weight of either form without its scale.
+__device__ __forceinline__ double plain_weight(float w) { return (double)w; }
+__device__ __forceinline__ double plain_weight(double w) { return w * (1.0 / kWeightScale); }
+
 // Dense bucket (p2 = alpha p*', Eq. 6): smallest k with alpha * prefix'(k) > y, where
 // prefix' is the prefix sum of p* with the entry of the token's own topic o replaced by
 // w_o (delta = w_o - p*(o)).  One lane per token.
-template <int kGroup>
-__device__ __forceinline__ int dense_bucket_search(const float* pstar, const double* cp, int K,
+template <int kGroup, class Weight>
+__device__ __forceinline__ int dense_bucket_search(const Weight* pstar, const double* cp, int K,
                                                    int ng, double alpha, double y, int o,
                                                    float w_o, double delta) {
     // Bisection with steps of falling powers of two: `lo` counts the groups known to lie
@@ -150,10 +167,9 @@ __device__ __forceinline__ int dense_bucket_search(const float* pstar, const dou
     const double before = (lo > 0 ? cp[lo - 1] : 0.0) + (k0 > o ? delta : 0.0);
     if (kGroup == 4) {
         // the four topics of group `lo`, taken in one read (p* beyond K is 0 and adds nothing)
-        const float4 w = *reinterpret_cast<const float4*>(pstar + k0);
-        const double a0 = before + (double)(k0 == o ? w_o : w.x);
-        const double a1 = a0 + (double)(k0 + 1 == o ? w_o : w.y);
-        const double a2 = a1 + (double)(k0 + 2 == o ? w_o : w.z);
+        const double a0 = before + (k0 == o ? (double)w_o : plain_weight(pstar[k0]));
+        const double a1 = a0 + (k0 + 1 == o ? (double)w_o : plain_weight(pstar[k0 + 1]));
+        const double a2 = a1 + (k0 + 2 == o ? (double)w_o : plain_weight(pstar[k0 + 2]));
         int found = k0 + 3;
         if (alpha * a2 > y) found = k0 + 2;
         if (alpha * a1 > y) found = k0 + 1;
@@ -165,7 +181,7 @@ __device__ __forceinline__ int dense_bucket_search(const float* pstar, const dou
     for (int j = 0; j < kGroup; ++j) {
         const int k = k0 + j;
         if (k >= K) break;
-        acc += (double)((k == o) ? w_o : pstar[k]);
+        acc += (k == o) ? (double)w_o : plain_weight(pstar[k]);
         if (alpha * acc > y) { found = k; break; }
     }
     return found;
@@ -227,15 +243,15 @@ __device__ __forceinline__ int group_previous_int(int v) {
 // ---------------------------------------------------------------- theta row layouts
 // A row's entries follow its 16-byte header in ascending topic order and are read in units of
 // 16 bytes.  A count beyond an entry's field is spread over several entries of the same topic.
-// key = 4 * topic = the byte offset of p*(topic) in LDS.
+// key = the byte offset of p*(topic).
 
-// 4 bytes per entry: count << 18 | topic << 2.  Any K.
+// 4 bytes per entry: count << 18 | topic << 2.  Any K; p* in fp32.
 struct PackedRows {
     typedef uint32_t Entry;
     static constexpr int kEntryBytes = 4, kUnitEntries = 4;
     static constexpr int kMaxCount = (1 << 14) - 1;
     static constexpr int kWavesPerSimd = 6;
-    static constexpr bool kOneEntryPerTopic = false;
+    static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = false;
     static __host__ __device__ __forceinline__ Entry make(int count, int topic) {
         return ((uint32_t)count << 18) | ((uint32_t)topic << 2);
     }
@@ -244,6 +260,7 @@ struct PackedRows {
     static __device__ __forceinline__ uint32_t word(const uint4& u, int j) {
         return j == 0 ? u.x : j == 1 ? u.y : j == 2 ? u.z : u.w;
     }
+    static __device__ __forceinline__ int key_of_topic(int k) { return k << 2; }
     static __device__ __forceinline__ int key(const uint4& u, int j) { return (int)(word(u, j) & 0x3fffcu); }
     static __device__ __forceinline__ int count(const uint4& u, int j) { return (int)(word(u, j) >> 18); }
 };
@@ -255,29 +272,102 @@ struct PackedRowsShort : PackedRows {
     static constexpr bool kOneEntryPerTopic = true;
 };
 
-// 2 bytes per entry: count << 12 | topic << 2 (ten bits of topic, four of count).  K < 1024.
+// The two layouts of K <= 2048, whose p* is staged in fp64.  An entry holds its topic above its
+// count: entries of a row rise as numbers, and "entry - (o, 0)", as an unsigned number, is at most
+// kMaxCount for the entries of topic o only, and is their count.
+//
+// 2 bytes per entry: topic << 3 | count (13 bits of topic, 3 of count).
 struct TinyRows {
     typedef uint16_t Entry;
     static constexpr int kEntryBytes = 2, kUnitEntries = 8;
-    static constexpr int kMaxCount = 15;
-    static constexpr int kMaxK = 1023;          // topics 0 .. K, K being the padding entries'
+    static constexpr int kMaxCount = 7;
     static constexpr int kWavesPerSimd = 5;
-    static constexpr bool kOneEntryPerTopic = false;
+    static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = true;
+    typedef uint16_t Pair __attribute__((ext_vector_type(2)));
     static __host__ __device__ __forceinline__ Entry make(int count, int topic) {
-        return (Entry)(((uint32_t)count << 12) | ((uint32_t)topic << 2));
+        return (Entry)(((uint32_t)topic << 3) | (uint32_t)count);
     }
-    static __host__ __device__ __forceinline__ int entry_topic(Entry e) { return (int)((e >> 2) & 0x3ffu); }
-    static __host__ __device__ __forceinline__ int entry_count(Entry e) { return (int)(e >> 12); }
-    static __device__ __forceinline__ uint32_t word(const uint4& u, int j) {
-        return (j >> 1) == 0 ? u.x : (j >> 1) == 1 ? u.y : (j >> 1) == 2 ? u.z : u.w;
+    static __host__ __device__ __forceinline__ int entry_topic(Entry e) { return (int)(e >> 3); }
+    static __host__ __device__ __forceinline__ int entry_count(Entry e) { return (int)(e & 7u); }
+    static __device__ __forceinline__ uint32_t word(const uint4& u, int i) {
+        return i == 0 ? u.x : i == 1 ? u.y : i == 2 ? u.z : u.w;
     }
+    static __device__ __forceinline__ int key_of_topic(int k) { return k << 3; }
     static __device__ __forceinline__ int key(const uint4& u, int j) {
-        const uint32_t d = word(u, j);
-        return (j & 1) ? (int)__builtin_amdgcn_ubfe(d, 16, 12) : (int)(d & 0xffcu);
+        const uint32_t d = word(u, j >> 1);
+        if ((j & 1) == 0) return (int)(d & 0xfff8u);
+        uint32_t k;                 // the upper half, masked: one instruction
+        asm("v_and_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD"
+            : "=v"(k) : "v"(d), "s"(0xfff8u));
+        return (int)k;
     }
     static __device__ __forceinline__ int count(const uint4& u, int j) {
-        const uint32_t d = word(u, j);
-        return (j & 1) ? (int)(d >> 28) : (int)__builtin_amdgcn_ubfe(d, 12, 4);
+        const uint32_t d = word(u, j >> 1);
+        return (j & 1) ? (int)__builtin_amdgcn_ubfe(d, 16, 3) : (int)(d & 7u);
+    }
+    // the tokens of topic o in a unit: of the differences to (o, 0), 8 or more counts nothing
+    static __device__ __forceinline__ uint32_t tokens_of(const uint4& u, int o) {
+        const Pair own = Pair((uint16_t)make(0, o)), none = Pair(8), one = Pair(1);
+        uint32_t n = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const Pair x = __builtin_elementwise_min(__builtin_bit_cast(Pair, word(u, i)) - own, none);
+            n = __builtin_amdgcn_udot2(__builtin_bit_cast(Pair, __builtin_bit_cast(uint32_t, x) & 0x00070007u), one, n, false);
+        }
+        return n;
+    }
+    // acc += count * weight over the eight entries, in their order
+    static __device__ __forceinline__ void add_products(const uint4& u, const double* w, double& acc) {
+        add_four(u.x, u.y, w, acc);
+        add_four(u.z, u.w, w + 4, acc);
+    }
+    static __device__ __forceinline__ void add_four(uint32_t d0, uint32_t d1, const double* w, double& acc) {
+        asm("v_mov_b32 v72, 0\n\tv_mov_b32 v74, 0\n\t"
+            "v_and_b32 v73, 7, %1\n\tv_bfe_u32 v75, %1, 16, 3\n\t"
+            "v_fma_f64 %0, v[72:73], %3, %0\n\tv_and_b32 v73, 7, %2\n\t"
+            "v_fma_f64 %0, v[74:75], %4, %0\n\tv_bfe_u32 v75, %2, 16, 3\n\t"
+            "v_fma_f64 %0, v[72:73], %5, %0\n\t"
+            "v_fma_f64 %0, v[74:75], %6, %0"
+            : "+&v"(acc)
+            : "v"(d0), "v"(d1), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3])
+            : "v72", "v73", "v74", "v75");
+    }
+};
+
+// 4 bytes per entry: topic << 16 | count (13 bits), for long documents over few topics.
+struct CountedRows {
+    typedef uint32_t Entry;
+    static constexpr int kEntryBytes = 4, kUnitEntries = 4;
+    static constexpr int kMaxCount = (1 << 13) - 1;
+    static constexpr int kWavesPerSimd = 5;
+    static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = true;
+    static __host__ __device__ __forceinline__ Entry make(int count, int topic) {
+        return ((uint32_t)topic << 16) | (uint32_t)count;
+    }
+    static __host__ __device__ __forceinline__ int entry_topic(Entry e) { return (int)(e >> 16); }
+    static __host__ __device__ __forceinline__ int entry_count(Entry e) { return (int)(e & 0x1fffu); }
+    static __device__ __forceinline__ uint32_t word(const uint4& u, int j) {
+        return j == 0 ? u.x : j == 1 ? u.y : j == 2 ? u.z : u.w;
+    }
+    static __device__ __forceinline__ int key_of_topic(int k) { return k << 3; }
+    static __device__ __forceinline__ int key(const uint4& u, int j) { return (int)(word(u, j) >> 13); }
+    static __device__ __forceinline__ int count(const uint4& u, int j) { return (int)(word(u, j) & 0x1fffu); }
+    static __device__ __forceinline__ uint32_t tokens_of(const uint4& u, int o) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) n += entry_topic(word(u, j)) == o ? (uint32_t)entry_count(word(u, j)) : 0u;
+        return n;
+    }
+    static __device__ __forceinline__ void add_products(const uint4& u, const double* w, double& acc) {
+        asm("v_mov_b32 v72, 0\n\tv_mov_b32 v74, 0\n\t"
+            "v_and_b32 v73, 0x1fff, %1\n\tv_and_b32 v75, 0x1fff, %2\n\t"
+            "v_fma_f64 %0, v[72:73], %5, %0\n\tv_and_b32 v73, 0x1fff, %3\n\t"
+            "v_fma_f64 %0, v[74:75], %6, %0\n\tv_and_b32 v75, 0x1fff, %4\n\t"
+            "v_fma_f64 %0, v[72:73], %7, %0\n\t"
+            "v_fma_f64 %0, v[74:75], %8, %0"
+            : "+&v"(acc)
+            : "v"(u.x), "v"(u.y), "v"(u.z), "v"(u.w), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3])
+            : "v72", "v73", "v74", "v75");
     }
 };
 
@@ -317,14 +407,18 @@ __device__ __forceinline__ void store_at(void* base, uint32_t byte_offset, T v) 
 template <class Layout>
 __device__ __forceinline__ int key_before_unit(const unsigned char* unit_ptr) {
     typedef typename Layout::Entry Entry;
-    return 4 * Layout::entry_topic(*reinterpret_cast<const Entry*>(unit_ptr - sizeof(Entry)));
+    return Layout::key_of_topic(Layout::entry_topic(*reinterpret_cast<const Entry*>(unit_ptr - sizeof(Entry))));
 }
 
-// p*(k) is staged at the very start of the workgroup's LDS, so a topic's key (4 k) is the
-// LDS address of its weight.
+// p*(k) is staged at the very start of the workgroup's LDS, so a topic's key (4 k, 8 k for fp64)
+// is the LDS address of its weight.
 __device__ __forceinline__ float lds_float_at(uint32_t byte_address) {
     typedef __attribute__((address_space(3))) const float* lds_float_ptr;
     return *(lds_float_ptr)(uintptr_t)byte_address;
+}
+__device__ __forceinline__ double lds_double_at(uint32_t byte_address) {
+    typedef __attribute__((address_space(3))) const double* lds_double_ptr;
+    return *(lds_double_ptr)(uintptr_t)byte_address;
 }
 
 // Where the walk over a row finds p*(k) by the entry's key 4 k: in LDS ...
@@ -539,6 +633,187 @@ __device__ __forceinline__ void row_pass_kept(const Weights& weight_at, TokenRec
     record_dense(rec, sl, d);
 }
 
+// ---- the walk with fp64 weights (kDoubleWeights).  VALU issue bounds the walk (85 % of the SIMDs'
+// cycles on 7.4e8 tokens at K = 1,000), so what counts is instructions per entry.  With fp32
+// weights an entry takes seven: key, count, two conversions to fp64, a comparison with the own
+// topic and a select, fma.  Here it takes three (key, count, fma): all entries are added with
+// p*(o) and their whole count, and what the token's own topic with its n tokens changes,
+// n (w_o - p*(o)) - w_o, is added where its unit ends, by the lane that has the unit.  An 8-byte
+// gather from random places of LDS costs what a 4-byte one does (7.4 cycles per wave and CU).
+// Measured, sampling launch: K = 1,000, 7.4e8 tokens 32.1 -> 29.8 ms; K = 1,537, 6.3e6 tokens
+// 0.61 -> 0.55 ms.  Looking for the own topic in every dword instead: 30.4 ms; finding its unit
+// before the passes, one token per lane: 37.9 ms (two or three more scattered loads per token);
+// four and six waves per SIMD: 32.6 and 30.5 ms.
+
+// What the lane adds at the end of each of its units for the own topic's entries met so far, in
+// a pass in which some token's own topic is spread over several units of a lane: every unit is
+// looked through.
+template <class Layout, int kUnits>
+__device__ __forceinline__ void own_share(const uint4* raw, int o, double delta, double once, double* add) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int c = 0; c < kUnits; ++c) {
+        n += Layout::tokens_of(raw[c], o);
+        add[c] = n > 0 ? fma((double)n, delta, -once) : 0.0;
+    }
+}
+
+// acc += count * weight over the entries of one unit.
+template <class Layout>
+__device__ __forceinline__ void unit_sum_plain(const uint4& raw, double& acc) {
+    double w[Layout::kUnitEntries];
+#pragma unroll
+    for (int j = 0; j < Layout::kUnitEntries; ++j) w[j] = lds_double_at((uint32_t)Layout::key(raw, j));
+    Layout::add_products(raw, w, acc);
+}
+
+template <class Layout, int kLanes, int kUnits>
+__device__ __forceinline__ void row_pass_double(TokenRec* rec, int sl, const uint4* raw, int lane) {
+    const int4 head = *reinterpret_cast<const int4*>(rec);     // off, units, o, w_o
+    const uint32_t off = (uint32_t)head.x;
+    const int own_key = Layout::key_of_topic(head.z), first_unit = sl * kUnits;
+    const double w_o = (double)__int_as_float(head.w);
+    const double delta = fma(lds_double_at((uint32_t)own_key), -kCountUnit, w_o);       // w_o - p*(o)
+    double at_end[kUnits], add[kUnits];
+    double acc = 0.0;
+#pragma unroll
+    for (int c = 0; c < kUnits; ++c) {
+        unit_sum_plain<Layout>(raw[c], acc);
+        at_end[c] = acc;
+    }
+    // The own topic's entries lie in the first unit whose last topic is not below it ...
+    auto first_key = [&](int c) { return Layout::key(raw[c], 0); };
+    auto last_key = [&](int c) { return Layout::key(raw[c], Layout::kUnitEntries - 1); };
+    bool reached[kUnits];
+#pragma unroll
+    for (int c = 0; c < kUnits; ++c) reached[c] = c == kUnits - 1 || last_key(c) >= own_key;
+    uint4 unit_of_own = raw[kUnits - 1];
+#pragma unroll
+    for (int c = kUnits - 2; c >= 0; --c) {
+        unit_of_own.x = reached[c] ? raw[c].x : unit_of_own.x;
+        unit_of_own.y = reached[c] ? raw[c].y : unit_of_own.y;
+        unit_of_own.z = reached[c] ? raw[c].z : unit_of_own.z;
+        unit_of_own.w = reached[c] ? raw[c].w : unit_of_own.w;
+    }
+    const uint32_t n_own = Layout::tokens_of(unit_of_own, head.z);
+    // (the token itself is taken out by the lane that has the topic's first entry: not if the
+    // previous sub-lane's last entry is of the topic too)
+    const int before = group_previous_int<kLanes>(last_key(kUnits - 1));
+    const double once = sl > 0 && before == own_key ? 0.0 : w_o;
+    double share = fma((double)n_own, delta, -once);
+    share = n_own > 0 ? share : 0.0;
+#pragma unroll
+    for (int c = 0; c < kUnits; ++c) add[c] = reached[c] ? share : 0.0;
+    // ... but for a topic spread over entries on both sides of an end between two units of the lane
+    bool spread = false;
+#pragma unroll
+    for (int c = 1; c < kUnits; ++c) spread |= last_key(c - 1) == own_key && first_key(c) == own_key;
+    if (kUnits > 1 && __builtin_expect(__ballot(spread) != 0, 0))
+        own_share<Layout, kUnits>(raw, head.z, delta, once, add);
+#pragma unroll
+    for (int c = 0; c < kUnits; ++c) at_end[c] += add[c];
+    acc = at_end[kUnits - 1];
+    const RowDraw d = row_draw<kLanes>(acc, rec, sl, lane);
+    // first unit whose end exceeds y, and the sum before it
+    int unit = kUnits - 1;
+#pragma unroll
+    for (int c = kUnits - 2; c >= 0; --c)
+        if (at_end[c] > d.y) unit = c;
+    if (__builtin_expect(__ballot(d.hit && !(acc > d.y)) != 0, 0)) {   // rounding left no sum above the draw:
+        asm volatile("");                            // (a branch of its own: it is almost never taken)
+        if (d.hit && !(acc > d.y)) {                 // take the lane's last unit with weight
+            double before_unit = 0.0;
+#pragma unroll
+            for (int c = 0; c < kUnits; ++c) {
+                if (at_end[c] > before_unit) unit = c;
+                before_unit = at_end[c];
+            }
+        }
+    }
+    double base = 0.0;
+#pragma unroll
+    for (int c = 1; c < kUnits; ++c)
+        if (unit >= c) base = at_end[c - 1];
+    if (d.hit) {
+        rec->off = off + 1u + (uint32_t)(first_unit + unit);
+        rec->nnz = kDrawInUnit;
+        rec->u = d.y - base;
+    }
+    record_dense(rec, sl, d);
+}
+
+// The same for rows too long for the kept shapes, one per wave (sub-lane = lane): one walk for
+// the sums, a second one over the hit lane's units.  Lane l owns the units [n l, n (l + 1)).
+template <class Layout>
+__device__ __forceinline__ void row_pass_double_long(const unsigned char* slots, TokenRec* rec, int lane) {
+    const int4 head = *reinterpret_cast<const int4*>(rec);
+    const uint32_t off = (uint32_t)head.x;
+    const int n_units = head.y, n = (n_units + kWave - 1) / kWave, u0 = lane * n;
+    const int own_key = Layout::key_of_topic(head.z);
+    const double w_o = (double)__int_as_float(head.w);
+    const double delta = fma(lds_double_at((uint32_t)own_key), -kCountUnit, w_o);
+    // the entry before the lane's first one (lanes past the row's end have no entries at all)
+    const bool leads = !(u0 < n_units &&
+        key_before_unit<Layout>(slots + ((size_t)off + 1u + (size_t)u0) * 16u) == own_key);
+    uint32_t own = 0;
+    double plain = 0.0;
+    auto next_end = [&](const uint4& raw) {       // the sum at the end of this unit
+        unit_sum_plain<Layout>(raw, plain);
+        own += Layout::tokens_of(raw, head.z);
+        return plain + (own > 0 ? fma((double)own, delta, leads ? -w_o : 0.0) : 0.0);
+    };
+    double acc = 0.0;
+    for (int c = 0; c < n; ++c) acc = next_end(load_unit(slots, off, u0 + c, u0 + c < n_units));
+    const RowDraw d = row_draw<kWave>(acc, rec, lane, lane);
+    if (__ballot(d.hit) != 0) {
+        bool found = false;
+        int unit = 0, last_unit = 0;
+        double base = 0.0, last_base = 0.0, before = 0.0;
+        own = 0;
+        plain = 0.0;
+        for (int c = 0; c < n; ++c) {
+            const double end = next_end(load_unit(slots, off, u0 + c, d.hit && u0 + c < n_units));
+            if (!found && end > d.y) { unit = c; base = before; found = true; }
+            if (end > before) { last_unit = c; last_base = before; }
+            before = end;
+        }
+        if (d.hit) {
+            rec->off = off + 1u + (uint32_t)(u0 + (found ? unit : last_unit));
+            rec->nnz = kDrawInUnit;
+            rec->u = d.y - (found ? base : last_base);
+        }
+    }
+    record_dense(rec, lane, d);
+}
+
+// The entry of one unit that holds the draw y (measured from the unit's start), as
+// topic_in_unit below: the first whose running sum exceeds y, else (rounding) the last one with
+// weight.  One token per lane.
+template <class Layout, bool kNear>
+__device__ __forceinline__ int topic_in_unit_double(const unsigned char* slots, uint32_t unit, int o, float w_o_f,
+                                                    double y) {
+    constexpr int n = Layout::kUnitEntries;
+    const unsigned char* p = kNear ? slots + (size_t)(uint32_t)(unit << 4) : slots + (size_t)unit * 16u;
+    const uint4 raw = *reinterpret_cast<const uint4*>(p);
+    const int own_key = Layout::key_of_topic(o);
+    const double w_o = kWeightScale * ((double)w_o_f * (1.0 / kSumScale));    // with the staged weights' scale
+    bool prev_own = key_before_unit<Layout>(p) == own_key;
+    double acc = 0.0;
+    int found = -1, last = Layout::key(raw, 0);     // keys: the first above y, the last with weight
+#pragma unroll
+    for (int j = 0; j < n; ++j) {
+        const int key = Layout::key(raw, j);
+        const bool own = key == own_key, first = own && !prev_own;
+        prev_own = own;
+        const double before = acc;
+        acc = fma(__hiloint2double(Layout::count(raw, j) - (first ? 1 : 0), 0),
+                  own ? w_o : lds_double_at((uint32_t)key), acc);
+        if (acc > before) last = key;
+        if (found < 0 && acc > y) found = key;
+    }
+    return (found >= 0 ? found : last) >> 3;
+}
+
 // The entry of one unit that holds the draw y (measured from the unit's start): the first
 // whose running sum exceeds y, else (rounding) the last one with weight.  One token per lane.
 template <class Layout, bool kNear, class Weights>
@@ -610,6 +885,8 @@ __device__ __forceinline__ void row_pass_long(const Weights& weight_at, const un
     record_dense(rec, lane, d);
 }
 
+template <int kValue> using Int = std::integral_constant<int, kValue>;
+
 // kFar: K is too large for p* to fit a workgroup's LDS.  p* of the workgroup's tile then lives in
 // the workgroup's own strip of device memory (the prefix sums and the records stay in LDS), and
 // the launch has as many workgroups as there are strips, each taking every grid-th tile.
@@ -623,15 +900,21 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int kGroup = dense_group(kWaves);
     const int K = a.K, Kpad = a.Kpad, ng = Kpad / kGroup;
-    const size_t pstar_lds = kFar ? 0 : (size_t)Kpad * 4;
-    float* pstar = kFar ? a.far_pstar + (size_t)blockIdx.x * (size_t)Kpad : reinterpret_cast<float*>(lds);
+    constexpr bool kDouble = Layout::kDoubleWeights;
+    static_assert(kDouble == (weight_bytes(kWaves) == 8) && !(kDouble && kFar), "LDS is sized by the number of waves");
+    typedef typename std::conditional<kDouble, double, float>::type Weight;
+    // (what a staged weight, and a sum over a row, carry as a factor)
+    constexpr double kStagedScale = kDouble ? kWeightScale : 1.0, kRowScale = kDouble ? kSumScale : 1.0;
+    const size_t pstar_lds = kFar ? 0 : (size_t)Kpad * sizeof(Weight);
+    Weight* pstar = reinterpret_cast<Weight*>(lds);
+    if constexpr (kFar) pstar = a.far_pstar + (size_t)blockIdx.x * (size_t)Kpad;
     double* cp = reinterpret_cast<double*>(lds + pstar_lds);
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);      // wave-uniform, in an SGPR
     unsigned char* wave_base = lds + pstar_lds + (size_t)((ng + 1) & ~1) * 8;
     TokenRec* my_rec = reinterpret_cast<TokenRec*>(wave_base) + wave * kWave;
     typedef typename std::conditional<kFar, FarWeights, LdsWeights>::type Weights;
-    Weights weight_at;
+    [[maybe_unused]] Weights weight_at;
     if constexpr (kFar) weight_at.base = reinterpret_cast<const unsigned char*>(pstar);
 
     // The workgroup's tiles: one, or (large K only) a run of small ones.  What says where the
@@ -719,21 +1002,21 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         for (int k = tid; k < Kpad; k += kWaves * kWave) {
             float w = 0.f;
             if (k < K) w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
-            pstar[k] = w;
+            pstar[k] = (Weight)(kStagedScale * (double)w);
         }
     } else {
         const uint16_t* phi_v = reinterpret_cast<const uint16_t*>(phi_cells) + phi_cell0;
         for (int k = tid; k < Kpad; k += kWaves * kWave) {
             float w = 0.f;
             if (k < K) w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
-            pstar[k] = w;
+            pstar[k] = (Weight)(kStagedScale * (double)w);
         }
     }
     __syncthreads();
     for (int g = tid; g < ng; g += kWaves * kWave) {
         double s = 0.0;
 #pragma unroll
-        for (int j = 0; j < kGroup; ++j) s += (double)pstar[g * kGroup + j];
+        for (int j = 0; j < kGroup; ++j) s += plain_weight(pstar[g * kGroup + j]);
         cp[g] = s;
         if (in_run()) group_sum[g] = s;
     }
@@ -796,9 +1079,10 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             const int32_t phi_own = (int32_t)((own_dword >> ((own_byte & 2u) << 3)) & phi_mask);
             mine.w_o = (float)(((double)(phi_own - 1) + ka->beta) /
                                ((double)(ka->n_k[mine.o] - 1) + ka->beta_V));
-            delta = (double)mine.w_o - (double)pstar[mine.o];
+            delta = (double)mine.w_o - plain_weight(pstar[mine.o]);
+            mine.w_o *= (float)kRowScale;
             // cp[ng - 1] = sum_k p*(k), read from LDS where it is needed; Q = alpha sum (Eq. 7)
-            mine.Qp = ka->alpha * (cp[ng - 1] + delta);
+            mine.Qp = kRowScale * (ka->alpha * (cp[ng - 1] + delta));
         }
         my_rec[lane] = mine;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -834,6 +1118,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             if (!any(over_64_3, t0, 0x1u)) return 9 + any(over_64_2, t0, 0x1u);
             return 11;
         };
+        constexpr int kNoPass = 12;
         auto lanes_log2 = [](int shape) { return (int)((0x666554433222ull >> (4 * shape)) & 0xfull); };
         auto units_of = [](int shape) { return (int)((0x032323232321ull >> (4 * shape)) & 0xfull); };
         // where a pass's rows are, and the loads of the units its lanes keep.  `rec` is the
@@ -872,34 +1157,57 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         auto pass = [&](uint4* mine_raw, uint4* next_raw) {
             const int shape = shape_next, sl = sl_next;
             TokenRec* rec = rec_next;
-            t_next += kWave >> lanes_log2(shape);
+            const int n_tokens = kWave >> lanes_log2(shape);
+            t_next += n_tokens;
             // The request is made whether or not a pass follows (after the batch's last pass
             // every lane loads padding units): the number of loads in flight behind this
             // pass's own is then the same on every path, and the pass waits for its own rows
             // only, not for the first of the following pass's as well.
             const int t_req = min(t_next, kWave - 1);
-            shape_next = shape_at(t_req);
+            shape_next = !kDouble || t_next < n_here ? shape_at(t_req) : kNoPass;
             request(t_req, shape_next, rec_next, sl_next, next_raw, t_next < n_here);
+            // (one walk per layout family; all have the same shapes)
+            auto row_pass = [&](auto lanes, auto units) {
+                if constexpr (kDouble) row_pass_double<Layout, lanes.value, units.value>(rec, sl, mine_raw, lane);
+                else row_pass_kept<Layout, lanes.value, units.value>(weight_at, rec, sl, mine_raw, lane);
+            };
             switch (shape) {
-            case 0: row_pass_kept<Layout, 4, 1>(weight_at, rec, sl, mine_raw, lane); break;
-            case 1: row_pass_kept<Layout, 4, 2>(weight_at, rec, sl, mine_raw, lane); break;
-            case 2: row_pass_kept<Layout, 4, 3>(weight_at, rec, sl, mine_raw, lane); break;
-            case 3: row_pass_kept<Layout, 8, 2>(weight_at, rec, sl, mine_raw, lane); break;
-            case 4: row_pass_kept<Layout, 8, 3>(weight_at, rec, sl, mine_raw, lane); break;
-            case 5: row_pass_kept<Layout, 16, 2>(weight_at, rec, sl, mine_raw, lane); break;
-            case 6: row_pass_kept<Layout, 16, 3>(weight_at, rec, sl, mine_raw, lane); break;
-            case 7: row_pass_kept<Layout, 32, 2>(weight_at, rec, sl, mine_raw, lane); break;
-            case 8: row_pass_kept<Layout, 32, 3>(weight_at, rec, sl, mine_raw, lane); break;
-            case 9: row_pass_kept<Layout, 64, 2>(weight_at, rec, sl, mine_raw, lane); break;
-            case 10: row_pass_kept<Layout, 64, 3>(weight_at, rec, sl, mine_raw, lane); break;
-            default: row_pass_long<Layout>(weight_at, a.slots, rec, lane); break;
+            case 0: row_pass(Int<4>(), Int<1>()); break;
+            case 1: row_pass(Int<4>(), Int<2>()); break;
+            case 2: row_pass(Int<4>(), Int<3>()); break;
+            case 3: row_pass(Int<8>(), Int<2>()); break;
+            case 4: row_pass(Int<8>(), Int<3>()); break;
+            case 5: row_pass(Int<16>(), Int<2>()); break;
+            case 6: row_pass(Int<16>(), Int<3>()); break;
+            case 7: row_pass(Int<32>(), Int<2>()); break;
+            case 8: row_pass(Int<32>(), Int<3>()); break;
+            case 9: row_pass(Int<64>(), Int<2>()); break;
+            case 10: row_pass(Int<64>(), Int<3>()); break;
+            case 11:
+                if constexpr (kDouble) row_pass_double_long<Layout>(a.slots, rec, lane);
+                if constexpr (kDouble) break;
+                [[fallthrough]];
+            default:                // (kDouble: kNoPass)
+                if constexpr (!kDouble) row_pass_long<Layout>(weight_at, a.slots, rec, lane);
+                break;
             }
         };
         uint4 raw_a[kKeptUnits], raw_b[kKeptUnits];
         request(0, shape_next, rec_next, sl_next, raw_a, true);
-        while (t_next < n_here) {
-            pass(raw_a, raw_b);
-            if (t_next < n_here) pass(raw_b, raw_a);
+        if constexpr (kDouble) {
+            // Always in twos, with a pass of nothing after an odd number: a way back to the loop's head
+            // from between the two would make the compiler wait, in front of the first one's request,
+            // for the rows it is about to work on.  (The twelve-wave kernels are 1 % slower with it:
+            // they spill more registers.)
+            do {
+                pass(raw_a, raw_b);
+                pass(raw_b, raw_a);
+            } while (t_next < n_here);
+        } else {
+            while (t_next < n_here) {
+                pass(raw_a, raw_b);
+                if (t_next < n_here) pass(raw_b, raw_a);
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -912,13 +1220,20 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         if (lane < batch && b * batch + lane < tl.count) {
             const TokenRec* rec = &my_rec[lane];
             const int4 head = *reinterpret_cast<const int4*>(rec);     // off, kind, o, w_o
-            const float w_o = __int_as_float(head.w);
             int z_new = head.x;
-            if (head.y == kDrawInUnit)
-                z_new = topic_in_unit<Layout, kNear>(weight_at, a.slots, (uint32_t)head.x, head.z << 2, w_o, rec->u);
-            if (head.y == kDrawDense)
-                z_new = dense_bucket_search<kGroup>(pstar, cp, K, ng, ka->alpha, rec->u, head.z, w_o,
-                                                    (double)w_o - (double)pstar[head.z]);
+            if (head.y == kDrawInUnit) {
+                if constexpr (kDouble)
+                    z_new = topic_in_unit_double<Layout, kNear>(a.slots, (uint32_t)head.x, head.z,
+                                                                __int_as_float(head.w), rec->u);
+                else
+                    z_new = topic_in_unit<Layout, kNear>(weight_at, a.slots, (uint32_t)head.x, head.z << 2,
+                                                         __int_as_float(head.w), rec->u);
+            }
+            if (head.y == kDrawDense) {
+                const float w_o = __int_as_float(head.w) * (float)(1.0 / kRowScale);
+                z_new = dense_bucket_search<kGroup>(pstar, cp, K, ng, ka->alpha, rec->u * (1.0 / kRowScale), head.z,
+                                                    w_o, (double)w_o - plain_weight(pstar[head.z]));
+            }
             store_at<uint16_t>(ka->z_next + tl.begin, (uint32_t)(b * batch + lane) << 1, (uint16_t)z_new);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -55,8 +55,10 @@ constexpr size_t kSlotAlign = 64;     // theta row slot alignment (bytes)
 // (twelve: two such workgroups fill a CU's six waves per SIMD, and their LDS fits twice)
 int sample_waves_for(int32_t K) { return K <= 2048 ? 4 : 12; }
 
-// theta rows with 2-byte entries where the topics fit their ten bits
-bool tiny_rows_for(int32_t K) { return K <= mlda::TinyRows::kMaxK; }
+// How a chunk's theta rows are laid out: 4-byte entries of any K for the workgroups of twelve
+// waves; for those of four (K <= 2048) 2-byte entries, or 4-byte entries with long counts.
+enum class RowKind { packed, tiny, counted };
+
 
 // What the sampler's LDS holds besides p* itself belongs to K as well: Kpad = K + 1 rounded up to
 // a multiple of the dense bucket's group (one zero entry of p* past the last topic: padding
@@ -77,24 +79,26 @@ bool far_weights_for(int32_t K) {
 // short_docs: no document has more tokens than a 4-byte entry counts; near: the theta slots of
 // the chunk end below 4 GiB, so that 32-bit byte offsets reach them
 template <bool kNear>
-const void* sample_kernel_of(int32_t K, bool short_docs) {
+const void* sample_kernel_of(int32_t K, RowKind rows, bool short_docs) {
     if (far_weights_for(K)) return (const void*)mlda::sample_kernel<12, mlda::PackedRows, true, kNear>;
-    if (tiny_rows_for(K)) return (const void*)mlda::sample_kernel<4, mlda::TinyRows, false, kNear>;
-    if (sample_waves_for(K) == 4)
-        return short_docs ? (const void*)mlda::sample_kernel<4, mlda::PackedRowsShort, false, kNear>
-                          : (const void*)mlda::sample_kernel<4, mlda::PackedRows, false, kNear>;
+    if (rows == RowKind::tiny) return (const void*)mlda::sample_kernel<4, mlda::TinyRows, false, kNear>;
+    if (rows == RowKind::counted) return (const void*)mlda::sample_kernel<4, mlda::CountedRows, false, kNear>;
     return short_docs ? (const void*)mlda::sample_kernel<12, mlda::PackedRowsShort, false, kNear>
                       : (const void*)mlda::sample_kernel<12, mlda::PackedRows, false, kNear>;
 }
-const void* sample_kernel_for(int32_t K, bool short_docs, bool near) {
-    return near ? sample_kernel_of<true>(K, short_docs) : sample_kernel_of<false>(K, short_docs);
+const void* sample_kernel_for(int32_t K, RowKind rows, bool short_docs, bool near) {
+    return near ? sample_kernel_of<true>(K, rows, short_docs) : sample_kernel_of<false>(K, rows, short_docs);
 }
 bool slots_near(size_t slots_bytes) { return slots_bytes <= 0xffffffffull; }
-const void* theta_kernel_for(bool tiny, bool wide_counters) {
-    if (tiny) return wide_counters ? (const void*)mlda::theta_rows_kernel<mlda::TinyRows, true>
-                                   : (const void*)mlda::theta_rows_kernel<mlda::TinyRows, false>;
-    return wide_counters ? (const void*)mlda::theta_rows_kernel<mlda::PackedRows, true>
-                         : (const void*)mlda::theta_rows_kernel<mlda::PackedRows, false>;
+template <class Layout>
+const void* theta_kernel_of(bool wide_counters) {
+    return wide_counters ? (const void*)mlda::theta_rows_kernel<Layout, true>
+                         : (const void*)mlda::theta_rows_kernel<Layout, false>;
+}
+const void* theta_kernel_for(RowKind rows, bool wide_counters) {
+    if (rows == RowKind::tiny) return theta_kernel_of<mlda::TinyRows>(wide_counters);
+    if (rows == RowKind::counted) return theta_kernel_of<mlda::CountedRows>(wide_counters);
+    return theta_kernel_of<mlda::PackedRows>(wide_counters);
 }
 constexpr int kMaxTimedIters = 1024;
 constexpr int kRunTiles = 16;           // small tiles a workgroup of the large-K sampler takes one after the other
@@ -117,6 +121,24 @@ constexpr int32_t kHistTopics = 32768; // 32-bit counters of the phi and n_k his
 size_t slot_bytes_for(int64_t n, int32_t K, int entry_bytes, int max_count) {
     const int64_t cap = std::min<int64_t>(n, (int64_t)K + n / max_count);
     return align_up((size_t)mlda::kRowHeader + align_up((size_t)cap * (size_t)entry_bytes, 16), kSlotAlign);
+}
+
+// Layout of the theta rows of D documents.  2-byte entries read half the bytes and, eight to a
+// unit, take fewer passes; but a count above 7 takes several of them, and a row of a long document
+// over few topics becomes several times as long.  What counts is the entries that all tokens'
+// walks meet: 4-byte entries where the 2-byte ones could be more than kTinyGrowth times as many.
+// (311 documents of 30,000 tokens, K = 299: 22.7 ms per sampling launch with rows of 2-byte entries
+// that the widest pass shape does not hold, 1.5 ms with 4-byte ones.)
+constexpr double kTinyGrowth = 1.5;
+RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t K) {
+    if (sample_waves_for(K) != 4) return RowKind::packed;
+    double tiny = 0.0, counted = 0.0;
+    for (int64_t d = 0; d < D; ++d) {
+        const int64_t n = doc_ptr[d + 1] - doc_ptr[d];
+        tiny += (double)n * (double)std::min<int64_t>(n, (int64_t)K + n / mlda::TinyRows::kMaxCount);
+        counted += (double)n * (double)std::min<int64_t>(n, K);
+    }
+    return tiny > kTinyGrowth * counted ? RowKind::counted : RowKind::tiny;
 }
 
 constexpr int kLoglikBlocks = 2048;
@@ -232,7 +254,7 @@ struct HostChunk {
     int64_t d_begin = 0, d_end = 0;
     int64_t tok_begin = 0;              // caller's index of the chunk's first token
     int64_t D = 0, T = 0;
-    bool tiny = false;                  // theta rows as 2-byte entries (K < 1024), else 4-byte
+    RowKind rows = RowKind::packed;     // layout of the theta rows
     bool wide_counters = false;         // some document has 2^16 tokens or more
     bool short_docs = true;             // no document has more tokens than a 4-byte entry counts
     size_t slots_bytes = 0;
@@ -273,13 +295,15 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
 
     int64_t longest_doc = 0;
     for (int64_t d = 0; d < D; ++d) longest_doc = std::max(longest_doc, len_of(d));
-    h.tiny = tiny_rows_for(K);
     // a count never exceeds the document's length: 16-bit counters in the theta rebuild if
     // they hold it
     h.wide_counters = longest_doc >= 65536;
     h.short_docs = longest_doc <= mlda::PackedRows::kMaxCount;
-    const int entry_bytes = h.tiny ? mlda::TinyRows::kEntryBytes : mlda::PackedRows::kEntryBytes;
-    const int max_count = h.tiny ? mlda::TinyRows::kMaxCount : mlda::PackedRows::kMaxCount;
+    h.rows = row_kind_for(doc_ptr_all + d_begin, D, K);
+    const int entry_bytes = h.rows == RowKind::tiny ? mlda::TinyRows::kEntryBytes : mlda::PackedRows::kEntryBytes;
+    const int max_count = h.rows == RowKind::tiny      ? mlda::TinyRows::kMaxCount
+                          : h.rows == RowKind::counted ? mlda::CountedRows::kMaxCount
+                                                       : mlda::PackedRows::kMaxCount;
 
     std::vector<int32_t> doc_order;              // documents by falling length
     std::vector<int64_t> order_tokens;           // tokens before each position of doc_order
@@ -524,7 +548,8 @@ struct mlda_ctx {
     uint2* doc_pairs = nullptr;          // streamed: {slot of the token's document, its topic}, document order
     mlda::DocRec* doc_order = nullptr;   // documents by falling length, as the theta rebuild walks them
     int32_t theta_grid = 0;
-    bool tiny = false, wide_counters = false, short_docs = true;
+    RowKind rows = RowKind::packed;
+    bool wide_counters = false, short_docs = true;
     int32_t* split_words = nullptr;
     uint16_t* z[2] = {nullptr, nullptr}; // word-major assignments
     uint16_t* z_doc = nullptr;           // streamed: the same in document order (in doc_map's place)
@@ -593,7 +618,7 @@ int blocks_for(int64_t n, int per) { return (int)((n + per - 1) / per); }
 void point_at(mlda_ctx* c, const HostChunk& h, unsigned char* base) {
     c->at = &h;
     c->D = h.D; c->T = h.T;
-    c->tiny = h.tiny;
+    c->rows = h.rows;
     c->wide_counters = h.wide_counters;
     c->short_docs = h.short_docs;
     c->slots_bytes = h.slots_bytes;
@@ -642,8 +667,9 @@ void derive_chunk_arrays(mlda_ctx* c) {
         hipLaunchKernelGGL(mlda::sort_doc_map_kernel, dim3((unsigned)grid), dim3(mlda::kWave), 0, c->stream,
                            c->doc_order, c->D, c->doc_map);
     }
-    const uint32_t pad = c->tiny ? (uint32_t)mlda::TinyRows::make(0, c->K) * 0x10001u
-                                 : (uint32_t)mlda::PackedRows::make(0, c->K);
+    const uint32_t pad = c->rows == RowKind::tiny      ? (uint32_t)mlda::TinyRows::make(0, c->K) * 0x10001u
+                         : c->rows == RowKind::counted ? (uint32_t)mlda::CountedRows::make(0, c->K)
+                                                       : (uint32_t)mlda::PackedRows::make(0, c->K);
     static_assert(kSlotAlign >= (mlda::kKeptUnits + 1) * 16, "the padding units lie before the first slot");
     hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(1), dim3(256), 0, c->stream, (int32_t*)c->slots,
                        (int64_t)(kSlotAlign / 4), (int32_t)pad);
@@ -792,8 +818,9 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
         // two documents per wave where a half-wave suits them: few topics, short documents
         const bool pairs = c->K <= kPairMaxK && !c->wide_counters && c->T <= 160 * c->D;
         const void* kernel =
-            pairs ? (c->tiny ? (const void*)theta_rows_pair_kernel<TinyRows> : (const void*)theta_rows_pair_kernel<PackedRows>)
-                  : theta_kernel_for(c->tiny, c->wide_counters);
+            !pairs                      ? theta_kernel_for(c->rows, c->wide_counters)
+            : c->rows == RowKind::tiny ? (const void*)theta_rows_pair_kernel<TinyRows>
+                                       : (const void*)theta_rows_pair_kernel<CountedRows>;
         const size_t lds = pairs ? theta_pair_lds_bytes(c->K) : theta_lds;
         const DocRec* docs = c->doc_order;
         uint2* row_rec = c->row_rec;
@@ -836,7 +863,8 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     const int32_t grid = c->far_weights ? std::min<int32_t>(a.n_tiles, kFarStrips)
                                         : a.n_single + (a.n_tiles - a.n_single + a.run_tiles - 1) / a.run_tiles;
     void* kernel_args[] = {&a};
-    HIP_TRY(hipLaunchKernel(sample_kernel_for(c->K, c->short_docs, slots_near(c->slots_bytes) && !c->wide_slot_offsets),
+    HIP_TRY(hipLaunchKernel(sample_kernel_for(c->K, c->rows, c->short_docs,
+                                              slots_near(c->slots_bytes) && !c->wide_slot_offsets),
                             dim3((unsigned)grid),
                             dim3((unsigned)(waves * mlda::kWave)), kernel_args, c->sample_lds, c->stream));
     return launch_check("sample_kernel");
@@ -962,12 +990,12 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(blocks_for(dwords, 256)), dim3(256), 0, c->stream,
                        (int32_t*)c->phi[0].narrow, dwords, 0);
     RC_TRY(launch_check("model set-up kernels"));
-    if (c->sample_lds > 48 * 1024)
+    if (c->sample_lds > 48 * 1024)          // (the workgroups of twelve waves only)
         for (bool short_docs : {false, true})
             for (bool near : {false, true})
                 // (the attribute belongs to the kernel, not to this context: contexts of different
                 // needs may live side by side, so it is raised to what the device allows)
-                HIP_TRY(hipFuncSetAttribute(sample_kernel_for(c->K, short_docs, near),
+                HIP_TRY(hipFuncSetAttribute(sample_kernel_for(c->K, RowKind::packed, short_docs, near),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit));
     if ((size_t)c->K * 4 > 48 * 1024) {
         const int hist_bytes = std::min<int32_t>(c->K, kHistTopics) * 4;
@@ -976,10 +1004,10 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
                                    (const void*)mlda::topic_totals_kernel<true>})
             HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, hist_bytes));
     }
-    for (bool wide : {false, true})
+    for (bool wide : {false, true})         // (large K only: 4-byte rows of any K)
         if (mlda::theta_lds_bytes(c->K, wide) > 48 * 1024 &&
             mlda::theta_lds_bytes(c->K, wide) <= (size_t)c->lds_limit)      // (else see check_theta_lds)
-            HIP_TRY(hipFuncSetAttribute(theta_kernel_for(tiny_rows_for(c->K), wide),
+            HIP_TRY(hipFuncSetAttribute(theta_kernel_for(RowKind::packed, wide),
                                         hipFuncAttributeMaxDynamicSharedMemorySize,
                                         (int)mlda::theta_lds_bytes(c->K, wide)));
     return MLDA_OK;
@@ -1142,7 +1170,8 @@ void unpack_rows_as(const mlda_ctx* c, const std::vector<uint2>& rec, const std:
 
 void unpack_rows(const mlda_ctx* c, const std::vector<uint2>& rec, const std::vector<unsigned char>& slots,
                  const int64_t* row_ptr, uint16_t* topics, int32_t* counts) {
-    if (c->tiny) unpack_rows_as<mlda::TinyRows>(c, rec, slots, row_ptr, topics, counts);
+    if (c->rows == RowKind::tiny) unpack_rows_as<mlda::TinyRows>(c, rec, slots, row_ptr, topics, counts);
+    else if (c->rows == RowKind::counted) unpack_rows_as<mlda::CountedRows>(c, rec, slots, row_ptr, topics, counts);
     else unpack_rows_as<mlda::PackedRows>(c, rec, slots, row_ptr, topics, counts);
 }
 
@@ -1684,7 +1713,7 @@ int mlda_get_sampler_bytes(mlda_ctx* c, double* bytes, int32_t capacity_iters, i
     HIP_TRY(hipMemcpyAsync(ring.data(), c->row_entries, (size_t)kEntryRing * 8, hipMemcpyDeviceToHost,
                            c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    const double entry_bytes = tiny_rows_for(c->K) ? 2.0 : 4.0;
+    const double entry_bytes = c->K < 1024 ? 2.0 : 4.0;     // of the nominal entries the rebuild counts
     if (c->streamed) {          // per iteration the sum over its chunk visits
         const int32_t m = std::min(c->timed_iters, capacity_iters), first = c->timed_iters - m;
         for (int32_t i = 0; i < m; ++i) bytes[i] = 0.0;

@@ -136,6 +136,39 @@ EDGE_CASES = [
 ]
 
 
+# Where the layouts of a theta row meet: (name, D, V, K, mean length).  Up to K = 2048 a row has 2-byte
+# entries with counts up to 7, or 4-byte entries with counts up to 8,191 where the 2-byte ones could
+# be more than 1.5 times as many.
+LAYOUT_CASES = [
+    ("tiny_many_splits",       60, 80,   24,   55),     # nearly every topic above 7 tokens, runs across units
+    ("tiny_runs_across_lanes", 25, 120,  200,  700),    # eight and more lanes to a row
+    ("counted_from_here",      60, 80,   24,   110),
+    ("counted_splits",         2,  60,   2,    30000),  # counts beyond 8,191
+    ("counted_wide_counters",  2,  60,   5,    70000),  # 2^16 tokens in a document
+    ("k_one",                  20, 30,   1,    40),
+    ("k_largest_fp64",         25, 200,  2048, 300),
+    ("k_first_fp32",           25, 200,  2049, 300),
+    ("tiny_longest_rows",      4,  300,  2048, 2500),   # beyond the widest pass shape
+]
+
+
+@pytest.mark.parametrize("wide_offsets", ["0", "1"])
+@pytest.mark.parametrize("case", LAYOUT_CASES, ids=[c[0] for c in LAYOUT_CASES])
+def test_row_layouts(mlda, case, wide_offsets, monkeypatch):
+    monkeypatch.setenv("MLDA_WIDE_SLOT_OFFSETS", wide_offsets)
+    name, D, V, K, mean_len = case
+    c = corpus_synth.tiny(D=D, V=V, K=K, mean_len=mean_len, seed=len(name), name=name)
+    alpha, beta = 50.0 / K, 0.01
+    say(name, "T", c.T)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, beta, SEED)
+    model.init_random()
+    z = oracle.init_topics(c.T, K, SEED)
+    assert np.array_equal(model.assignments(), z)
+    for it in (1, 2, 3):
+        z = check_step(model, c, z, V, K, alpha, beta, SEED, it)
+    model.close()
+
+
 @pytest.mark.parametrize("case", EDGE_CASES, ids=[c[0] for c in EDGE_CASES])
 def test_edge_shapes(mlda, case):
     name, D, V, K, mean_len = case
