@@ -779,6 +779,51 @@ __global__ void to_word_major_kernel(const uint16_t* z_doc, const int32_t* tok_i
     if (pos < T) z_word[pos] = z_doc[(int64_t)tok_id[pos] - first];
 }
 
+// The rows of theta for the caller: the distinct topics of document d (kTopics), or 16 bits of their
+// counts from bit `shift` on, at out[doc_ptr[d] ..].  A document has no more topics than tokens, so the
+// rows of all documents fit a buffer of one 16-bit value per token, each at its tokens' place.
+// One wave per document, persistent; bound by the slots' bytes.  (A state of 2e7 tokens at K = 1,000
+// installed and taken out: 131 ms when the host unpacked the slots entry by entry and all transfers
+// went through pageable memory, 12 ms with this and the pinned pieces of through_ring.)
+template <class Layout, bool kTopics>
+__global__ __launch_bounds__(kWave) void export_rows_kernel(const uint2* row_rec, const int32_t* doc_ptr, int64_t D,
+                                                            const unsigned char* slots, int shift, uint16_t* out) {
+    typedef typename Layout::Entry Entry;
+    const int lane = (int)threadIdx.x;
+    for (int64_t d = blockIdx.x; d < D; d += gridDim.x) {
+        const uint2 rec = row_rec[d];
+        if (rec.y == 0) continue;                       // (the same for the whole wave)
+        const unsigned char* head = slots + (size_t)rec.x * 16u;
+        const int n = (int)*reinterpret_cast<const uint32_t*>(head);
+        const Entry* ent = reinterpret_cast<const Entry*>(head + kRowHeader);
+        uint16_t* row = out + doc_ptr[d];
+        int before = 0;                                 // distinct topics of the entries so far
+        for (int base = 0; base < n; base += kWave) {
+            const int e = base + lane;
+            int topic = -1;
+            bool first = false;
+            if (e < n) {
+                topic = Layout::entry_topic(ent[e]);
+                // (in front of the first entry lies a padding entry, of no topic of the row)
+                first = topic != Layout::entry_topic(ent[e - 1]);
+            }
+            const uint64_t firsts = __ballot(first);
+            if (first) {
+                const int at = before + __popcll(firsts & (((uint64_t)1 << lane) - 1));
+                uint32_t value = (uint32_t)topic;
+                if (!kTopics) {
+                    value = 0;
+                    for (int j = e; j < n && Layout::entry_topic(ent[j]) == topic; ++j)
+                        value += (uint32_t)Layout::entry_count(ent[j]);
+                    value >>= shift;
+                }
+                row[at] = (uint16_t)value;
+            }
+            before += __popcll(firsts);
+        }
+    }
+}
+
 // ------------------------------------------------------------------ log-likelihood kernels
 
 // Word side: sum over all cells of lgG(n_wk + beta) - lgG(beta), plus the topic totals' term.

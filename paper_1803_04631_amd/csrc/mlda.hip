@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -564,6 +565,12 @@ struct mlda_ctx {
     int32_t run_tiles = 1;
     int64_t run_tokens = 0;              // tokens of the tiles taken in runs
 
+    // large transfers between the device and the caller's memory (see through_ring): pinned pieces,
+    // made by the first of them, one per worker thread
+    unsigned char* ring = nullptr;
+    std::vector<hipEvent_t> ring_events;
+    bool ring_failed = false;
+
     int static_device = -1;              // >= 0: the workspace is that device's static array
 };
 
@@ -1110,69 +1117,168 @@ void destroy(mlda_ctx* c) {
         if (c->slot_free[s]) (void)hipEventDestroy(c->slot_free[s]);
     }
     if (c->z_host) (void)hipHostFree(c->z_host);
+    for (hipEvent_t ev : c->ring_events) (void)hipEventDestroy(ev);
+    if (c->ring) (void)hipHostFree(c->ring);
     release_scratch(c);
     delete c;
 }
 
-// Rows of theta of the attached chunk, unpacked into the caller's CSR arrays (documents
-// h.d_begin ..; row_ptr already holds the row starts).
-int fetch_rows(mlda_ctx* c, std::vector<uint2>& rec, std::vector<unsigned char>& slots) {
-    try {
-        rec.resize((size_t)c->D);
-        slots.resize(c->slots_bytes);
-    } catch (const std::bad_alloc&) {
-        return fail(MLDA_ENOMEM, "out of host memory");
+// ---- large transfers.  HIP moves pageable memory through one thread's copy to and from its own
+// pinned buffers: 10 GB/s into fresh pages (1.5 GB of assignments: 140 ms), while the link carries
+// 50.  Here kRingWorkers threads each own a pinned piece of kRingPiece bytes and take every
+// kRingWorkers-th piece of the transfer: the copies queue up on the context's stream, and what a
+// piece needs on the host (a copy, a widening) is done by its thread while the others' are on
+// their way.  From kRingFrom bytes on: below, making the ring (once per context) costs about what
+// it saves.  Ten iterations on 7.4e8 tokens and their assignments fetched: 535 -> 432 ms; five on
+// 9.9e7: 59.5 -> 45.2 ms (first time on a new context 58 -> 45 ms).  A context on the static workspace, and one for which no pinned memory is left,
+// does without.
+constexpr int kRingWorkers = 8;
+constexpr size_t kRingPiece = (size_t)2 << 20;
+constexpr size_t kRingFrom = (size_t)32 << 20;
+
+bool ring_ready(mlda_ctx* c) {
+    if (c->ring) return true;
+    if (c->ring_failed || c->static_device >= 0) return false;
+    c->ring_failed = true;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kRingWorkers * kRingPiece, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
     }
-    if (c->D > 0)
-        HIP_TRY(hipMemcpyAsync(rec.data(), c->row_rec, (size_t)c->D * 8, hipMemcpyDeviceToHost, c->stream));
-    if (c->slots_bytes > 0)
-        HIP_TRY(hipMemcpyAsync(slots.data(), c->slots, c->slots_bytes, hipMemcpyDeviceToHost, c->stream));
+    c->ring = (unsigned char*)p;
+    try { c->ring_events.reserve(kRingWorkers); } catch (const std::bad_alloc&) {}
+    while (c->ring_events.capacity() >= (size_t)kRingWorkers && c->ring_events.size() < (size_t)kRingWorkers) {
+        hipEvent_t ev;
+        if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); break; }
+        c->ring_events.push_back(ev);
+    }
+    if (c->ring_events.size() < (size_t)kRingWorkers) {
+        (void)hipHostFree(c->ring);
+        c->ring = nullptr;
+        return false;
+    }
+    c->ring_failed = false;
+    return true;
+}
+
+// per_piece(pinned piece, event, offset, bytes) -> hipError_t for every piece, on the worker threads.
+template <class F>
+int through_ring(mlda_ctx* c, size_t bytes, F&& per_piece) {
+    int device = 0;
+    HIP_TRY(hipGetDevice(&device));
+    hipError_t first_error[kRingWorkers];
+    for (hipError_t& e : first_error) e = hipSuccess;
+    const bool ran = parallel_chunks(kRingWorkers, [&](int w) {
+        hipError_t e = hipSetDevice(device);
+        for (size_t at = (size_t)w * kRingPiece; e == hipSuccess && at < bytes; at += kRingWorkers * kRingPiece)
+            e = per_piece(c->ring + (size_t)w * kRingPiece, c->ring_events[(size_t)w], at, std::min(kRingPiece, bytes - at));
+        first_error[w] = e;
+    });
+    for (hipError_t e : first_error)
+        if (e != hipSuccess) {
+            (void)hipStreamSynchronize(c->stream);
+            return fail(MLDA_EHIP, std::string("copy between device and host: ") + hipGetErrorString(e));
+        }
+    if (!ran) return fail(MLDA_ENOMEM, "out of host memory");
+    return MLDA_OK;
+}
+
+// Device memory, handed to take(offset, piece, bytes) piece by piece: on several threads at once, or
+// as a whole through `whole`, which then must hold all of it (made here).
+template <class F>
+int fetch_pieces(mlda_ctx* c, const void* dev, size_t bytes, F&& take) {
+    if (bytes == 0) return MLDA_OK;
+    if (bytes >= kRingFrom && ring_ready(c))
+        return through_ring(c, bytes, [&](unsigned char* piece, hipEvent_t ev, size_t at, size_t n) {
+            hipError_t e = hipMemcpyAsync(piece, (const unsigned char*)dev + at, n, hipMemcpyDeviceToHost, c->stream);
+            if (e == hipSuccess) e = hipEventRecord(ev, c->stream);
+            if (e == hipSuccess) e = hipEventSynchronize(ev);
+            if (e == hipSuccess) take(at, (const unsigned char*)piece, n);
+            return e;
+        });
+    std::vector<unsigned char> whole;
+    try { whole.resize(bytes); } catch (const std::bad_alloc&) { return fail(MLDA_ENOMEM, "out of host memory"); }
+    HIP_TRY(hipMemcpyAsync(whole.data(), dev, bytes, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    take(0, (const unsigned char*)whole.data(), bytes);
+    return MLDA_OK;
+}
+
+// Device memory into the caller's, and back; both are done on return.
+int fetch(mlda_ctx* c, void* host, const void* dev, size_t bytes) {
+    if (bytes >= kRingFrom && ring_ready(c))
+        return fetch_pieces(c, dev, bytes, [&](size_t at, const unsigned char* piece, size_t n) {
+            std::memcpy((unsigned char*)host + at, piece, n);
+        });
+    if (bytes > 0) HIP_TRY(hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return MLDA_OK;
+}
+int send(mlda_ctx* c, void* dev, const void* host, size_t bytes) {
+    if (bytes >= kRingFrom && ring_ready(c))
+        return through_ring(c, bytes, [&](unsigned char* piece, hipEvent_t ev, size_t at, size_t n) {
+            std::memcpy(piece, (const unsigned char*)host + at, n);
+            hipError_t e = hipMemcpyAsync((unsigned char*)dev + at, piece, n, hipMemcpyHostToDevice, c->stream);
+            if (e == hipSuccess) e = hipEventRecord(ev, c->stream);
+            if (e == hipSuccess) e = hipEventSynchronize(ev);
+            return e;
+        });
+    if (bytes > 0) HIP_TRY(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return MLDA_OK;
+}
+
+// n values of host memory in parts, side by side where there are enough of them; false: a part
+// could not be run.
+template <class F>
+bool in_parts(int64_t n, F&& part) {
+    const int parts = (int)std::min<int64_t>(kRingWorkers, n / ((int64_t)1 << 22) + 1);
+    const int64_t per = (n + parts - 1) / parts;
+    return parallel_chunks(parts, [&](int p) { part(std::min(n, per * p), std::min(n, per * (p + 1))); });
 }
 
 int fetch_row_rec(mlda_ctx* c, std::vector<uint2>& rec) {
     try { rec.resize((size_t)c->D); } catch (const std::bad_alloc&) {
         return fail(MLDA_ENOMEM, "out of host memory");
     }
-    if (c->D > 0)
-        HIP_TRY(hipMemcpyAsync(rec.data(), c->row_rec, (size_t)c->D * 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return MLDA_OK;
+    return fetch(c, rec.data(), c->row_rec, (size_t)c->D * 8);
 }
 
-// rec[d].y = distinct topics of row d (the length of its CSR row); the slot's header holds the
-// number of entries, of which several in a row may share a topic (a count spread over them).
+// Rows of theta of the attached chunk into the caller's CSR arrays (row_ptr of its documents in
+// place; rec[d].y = distinct topics of row d).  The device lays them out at their tokens' places in
+// the spare assignment buffer, as 16-bit values; the gaps are closed here.
 template <class Layout>
-void unpack_rows_as(const mlda_ctx* c, const std::vector<uint2>& rec, const std::vector<unsigned char>& slots,
-                    const int64_t* row_ptr, uint16_t* topics, int32_t* counts) {
-    typedef typename Layout::Entry Entry;
-    for (int64_t d = 0; d < c->D; ++d) {
-        if (rec[(size_t)d].y == 0) continue;
-        const unsigned char* head = slots.data() + (size_t)rec[(size_t)d].x * 16;
-        uint32_t n_entries;
-        std::memcpy(&n_entries, head, 4);
-        const Entry* ent = reinterpret_cast<const Entry*>(head + mlda::kRowHeader);
-        int64_t at = row_ptr[d] - 1;
-        int last_topic = -1;
-        for (uint32_t j = 0; j < n_entries; ++j) {
-            const int topic = Layout::entry_topic(ent[j]), count = Layout::entry_count(ent[j]);
-            if (topic != last_topic) {
-                ++at;
-                topics[at] = (uint16_t)topic;
-                counts[at] = 0;
-                last_topic = topic;
+int export_rows(mlda_ctx* c, const std::vector<uint2>& rec, const int64_t* row_ptr, uint16_t* topics, int32_t* counts) {
+    uint16_t* spare = c->z[c->cur ^ 1];             // free between steps and chunk visits
+    std::vector<int32_t> doc_ptr;
+    try { doc_ptr.resize((size_t)c->D + 1); } catch (const std::bad_alloc&) { return fail(MLDA_ENOMEM, "out of host memory"); }
+    RC_TRY(fetch(c, doc_ptr.data(), c->doc_ptr, ((size_t)c->D + 1) * 4));
+    const dim3 grid((unsigned)std::min<int64_t>(c->D, (int64_t)c->n_cus * 32));
+    // place(row entry, value) for the values of the tokens' places [at, at + n)
+    auto fetch_values = [&](auto&& place) {
+        return fetch_pieces(c, spare, (size_t)c->T * 2, [&](size_t at_byte, const unsigned char* piece, size_t bytes) {
+            const uint16_t* value = (const uint16_t*)piece;
+            const int64_t at = (int64_t)(at_byte / 2), end = at + (int64_t)(bytes / 2);
+            int64_t d = std::upper_bound(doc_ptr.begin(), doc_ptr.end(), (int32_t)at) - doc_ptr.begin() - 1;
+            for (; d < c->D && doc_ptr[(size_t)d] < end; ++d) {
+                const int64_t first = doc_ptr[(size_t)d], last = first + rec[(size_t)d].y;
+                for (int64_t t = std::max(first, at); t < std::min(last, end); ++t)
+                    place(row_ptr[d] + (t - first), value[t - at]);
             }
-            counts[at] += count;
-        }
+        });
+    };
+    hipLaunchKernelGGL((mlda::export_rows_kernel<Layout, true>), grid, dim3(mlda::kWave), 0, c->stream, c->row_rec,
+                       c->doc_ptr, c->D, c->slots, 0, spare);
+    RC_TRY(launch_check("export_rows_kernel"));
+    RC_TRY(fetch_values([&](int64_t i, uint16_t v) { topics[i] = v; }));
+    for (int shift = 0; shift == 0 || (c->wide_counters && shift == 16); shift += 16) {
+        hipLaunchKernelGGL((mlda::export_rows_kernel<Layout, false>), grid, dim3(mlda::kWave), 0, c->stream, c->row_rec,
+                           c->doc_ptr, c->D, c->slots, shift, spare);
+        RC_TRY(launch_check("export_rows_kernel"));
+        if (shift == 0) RC_TRY(fetch_values([&](int64_t i, uint16_t v) { counts[i] = (int32_t)v; }));
+        else RC_TRY(fetch_values([&](int64_t i, uint16_t v) { counts[i] += (int32_t)v << 16; }));
     }
-}
-
-void unpack_rows(const mlda_ctx* c, const std::vector<uint2>& rec, const std::vector<unsigned char>& slots,
-                 const int64_t* row_ptr, uint16_t* topics, int32_t* counts) {
-    if (c->rows == RowKind::tiny) unpack_rows_as<mlda::TinyRows>(c, rec, slots, row_ptr, topics, counts);
-    else if (c->rows == RowKind::counted) unpack_rows_as<mlda::CountedRows>(c, rec, slots, row_ptr, topics, counts);
-    else unpack_rows_as<mlda::PackedRows>(c, rec, slots, row_ptr, topics, counts);
+    return MLDA_OK;
 }
 
 // Streamed: phi and n_k of the assignments in z_host (after init or set_assignments);
@@ -1426,21 +1532,27 @@ int mlda_set_assignments(mlda_ctx* c, const uint16_t* z, int32_t iter) {
     if (!c) return fail(MLDA_EINVAL, "null context");
     if (c->T_all > 0 && !z) return fail(MLDA_EINVAL, "z is null");
     if (iter < 0) return fail(MLDA_EINVAL, "iter must be >= 0");
-    for (int64_t t = 0; t < c->T_all; ++t)
-        if (z[t] >= c->K) return fail(MLDA_EINVAL, "topic >= K in z");
+    std::atomic<bool> beyond{false};
+    if (!in_parts(c->T_all, [&](int64_t a, int64_t b) {
+            int most = -1;
+            for (int64_t t = a; t < b; ++t) most = std::max(most, (int)z[t]);
+            if (most >= c->K) beyond = true;
+        }))
+        return fail(MLDA_ENOMEM, "out of host memory");
+    if (beyond) return fail(MLDA_EINVAL, "topic >= K in z");
     if (c->streamed) {
         HIP_TRY(hipStreamSynchronize(c->stream));
         HIP_TRY(hipStreamSynchronize(c->copy_stream));
         HIP_TRY(hipStreamSynchronize(c->down_stream));
-        if (c->T_all > 0) std::memcpy(c->z_host, z, (size_t)c->T_all * 2);
+        if (!in_parts(c->T_all, [&](int64_t a, int64_t b) { std::memcpy(c->z_host + a, z + a, (size_t)(b - a) * 2); }))
+            return fail(MLDA_ENOMEM, "out of host memory");
         RC_TRY(rebuild_model_streamed(c, false));
     } else {
         if (c->T > 0) {
             uint16_t* tmp = c->z[c->cur ^ 1];
-            HIP_TRY(hipMemcpyAsync(tmp, z, (size_t)c->T * 2, hipMemcpyHostToDevice, c->stream));
+            RC_TRY(send(c, tmp, z, (size_t)c->T * 2));    // (done: the caller's z may go away)
             hipLaunchKernelGGL(mlda::to_word_major_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0,
                                c->stream, tmp, c->tok_id, c->z[c->cur], c->T, (int64_t)0);
-            HIP_TRY(hipStreamSynchronize(c->stream));     // the caller's z may go away after return
         }
         RC_TRY(rebuild_phi(c, c->z[c->cur], 0));
         RC_TRY(rebuild_theta(c, c->z[c->cur]));
@@ -1567,37 +1679,41 @@ int mlda_get_assignments(mlda_ctx* c, uint16_t* z) {
     if (c->streamed) {
         HIP_TRY(hipStreamSynchronize(c->stream));
         HIP_TRY(hipStreamSynchronize(c->down_stream));
-        std::memcpy(z, c->z_host, (size_t)c->T_all * 2);
+        if (!in_parts(c->T_all, [&](int64_t a, int64_t b) { std::memcpy(z + a, c->z_host + a, (size_t)(b - a) * 2); }))
+            return fail(MLDA_ENOMEM, "out of host memory");
         return MLDA_OK;
     }
     uint16_t* tmp = c->z[c->cur ^ 1];      // free between steps
     hipLaunchKernelGGL(mlda::to_doc_major_scatter_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0, c->stream,
                        c->z[c->cur], c->tok_id, tmp, c->T, c->at->tok_begin);
-    HIP_TRY(hipMemcpyAsync(z, tmp, (size_t)c->T * 2, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return MLDA_OK;
+    RC_TRY(launch_check("to_doc_major_scatter_kernel"));
+    return fetch(c, z, tmp, (size_t)c->T * 2);
 }
 
 int mlda_get_word_topic(mlda_ctx* c, int32_t* n_wk) {
     RC_TRY(need_state(c));
     if (!n_wk) return fail(MLDA_EINVAL, "n_wk is null");
     // the 16-bit matrix and the wide rows are fetched as they are and widened here
+    std::vector<int32_t> words;                     // of the wide rows
+    try { words.resize((size_t)c->n_wide); } catch (const std::bad_alloc&) { return fail(MLDA_ENOMEM, "out of host memory"); }
+    for (int32_t v = 0; v < c->V; ++v)
+        if (c->wide_row[(size_t)v] >= 0) words[(size_t)c->wide_row[(size_t)v]] = v;
     const size_t cells = (size_t)c->V * (size_t)c->K, wide_cells = (size_t)c->n_wide * (size_t)c->K;
-    std::vector<uint16_t> narrow;
-    std::vector<int32_t> wide;
-    try { narrow.resize(cells); wide.resize(wide_cells); }
-    catch (const std::bad_alloc&) { return fail(MLDA_ENOMEM, "out of host memory"); }
     const mlda::PhiView& phi = c->phi[c->model_cur];
-    HIP_TRY(hipMemcpyAsync(narrow.data(), phi.narrow, cells * 2, hipMemcpyDeviceToHost, c->stream));
+    RC_TRY(fetch_pieces(c, phi.narrow, cells * 2, [&](size_t at, const unsigned char* piece, size_t bytes) {
+        const uint16_t* cell = (const uint16_t*)piece;
+        int32_t* to = n_wk + at / 2;
+        for (size_t i = 0; i < bytes / 2; ++i) to[i] = cell[i];
+    }));
     if (wide_cells > 0)
-        HIP_TRY(hipMemcpyAsync(wide.data(), phi.wide, wide_cells * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    for (int32_t v = 0; v < c->V; ++v) {
-        const int32_t r = c->wide_row[(size_t)v];
-        int32_t* row = n_wk + (size_t)v * (size_t)c->K;
-        if (r >= 0) std::memcpy(row, wide.data() + (size_t)r * (size_t)c->K, (size_t)c->K * 4);
-        else for (int32_t k = 0; k < c->K; ++k) row[k] = narrow[(size_t)v * (size_t)c->K + (size_t)k];
-    }
+        RC_TRY(fetch_pieces(c, phi.wide, wide_cells * 4, [&](size_t at, const unsigned char* piece, size_t bytes) {
+            const int32_t* cell = (const int32_t*)piece;
+            for (size_t i = at / 4, end = (at + bytes) / 4; i < end;) {      // row by row
+                const size_t r = i / (size_t)c->K, k = i % (size_t)c->K, n = std::min(end - i, (size_t)c->K - k);
+                std::memcpy(n_wk + (size_t)words[r] * (size_t)c->K + k, cell + (i - at / 4), n * 4);
+                i += n;
+            }
+        }));
     return MLDA_OK;
 }
 
@@ -1632,15 +1748,16 @@ int mlda_get_doc_topic_csr(mlda_ctx* c, int64_t* row_ptr, uint16_t* topics, int3
     RC_TRY(need_state(c));
     if (!row_ptr) return fail(MLDA_EINVAL, "row_ptr is null");
     std::vector<uint2> rec;
-    std::vector<unsigned char> slots;
     row_ptr[0] = 0;
     auto take_rows = [&](const HostChunk& h) {
-        RC_TRY(fetch_rows(c, rec, slots));
+        RC_TRY(fetch_row_rec(c, rec));
         int64_t* ptr = row_ptr + h.d_begin;
         for (int64_t d = 0; d < c->D; ++d) ptr[d + 1] = ptr[d] + rec[(size_t)d].y;
         if (ptr[c->D] > ptr[0] && (!topics || !counts)) return fail(MLDA_EINVAL, "topics or counts is null");
-        unpack_rows(c, rec, slots, ptr, topics, counts);
-        return (int)MLDA_OK;
+        if (ptr[c->D] == ptr[0]) return (int)MLDA_OK;
+        if (c->rows == RowKind::tiny) return export_rows<mlda::TinyRows>(c, rec, ptr, topics, counts);
+        if (c->rows == RowKind::counted) return export_rows<mlda::CountedRows>(c, rec, ptr, topics, counts);
+        return export_rows<mlda::PackedRows>(c, rec, ptr, topics, counts);
     };
     if (c->streamed) {
         // chunks are visited in document order, so every chunk finds its first row start in place

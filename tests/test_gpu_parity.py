@@ -145,6 +145,7 @@ LAYOUT_CASES = [
     ("counted_from_here",      60, 80,   24,   110),
     ("counted_splits",         2,  60,   2,    30000),  # counts beyond 8,191
     ("counted_wide_counters",  2,  60,   5,    70000),  # 2^16 tokens in a document
+    ("counts_beyond_16_bits",  2,  40,   1,    70000),
     ("k_one",                  20, 30,   1,    40),
     ("k_largest_fp64",         25, 200,  2048, 300),
     ("k_first_fp32",           25, 200,  2049, 300),
