@@ -14,12 +14,20 @@ __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
-// Rows of words whose tokens span several segments are accumulated with atomics and must
-// start at zero.  grid = (#split words, ceil(K / blockDim)).
-__global__ void zero_rows_kernel(const int32_t* words, PhiView phi, int32_t K) {
+// What the rebuilds of one state add to must start at zero: the rows of words whose tokens span
+// several segments, the topic totals, the counter of row entries.  One launch for all three (a
+// launch and the gap before it take 8 us, a third of a whole rebuild on a corpus of 1e5 tokens).
+// grid = (#split words + 1, ceil(K / blockDim)).
+__global__ void zero_sums_kernel(const int32_t* split_words, PhiView phi, int32_t K, int32_t* n_k,
+                                 unsigned long long* row_entries) {
     const int k = (int)(blockIdx.y * blockDim.x + threadIdx.x);
+    if (blockIdx.x == 0) {
+        if (k < K) n_k[k] = 0;
+        if (k == 0) *row_entries = 0ull;
+        return;
+    }
     if (k >= K) return;
-    const int v = words[blockIdx.x], wide_row = phi.wide_row[v];
+    const int v = split_words[blockIdx.x - 1], wide_row = phi.wide_row[v];
     if (wide_row >= 0) phi.wide[(size_t)wide_row * (size_t)K + k] = 0;
     else phi.narrow[(size_t)v * (size_t)K + k] = 0;
 }
@@ -126,8 +134,28 @@ __global__ __launch_bounds__(256) void topic_totals_from_rows_kernel(PhiView phi
 // ------------------------------------------------------------------ log-likelihood helpers
 // log p(w,z) = sum_k [lgG(V beta) - lgG(n_k + V beta)] + sum_{v,k} [lgG(n_wk + beta) - lgG(beta)]
 //            + sum_d [lgG(K alpha) - lgG(N_d + K alpha)] + sum_{d,k} [lgG(n_dk + alpha) - lgG(alpha)]
-// Each workgroup writes one fp64 partial; a last single-workgroup kernel adds them in a
-// fixed order, so the value does not depend on scheduling.
+// Each workgroup writes one fp64 partial; one workgroup adds them in a fixed order, so the
+// value does not depend on scheduling.
+
+// The sum over a workgroup of 256 threads of the n partials each thread takes every 256th of.
+// (kShared: the partials come from workgroups of the same launch, and are read past the caches.)
+template <bool kShared>
+__device__ __forceinline__ double partials_sum(const double* partial, int n) {
+    double acc = 0.0;
+    for (int i = (int)threadIdx.x; i < n; i += 256)
+        acc += kShared ? __hip_atomic_load(partial + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : partial[i];
+    return acc;
+}
+__device__ __forceinline__ double block_sum_256(double acc) {
+    __shared__ double buf[256];
+    buf[threadIdx.x] = acc;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) buf[threadIdx.x] += buf[threadIdx.x + s];
+        __syncthreads();
+    }
+    return buf[0];
+}
 
 __device__ __forceinline__ void block_partial_store(double v, double* partial) {
     __shared__ double wsum[16];
@@ -835,8 +863,10 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
                                                                int64_t n_wide_cells,
                                                                const int32_t* n_k, int32_t K,
                                                                double beta, double v_beta,
-                                                               const double* lg_table,
-                                                               double* partial) {
+                                                               const double* lg_table, double* partial,
+                                                               const double* theta_partial, int n_theta,
+                                                               const double* theta_sum, const double* doc_term,
+                                                               unsigned int* ticket, double* out) {
     __shared__ double table[kLgTable];
     for (int c = (int)threadIdx.x; c < kLgTable; c += 256) table[c] = lg_table[c];
     const double lg_beta = lg_table[kLgTable];
@@ -892,10 +922,28 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
             acc += lg_vb - lgamma((double)n_k[k] + v_beta);
     }
     block_partial_store(acc, partial);
+    // The workgroup that finishes last adds up: the partials of all of them, those of the theta
+    // rebuild (or, streamed, their sum) and the documents' term.
+    __shared__ bool last;
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    double sum = partials_sum<true>(partial, (int)gridDim.x) + partials_sum<false>(theta_partial, n_theta);
+    if (threadIdx.x == 0) {
+        if (theta_sum) sum += *theta_sum;
+        sum += *doc_term;
+        *ticket = 0u;               // for the next launch
+    }
+    sum = block_sum_256(sum);
+    if (threadIdx.x == 0) *out = sum;
 }
 
 // The per-document term lgG(K alpha) - lgG(N_d + K alpha), one thread per document (the
-// entries of the theta rows are summed by theta_rows_kernel).
+// entries of the theta rows are summed by theta_rows_kernel).  A constant of the corpus.
 __global__ __launch_bounds__(256) void loglik_doc_term_kernel(const int32_t* doc_ptr, int64_t D,
                                                               double k_alpha, double* partial) {
     const double lg_ka = lgamma(k_alpha);
@@ -906,25 +954,12 @@ __global__ __launch_bounds__(256) void loglik_doc_term_kernel(const int32_t* doc
     block_partial_store(acc, partial);
 }
 
-// out = (add_to_out ? *out : 0) + sum of the n partials + *extra (if given).  One workgroup,
-// fixed order.
-__global__ __launch_bounds__(256) void loglik_final_kernel(const double* partial, int n,
-                                                           const double* extra, int add_to_out,
-                                                           double* out) {
-    __shared__ double buf[256];
-    double acc = 0.0;
-    for (int i = (int)threadIdx.x; i < n; i += 256) acc += partial[i];
-    if (threadIdx.x == 0) {
-        if (extra) acc += *extra;
-        if (add_to_out) acc += *out;
-    }
-    buf[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) buf[threadIdx.x] += buf[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = buf[0];
+// out = (add_to_out ? *out : 0) + sum of the n partials.  One workgroup, fixed order.
+__global__ __launch_bounds__(256) void loglik_final_kernel(const double* partial, int n, int add_to_out, double* out) {
+    double acc = partials_sum<false>(partial, n);
+    if (threadIdx.x == 0 && add_to_out) acc += *out;
+    acc = block_sum_256(acc);
+    if (threadIdx.x == 0) *out = acc;
 }
 
 }  // namespace mlda

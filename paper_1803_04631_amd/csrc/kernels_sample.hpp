@@ -85,6 +85,7 @@ struct SampleArgs {
     // K too large for p* to fit a workgroup's LDS (sample_kernel<12, .., true>): workgroup b keeps
     // p* of its current tile in far_pstar[b * Kpad ..] and takes the tiles b, b + grid, ...
     float* far_pstar;
+    int32_t min_batch;          // workgroups of four waves: tokens a wave takes at a time at least
 };
 
 constexpr int kRowHeader = 16;  // bytes before a theta row's entries
@@ -1040,8 +1041,10 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     // A wave takes up to 64 tokens at a time.  A tile too small to give every wave such a batch
     // is dealt out in smaller batches, so that all waves work on it side by side: the passes
     // of one batch follow each other, each waiting for its rows.
-    const int batch = kWaves == 4 ? kWave
-                    : min(kWave, max(kMinBatch, ((tl.count + kWaves - 1) / kWaves + 3) & ~3));
+    // (Full batches are less work in all, which is what counts where the chip is full; at K > 2048,
+    // and where all tiles are in flight at once, it is the time of one tile.)
+    const int batch = min(kWave, max(kWaves == 4 ? a.min_batch : kMinBatch,
+                                     ((tl.count + kWaves - 1) / kWaves + 3) & ~3));
     const int n_batches = (tl.count + batch - 1) / batch;
     for (int b = wave; b < n_batches; b += kWaves) {
         // ---- one token per lane: token, uniform, own-count correction

@@ -755,13 +755,10 @@ int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which) {
     const size_t hist_bytes = (size_t)span * 4;
     const bool ranges = c->K > kHistTopics;
     if (!c->streamed) {
-        if (c->n_split > 0) {
-            dim3 grid((unsigned)c->n_split, (unsigned)blocks_for(c->K, 256));
-            hipLaunchKernelGGL(zero_rows_kernel, grid, dim3(256), 0, c->stream, c->split_words,
-                               c->phi[which], c->K);
-        }
-        hipLaunchKernelGGL(fill_i32_kernel, dim3(blocks_for(c->K, 256)), dim3(256), 0, c->stream,
-                           c->n_k[which], (int64_t)c->K, 0);
+        // (the counter is that of the theta rebuild that follows)
+        const dim3 grid((unsigned)c->n_split + 1u, (unsigned)blocks_for(c->K, 256));
+        hipLaunchKernelGGL(zero_sums_kernel, grid, dim3(256), 0, c->stream, c->split_words, c->phi[which], c->K,
+                           c->n_k[which], c->row_entries + (c->rebuilds % kEntryRing));
     }
     if (c->n_tiles > 0) {
         if (!ranges)
@@ -821,7 +818,7 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
     if (c->D > 0) {
         const size_t theta_lds = theta_lds_bytes(c->K, c->wide_counters);
         unsigned long long* entries = c->row_entries + (c->rebuilds % kEntryRing);
-        hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, c->stream, entries);
+        if (c->streamed) hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, c->stream, entries);    // (else rebuild_phi did)
         // two documents per wave where a half-wave suits them: few topics, short documents
         const bool pairs = c->K <= kPairMaxK && !c->wide_counters && c->T <= 160 * c->D;
         const void* kernel =
@@ -866,6 +863,8 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     a.n_single = c->run_tiles > 1 ? c->n_single : c->n_tiles;
     a.run_tiles = c->run_tiles;
     a.far_pstar = c->far_pstar;
+    // few enough tiles for all to be in flight at once: nothing is gained by full batches then
+    a.min_batch = c->n_tiles <= 8 * c->n_cus ? mlda::kMinBatch * 2 : mlda::kWave;
     const int waves = sample_waves_for(c->K);
     const int32_t grid = c->far_weights ? std::min<int32_t>(a.n_tiles, kFarStrips)
                                         : a.n_single + (a.n_tiles - a.n_single + a.run_tiles - 1) / a.run_tiles;
@@ -877,44 +876,29 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     return launch_check("sample_kernel");
 }
 
-// Log-likelihood of the current state, one chunk: word side, document term, theta partials
-// left by the last rebuild_theta.
+// The word side of the log-likelihood and the value: with the theta partials that the last
+// rebuild_theta left (one chunk), or their sum over all chunks (streamed), and the documents' term.
 int launch_loglik(mlda_ctx* c) {
     using namespace mlda;
-    hipLaunchKernelGGL(loglik_word_side_kernel, dim3(kLoglikBlocks), dim3(256), 0, c->stream,
-                       c->phi[c->model_cur], (int64_t)c->V * c->K, (int64_t)c->n_wide * c->K,
-                       c->n_k[c->model_cur], c->K, c->beta,
-                       (double)c->V * c->beta, c->lg_table_beta, c->ll_partial);
-    hipLaunchKernelGGL(loglik_doc_term_kernel, dim3(kLoglikBlocks), dim3(256), 0, c->stream, c->doc_ptr,
-                       c->D, (double)c->K * c->alpha, c->ll_partial + kLoglikBlocks);
-    hipLaunchKernelGGL(loglik_final_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial,
-                       2 * kLoglikBlocks + c->theta_grid, (const double*)nullptr, 0, c->ll_scalars);
+    const int64_t cells = (int64_t)c->V * c->K, wide_cells = (int64_t)c->n_wide * c->K;
+    // a thread reads 16 bytes at a time; no more workgroups (and partials) than that gives work
+    const int blocks = (int)std::min<int64_t>(kLoglikBlocks, std::max(cells / 8, wide_cells / 4) / 256 + 1);
+    hipLaunchKernelGGL(loglik_word_side_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream,
+                       c->phi[c->model_cur], cells, wide_cells, c->n_k[c->model_cur], c->K, c->beta,
+                       (double)c->V * c->beta, c->lg_table_beta, c->ll_partial,
+                       (const double*)(c->ll_partial + 2 * kLoglikBlocks), c->streamed ? 0 : c->theta_grid,
+                       c->streamed ? (const double*)(c->ll_scalars + 1) : (const double*)nullptr,
+                       (const double*)(c->ll_scalars + 2), (unsigned int*)(c->ll_scalars + 3), c->ll_scalars);
     c->ll_fresh = true;
-    return launch_check("log-likelihood kernels");
+    return launch_check("log-likelihood kernel");
 }
 
 // Streamed: the theta partials of the chunk just rebuilt are added to the running sum ...
 int add_theta_loglik(mlda_ctx* c, bool first) {
     hipLaunchKernelGGL(mlda::loglik_final_kernel, dim3(1), dim3(256), 0, c->stream,
-                       c->ll_partial + 2 * kLoglikBlocks, c->D > 0 ? c->theta_grid : 0,
-                       (const double*)nullptr, first ? 0 : 1, c->ll_scalars + 1);
+                       c->ll_partial + 2 * kLoglikBlocks, c->D > 0 ? c->theta_grid : 0, first ? 0 : 1,
+                       c->ll_scalars + 1);
     return launch_check("loglik_final_kernel");
-}
-
-// ... and the value is the word side plus that sum plus the documents' term (a constant of
-// the corpus, scalars[2]).
-int finish_loglik_streamed(mlda_ctx* c) {
-    using namespace mlda;
-    hipLaunchKernelGGL(loglik_word_side_kernel, dim3(kLoglikBlocks), dim3(256), 0, c->stream,
-                       c->phi[c->model_cur], (int64_t)c->V * c->K, (int64_t)c->n_wide * c->K,
-                       c->n_k[c->model_cur], c->K, c->beta,
-                       (double)c->V * c->beta, c->lg_table_beta, c->ll_partial);
-    hipLaunchKernelGGL(loglik_final_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial, kLoglikBlocks,
-                       (const double*)(c->ll_scalars + 1), 0, c->ll_scalars);
-    hipLaunchKernelGGL(loglik_final_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial, 0,
-                       (const double*)(c->ll_scalars + 2), 1, c->ll_scalars);
-    c->ll_fresh = true;
-    return launch_check("log-likelihood kernels");
 }
 
 int need_state(const mlda_ctx* c) {
@@ -996,6 +980,8 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     const int64_t dwords = (int64_t)(c->phi_bytes / 4);
     hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(blocks_for(dwords, 256)), dim3(256), 0, c->stream,
                        (int32_t*)c->phi[0].narrow, dwords, 0);
+    hipLaunchKernelGGL(mlda::zero_u64_kernel, dim3(1), dim3(1), 0, c->stream,
+                       (unsigned long long*)(c->ll_scalars + 3));     // launch_loglik's ticket
     RC_TRY(launch_check("model set-up kernels"));
     if (c->sample_lds > 48 * 1024)          // (the workgroups of twelve waves only)
         for (bool short_docs : {false, true})
@@ -1313,8 +1299,8 @@ int for_each_chunk_rows(mlda_ctx* c, F&& visit) {
         RC_TRY(store_z_and_release(c, m, false));
     }
     if (first) {            // no documents at all: the sum is empty
-        hipLaunchKernelGGL(mlda::loglik_final_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial, 0,
-                           (const double*)nullptr, 0, c->ll_scalars + 1);
+        hipLaunchKernelGGL(mlda::loglik_final_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial, 0, 0,
+                           c->ll_scalars + 1);
         RC_TRY(launch_check("loglik_final_kernel"));
     }
     return MLDA_OK;
@@ -1409,6 +1395,14 @@ static int create_resident(mlda_ctx** out, const int64_t* doc_ptr, const int32_t
             e = hipMemcpyAsync(c->slot_base[0], h.arena, h.L.static_bytes, hipMemcpyHostToDevice, c->stream);
         if (e != hipSuccess) rc = fail(MLDA_EHIP, std::string("uploading the corpus: ") + hipGetErrorString(e));
         if (rc == MLDA_OK) { derive_chunk_arrays(c); rc = finish_create(c, base, ML); }
+        if (rc == MLDA_OK) {        // the documents' term of the log-likelihood never changes
+            const int blocks = (int)std::min<int64_t>(kLoglikBlocks, D / 256 + 1);
+            hipLaunchKernelGGL(mlda::loglik_doc_term_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream, c->doc_ptr, D,
+                               (double)K * alpha, c->ll_partial);
+            hipLaunchKernelGGL(mlda::loglik_final_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial, blocks, 0,
+                               c->ll_scalars + 2);
+            rc = launch_check("document term kernels");
+        }
         // the upload reads the host arena until the stream has drained: wait for it before the
         // arena goes, whether or not everything before went well
         e = hipStreamSynchronize(c->stream);
@@ -1612,11 +1606,11 @@ static int step_streamed(mlda_ctx* c, bool loglik, int32_t timed_row) {
     c->ll_fresh = false;
     if (loglik) {
         if (first) {
-            hipLaunchKernelGGL(mlda::loglik_final_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial, 0,
-                               (const double*)nullptr, 0, c->ll_scalars + 1);
+            hipLaunchKernelGGL(mlda::loglik_final_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial, 0, 0,
+                               c->ll_scalars + 1);
             RC_TRY(launch_check("loglik_final_kernel"));
         }
-        RC_TRY(finish_loglik_streamed(c));
+        RC_TRY(launch_loglik(c));
     }
     return MLDA_OK;
 }
@@ -1649,7 +1643,7 @@ int mlda_step(mlda_ctx* c, int32_t n_iters, uint32_t flags) {
     for (int32_t i = 0; i < n_iters; ++i) {
         const int32_t slot = i - (n_iters - timed);
         hipEvent_t* ev = slot >= 0 ? &c->events[(size_t)slot * 5] : nullptr;
-        if (ev) HIP_TRY(hipEventRecord(ev[0], c->stream));
+        if (slot == 0) HIP_TRY(hipEventRecord(ev[0], c->stream));   // (later ones start where the one before ended)
         uint16_t* z_next = c->z[c->cur ^ 1];
         RC_TRY(launch_sampler(c, c->z[c->cur], z_next));
         if (ev) HIP_TRY(hipEventRecord(ev[1], c->stream));
@@ -1774,7 +1768,7 @@ int mlda_get_loglik(mlda_ctx* c, double* ll) {
     if (!c->ll_fresh) {
         if (c->streamed) {
             RC_TRY(for_each_chunk_rows(c, [](const HostChunk&) { return (int)MLDA_OK; }));
-            RC_TRY(finish_loglik_streamed(c));
+            RC_TRY(launch_loglik(c));
         } else {
             RC_TRY(launch_loglik(c));
         }
@@ -1812,7 +1806,8 @@ int mlda_get_timing(mlda_ctx* c, double* ms, int32_t capacity_iters, int32_t* n_
         hipEvent_t* ev = &c->events[(size_t)(first + i) * 5];
         for (int j = 0; j < 4; ++j) {
             float t = 0.f;
-            HIP_TRY(hipEventElapsedTime(&t, ev[j], ev[j + 1]));
+            const hipEvent_t start = j == 0 && first + i > 0 ? ev[-1] : ev[j];
+            HIP_TRY(hipEventElapsedTime(&t, start, ev[j + 1]));
             ms[(size_t)i * 4 + j] = (double)t;
         }
     }
