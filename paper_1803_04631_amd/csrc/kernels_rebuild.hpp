@@ -314,8 +314,12 @@ __device__ __forceinline__ void close_row(unsigned char* head, int n_entries, in
 // length rather than K.  While the counts pass through registers the kernel also adds up the
 // theta entries' term of the log-likelihood, sum_{d,k} lgG(n_dk + alpha) - lgG(alpha), one
 // partial per workgroup.
-template <class Layout, bool kWide>
-__global__ __launch_bounds__(kWave) void theta_rows_kernel(const DocRec* docs,
+// kDocWaves: waves that count a document together.  One, but where the documents are too few for
+// a wave each to fill the chip and long enough to be counted by many: a wave alone takes
+// 0.79 ms for the longest of 311 documents of 30,000 tokens, sixteen take 0.11 ms.
+constexpr int kLongDocWaves = 16;
+template <class Layout, bool kWide, int kDocWaves = 1>
+__global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const DocRec* docs,
                                                            const int32_t* doc_map,
                                                            const uint16_t* z, uint2* row_rec,
                                                            unsigned char* slots, int64_t D, int64_t T,
@@ -338,13 +342,16 @@ __global__ __launch_bounds__(kWave) void theta_rows_kernel(const DocRec* docs,
     constexpr bool kMore = sizeof(Entry) == 2 && !kWide;
     constexpr bool kNominal = Layout::kDoubleWeights;      // (the entries of the other layout are the nominal ones)
     [[maybe_unused]] uint32_t* more = reinterpret_cast<uint32_t*>(table + kThetaLgTable);
-    const int lane = (int)threadIdx.x;
+    // the document's tokens are dealt to all threads (`me` of `width`); its row is the first wave's
+    constexpr int width = kWave * kDocWaves;
+    const int me = (int)threadIdx.x, lane = me & (kWave - 1);
+    const bool writes_row = kDocWaves == 1 || me < kWave;
     const double lg_alpha = lg_table[kLgTable];
-    for (int k = lane; k < n_counters; k += kWave) hist[k] = 0u;
-    for (int k = lane; k < n_marks; k += kWave) marks[k] = 0u;
+    for (int k = me; k < n_counters; k += width) hist[k] = 0u;
+    for (int k = me; k < n_marks; k += width) marks[k] = 0u;
     if constexpr (kMore)
-        for (int k = lane; k < n_marks; k += kWave) more[k] = 0u;
-    for (int c = lane; c < kThetaLgTable; c += kWave) table[c] = lg_table[c];
+        for (int k = me; k < n_marks; k += width) more[k] = 0u;
+    for (int c = me; c < kThetaLgTable; c += width) table[c] = lg_table[c];
     __syncthreads();
     unsigned long long visited = 0;      // sum of N_d * (nominal entries of row d) over this wave's documents
     double ll = 0.0;
@@ -391,20 +398,20 @@ __global__ __launch_bounds__(kWave) void theta_rows_kernel(const DocRec* docs,
     DocRec cur = record(i), nxt = record(i + step), after = record(i + 2 * step);
     int k0, k1;
     {
-        const int c0 = doc_token_position_any(doc_map, cur, lane);
-        const int c1 = doc_token_position_any(doc_map, cur, lane + kWave);
-        k0 = doc_token_topic(z, c0, cur, lane);
-        k1 = doc_token_topic(z, c1, cur, lane + kWave);
+        const int c0 = doc_token_position_any(doc_map, cur, me);
+        const int c1 = doc_token_position_any(doc_map, cur, me + width);
+        k0 = doc_token_topic(z, c0, cur, me);
+        k1 = doc_token_topic(z, c1, cur, me + width);
     }
-    int p0 = doc_token_position_any(doc_map, nxt, lane);
-    int p1 = doc_token_position_any(doc_map, nxt, lane + kWave);
+    int p0 = doc_token_position_any(doc_map, nxt, me);
+    int p1 = doc_token_position_any(doc_map, nxt, me + width);
     for (; i < D; i += step) {
         // on their way while this document is counted: the next document's topics, the
         // positions of the one after, the record after that
-        const int n0 = doc_token_topic(z, p0, nxt, lane);
-        const int n1 = doc_token_topic(z, p1, nxt, lane + kWave);
-        const int q0 = doc_token_position_any(doc_map, after, lane);
-        const int q1 = doc_token_position_any(doc_map, after, lane + kWave);
+        const int n0 = doc_token_topic(z, p0, nxt, me);
+        const int n1 = doc_token_topic(z, p1, nxt, me + width);
+        const int q0 = doc_token_position_any(doc_map, after, me);
+        const int q1 = doc_token_position_any(doc_map, after, me + width);
         const DocRec later = record(i + 3 * step);
 
         const bool long_doc = cur.n > Layout::kMaxCount;     // (the same for the whole wave)
@@ -427,22 +434,27 @@ __global__ __launch_bounds__(kWave) void theta_rows_kernel(const DocRec* docs,
         count(k1);
         // the rest of a longer document, four tokens per lane at a time: their positions
         // first, then their topics, each group of loads in flight together
-        for (int j = 2 * kWave + lane; j - lane < cur.n; j += 4 * kWave) {
+        for (int j = 2 * width + me; j - me < cur.n; j += 4 * width) {
             int at[4], k[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) at[t] = doc_token_position_any(doc_map, cur, j + t * kWave);
+            for (int t = 0; t < 4; ++t) at[t] = doc_token_position_any(doc_map, cur, j + t * width);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) k[t] = doc_token_topic(z, at[t], cur, j + t * kWave);
+            for (int t = 0; t < 4; ++t) k[t] = doc_token_topic(z, at[t], cur, j + t * width);
 #pragma unroll
             for (int t = 0; t < 4; ++t) count(k[t]);
         }
-        __syncthreads();
         // some count of the document takes several entries
-        const bool may_split = __ballot(outgrown) != 0;
+        bool may_split;
+        if constexpr (kDocWaves == 1) {
+            __syncthreads();
+            may_split = __ballot(outgrown) != 0;
+        } else {
+            may_split = __syncthreads_or(outgrown) != 0;
+        }
         any_split |= may_split;
         // Each lane owns one word of marks (32 topics) per round and writes its non-zero bins
         // in ascending order behind those of the lanes below it.
-        for (int base = 0; base < n_marks; base += kWave) {
+        for (int base = 0; writes_row && base < n_marks; base += kWave) {
             const int wi = base + lane;
             uint32_t w = wi < n_marks ? marks[wi] : 0u;
             if (__ballot(w != 0u) == 0) continue;
@@ -500,10 +512,12 @@ __global__ __launch_bounds__(kWave) void theta_rows_kernel(const DocRec* docs,
         }
         if (k_lo + span < K) __syncthreads();
         }
-        close_row<Layout>(head, filled, K, lane, true);
-        const int nnz = any_split ? wave_sum(distinct) : filled;
-        if (lane == 0) row_rec[cur.doc].y = (uint32_t)nnz;      // distinct topics, for the getters
-        visited += (unsigned long long)cur.n * (unsigned long long)(kNominal && any_split ? wave_sum(nominal) : filled);
+        if (writes_row) {
+            close_row<Layout>(head, filled, K, lane, true);
+            const int nnz = any_split ? wave_sum(distinct) : filled;
+            if (lane == 0) row_rec[cur.doc].y = (uint32_t)nnz;      // distinct topics, for the getters
+            visited += (unsigned long long)cur.n * (unsigned long long)(kNominal && any_split ? wave_sum(nominal) : filled);
+        }
         __syncthreads();
         cur = nxt; nxt = after; after = later; k0 = n0; k1 = n1; p0 = q0; p1 = q1;
     }

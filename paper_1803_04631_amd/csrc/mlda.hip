@@ -91,15 +91,26 @@ const void* sample_kernel_for(int32_t K, RowKind rows, bool short_docs, bool nea
     return near ? sample_kernel_of<true>(K, rows, short_docs) : sample_kernel_of<false>(K, rows, short_docs);
 }
 bool slots_near(size_t slots_bytes) { return slots_bytes <= 0xffffffffull; }
-template <class Layout>
-const void* theta_kernel_of(bool wide_counters) {
-    return wide_counters ? (const void*)mlda::theta_rows_kernel<Layout, true>
-                         : (const void*)mlda::theta_rows_kernel<Layout, false>;
+// Few long documents are counted by kLongDocWaves waves each: when there are no more of them than
+// half the waves the chip holds of the one-wave kernel (16 per CU), and each wave still has
+// several hundred tokens.
+bool long_docs_for(int64_t D, int64_t T, int n_cus) {
+    return D > 0 && D <= (int64_t)n_cus * 8 && T / D >= 4096;
 }
-const void* theta_kernel_for(RowKind rows, bool wide_counters) {
-    if (rows == RowKind::tiny) return theta_kernel_of<mlda::TinyRows>(wide_counters);
-    if (rows == RowKind::counted) return theta_kernel_of<mlda::CountedRows>(wide_counters);
-    return theta_kernel_of<mlda::PackedRows>(wide_counters);
+template <class Layout, int kDocWaves>
+const void* theta_kernel_of(bool wide_counters) {
+    return wide_counters ? (const void*)mlda::theta_rows_kernel<Layout, true, kDocWaves>
+                         : (const void*)mlda::theta_rows_kernel<Layout, false, kDocWaves>;
+}
+template <int kDocWaves>
+const void* theta_kernel_with(RowKind rows, bool wide_counters) {
+    if (rows == RowKind::tiny) return theta_kernel_of<mlda::TinyRows, kDocWaves>(wide_counters);
+    if (rows == RowKind::counted) return theta_kernel_of<mlda::CountedRows, kDocWaves>(wide_counters);
+    return theta_kernel_of<mlda::PackedRows, kDocWaves>(wide_counters);
+}
+const void* theta_kernel_for(RowKind rows, bool wide_counters, bool long_docs) {
+    return long_docs ? theta_kernel_with<mlda::kLongDocWaves>(rows, wide_counters)
+                     : theta_kernel_with<1>(rows, wide_counters);
 }
 constexpr int kMaxTimedIters = 1024;
 constexpr int kRunTiles = 16;           // small tiles a workgroup of the large-K sampler takes one after the other
@@ -821,8 +832,9 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
         if (c->streamed) hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, c->stream, entries);    // (else rebuild_phi did)
         // two documents per wave where a half-wave suits them: few topics, short documents
         const bool pairs = c->K <= kPairMaxK && !c->wide_counters && c->T <= 160 * c->D;
+        const bool long_docs = long_docs_for(c->D, c->T, c->n_cus);
         const void* kernel =
-            !pairs                      ? theta_kernel_for(c->rows, c->wide_counters)
+            !pairs                      ? theta_kernel_for(c->rows, c->wide_counters, long_docs)
             : c->rows == RowKind::tiny ? (const void*)theta_rows_pair_kernel<TinyRows>
                                        : (const void*)theta_rows_pair_kernel<CountedRows>;
         const size_t lds = pairs ? theta_pair_lds_bytes(c->K) : theta_lds;
@@ -835,7 +847,8 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
         const double* lg_table = c->lg_table;
         double* ll_partial = c->ll_partial + 2 * kLoglikBlocks;
         void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &entries, &ll_partial};
-        HIP_TRY(hipLaunchKernel(kernel, dim3((unsigned)c->theta_grid), dim3(kWave), args, lds, c->stream));
+        HIP_TRY(hipLaunchKernel(kernel, dim3((unsigned)c->theta_grid), dim3((unsigned)(long_docs ? kWave * kLongDocWaves : kWave)),
+                                args, lds, c->stream));
     }
     c->rebuilds += 1;
     return launch_check("theta rebuild kernel");
@@ -1000,9 +1013,10 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     for (bool wide : {false, true})         // (large K only: 4-byte rows of any K)
         if (mlda::theta_lds_bytes(c->K, wide) > 48 * 1024 &&
             mlda::theta_lds_bytes(c->K, wide) <= (size_t)c->lds_limit)      // (else see check_theta_lds)
-            HIP_TRY(hipFuncSetAttribute(theta_kernel_for(RowKind::packed, wide),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)mlda::theta_lds_bytes(c->K, wide)));
+            for (bool long_docs : {false, true})
+                HIP_TRY(hipFuncSetAttribute(theta_kernel_for(RowKind::packed, wide, long_docs),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)mlda::theta_lds_bytes(c->K, wide)));
     return MLDA_OK;
 }
 

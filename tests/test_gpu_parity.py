@@ -146,6 +146,8 @@ LAYOUT_CASES = [
     ("counted_splits",         2,  60,   2,    30000),  # counts beyond 8,191
     ("counted_wide_counters",  2,  60,   5,    70000),  # 2^16 tokens in a document
     ("counts_beyond_16_bits",  2,  40,   1,    70000),
+    ("tiny_long_docs",         3,  300,  2000, 5000),   # sixteen waves count a document together
+    ("packed_long_docs",       3,  300,  3000, 5000),
     ("k_one",                  20, 30,   1,    40),
     ("k_largest_fp64",         25, 200,  2048, 300),
     ("k_first_fp32",           25, 200,  2049, 300),
