@@ -157,6 +157,20 @@ __device__ __forceinline__ double block_sum_256(double acc) {
     return buf[0];
 }
 
+// The log-likelihood: the word side's partials, those of the theta rebuild (or, streamed, their
+// sum) and the documents' term.
+template <bool kShared>
+__device__ __forceinline__ void store_loglik(const double* partial, int n, const double* theta_partial, int n_theta,
+                                             const double* theta_sum, const double* doc_term, double* out) {
+    double sum = partials_sum<kShared>(partial, n) + partials_sum<false>(theta_partial, n_theta);
+    if (threadIdx.x == 0) {
+        if (theta_sum) sum += *theta_sum;
+        sum += *doc_term;
+    }
+    sum = block_sum_256(sum);
+    if (threadIdx.x == 0) *out = sum;
+}
+
 __device__ __forceinline__ void block_partial_store(double v, double* partial) {
     __shared__ double wsum[16];
     const int lane = lane_id(), wave = (int)threadIdx.x / kWave;
@@ -881,6 +895,7 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
                                                                const double* theta_partial, int n_theta,
                                                                const double* theta_sum, const double* doc_term,
                                                                unsigned int* ticket, double* out) {
+    // (ticket: null if loglik_value_kernel follows)
     __shared__ double table[kLgTable];
     for (int c = (int)threadIdx.x; c < kLgTable; c += 256) table[c] = lg_table[c];
     const double lg_beta = lg_table[kLgTable];
@@ -936,8 +951,10 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
             acc += lg_vb - lgamma((double)n_k[k] + v_beta);
     }
     block_partial_store(acc, partial);
-    // The workgroup that finishes last adds up: the partials of all of them, those of the theta
-    // rebuild (or, streamed, their sum) and the documents' term.
+    // A small launch needs no other: the workgroup that finishes last adds up.  (Its fences take
+    // longer than a launch once there are many workgroups: 2,048 of them 52 us against 26 with
+    // loglik_value_kernel; 50 of them 12 against 19.)
+    if (!ticket) return;
     __shared__ bool last;
     if (threadIdx.x == 0) {
         __threadfence();
@@ -946,14 +963,15 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
     __syncthreads();
     if (!last) return;
     __threadfence();
-    double sum = partials_sum<true>(partial, (int)gridDim.x) + partials_sum<false>(theta_partial, n_theta);
-    if (threadIdx.x == 0) {
-        if (theta_sum) sum += *theta_sum;
-        sum += *doc_term;
-        *ticket = 0u;               // for the next launch
-    }
-    sum = block_sum_256(sum);
-    if (threadIdx.x == 0) *out = sum;
+    if (threadIdx.x == 0) *ticket = 0u;               // for the next launch
+    store_loglik<true>(partial, (int)gridDim.x, theta_partial, n_theta, theta_sum, doc_term, out);
+}
+
+// The value after a large loglik_word_side_kernel.  One workgroup.
+__global__ __launch_bounds__(256) void loglik_value_kernel(const double* partial, int n, const double* theta_partial,
+                                                           int n_theta, const double* theta_sum,
+                                                           const double* doc_term, double* out) {
+    store_loglik<false>(partial, n, theta_partial, n_theta, theta_sum, doc_term, out);
 }
 
 // The per-document term lgG(K alpha) - lgG(N_d + K alpha), one thread per document (the

@@ -154,6 +154,7 @@ RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t K) {
 }
 
 constexpr int kLoglikBlocks = 2048;
+constexpr int kSmallLoglikBlocks = 256;     // up to so many, the word side's last workgroup adds up
 constexpr int kMaxThetaGrid = 8192;    // workgroups of the theta rebuild (each leaves one likelihood partial)
 constexpr int kEntryRing = 2048;      // per-rebuild counters of theta row entries (> kMaxTimedIters)
 
@@ -894,14 +895,21 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
 int launch_loglik(mlda_ctx* c) {
     using namespace mlda;
     const int64_t cells = (int64_t)c->V * c->K, wide_cells = (int64_t)c->n_wide * c->K;
-    // a thread reads 16 bytes at a time; no more workgroups (and partials) than that gives work
-    const int blocks = (int)std::min<int64_t>(kLoglikBlocks, std::max(cells / 8, wide_cells / 4) / 256 + 1);
+    // a thread reads 16 bytes at a time
+    const int64_t wanted = std::max(cells / 8, wide_cells / 4) / 256 + 1;
+    const bool small = wanted <= kSmallLoglikBlocks;
+    const int blocks = small ? (int)wanted : kLoglikBlocks;
+    const double* theta_partial = c->ll_partial + 2 * kLoglikBlocks;
+    const int n_theta = c->streamed ? 0 : c->theta_grid;
+    const double* theta_sum = c->streamed ? c->ll_scalars + 1 : nullptr;
+    const double* doc_term = c->ll_scalars + 2;
     hipLaunchKernelGGL(loglik_word_side_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream,
                        c->phi[c->model_cur], cells, wide_cells, c->n_k[c->model_cur], c->K, c->beta,
-                       (double)c->V * c->beta, c->lg_table_beta, c->ll_partial,
-                       (const double*)(c->ll_partial + 2 * kLoglikBlocks), c->streamed ? 0 : c->theta_grid,
-                       c->streamed ? (const double*)(c->ll_scalars + 1) : (const double*)nullptr,
-                       (const double*)(c->ll_scalars + 2), (unsigned int*)(c->ll_scalars + 3), c->ll_scalars);
+                       (double)c->V * c->beta, c->lg_table_beta, c->ll_partial, theta_partial, n_theta, theta_sum,
+                       doc_term, small ? (unsigned int*)(c->ll_scalars + 3) : (unsigned int*)nullptr, c->ll_scalars);
+    if (!small)
+        hipLaunchKernelGGL(loglik_value_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial, blocks, theta_partial,
+                           n_theta, theta_sum, doc_term, c->ll_scalars);
     c->ll_fresh = true;
     return launch_check("log-likelihood kernel");
 }
