@@ -36,7 +36,7 @@
  *     memory, keeps the workspace until mlda_destroy, and launches all kernels on
  *     that stream (a context made by mlda_create_streamed also owns pinned host
  *     memory and two copy streams; any context but those of mlda_create_static takes 16 MB
- *     of pinned host memory at its first transfer of 32 MB or more, and moves such transfers
+ *     of pinned host memory at its first transfer of 8 MB or more, and moves such transfers
  *     with up to eight threads that end with the call).  Getters synchronise the stream.
  *   - A context is not thread-safe.  Token order at the boundary is always the
  *     caller's document-major order; the word-major order used on the device is

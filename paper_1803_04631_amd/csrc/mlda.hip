@@ -1136,13 +1136,14 @@ void destroy(mlda_ctx* c) {
 // 50.  Here kRingWorkers threads each own a pinned piece of kRingPiece bytes and take every
 // kRingWorkers-th piece of the transfer: the copies queue up on the context's stream, and what a
 // piece needs on the host (a copy, a widening) is done by its thread while the others' are on
-// their way.  From kRingFrom bytes on: below, making the ring (once per context) costs about what
-// it saves.  Ten iterations on 7.4e8 tokens and their assignments fetched: 535 -> 432 ms; five on
+// their way.  From kRingFrom bytes on (four pieces: below, too few
+// threads have work; with 32 MB as the line, five iterations on 6.3e6 tokens and their 12.6 MB took 4.42 ms,
+// now 4.12, the first time on a new context 5.36 and 5.17).  Ten iterations on 7.4e8 tokens and their assignments fetched: 535 -> 432 ms; five on
 // 9.9e7: 59.5 -> 45.2 ms (first time on a new context 58 -> 45 ms).  A context on the static workspace, and one for which no pinned memory is left,
 // does without.
 constexpr int kRingWorkers = 8;
 constexpr size_t kRingPiece = (size_t)2 << 20;
-constexpr size_t kRingFrom = (size_t)32 << 20;
+constexpr size_t kRingFrom = (size_t)8 << 20;
 
 bool ring_ready(mlda_ctx* c) {
     if (c->ring) return true;
