@@ -278,15 +278,15 @@ __device__ __forceinline__ int write_entries(typename Layout::Entry* ent, int at
     return at;
 }
 
-// Entries that a count c > 0 is taken as in the sampler's algorithmic bytes, whatever the layout in
+// Entries that a count c is taken as in the sampler's algorithmic bytes, whatever the layout in
 // use: entries of up to 15 tokens where K < 1024 (2 bytes each), of up to 16,383 (4 bytes) beyond.
 __device__ __forceinline__ int nominal_entries(int c, int K) {
     return K < 1024 ? (c + 14) / 15 : (c + 16382) / 16383;
 }
 
 // 2-byte entries hold counts up to 7 only, and rows with larger ones are common.  Their entries
-// are counted while the tokens are: the token that is one more than a multiple of kMaxCount (of 15)
-// begins another entry (another nominal one).  Added to the counter of the topic's 32, the
+// are counted while the tokens are: the token that is one more than a multiple of kMaxCount (of 15
+// or 16,383) begins another entry (another nominal one).  Added to the counter of the topic's 32, the
 // entries in the lower half, the nominal ones in the upper (fewer than 2^16 tokens: neither
 // overflows).  Against looking every bin of such a row up again: 7.2 -> 6.05 ms for 8.2e6 documents
 // of 90 tokens at K = 1,000.
@@ -294,7 +294,7 @@ template <class Layout>
 __device__ __forceinline__ void more_entries(uint32_t* more, int k, int before, int K) {
     if (before >= Layout::kMaxCount) {
         const uint32_t another = before % Layout::kMaxCount == 0 ? 1u : 0u;
-        const uint32_t nominal = K < 1024 && before % 15 == 0 ? 1u << 16 : 0u;
+        const uint32_t nominal = (K < 1024 ? before % 15 : before % 16383) == 0 ? 1u << 16 : 0u;
         if (another | nominal) atomicAdd(&more[k >> 5], another | nominal);
     }
 }
@@ -354,7 +354,9 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
     uint32_t* marks = reinterpret_cast<uint32_t*>(lds + theta_counter_bytes(K, kWide));
     double* table = reinterpret_cast<double*>(lds + theta_hist_bytes(K, kWide));
     constexpr bool kMore = sizeof(Entry) == 2 && !kWide;
-    constexpr bool kNominal = Layout::kDoubleWeights;      // (the entries of the other layout are the nominal ones)
+    // nominal entries: those of the row where the layout is PackedRows; counted with the tokens (kMore), or
+    // bin by bin as the row is written
+    constexpr bool kNominal = Layout::kDoubleWeights, kNominalByBin = kNominal && !kMore;
     [[maybe_unused]] uint32_t* more = reinterpret_cast<uint32_t*>(table + kThetaLgTable);
     // the document's tokens are dealt to all threads (`me` of `width`); its row is the first wave's
     constexpr int width = kWave * kDocWaves;
@@ -481,13 +483,8 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
                 if (m != 0u) more[wi] = 0u;
             } else if (may_split) {    // the lane's entries, counted one bin at a time
                 mine = 0;
-                for (uint32_t rest = w; rest != 0u; rest &= rest - 1u) {
-                    const int c = count_of(wi * 32 + __ffs((int)rest) - 1);
-                    mine += entries_of<Layout>(c);
-                    if (kNominal) nominal += nominal_entries(c, K);
-                }
-            } else if (kNominal) {
-                nominal += mine;
+                for (uint32_t rest = w; rest != 0u; rest &= rest - 1u)
+                    mine += entries_of<Layout>(count_of(wi * 32 + __ffs((int)rest) - 1));
             }
             const int upto = wave_inclusive_sum(mine);
             int at = filled + upto - mine;
@@ -502,6 +499,7 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
                         c = (int)hist[k];
                         hist[k] = 0u;
                         at = write_entries<Layout>(ent, at, k_lo + k, c);
+                        if (kNominalByBin) nominal += nominal_entries(c, K);
                     }
                     add_ll(c);
                 }
@@ -518,6 +516,7 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
                         hi = (int)(both >> 16);
                         if (lo != 0) at = write_entries<Layout>(ent, at, k, lo);
                         if (hi != 0) at = write_entries<Layout>(ent, at, k + 1, hi);
+                        if (kNominalByBin) nominal += nominal_entries(lo, K) + nominal_entries(hi, K);
                     }
                     add_ll(lo);
                     add_ll(hi);
@@ -530,7 +529,7 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
             close_row<Layout>(head, filled, K, lane, true);
             const int nnz = any_split ? wave_sum(distinct) : filled;
             if (lane == 0) row_rec[cur.doc].y = (uint32_t)nnz;      // distinct topics, for the getters
-            visited += (unsigned long long)cur.n * (unsigned long long)(kNominal && any_split ? wave_sum(nominal) : filled);
+            visited += (unsigned long long)cur.n * (unsigned long long)(kNominalByBin || (kNominal && any_split) ? wave_sum(nominal) : filled);
         }
         __syncthreads();
         cur = nxt; nxt = after; after = later; k0 = n0; k1 = n1; p0 = q0; p1 = q1;
@@ -630,19 +629,17 @@ __global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* do
         // lane hl of a half owns mark word hl: 32 topics = 16 counter pairs
         const uint32_t w = hl < n_marks ? marks[hl] : 0u;
         const int distinct = __popc(w);
-        int mine = distinct, nominal = distinct;
+        int mine = distinct, nominal = kMore ? distinct : 0;
         if (kMore && __ballot(outgrown) != 0) {      // some count of the pair takes several entries
             const uint32_t m = more[hl];
             mine += (int)(m & 0xffffu);
             nominal += (int)(m >> 16);
             if (m != 0u) more[hl] = 0u;
         } else if (__ballot(outgrown) != 0) {
-            mine = nominal = 0;
+            mine = 0;
             for (uint32_t rest = w; rest != 0u; rest &= rest - 1u) {
                 const int k = hl * 32 + __ffs((int)rest) - 1;
-                const int c = (int)((hist[k >> 1] >> ((k & 1) << 4)) & 0xffffu);
-                mine += entries_of<Layout>(c);
-                nominal += nominal_entries(c, K);
+                mine += entries_of<Layout>((int)((hist[k >> 1] >> ((k & 1) << 4)) & 0xffffu));
             }
         }
         // prefix over the 32 lanes of each half: the wave-wide scan without its last step
@@ -657,20 +654,18 @@ __global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* do
         const int upto = half_inclusive_sum(mine);
         const int n_a = read_lane(upto, 31), n_b = read_lane(upto, 63);
         const int n_entries = half ? n_b : n_a;
-        int nnz = n_entries, n_nominal = n_entries;       // distinct topics of the row
-        if (__ballot(mine != distinct) != 0) {
-            const int d_upto = half_inclusive_sum(distinct), nominal_upto = half_inclusive_sum(nominal);
-            const int d_a = read_lane(d_upto, 31), d_b = read_lane(d_upto, 63);
-            const int m_a = read_lane(nominal_upto, 31), m_b = read_lane(nominal_upto, 63);
-            nnz = half ? d_b : d_a;
-            n_nominal = half ? m_b : m_a;
-        }
+        auto half_sum = [&](int v) {
+            const int v_upto = half_inclusive_sum(v), v_a = read_lane(v_upto, 31), v_b = read_lane(v_upto, 63);
+            return half ? v_b : v_a;
+        };
+        const bool any_split = __ballot(mine != distinct) != 0;
+        const int nnz = any_split ? half_sum(distinct) : n_entries;       // distinct topics of the row
         int at = upto - mine;
         if (w != 0u) marks[hl] = 0u;
         uint32_t pairs = (w | (w >> 1)) & 0x55555555u;
         const bool real = 2 * i + half < D;              // the last pair may lack its second document
         const int n_longer = max(n_a, n_b);
-        if ((kMore || __ballot(mine != distinct) == 0) && n_longer <= kPairStage) {
+        if ((kMore || !any_split) && n_longer <= kPairStage) {
             // The usual case: the lanes that own the bins only line the
             // entries up in LDS; the lanes then take them one each, so that the row leaves in
             // whole consecutive stores and the likelihood's term is added with all lanes busy.
@@ -696,6 +691,7 @@ __global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* do
                     const int lo = (int)(both & 0xffffu), hi = (int)(both >> 16);
                     if (lo != 0) at = line_up(at, k, lo);
                     if (hi != 0) at = line_up(at, k + 1, hi);
+                    if (!kMore) nominal += nominal_entries(lo, K) + nominal_entries(hi, K);
                 }
             }
             __syncthreads();
@@ -721,12 +717,14 @@ __global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* do
                     hi = (int)(both >> 16);
                     if (lo != 0) at = write_entries<Layout>(ent, at, k, lo);
                     if (hi != 0) at = write_entries<Layout>(ent, at, k + 1, hi);
+                    if (!kMore) nominal += nominal_entries(lo, K) + nominal_entries(hi, K);
                 }
                 add_ll(lo);
                 add_ll(hi);
             }
         }
         close_row<Layout>(head, n_entries, K, hl, real);
+        const int n_nominal = kMore && !any_split ? n_entries : half_sum(nominal);
         if (real && hl == 0) {
             row_rec[cur.doc].y = (uint32_t)nnz;          // distinct topics, for the getters
             visited += (unsigned long long)cur.n * (unsigned long long)n_nominal;

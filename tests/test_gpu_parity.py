@@ -519,6 +519,42 @@ def test_step_with_loglik_flag_and_timing(mlda):
     model.close()
 
 
+# (name, K, document lengths as (how many, tokens)): every way a row of theta is built for K <= 2048.
+# Counts are far beyond 15 (K < 1024) and 16,383 (K >= 1024).
+BYTES_CASES = [
+    ("four_byte_rows_two_documents_per_wave", 24,   [(60, 110)]),
+    ("four_byte_rows_one_wave",               24,   [(40, 600)]),
+    ("four_byte_rows_sixteen_waves",          50,   [(4, 6000)]),
+    ("four_byte_rows_wide_counters",          5,    [(2, 70000)]),
+    ("two_byte_rows_long_count",              1500, [(2000, 300), (1, 20000)]),
+    ("two_byte_rows_wide_counters",           2048, [(700, 1500), (1, 66000)]),
+]
+
+
+@pytest.mark.parametrize("case", BYTES_CASES, ids=[c[0] for c in BYTES_CASES])
+def test_sampler_bytes_in_every_row_layout(mlda, case):
+    """The algorithmic bytes are those of entries of up to 15 tokens (2 bytes, K < 1024) or 16,383
+    (4 bytes), whatever the entries of the layout in use hold."""
+    name, K, docs = case
+    V, alpha, beta = 60, 50.0 / K, 0.01
+    lens = np.concatenate([np.full(n, length, dtype=np.int64) for n, length in docs])
+    doc_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    rng = np.random.default_rng(len(name))
+    words = rng.integers(V, size=int(lens.sum())).astype(np.int32)
+    z = rng.integers(K, size=len(words)).astype(np.uint16)
+    z[doc_ptr[-2]:doc_ptr[-1]] = K // 2           # the last document sits in one topic
+    model = mlda.Mlda(doc_ptr, words, V, K, alpha, beta, SEED)
+    model.set_assignments(z)
+    model.step(1)
+    row_ptr, _, counts = oracle.doc_topic_csr(doc_ptr, z, K)
+    entries = np.add.reduceat(-(-counts.astype(np.int64) // (15 if K < 1024 else 16383)), row_ptr[:-1])
+    per_word = np.bincount(words, minlength=V)
+    want = (16.0 * len(words) + (2.0 if K < 1024 else 4.0) * float((lens * entries).sum())
+            + K * (2.0 * np.ceil(per_word / 1024).sum() + 2.0 * np.ceil(per_word[per_word >= 2**16] / 1024).sum()))
+    assert model.sampler_bytes()[-1] == want
+    model.close()
+
+
 def test_sampler_bytes_with_runs_of_small_words(mlda):
     """K > 2048: the words of at most 1024 tokens are sampled in runs of 16 and count 6 bytes per
     token instead of a row of phi each, but for the first word of every run."""
