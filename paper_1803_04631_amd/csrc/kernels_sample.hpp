@@ -101,9 +101,9 @@ struct __align__(16) TokenRec { // per-lane phase -> per-group phase, 32 bytes
     uint32_t off;               // slot offset of the token's theta row, 16-byte units
     int32_t nnz;                // 16-byte units of entries of the row
     int32_t o;                  // current topic
-    float w_o;                  // p*(o) with the token itself removed, times kSumScale where p* is fp64
+    float w_o;                  // p*(o) with the token itself removed
     double u;
-    double Qp;                  // alpha * sum_k p*'(k), scaled the same
+    double Qp;                  // alpha * sum_k p*'(k), times kSumScale where p* is fp64
 };
 constexpr int kDrawInUnit = -1; // off = the 16-byte unit of the slot buffer that holds the draw,
                                 // u = what is left of the draw at the unit's start
@@ -134,11 +134,11 @@ constexpr int kRunTileTokens = 1024;    // a tile of a run holds a whole word of
 // A count becomes a factor without a conversion: its bits, taken as the upper dword of a double
 // whose lower dword is zero, are the denormal number count * kCountUnit.  The weights staged in
 // LDS carry kWeightScale, so a product (exact, as before) is count * p* * kSumScale: powers of two
-// that change no rounding anywhere.  p* < 1, hence a weight stays finite; p* > 2^-60 or so, hence
-// no product comes near the denormal numbers again.
+// that change no rounding anywhere.  p* <= 1, hence a weight stays finite; an fp32 p* other than 0
+// is at least 2^-149, hence no product comes near the denormal numbers again.
 constexpr double kWeightScale = 0x1p1000;
 constexpr double kCountUnit = 0x1p-1042;
-constexpr double kSumScale = 0x1p-42;
+constexpr double kSumScale = kWeightScale * kCountUnit;
 
 // A staged weight of either form without its scale.
 __device__ __forceinline__ double plain_weight(float w) { return (double)w; }
@@ -274,8 +274,8 @@ struct PackedRowsShort : PackedRows {
 };
 
 // The two layouts of K <= 2048, whose p* is staged in fp64.  An entry holds its topic above its
-// count: entries of a row rise as numbers, and "entry - (o, 0)", as an unsigned number, is at most
-// kMaxCount for the entries of topic o only, and is their count.
+// count: entries of a row rise as numbers, and "(o, kMaxCount) - entry", as an unsigned number, is at
+// most kMaxCount for the entries of topic o only.
 //
 // 2 bytes per entry: topic << 3 | count (13 bits of topic, 3 of count).
 struct TinyRows {
@@ -306,16 +306,17 @@ struct TinyRows {
         const uint32_t d = word(u, j >> 1);
         return (j & 1) ? (int)__builtin_amdgcn_ubfe(d, 16, 3) : (int)(d & 7u);
     }
-    // the tokens of topic o in a unit: of the differences to (o, 0), 8 or more counts nothing
-    static __device__ __forceinline__ uint32_t tokens_of(const uint4& u, int o) {
-        const Pair own = Pair((uint16_t)make(0, o)), none = Pair(8), one = Pair(1);
-        uint32_t n = 0;
+    // The entries of topic o lose their tokens, which are added to n: of the distances to (o, 7), as
+    // unsigned numbers, those of 7 and less are the entries of o, and what they lack to 7 the count.
+    static __device__ __forceinline__ void take_out(uint4& u, int o, uint32_t& n) {
+        const Pair most = Pair((uint16_t)make(kMaxCount, o)), one = Pair(1);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const Pair x = __builtin_elementwise_min(__builtin_bit_cast(Pair, word(u, i)) - own, none);
-            n = __builtin_amdgcn_udot2(__builtin_bit_cast(Pair, __builtin_bit_cast(uint32_t, x) & 0x00070007u), one, n, false);
+            uint32_t& d = i == 0 ? u.x : i == 1 ? u.y : i == 2 ? u.z : u.w;
+            const Pair own = __builtin_elementwise_sub_sat(Pair(kMaxCount), most - __builtin_bit_cast(Pair, d));
+            n = __builtin_amdgcn_udot2(own, one, n, false);
+            d -= __builtin_bit_cast(uint32_t, own);         // (no half below zero: own is its count, or 0)
         }
-        return n;
     }
     // acc += count * weight over the eight entries, in their order
     static __device__ __forceinline__ void add_products(const uint4& u, const double* w, double& acc) {
@@ -353,11 +354,15 @@ struct CountedRows {
     static __device__ __forceinline__ int key_of_topic(int k) { return k << 3; }
     static __device__ __forceinline__ int key(const uint4& u, int j) { return (int)(word(u, j) >> 13); }
     static __device__ __forceinline__ int count(const uint4& u, int j) { return (int)(word(u, j) & 0x1fffu); }
-    static __device__ __forceinline__ uint32_t tokens_of(const uint4& u, int o) {
-        uint32_t n = 0;
+    static __device__ __forceinline__ void take_out(uint4& u, int o, uint32_t& n) {     // as above
+        const uint32_t most = make(kMaxCount, o);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) n += entry_topic(word(u, j)) == o ? (uint32_t)entry_count(word(u, j)) : 0u;
-        return n;
+        for (int i = 0; i < 4; ++i) {
+            uint32_t& d = i == 0 ? u.x : i == 1 ? u.y : i == 2 ? u.z : u.w;
+            const uint32_t own = __builtin_elementwise_sub_sat((uint32_t)kMaxCount, most - d);
+            n += own;
+            d -= own;
+        }
     }
     static __device__ __forceinline__ void add_products(const uint4& u, const double* w, double& acc) {
         asm("v_mov_b32 v72, 0\n\tv_mov_b32 v74, 0\n\t"
@@ -637,27 +642,16 @@ __device__ __forceinline__ void row_pass_kept(const Weights& weight_at, TokenRec
 // ---- the walk with fp64 weights (kDoubleWeights).  VALU issue bounds the walk (85 % of the SIMDs'
 // cycles on 7.4e8 tokens at K = 1,000), so what counts is instructions per entry.  With fp32
 // weights an entry takes seven: key, count, two conversions to fp64, a comparison with the own
-// topic and a select, fma.  Here it takes three (key, count, fma): all entries are added with
-// p*(o) and their whole count, and what the token's own topic with its n tokens changes,
-// n (w_o - p*(o)) - w_o, is added where its unit ends, by the lane that has the unit.  An 8-byte
-// gather from random places of LDS costs what a 4-byte one does (7.4 cycles per wave and CU).
-// Measured, sampling launch: K = 1,000, 7.4e8 tokens 32.1 -> 29.8 ms; K = 1,537, 6.3e6 tokens
-// 0.61 -> 0.55 ms.  Looking for the own topic in every dword instead: 30.4 ms; finding its unit
-// before the passes, one token per lane: 37.9 ms (two or three more scattered loads per token);
-// four and six waves per SIMD: 32.6 and 30.5 ms.
-
-// What the lane adds at the end of each of its units for the own topic's entries met so far, in
-// a pass in which some token's own topic is spread over several units of a lane: every unit is
-// looked through.
-template <class Layout, int kUnits>
-__device__ __forceinline__ void own_share(const uint4* raw, int o, double delta, double once, double* add) {
-    uint32_t n = 0;
-#pragma unroll
-    for (int c = 0; c < kUnits; ++c) {
-        n += Layout::tokens_of(raw[c], o);
-        add[c] = n > 0 ? fma((double)n, delta, -once) : 0.0;
-    }
-}
+// topic and a select, fma.  Here it takes three (key, count, fma), and two (4-byte entries: four) for
+// the token's own topic: its entries are taken out of the row first, so that p*(o) is in no sum.  (It
+// may be any number of times larger than all the rest: 1 / beta times for a word seen once.)  Its
+// tokens, without the one that is sampled, weigh w_o where the unit ends.
+// An 8-byte gather from random places of LDS costs what a 4-byte one does (7.4 cycles per wave and CU).
+// Measured, sampling launch: fp32 weights 32.1 ms for 7.4e8 tokens at K = 1,000 and 6.65 ms for 9.9e7
+// late in training, this walk 30.5 and 6.36 ms.  The own topic added with p*(o) and corrected where its
+// unit ends: 30.3 and 6.61 ms (split rows went a longer way), and a fifth of the draws wrong at
+// beta = 1e-30.  Finding its unit before the passes, one token per lane: 37.9 ms (two or three more
+// scattered loads per token); four and six waves per SIMD: 32.6 and 30.5 ms.
 
 // acc += count * weight over the entries of one unit.
 template <class Layout>
@@ -668,54 +662,35 @@ __device__ __forceinline__ void unit_sum_plain(const uint4& raw, double& acc) {
     Layout::add_products(raw, w, acc);
 }
 
+// The sum at the end of a unit whose sum without the own topic is `others`, `n` the own topic's
+// tokens up to there: one less where the lane has the topic's first entry (`itself` = 1), whose
+// count holds the token itself.
+__device__ __forceinline__ double with_own_topic(double others, uint32_t n, uint32_t itself, double w_o) {
+    return fma(__hiloint2double((int)__builtin_elementwise_sub_sat(n, itself), 0), w_o, others);
+}
+
 template <class Layout, int kLanes, int kUnits>
 __device__ __forceinline__ void row_pass_double(TokenRec* rec, int sl, const uint4* raw, int lane) {
     const int4 head = *reinterpret_cast<const int4*>(rec);     // off, units, o, w_o
     const uint32_t off = (uint32_t)head.x;
     const int own_key = Layout::key_of_topic(head.z), first_unit = sl * kUnits;
-    const double w_o = (double)__int_as_float(head.w);
-    const double delta = fma(lds_double_at((uint32_t)own_key), -kCountUnit, w_o);       // w_o - p*(o)
-    double at_end[kUnits], add[kUnits];
+    const double w_o = kWeightScale * (double)__int_as_float(head.w);       // as the staged weights
+    // the topic's first entry is this lane's unless the previous sub-lane's last one is of the topic
+    const int before = group_previous_int<kLanes>(Layout::key(raw[kUnits - 1], Layout::kUnitEntries - 1));
+    const uint32_t itself = sl > 0 && before == own_key ? 0u : 1u;
+    double at_end[kUnits];
     double acc = 0.0;
+    uint32_t n_own = 0;
 #pragma unroll
     for (int c = 0; c < kUnits; ++c) {
-        unit_sum_plain<Layout>(raw[c], acc);
-        at_end[c] = acc;
+        uint4 unit = raw[c];
+        Layout::take_out(unit, head.z, n_own);
+        unit_sum_plain<Layout>(unit, acc);
+        at_end[c] = with_own_topic(acc, n_own, itself, w_o);
     }
-    // The own topic's entries lie in the first unit whose last topic is not below it ...
-    auto first_key = [&](int c) { return Layout::key(raw[c], 0); };
-    auto last_key = [&](int c) { return Layout::key(raw[c], Layout::kUnitEntries - 1); };
-    bool reached[kUnits];
-#pragma unroll
-    for (int c = 0; c < kUnits; ++c) reached[c] = c == kUnits - 1 || last_key(c) >= own_key;
-    uint4 unit_of_own = raw[kUnits - 1];
-#pragma unroll
-    for (int c = kUnits - 2; c >= 0; --c) {
-        unit_of_own.x = reached[c] ? raw[c].x : unit_of_own.x;
-        unit_of_own.y = reached[c] ? raw[c].y : unit_of_own.y;
-        unit_of_own.z = reached[c] ? raw[c].z : unit_of_own.z;
-        unit_of_own.w = reached[c] ? raw[c].w : unit_of_own.w;
-    }
-    const uint32_t n_own = Layout::tokens_of(unit_of_own, head.z);
-    // (the token itself is taken out by the lane that has the topic's first entry: not if the
-    // previous sub-lane's last entry is of the topic too)
-    const int before = group_previous_int<kLanes>(last_key(kUnits - 1));
-    const double once = sl > 0 && before == own_key ? 0.0 : w_o;
-    double share = fma((double)n_own, delta, -once);
-    share = n_own > 0 ? share : 0.0;
-#pragma unroll
-    for (int c = 0; c < kUnits; ++c) add[c] = reached[c] ? share : 0.0;
-    // ... but for a topic spread over entries on both sides of an end between two units of the lane
-    bool spread = false;
-#pragma unroll
-    for (int c = 1; c < kUnits; ++c) spread |= last_key(c - 1) == own_key && first_key(c) == own_key;
-    if (kUnits > 1 && __builtin_expect(__ballot(spread) != 0, 0))
-        own_share<Layout, kUnits>(raw, head.z, delta, once, add);
-#pragma unroll
-    for (int c = 0; c < kUnits; ++c) at_end[c] += add[c];
     acc = at_end[kUnits - 1];
     const RowDraw d = row_draw<kLanes>(acc, rec, sl, lane);
-    // first unit whose end exceeds y, and the sum before it
+    // first unit whose end exceeds y (the sums never decrease), and the sum before it
     int unit = kUnits - 1;
 #pragma unroll
     for (int c = kUnits - 2; c >= 0; --c)
@@ -751,17 +726,16 @@ __device__ __forceinline__ void row_pass_double_long(const unsigned char* slots,
     const uint32_t off = (uint32_t)head.x;
     const int n_units = head.y, n = (n_units + kWave - 1) / kWave, u0 = lane * n;
     const int own_key = Layout::key_of_topic(head.z);
-    const double w_o = (double)__int_as_float(head.w);
-    const double delta = fma(lds_double_at((uint32_t)own_key), -kCountUnit, w_o);
+    const double w_o = kWeightScale * (double)__int_as_float(head.w);
     // the entry before the lane's first one (lanes past the row's end have no entries at all)
-    const bool leads = !(u0 < n_units &&
-        key_before_unit<Layout>(slots + ((size_t)off + 1u + (size_t)u0) * 16u) == own_key);
+    const uint32_t itself = u0 < n_units &&
+        key_before_unit<Layout>(slots + ((size_t)off + 1u + (size_t)u0) * 16u) == own_key ? 0u : 1u;
     uint32_t own = 0;
-    double plain = 0.0;
-    auto next_end = [&](const uint4& raw) {       // the sum at the end of this unit
-        unit_sum_plain<Layout>(raw, plain);
-        own += Layout::tokens_of(raw, head.z);
-        return plain + (own > 0 ? fma((double)own, delta, leads ? -w_o : 0.0) : 0.0);
+    double others = 0.0;
+    auto next_end = [&](uint4 unit) {       // the sum at the end of this unit
+        Layout::take_out(unit, head.z, own);
+        unit_sum_plain<Layout>(unit, others);
+        return with_own_topic(others, own, itself, w_o);
     };
     double acc = 0.0;
     for (int c = 0; c < n; ++c) acc = next_end(load_unit(slots, off, u0 + c, u0 + c < n_units));
@@ -771,7 +745,7 @@ __device__ __forceinline__ void row_pass_double_long(const unsigned char* slots,
         int unit = 0, last_unit = 0;
         double base = 0.0, last_base = 0.0, before = 0.0;
         own = 0;
-        plain = 0.0;
+        others = 0.0;
         for (int c = 0; c < n; ++c) {
             const double end = next_end(load_unit(slots, off, u0 + c, d.hit && u0 + c < n_units));
             if (!found && end > d.y) { unit = c; base = before; found = true; }
@@ -797,7 +771,7 @@ __device__ __forceinline__ int topic_in_unit_double(const unsigned char* slots, 
     const unsigned char* p = kNear ? slots + (size_t)(uint32_t)(unit << 4) : slots + (size_t)unit * 16u;
     const uint4 raw = *reinterpret_cast<const uint4*>(p);
     const int own_key = Layout::key_of_topic(o);
-    const double w_o = kWeightScale * ((double)w_o_f * (1.0 / kSumScale));    // with the staged weights' scale
+    const double w_o = kWeightScale * (double)w_o_f;    // as the staged weights
     bool prev_own = key_before_unit<Layout>(p) == own_key;
     double acc = 0.0;
     int found = -1, last = Layout::key(raw, 0);     // keys: the first above y, the last with weight
@@ -1083,7 +1057,6 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             mine.w_o = (float)(((double)(phi_own - 1) + ka->beta) /
                                ((double)(ka->n_k[mine.o] - 1) + ka->beta_V));
             delta = (double)mine.w_o - plain_weight(pstar[mine.o]);
-            mine.w_o *= (float)kRowScale;
             // cp[ng - 1] = sum_k p*(k), read from LDS where it is needed; Q = alpha sum (Eq. 7)
             mine.Qp = kRowScale * (ka->alpha * (cp[ng - 1] + delta));
         }
@@ -1233,7 +1206,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                                                          __int_as_float(head.w), rec->u);
             }
             if (head.y == kDrawDense) {
-                const float w_o = __int_as_float(head.w) * (float)(1.0 / kRowScale);
+                const float w_o = __int_as_float(head.w);
                 z_new = dense_bucket_search<kGroup>(pstar, cp, K, ng, ka->alpha, rec->u * (1.0 / kRowScale), head.z,
                                                     w_o, (double)w_o - plain_weight(pstar[head.z]));
             }

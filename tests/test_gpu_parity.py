@@ -172,6 +172,40 @@ def test_row_layouts(mlda, case, wide_offsets, monkeypatch):
     model.close()
 
 
+# Rows of every way the walk over fp64 weights goes: (name, K, documents, tokens each).
+SMALL_BETA_CASES = [
+    ("two_byte_rows",         24,   400, 50),
+    ("two_byte_rows_wider",   300,  60,  400),
+    ("two_byte_longest_rows", 2000, 3,   5000),
+    ("four_byte_rows",        24,   40,  600),
+    ("four_byte_longest_rows", 2000, 2,  17000),
+]
+
+
+@pytest.mark.parametrize("beta", [1e-10, 1e-14, 1e-30])
+@pytest.mark.parametrize("case", SMALL_BETA_CASES, ids=[c[0] for c in SMALL_BETA_CASES])
+def test_small_beta(mlda, case, beta):
+    """Words seen once or twice under a beta far below 1: p* of the token's own topic is 1/beta
+    times what is left of it without the token, and than the other topics'.  A sum that held it and
+    gave it back would have nothing left of the rest; alpha is so small that the row decides.
+    (p* stays a normal fp32 number: beta / n_k > 1e-36.)"""
+    name, K, D, length = case
+    T, V = D * length, D * length // 2
+    rng = np.random.default_rng(K + D)
+
+    class C:  # minimal corpus record
+        pass
+    c = C(); c.doc_ptr = np.arange(D + 1, dtype=np.int64) * length; c.T = T
+    c.word_ids = rng.integers(V, size=T).astype(np.int32)
+    alpha = 1e-30
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, beta, SEED)
+    model.init_random()
+    z = oracle.init_topics(T, K, SEED)
+    for it in (1, 2):
+        z = check_step(model, c, z, V, K, alpha, beta, SEED, it)
+    model.close()
+
+
 @pytest.mark.parametrize("case", EDGE_CASES, ids=[c[0] for c in EDGE_CASES])
 def test_edge_shapes(mlda, case):
     name, D, V, K, mean_len = case
