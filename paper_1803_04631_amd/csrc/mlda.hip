@@ -1175,19 +1175,21 @@ template <class F>
 int through_ring(mlda_ctx* c, size_t bytes, F&& per_piece) {
     int device = 0;
     HIP_TRY(hipGetDevice(&device));
+    // This handle names another stream in every thread: what the caller's has queued must be done
+    // before the workers' copies start.
+    if (c->stream == hipStreamPerThread) HIP_TRY(hipStreamSynchronize(c->stream));
     hipError_t first_error[kRingWorkers];
     for (hipError_t& e : first_error) e = hipSuccess;
     const bool ran = parallel_chunks(kRingWorkers, [&](int w) {
         hipError_t e = hipSetDevice(device);
         for (size_t at = (size_t)w * kRingPiece; e == hipSuccess && at < bytes; at += kRingWorkers * kRingPiece)
             e = per_piece(c->ring + (size_t)w * kRingPiece, c->ring_events[(size_t)w], at, std::min(kRingPiece, bytes - at));
+        if (e != hipSuccess) (void)hipStreamSynchronize(c->stream);     // (no copy into the piece is left)
         first_error[w] = e;
     });
     for (hipError_t e : first_error)
-        if (e != hipSuccess) {
-            (void)hipStreamSynchronize(c->stream);
+        if (e != hipSuccess)
             return fail(MLDA_EHIP, std::string("copy between device and host: ") + hipGetErrorString(e));
-        }
     if (!ran) return fail(MLDA_ENOMEM, "out of host memory");
     return MLDA_OK;
 }

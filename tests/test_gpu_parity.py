@@ -474,6 +474,40 @@ def test_phi_cell_widths(mlda):
         model.close()
 
 
+@pytest.mark.parametrize("how", ["own_stream", "stream_per_thread", "streamed"])
+def test_large_transfers(mlda, how):
+    """Transfers of 8 MB and more go through eight pinned pieces of 2 MB, each with a thread of its own:
+    18 MB of assignments and row values and 9 MB of word counts here, so that a thread has several
+    pieces and the last one is short; a document of 70,000 tokens of one topic (counts of more than
+    16 bits are fetched in two halves), a word with 32-bit counts, empty documents.  The handle
+    hipStreamPerThread names another stream in every thread."""
+    import torch
+    V, K, alpha, beta = 70000, 64, 0.5, 0.01
+    rng = np.random.default_rng(7)
+    lens = rng.integers(0, 200, size=92000).astype(np.int64)
+    lens[::1000] = 0
+    lens[40000] = 70000
+
+    class C:  # minimal corpus record
+        pass
+    c = C(); c.doc_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    c.T = int(lens.sum())
+    assert 9.0e6 < c.T < 9.4e6 and c.T % (1 << 20) != 0
+    c.word_ids = rng.integers(V, size=c.T).astype(np.int32)
+    c.word_ids[rng.integers(c.T, size=100000)] = 3
+    z = rng.integers(K, size=c.T).astype(np.uint16)
+    z[c.doc_ptr[40000]:c.doc_ptr[40001]] = 5
+    stream = torch.cuda.ExternalStream(2) if how == "stream_per_thread" else torch.cuda.current_stream()
+    with torch.cuda.stream(stream):
+        model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, beta, SEED, chunks=2 if how == "streamed" else 1)
+        assert how != "stream_per_thread" or model.stream.cuda_stream == 2
+        model.set_assignments(z)
+        assert np.array_equal(model.assignments(), z)
+        check_counts(model, c, z, V, K)
+        check_step(model, c, z, V, K, alpha, beta, SEED, 1)
+        model.close()
+
+
 def test_empty_corpus(mlda):
     doc_ptr = np.zeros(4, dtype=np.int64)
     model = mlda.Mlda(doc_ptr, np.zeros(0, dtype=np.int32), 5, 3, 0.5, 0.01, 1)
