@@ -284,15 +284,17 @@ __device__ __forceinline__ int nominal_entries(int c, int K) {
     return K < 1024 ? (c + 14) / 15 : (c + 16382) / 16383;
 }
 
-// 2-byte entries hold counts up to 7 only, and rows with larger ones are common.  Their entries
+// 2-byte entries hold counts up to 7 (31, 63) only, and rows with larger ones are common.  Their entries
 // are counted while the tokens are: the token that is one more than a multiple of kMaxCount (of 15
 // or 16,383) begins another entry (another nominal one).  Added to the counter of the topic's 32, the
 // entries in the lower half, the nominal ones in the upper (fewer than 2^16 tokens: neither
 // overflows).  Against looking every bin of such a row up again: 7.2 -> 6.05 ms for 8.2e6 documents
 // of 90 tokens at K = 1,000.
+// kPlainCount: a count up to which a topic of a row is one entry, and one nominal entry.
+template <class Layout> constexpr int kPlainCount = Layout::kEntryBytes == 2 && Layout::kMaxCount > 15 ? 15 : Layout::kMaxCount;
 template <class Layout>
 __device__ __forceinline__ void more_entries(uint32_t* more, int k, int before, int K) {
-    if (before >= Layout::kMaxCount) {
+    if (before >= kPlainCount<Layout>) {
         const uint32_t another = before % Layout::kMaxCount == 0 ? 1u : 0u;
         const uint32_t nominal = (K < 1024 ? before % 15 : before % 16383) == 0 ? 1u << 16 : 0u;
         if (another | nominal) atomicAdd(&more[k >> 5], another | nominal);
@@ -323,7 +325,7 @@ __device__ __forceinline__ void close_row(unsigned char* head, int n_entries, in
 // (record -> map -> z), so it is software-pipelined: while the current document is counted,
 // the topics of the wave's next document, the map entries of the one after and the record
 // after that are already on their way.  Rows are written in the layout the sampler reads
-// (PackedRows or TinyRows, see kernels_sample.hpp).  The compaction visits only the 32-topic
+// (see kernels_sample.hpp).  The compaction visits only the 32-topic
 // groups that hold a non-zero bin (one mark bit per topic), so its cost follows the row's
 // length rather than K.  While the counts pass through registers the kernel also adds up the
 // theta entries' term of the log-likelihood, sum_{d,k} lgG(n_dk + alpha) - lgG(alpha), one
@@ -380,13 +382,13 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
                 ll += c < kLgTable ? lg_table[c] : lgamma_large((double)c + alpha) - lg_alpha;
         }
     };
-    // one more token of topic k; true if the topic's count has outgrown one entry
+    // one more token of topic k; true if the topic's count has outgrown one entry (kPlainCount)
     auto count_topic = [&](int k) -> bool {
         atomicOr(&marks[k >> 5], 1u << (k & 31));
-        if (kWide) return (int)atomicAdd(&hist[k], 1u) >= Layout::kMaxCount;
+        if (kWide) return (int)atomicAdd(&hist[k], 1u) >= kPlainCount<Layout>;
         const int before = (int)((atomicAdd(&hist[k >> 1], 1u << ((k & 1) << 4)) >> ((k & 1) << 4)) & 0xffffu);
         if constexpr (kMore) more_entries<Layout>(more, k, before, K);
-        return before >= Layout::kMaxCount;
+        return before >= kPlainCount<Layout>;
     };
     // the same for a document too short for that (the atomics then return nothing)
     auto count_topic_short = [&](int k) {
@@ -430,7 +432,7 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
         const int q1 = doc_token_position_any(doc_map, after, me + width);
         const DocRec later = record(i + 3 * step);
 
-        const bool long_doc = cur.n > Layout::kMaxCount;     // (the same for the whole wave)
+        const bool long_doc = cur.n > kPlainCount<Layout>;     // (the same for the whole wave)
         unsigned char* head = slots + (size_t)cur.slot * 16u;
         Entry* ent = reinterpret_cast<Entry*>(head + kRowHeader);
         int filled = 0, distinct = 0, nominal = 0;
@@ -590,13 +592,13 @@ __global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* do
                 ll += c < kLgTable ? lg_table[c] : lgamma_large((double)c + alpha) - lg_alpha;
         }
     };
-    // one more token of topic k; true if the topic's count has outgrown one entry
+    // one more token of topic k; true if the topic's count has outgrown one entry (kPlainCount)
     auto count_topic = [&](int k) -> bool {
         const uint32_t both = atomicAdd(&hist[k >> 1], 1u << ((k & 1) << 4));
         atomicOr(&marks[k >> 5], 1u << (k & 31));
         const int before = (int)((both >> ((k & 1) << 4)) & 0xffffu);
         if constexpr (kMore) more_entries<Layout>(more, k, before, K);
-        return before >= Layout::kMaxCount;
+        return before >= kPlainCount<Layout>;
     };
     auto topic_at = [&](const DocRec& r, int j) {       // topic of the document's token j, -1 past its end
         const int p = doc_token_position(doc_map, r, j);
@@ -630,12 +632,13 @@ __global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* do
         const uint32_t w = hl < n_marks ? marks[hl] : 0u;
         const int distinct = __popc(w);
         int mine = distinct, nominal = kMore ? distinct : 0;
-        if (kMore && __ballot(outgrown) != 0) {      // some count of the pair takes several entries
+        const bool any_outgrown = __ballot(outgrown) != 0;
+        if (kMore && any_outgrown) {                 // some count of the pair takes several entries
             const uint32_t m = more[hl];
             mine += (int)(m & 0xffffu);
             nominal += (int)(m >> 16);
             if (m != 0u) more[hl] = 0u;
-        } else if (__ballot(outgrown) != 0) {
+        } else if (any_outgrown) {
             mine = 0;
             for (uint32_t rest = w; rest != 0u; rest &= rest - 1u) {
                 const int k = hl * 32 + __ffs((int)rest) - 1;
@@ -724,7 +727,7 @@ __global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* do
             }
         }
         close_row<Layout>(head, n_entries, K, hl, real);
-        const int n_nominal = kMore && !any_split ? n_entries : half_sum(nominal);
+        const int n_nominal = kMore && !any_outgrown ? n_entries : half_sum(nominal);
         if (real && hl == 0) {
             row_rec[cur.doc].y = (uint32_t)nnz;          // distinct topics, for the getters
             visited += (unsigned long long)cur.n * (unsigned long long)n_nominal;

@@ -30,7 +30,7 @@
 //     results travel between the per-lane and per-group phases through small per-wave LDS
 //     records;
 //   - a theta row is a run of entries (topic, count) in ascending topic order, 2 bytes each
-//     where K <= 2048 (13 bits of topic, 3 of count; 4 bytes for long documents over few topics),
+//     where K <= 2048 (3, 5 or 6 bits of count; 4 bytes for long documents over few topics),
 //     else 4 bytes (16 bits of topic, 14 of count); a count too large for its field is written
 //     as several entries of the same topic, one after the other, which changes no sum.  Only
 //     the first entry of the token's own topic gives up the token itself;
@@ -69,7 +69,7 @@ struct SampleArgs {
     uint16_t* z_next;           // [T] word-major, written
     // theta rows: a slot (offset in 16-byte units) starts with a header of kRowHeader bytes
     // whose first word is the row's number of entries and whose last bytes are a padding
-    // entry, then holds the entries in one of the two layouts below (PackedRows / TinyRows),
+    // entry, then holds the entries in one of the layouts below (PackedRows, TinyRows, CountedRows),
     // filled up to a whole 16-byte unit with padding entries (count 0, topic K)
     const unsigned char* slots;
     PhiView phi;
@@ -277,25 +277,31 @@ struct PackedRowsShort : PackedRows {
 // count: entries of a row rise as numbers, and "(o, kMaxCount) - entry", as an unsigned number, is at
 // most kMaxCount for the entries of topic o only.
 //
-// 2 bytes per entry: topic << 3 | count (13 bits of topic, 3 of count).
+// 2 bytes per entry: topic << kCountBits | count.  With three bits of count a topic's place in the
+// entry is the byte offset of its p*; with more of them (five for K < 2048, six for K < 1024: all that
+// the topics leave) a pair of entries is shifted there by one instruction more, which short documents
+// need not pay: row_kind_for.
+template <int kCountBits>
 struct TinyRows {
     typedef uint16_t Entry;
     static constexpr int kEntryBytes = 2, kUnitEntries = 8;
-    static constexpr int kMaxCount = 7;
+    static constexpr int kMaxCount = (1 << kCountBits) - 1;
+    static constexpr int kMaxK = (1 << (16 - kCountBits)) - 1;      // topics 0 .. K, K being the padding entries'
     static constexpr int kWavesPerSimd = 5;
     static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = true;
     typedef uint16_t Pair __attribute__((ext_vector_type(2)));
     static __host__ __device__ __forceinline__ Entry make(int count, int topic) {
-        return (Entry)(((uint32_t)topic << 3) | (uint32_t)count);
+        return (Entry)(((uint32_t)topic << kCountBits) | (uint32_t)count);
     }
-    static __host__ __device__ __forceinline__ int entry_topic(Entry e) { return (int)(e >> 3); }
-    static __host__ __device__ __forceinline__ int entry_count(Entry e) { return (int)(e & 7u); }
+    static __host__ __device__ __forceinline__ int entry_topic(Entry e) { return (int)(e >> kCountBits); }
+    static __host__ __device__ __forceinline__ int entry_count(Entry e) { return (int)(e & (uint32_t)kMaxCount); }
     static __device__ __forceinline__ uint32_t word(const uint4& u, int i) {
         return i == 0 ? u.x : i == 1 ? u.y : i == 2 ? u.z : u.w;
     }
     static __device__ __forceinline__ int key_of_topic(int k) { return k << 3; }
     static __device__ __forceinline__ int key(const uint4& u, int j) {
-        const uint32_t d = word(u, j >> 1);
+        const Pair both = __builtin_bit_cast(Pair, word(u, j >> 1));
+        const uint32_t d = __builtin_bit_cast(uint32_t, kCountBits > 3 ? both >> (uint16_t)(kCountBits - 3) : both);
         if ((j & 1) == 0) return (int)(d & 0xfff8u);
         uint32_t k;                 // the upper half, masked: one instruction
         asm("v_and_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD"
@@ -304,10 +310,11 @@ struct TinyRows {
     }
     static __device__ __forceinline__ int count(const uint4& u, int j) {
         const uint32_t d = word(u, j >> 1);
-        return (j & 1) ? (int)__builtin_amdgcn_ubfe(d, 16, 3) : (int)(d & 7u);
+        return (j & 1) ? (int)__builtin_amdgcn_ubfe(d, 16, kCountBits) : (int)(d & (uint32_t)kMaxCount);
     }
-    // The entries of topic o lose their tokens, which are added to n: of the distances to (o, 7), as
-    // unsigned numbers, those of 7 and less are the entries of o, and what they lack to 7 the count.
+    // The entries of topic o lose their tokens, which are added to n: of the distances to (o,
+    // kMaxCount), as unsigned numbers, those of kMaxCount and less are the entries of o, and what they
+    // lack to kMaxCount the count.
     static __device__ __forceinline__ void take_out(uint4& u, int o, uint32_t& n) {
         const Pair most = Pair((uint16_t)make(kMaxCount, o)), one = Pair(1);
 #pragma unroll
@@ -325,13 +332,13 @@ struct TinyRows {
     }
     static __device__ __forceinline__ void add_four(uint32_t d0, uint32_t d1, const double* w, double& acc) {
         asm("v_mov_b32 v72, 0\n\tv_mov_b32 v74, 0\n\t"
-            "v_and_b32 v73, 7, %1\n\tv_bfe_u32 v75, %1, 16, 3\n\t"
-            "v_fma_f64 %0, v[72:73], %3, %0\n\tv_and_b32 v73, 7, %2\n\t"
-            "v_fma_f64 %0, v[74:75], %4, %0\n\tv_bfe_u32 v75, %2, 16, 3\n\t"
+            "v_and_b32 v73, %7, %1\n\tv_bfe_u32 v75, %1, 16, %8\n\t"
+            "v_fma_f64 %0, v[72:73], %3, %0\n\tv_and_b32 v73, %7, %2\n\t"
+            "v_fma_f64 %0, v[74:75], %4, %0\n\tv_bfe_u32 v75, %2, 16, %8\n\t"
             "v_fma_f64 %0, v[72:73], %5, %0\n\t"
             "v_fma_f64 %0, v[74:75], %6, %0"
             : "+&v"(acc)
-            : "v"(d0), "v"(d1), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3])
+            : "v"(d0), "v"(d1), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "n"(kMaxCount), "n"(kCountBits)
             : "v72", "v73", "v74", "v75");
     }
 };

@@ -57,9 +57,21 @@ constexpr size_t kSlotAlign = 64;     // theta row slot alignment (bytes)
 int sample_waves_for(int32_t K) { return K <= 2048 ? 4 : 12; }
 
 // How a chunk's theta rows are laid out: 4-byte entries of any K for the workgroups of twelve
-// waves; for those of four (K <= 2048) 2-byte entries, or 4-byte entries with long counts.
-enum class RowKind { packed, tiny, counted };
+// waves; for those of four (K <= 2048) 2-byte entries with 3, 5 or 6 bits of count, or 4-byte
+// entries with long counts.
+enum class RowKind { packed, tiny3, tiny5, tiny6, counted };
 
+// f(layout) for the layout of that kind.
+template <class F>
+auto with_layout(RowKind rows, F&& f) {
+    switch (rows) {
+    case RowKind::tiny3: return f(mlda::TinyRows<3>());
+    case RowKind::tiny5: return f(mlda::TinyRows<5>());
+    case RowKind::tiny6: return f(mlda::TinyRows<6>());
+    case RowKind::counted: return f(mlda::CountedRows());
+    default: return f(mlda::PackedRows());
+    }
+}
 
 // What the sampler's LDS holds besides p* itself belongs to K as well: Kpad = K + 1 rounded up to
 // a multiple of the dense bucket's group (one zero entry of p* past the last topic: padding
@@ -82,10 +94,11 @@ bool far_weights_for(int32_t K) {
 template <bool kNear>
 const void* sample_kernel_of(int32_t K, RowKind rows, bool short_docs) {
     if (far_weights_for(K)) return (const void*)mlda::sample_kernel<12, mlda::PackedRows, true, kNear>;
-    if (rows == RowKind::tiny) return (const void*)mlda::sample_kernel<4, mlda::TinyRows, false, kNear>;
-    if (rows == RowKind::counted) return (const void*)mlda::sample_kernel<4, mlda::CountedRows, false, kNear>;
-    return short_docs ? (const void*)mlda::sample_kernel<12, mlda::PackedRowsShort, false, kNear>
-                      : (const void*)mlda::sample_kernel<12, mlda::PackedRows, false, kNear>;
+    if (rows == RowKind::packed && short_docs) return (const void*)mlda::sample_kernel<12, mlda::PackedRowsShort, false, kNear>;
+    return with_layout(rows, [](auto layout) {
+        typedef decltype(layout) Layout;
+        return (const void*)mlda::sample_kernel<Layout::kDoubleWeights ? 4 : 12, Layout, false, kNear>;
+    });
 }
 const void* sample_kernel_for(int32_t K, RowKind rows, bool short_docs, bool near) {
     return near ? sample_kernel_of<true>(K, rows, short_docs) : sample_kernel_of<false>(K, rows, short_docs);
@@ -97,20 +110,24 @@ bool slots_near(size_t slots_bytes) { return slots_bytes <= 0xffffffffull; }
 bool long_docs_for(int64_t D, int64_t T, int n_cus) {
     return D > 0 && D <= (int64_t)n_cus * 8 && T / D >= 4096;
 }
-template <class Layout, int kDocWaves>
-const void* theta_kernel_of(bool wide_counters) {
-    return wide_counters ? (const void*)mlda::theta_rows_kernel<Layout, true, kDocWaves>
-                         : (const void*)mlda::theta_rows_kernel<Layout, false, kDocWaves>;
-}
 template <int kDocWaves>
 const void* theta_kernel_with(RowKind rows, bool wide_counters) {
-    if (rows == RowKind::tiny) return theta_kernel_of<mlda::TinyRows, kDocWaves>(wide_counters);
-    if (rows == RowKind::counted) return theta_kernel_of<mlda::CountedRows, kDocWaves>(wide_counters);
-    return theta_kernel_of<mlda::PackedRows, kDocWaves>(wide_counters);
+    return with_layout(rows, [&](auto layout) {
+        typedef decltype(layout) Layout;
+        return wide_counters ? (const void*)mlda::theta_rows_kernel<Layout, true, kDocWaves>
+                             : (const void*)mlda::theta_rows_kernel<Layout, false, kDocWaves>;
+    });
 }
 const void* theta_kernel_for(RowKind rows, bool wide_counters, bool long_docs) {
     return long_docs ? theta_kernel_with<mlda::kLongDocWaves>(rows, wide_counters)
                      : theta_kernel_with<1>(rows, wide_counters);
+}
+// (two documents per wave; K <= kPairMaxK)
+const void* theta_pair_kernel_for(RowKind rows) {
+    return with_layout(rows, [](auto layout) -> const void* {
+        if constexpr (layout.kDoubleWeights) return (const void*)mlda::theta_rows_pair_kernel<decltype(layout)>;
+        return nullptr;
+    });
 }
 constexpr int kMaxTimedIters = 1024;
 constexpr int kRunTiles = 16;           // small tiles a workgroup of the large-K sampler takes one after the other
@@ -135,22 +152,44 @@ size_t slot_bytes_for(int64_t n, int32_t K, int entry_bytes, int max_count) {
     return align_up((size_t)mlda::kRowHeader + align_up((size_t)cap * (size_t)entry_bytes, 16), kSlotAlign);
 }
 
-// Layout of the theta rows of D documents.  2-byte entries read half the bytes and, eight to a
-// unit, take fewer passes; but a count above 7 takes several of them, and a row of a long document
-// over few topics becomes several times as long.  What counts is the entries that all tokens'
-// walks meet: 4-byte entries where the 2-byte ones could be more than kTinyGrowth times as many.
-// (311 documents of 30,000 tokens, K = 299: 22.7 ms per sampling launch with rows of 2-byte entries
-// that the widest pass shape does not hold, 1.5 ms with 4-byte ones.)
-constexpr double kTinyGrowth = 1.5;
+// Layout of the theta rows of D documents (K <= 2048), from their lengths: the rows themselves change
+// with every iteration, from spread over many topics at a random start to counts of many tokens.
+// 2-byte entries read half the bytes and, eight to a unit, take fewer passes; but a count beyond its
+// field takes several of them.  Measured, sampling launch on 5e6 tokens in equal documents, from a random
+// start / trained / concentrated (alpha = 0.05), us:
+//                               3 bits          5 or 6 bits       4 bytes
+//   K = 1,000, 100 tokens    234/ 224/ 219    242/ 228/ 219     285/ 269/ 263
+//             400            382/ 343/ 337    392/ 329/ 293     489/ 415/ 387
+//             800            613/ 485/ 474    585/ 358/ 348     810/ 449/ 429
+//          12,000           6386/5442/5625   1727/ 708/ 645    4214/ 720/ 569
+//   K = 300,  4,000          1186/1081/1082    628/ 344/ 267     845/ 385/ 196
+//          12,000           5357/5371/5244    623/ 594/ 466     865/ 409/ 206
+//   K = 2,000, 12,000        6573/5479/5562   4854/1198/1224    6294/ 854/ 949
+//   K = 24,   400             190/ 189/ 154    141/ 139/ 127     137/ 135/ 108
+// Three bits of count, an instruction less for two entries, where documents are short (what counts is the
+// length that a token meets) and few counts can outgrow them.  4 bytes where a row could have so
+// many more of the 2-byte entries (of six bits a quarter, of five 0.15 times as many), or where the topics
+// are so few that a row of either kind is worked on by four lanes.
+constexpr int kShortDocs = 400, kFewTopics = 32;
+constexpr double kTinyGrowth = 1.25, kTinyGrowth5 = 1.15;
 RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t K) {
     if (sample_waves_for(K) != 4) return RowKind::packed;
-    double tiny = 0.0, counted = 0.0;
+    const RowKind tiny = K <= mlda::TinyRows<6>::kMaxK ? RowKind::tiny6 : K <= mlda::TinyRows<5>::kMaxK ? RowKind::tiny5 : RowKind::tiny3;
+    const int max_count = with_layout(tiny, [](auto layout) { return layout.kMaxCount; });
+    // sums over the tokens: 1, their document's length, and the most entries its row can have
+    double tokens = 0.0, length = 0.0, counted = 0.0, tiny3 = 0.0, wider = 0.0;
     for (int64_t d = 0; d < D; ++d) {
         const int64_t n = doc_ptr[d + 1] - doc_ptr[d];
-        tiny += (double)n * (double)std::min<int64_t>(n, (int64_t)K + n / mlda::TinyRows::kMaxCount);
-        counted += (double)n * (double)std::min<int64_t>(n, K);
+        const double w = (double)n;
+        tokens += w;
+        length += w * (double)n;
+        counted += w * (double)std::min<int64_t>(n, K);
+        tiny3 += w * (double)std::min<int64_t>(n, (int64_t)K + n / mlda::TinyRows<3>::kMaxCount);
+        wider += w * (double)std::min<int64_t>(n, (int64_t)K + n / max_count);
     }
-    return tiny > kTinyGrowth * counted ? RowKind::counted : RowKind::tiny;
+    if (length <= kShortDocs * tokens && tiny3 <= kTinyGrowth * counted) return RowKind::tiny3;
+    if (K <= kFewTopics) return RowKind::counted;
+    return wider > (tiny == RowKind::tiny6 ? kTinyGrowth : kTinyGrowth5) * counted ? RowKind::counted : tiny;
 }
 
 constexpr int kLoglikBlocks = 2048;
@@ -313,10 +352,8 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
     h.wide_counters = longest_doc >= 65536;
     h.short_docs = longest_doc <= mlda::PackedRows::kMaxCount;
     h.rows = row_kind_for(doc_ptr_all + d_begin, D, K);
-    const int entry_bytes = h.rows == RowKind::tiny ? mlda::TinyRows::kEntryBytes : mlda::PackedRows::kEntryBytes;
-    const int max_count = h.rows == RowKind::tiny      ? mlda::TinyRows::kMaxCount
-                          : h.rows == RowKind::counted ? mlda::CountedRows::kMaxCount
-                                                       : mlda::PackedRows::kMaxCount;
+    const int entry_bytes = with_layout(h.rows, [](auto layout) { return layout.kEntryBytes; });
+    const int max_count = with_layout(h.rows, [](auto layout) { return layout.kMaxCount; });
 
     std::vector<int32_t> doc_order;              // documents by falling length
     std::vector<int64_t> order_tokens;           // tokens before each position of doc_order
@@ -686,9 +723,9 @@ void derive_chunk_arrays(mlda_ctx* c) {
         hipLaunchKernelGGL(mlda::sort_doc_map_kernel, dim3((unsigned)grid), dim3(mlda::kWave), 0, c->stream,
                            c->doc_order, c->D, c->doc_map);
     }
-    const uint32_t pad = c->rows == RowKind::tiny      ? (uint32_t)mlda::TinyRows::make(0, c->K) * 0x10001u
-                         : c->rows == RowKind::counted ? (uint32_t)mlda::CountedRows::make(0, c->K)
-                                                       : (uint32_t)mlda::PackedRows::make(0, c->K);
+    const uint32_t pad = with_layout(c->rows, [&](auto layout) {
+        return (uint32_t)layout.make(0, c->K) * (layout.kEntryBytes == 2 ? 0x10001u : 1u);
+    });
     static_assert(kSlotAlign >= (mlda::kKeptUnits + 1) * 16, "the padding units lie before the first slot");
     hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(1), dim3(256), 0, c->stream, (int32_t*)c->slots,
                        (int64_t)(kSlotAlign / 4), (int32_t)pad);
@@ -835,9 +872,7 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
         const bool pairs = c->K <= kPairMaxK && !c->wide_counters && c->T <= 160 * c->D;
         const bool long_docs = long_docs_for(c->D, c->T, c->n_cus);
         const void* kernel =
-            !pairs                      ? theta_kernel_for(c->rows, c->wide_counters, long_docs)
-            : c->rows == RowKind::tiny ? (const void*)theta_rows_pair_kernel<TinyRows>
-                                       : (const void*)theta_rows_pair_kernel<CountedRows>;
+            pairs ? theta_pair_kernel_for(c->rows) : theta_kernel_for(c->rows, c->wide_counters, long_docs);
         const size_t lds = pairs ? theta_pair_lds_bytes(c->K) : theta_lds;
         const DocRec* docs = c->doc_order;
         uint2* row_rec = c->row_rec;
@@ -1774,9 +1809,7 @@ int mlda_get_doc_topic_csr(mlda_ctx* c, int64_t* row_ptr, uint16_t* topics, int3
         for (int64_t d = 0; d < c->D; ++d) ptr[d + 1] = ptr[d] + rec[(size_t)d].y;
         if (ptr[c->D] > ptr[0] && (!topics || !counts)) return fail(MLDA_EINVAL, "topics or counts is null");
         if (ptr[c->D] == ptr[0]) return (int)MLDA_OK;
-        if (c->rows == RowKind::tiny) return export_rows<mlda::TinyRows>(c, rec, ptr, topics, counts);
-        if (c->rows == RowKind::counted) return export_rows<mlda::CountedRows>(c, rec, ptr, topics, counts);
-        return export_rows<mlda::PackedRows>(c, rec, ptr, topics, counts);
+        return with_layout(c->rows, [&](auto layout) { return export_rows<decltype(layout)>(c, rec, ptr, topics, counts); });
     };
     if (c->streamed) {
         // chunks are visited in document order, so every chunk finds its first row start in place

@@ -124,34 +124,37 @@ EDGE_CASES = [
     ("k_beyond_lds",         40,  300,  31000, 400),
     ("k_beyond_lds_many_words", 200, 1500, 33000, 40),
     ("k_largest",            30,  200,  65535, 300),
-    # long documents over few topics: counts far beyond one entry's field are spread over
-    # several entries of the same topic (2-byte entries hold counts up to 15)
+    # long documents over few topics: counts up to 1,000 in 4-byte entries
     ("huge_docs_split_rows", 3,   400,  700, 17000),
     ("huge_docs_few_topics", 4,   50,   24,  16500),
-    # rows too long for the kept pass shapes: walked twice by a whole wave (4-byte and 2-byte entries)
+    # rows too long for the kept pass shapes: walked twice by a whole wave
     ("rows_over_768",        6,   300,  1200, 9000),
     ("rows_over_768_split",  3,   300,  1100, 17500),
-    ("rows_near_k_tiny",     3,   300,  1023, 30000),     # the largest K of the 2-byte entries
-    ("k_first_packed",       30,  300,  1024, 400),       # the smallest K of the 4-byte entries
+    ("rows_near_k_1023",     3,   300,  1023, 30000),
+    # 2-byte entries with six bits of count up to K = 1,023, five up to 2,047, three at 2,048
+    ("k_last_six_bits",      30,  300,  1023, 600),
+    ("k_first_five_bits",    30,  300,  1024, 400),
+    ("k_last_five_bits",     30,  300,  2047, 600),
+    ("k_2048_three_bits",    30,  300,  2048, 600),
 ]
 
 
 # Where the layouts of a theta row meet: (name, D, V, K, mean length).  Up to K = 2048 a row has 2-byte
-# entries with counts up to 7, or 4-byte entries with counts up to 8,191 where the 2-byte ones could
-# be more than 1.5 times as many.
+# entries with three bits of count (short documents), six (K < 1024) or five (K < 2048), or, for documents
+# long beside the topics, 4-byte entries with counts up to 8,191; beyond, 4-byte entries with 16,383.
 LAYOUT_CASES = [
-    ("tiny_many_splits",       60, 80,   24,   55),     # nearly every topic above 7 tokens, runs across units
-    ("tiny_runs_across_lanes", 25, 120,  200,  700),    # eight and more lanes to a row
+    ("counted_few_topics",     60, 80,   24,   55),
+    ("six_bits_wider_rows",    25, 120,  200,  700),    # eight and more lanes to a row
     ("counted_from_here",      60, 80,   24,   110),
     ("counted_splits",         2,  60,   2,    30000),  # counts beyond 8,191
     ("counted_wide_counters",  2,  60,   5,    70000),  # 2^16 tokens in a document
     ("counts_beyond_16_bits",  2,  40,   1,    70000),
-    ("tiny_long_docs",         3,  300,  2000, 5000),   # sixteen waves count a document together
+    ("five_bits_long_docs",    3,  300,  2000, 5000),   # sixteen waves count a document; beyond the widest shape
     ("packed_long_docs",       3,  300,  3000, 5000),
     ("k_one",                  20, 30,   1,    40),
     ("k_largest_fp64",         25, 200,  2048, 300),
     ("k_first_fp32",           25, 200,  2049, 300),
-    ("tiny_longest_rows",      4,  300,  2048, 2500),   # beyond the widest pass shape
+    ("counted_longest_rows",   4,  300,  2048, 2500),   # beyond the widest pass shape
 ]
 
 
@@ -172,10 +175,63 @@ def test_row_layouts(mlda, case, wide_offsets, monkeypatch):
     model.close()
 
 
+# (name, K, document lengths as (how many, tokens))
+SPLIT_CASES = [
+    ("three_bits",               1000, [(60, 300)]),
+    ("three_bits_pair_of_docs",  120,  [(200, 140)]),
+    ("five_bits",                1500, [(20, 1500)]),
+    ("six_bits",                 500,  [(20, 1500)]),
+    ("six_bits_pair_of_docs",    60,   [(200, 150)]),
+    ("six_bits_sixteen_waves",   1000, [(6, 5000)]),
+    ("six_bits_wide_counters",   1023, [(100, 4000), (1, 66000)]),
+    ("counted",                  24,   [(40, 600)]),
+    ("counted_sixteen_waves",    24,   [(4, 30000)]),
+    ("packed",                   3000, [(6, 40000)]),
+]
+
+
+@pytest.mark.parametrize("wide_offsets", ["0", "1"])
+@pytest.mark.parametrize("case", SPLIT_CASES, ids=[c[0] for c in SPLIT_CASES])
+def test_counts_at_the_ends_of_their_fields(mlda, case, wide_offsets, monkeypatch):
+    """Counts of exactly what an entry of each layout holds and one more (7, 15, 31, 63, 8,191, 16,383
+    and their doubles, as far as the document goes), the rest of the document in its first, a middle
+    and its last topic, so that a topic's entries run across units and lanes; beside documents
+    spread over all topics (rows beyond the widest shape where K is large)."""
+    monkeypatch.setenv("MLDA_WIDE_SLOT_OFFSETS", wide_offsets)
+    name, K, docs = case
+    V, alpha, beta = 60, 50.0 / K, 0.01
+    lens = np.concatenate([np.full(n, length, dtype=np.int64) for n, length in docs])
+
+    class C:  # minimal corpus record
+        pass
+    c = C(); c.doc_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64); c.T = int(lens.sum())
+    rng = np.random.default_rng(len(name))
+    c.word_ids = rng.integers(V, size=c.T).astype(np.int32)
+    z = rng.integers(K, size=c.T).astype(np.uint16)
+    for d, n in enumerate(lens):
+        if d % 2:
+            continue
+        row = np.empty(n, dtype=np.uint16)
+        at = 0
+        for k, count in enumerate([7, 8, 14, 15, 16, 31, 32, 63, 64, 126, 127, 8191, 8192, 16383, 16384]):
+            if at + count <= n // 2 or (count > 8000 and at + count <= n):
+                row[at:at + count] = 1 + k
+                at += count
+        row[at:] = rng.choice([0, K // 2, K - 1], size=n - at)
+        z[c.doc_ptr[d]:c.doc_ptr[d + 1]] = rng.permutation(row)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, beta, SEED)
+    model.set_assignments(z)
+    check_counts(model, c, z, V, K)
+    for it in (1, 2):
+        z = check_step(model, c, z, V, K, alpha, beta, SEED, it)
+    model.close()
+
+
 # Rows of every way the walk over fp64 weights goes: (name, K, documents, tokens each).
 SMALL_BETA_CASES = [
-    ("two_byte_rows",         24,   400, 50),
+    ("two_byte_rows",         60,   400, 50),
     ("two_byte_rows_wider",   300,  60,  400),
+    ("two_byte_rows_six_bits", 300, 20,  1000),
     ("two_byte_longest_rows", 2000, 3,   5000),
     ("four_byte_rows",        24,   40,  600),
     ("four_byte_longest_rows", 2000, 2,  17000),
@@ -221,8 +277,8 @@ def test_edge_shapes(mlda, case):
     model.close()
 
 
-@pytest.mark.parametrize("case", [("tiny_rows", 60, 90, 65, 300), ("packed_rows", 30, 300, 1024, 400),
-                                  ("packed_rows_long_docs", 3, 300, 1100, 17500),
+@pytest.mark.parametrize("case", [("six_bits", 60, 90, 65, 300), ("five_bits", 30, 300, 1024, 600),
+                                  ("counted_long_docs", 3, 300, 1100, 17500),
                                   ("large_k", 300, 2000, 10000, 120), ("k_beyond_lds", 40, 300, 31000, 400)],
                          ids=lambda c: c[0])
 def test_wide_slot_offsets(mlda, case, monkeypatch):
@@ -271,7 +327,7 @@ def test_long_document_with_more_topics_than_32bit_counters_fit(mlda):
 @pytest.mark.parametrize("K", [500, 1500])
 def test_counts_beyond_one_entry(mlda, K):
     """Documents whose tokens sit in one or two topics: counts of 20,000 to 70,000, which no entry
-    of a theta row holds (15 with 2-byte entries, K = 500; 16,383 with 4-byte entries, K = 1500),
+    of a theta row holds (8,191 at most),
     so that a topic takes several entries in a row, also across the lanes of the row walk; a
     document of 2^16 tokens or more needs 32-bit counters in the rebuild."""
     V = 60
@@ -595,7 +651,9 @@ BYTES_CASES = [
     ("four_byte_rows_sixteen_waves",          50,   [(4, 6000)]),
     ("four_byte_rows_wide_counters",          5,    [(2, 70000)]),
     ("two_byte_rows_long_count",              1500, [(2000, 300), (1, 20000)]),
-    ("two_byte_rows_wide_counters",           2048, [(700, 1500), (1, 66000)]),
+    ("two_byte_rows_wide_counters",           2048, [(2000, 1500), (1, 66000)]),
+    ("six_bits_two_documents_per_wave",       60,   [(200, 150)]),
+    ("six_bits_one_wave",                     300,  [(30, 1500)]),
 ]
 
 
