@@ -176,6 +176,7 @@ RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t K) {
     if (sample_waves_for(K) != 4) return RowKind::packed;
     const RowKind tiny = K <= mlda::TinyRows<6>::kMaxK ? RowKind::tiny6 : K <= mlda::TinyRows<5>::kMaxK ? RowKind::tiny5 : RowKind::tiny3;
     const int max_count = with_layout(tiny, [](auto layout) { return layout.kMaxCount; });
+    auto most_entries = [&](int64_t n, int max) { return (double)(n <= K ? n : std::min<int64_t>(n, (int64_t)K + n / max)); };
     // sums over the tokens: 1, their document's length, and the most entries its row can have
     double tokens = 0.0, length = 0.0, counted = 0.0, tiny3 = 0.0, wider = 0.0;
     for (int64_t d = 0; d < D; ++d) {
@@ -184,8 +185,8 @@ RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t K) {
         tokens += w;
         length += w * (double)n;
         counted += w * (double)std::min<int64_t>(n, K);
-        tiny3 += w * (double)std::min<int64_t>(n, (int64_t)K + n / mlda::TinyRows<3>::kMaxCount);
-        wider += w * (double)std::min<int64_t>(n, (int64_t)K + n / max_count);
+        tiny3 += w * most_entries(n, mlda::TinyRows<3>::kMaxCount);
+        wider += w * most_entries(n, max_count);
     }
     if (length <= kShortDocs * tokens && tiny3 <= kTinyGrowth * counted) return RowKind::tiny3;
     if (K <= kFewTopics) return RowKind::counted;
