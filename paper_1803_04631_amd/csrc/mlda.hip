@@ -104,11 +104,16 @@ const void* sample_kernel_for(int32_t K, RowKind rows, bool short_docs, bool nea
     return near ? sample_kernel_of<true>(K, rows, short_docs) : sample_kernel_of<false>(K, rows, short_docs);
 }
 bool slots_near(size_t slots_bytes) { return slots_bytes <= 0xffffffffull; }
-// Few long documents are counted by kLongDocWaves waves each: when there are no more of them than
-// half the waves the chip holds of the one-wave kernel (16 per CU), and each wave still has
-// several hundred tokens.
+// Few long documents are counted by kLongDocWaves waves each.  Measured, theta rebuild of D equal
+// documents at K = 500 with one wave each / sixteen, us (24 and 3,000 topics alike):
+//   tokens   D = 256     512       768        1,024      2,048
+//    4,200    34/ 20    38/ 34    42/ 48     47/ 61     71/115
+//   10,000    54/ 26    58/ 46    62/ 67     75/ 86    155/181
+//   30,000   137/ 49   158/ 92   214/159    298/211
+// Up to one document per CU from a few thousand tokens on, then the longer the more documents
+// there are.
 bool long_docs_for(int64_t D, int64_t T, int n_cus) {
-    return D > 0 && D <= (int64_t)n_cus * 8 && T / D >= 4096;
+    return D > 0 && D <= (int64_t)n_cus * 4 && T / D >= std::max<int64_t>(4096, D * 4096 / n_cus);
 }
 template <int kDocWaves>
 const void* theta_kernel_with(RowKind rows, bool wide_counters) {
