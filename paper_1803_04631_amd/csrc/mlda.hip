@@ -1296,9 +1296,45 @@ int fetch_row_rec(mlda_ctx* c, std::vector<uint2>& rec) {
     return fetch(c, rec.data(), c->row_rec, (size_t)c->D * 8);
 }
 
-// Rows of theta of the attached chunk into the caller's CSR arrays (row_ptr of its documents in
-// place; rec[d].y = distinct topics of row d).  The device lays them out at their tokens' places in
-// the spare assignment buffer, as 16-bit values; the gaps are closed here.
+// Whether the rows of the attached chunk are taken from a copy of its slots, unpacked here, or laid
+// out by the device: that takes two passes over 2 bytes per token and as many more round trips.
+// Measured (copy / device, us): 8e3 tokens, K = 24: 41 / 100; 2.5e5, K = 500, documents of 300 (0.4 MB of
+// slots) 129 / 144, twice as many 329 / 208; 4e6 tokens, K = 24, documents of 300 (1.7 MB) 448 / 1694,
+// K = 500 (5.5 MB) 2067 / 1544.  From kRingFrom on the device's values come through the pinned pieces.
+constexpr size_t kUnpackBytes = (size_t)512 << 10;
+bool rows_unpacked_here(const mlda_ctx* c) {
+    return c->slots_bytes <= kUnpackBytes || (c->slots_bytes <= (size_t)c->T && (size_t)c->T * 2 < kRingFrom);
+}
+
+// Rows of theta of the attached chunk from a copy of its slots into the caller's CSR arrays (row_ptr of
+// its documents in place; rec[d].y = distinct topics of row d, the length of its CSR row; the slot's
+// header holds the number of entries, of which several in a row may share a topic).
+template <class Layout>
+void unpack_rows(const mlda_ctx* c, const std::vector<uint2>& rec, const std::vector<unsigned char>& slots,
+                 const int64_t* row_ptr, uint16_t* topics, int32_t* counts) {
+    typedef typename Layout::Entry Entry;
+    for (int64_t d = 0; d < c->D; ++d) {
+        if (rec[(size_t)d].y == 0) continue;
+        const unsigned char* head = slots.data() + (size_t)rec[(size_t)d].x * 16;
+        uint32_t n_entries;
+        std::memcpy(&n_entries, head, 4);
+        const Entry* ent = reinterpret_cast<const Entry*>(head + mlda::kRowHeader);
+        int64_t at = row_ptr[d] - 1;
+        int last_topic = -1;
+        for (uint32_t j = 0; j < n_entries; ++j) {
+            const int topic = Layout::entry_topic(ent[j]), count = Layout::entry_count(ent[j]);
+            if (topic != last_topic) {
+                topics[++at] = (uint16_t)topic;
+                counts[at] = 0;
+                last_topic = topic;
+            }
+            counts[at] += count;
+        }
+    }
+}
+
+// The same, laid out by the device at the rows' tokens' places in the spare assignment buffer, as 16-bit
+// values; the gaps are closed here.
 template <class Layout>
 int export_rows(mlda_ctx* c, const std::vector<uint2>& rec, const int64_t* row_ptr, uint16_t* topics, int32_t* counts) {
     uint16_t* spare = c->z[c->cur ^ 1];             // free between steps and chunk visits
@@ -1808,14 +1844,24 @@ int mlda_get_doc_topic_csr(mlda_ctx* c, int64_t* row_ptr, uint16_t* topics, int3
     RC_TRY(need_state(c));
     if (!row_ptr) return fail(MLDA_EINVAL, "row_ptr is null");
     std::vector<uint2> rec;
+    std::vector<unsigned char> slots;
     row_ptr[0] = 0;
     auto take_rows = [&](const HostChunk& h) {
+        const bool unpack = rows_unpacked_here(c);
+        if (unpack) {           // on its way with the lengths
+            try { slots.resize(c->slots_bytes); } catch (const std::bad_alloc&) { return fail(MLDA_ENOMEM, "out of host memory"); }
+            HIP_TRY(hipMemcpyAsync(slots.data(), c->slots, c->slots_bytes, hipMemcpyDeviceToHost, c->stream));
+        }
         RC_TRY(fetch_row_rec(c, rec));
         int64_t* ptr = row_ptr + h.d_begin;
         for (int64_t d = 0; d < c->D; ++d) ptr[d + 1] = ptr[d] + rec[(size_t)d].y;
         if (ptr[c->D] > ptr[0] && (!topics || !counts)) return fail(MLDA_EINVAL, "topics or counts is null");
         if (ptr[c->D] == ptr[0]) return (int)MLDA_OK;
-        return with_layout(c->rows, [&](auto layout) { return export_rows<decltype(layout)>(c, rec, ptr, topics, counts); });
+        return with_layout(c->rows, [&](auto layout) {
+            if (!unpack) return export_rows<decltype(layout)>(c, rec, ptr, topics, counts);
+            unpack_rows<decltype(layout)>(c, rec, slots, ptr, topics, counts);
+            return (int)MLDA_OK;
+        });
     };
     if (c->streamed) {
         // chunks are visited in document order, so every chunk finds its first row start in place

@@ -357,6 +357,40 @@ def test_counts_beyond_one_entry(mlda, K):
     model.close()
 
 
+# Rows whose slots are more than 512 KB and more than a byte per token, also of half the documents:
+# (name, D, K, tokens each)
+EXPORT_CASES = [
+    ("three_bits", 7000, 100,  100),
+    ("five_bits",  1000, 1500, 600),
+    ("six_bits",   1040, 500,  600),
+    ("counted",    10000,24,   110),
+    ("packed",     1000, 3000, 300),
+]
+
+
+@pytest.mark.parametrize("chunks", [1, 2])
+@pytest.mark.parametrize("case", EXPORT_CASES, ids=[c[0] for c in EXPORT_CASES])
+def test_rows_laid_out_by_the_device(mlda, case, chunks):
+    """The rows of theta are unpacked from a copy of small slots (the other tests) and laid out by the
+    device otherwise, in every layout: spread rows beside rows of one topic of many entries."""
+    name, D, K, length = case
+    T, V = D * length, 50
+    rng = np.random.default_rng(K)
+
+    class C:  # minimal corpus record
+        pass
+    c = C(); c.doc_ptr = np.arange(D + 1, dtype=np.int64) * length; c.T = T
+    c.word_ids = rng.integers(V, size=T).astype(np.int32)
+    z = rng.integers(K, size=(D, length)).astype(np.uint16)
+    z[::3] = rng.integers(K, size=(len(z[::3]), 1))
+    z[1::3, length // 2:] = K - 1
+    z = z.reshape(-1)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, 0.1, 0.01, SEED, chunks=chunks)
+    model.set_assignments(z)
+    check_counts(model, c, z, V, K)
+    model.close()
+
+
 def test_mixed_row_lengths(mlda):
     """Documents of 3 to ~1500 tokens over few words: every group width and quad count of the
     row walk occurs, and the 64 tokens a wave takes together mix several of them."""
