@@ -110,19 +110,16 @@ constexpr int kDrawInUnit = -1; // off = the 16-byte unit of the slot buffer tha
 constexpr int kDrawDense = -2;  // the draw falls into the dense bucket p2; u = its position there
 constexpr int kDrawTopic = -3;  // off = the new topic itself
 
-// p* of the tile's word is staged as fp64 in the workgroups of four waves (K <= 2048), as fp32 in
-// those of twelve, where fp64 would cost a CU its second workgroup.
-__host__ __device__ constexpr int weight_bytes(int waves) { return waves == 4 ? 8 : 4; }
-
-// LDS bytes of sample_kernel<kWaves> for a given Kpad.
-__host__ __device__ constexpr size_t sample_lds_bytes(int Kpad, int waves) {
-    return (size_t)Kpad * weight_bytes(waves) + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 +
+// p* of the tile's word is staged as fp64 or fp32 (Layout::kDoubleWeights), as fp32 always in the
+// workgroups of twelve waves, where fp64 would cost a CU its second workgroup.
+//
+// LDS bytes of sample_kernel<kWaves> for a given Kpad and bytes of a staged weight.
+__host__ __device__ constexpr size_t sample_lds_bytes(int Kpad, int waves, int weight_bytes) {
+    return (size_t)Kpad * weight_bytes + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 +
            (size_t)waves * kWave * sizeof(TokenRec);
 }
 // The same when p* stays in device memory: the prefix sums and the waves' records only.
-__host__ __device__ constexpr size_t sample_far_lds_bytes(int Kpad, int waves) {
-    return sample_lds_bytes(Kpad, waves) - (size_t)Kpad * weight_bytes(waves);
-}
+__host__ __device__ constexpr size_t sample_far_lds_bytes(int Kpad, int waves) { return sample_lds_bytes(Kpad, waves, 0); }
 // What runs of small tiles keep in LDS besides: the groups' own sums (the prefix sums are made
 // from them again after every change) and one bit per group for "changed".
 __host__ __device__ constexpr size_t sample_run_lds_bytes(int Kpad, int waves) {
@@ -883,7 +880,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     constexpr int kGroup = dense_group(kWaves);
     const int K = a.K, Kpad = a.Kpad, ng = Kpad / kGroup;
     constexpr bool kDouble = Layout::kDoubleWeights;
-    static_assert(kDouble == (weight_bytes(kWaves) == 8) && !(kDouble && kFar), "LDS is sized by the number of waves");
+    static_assert(!(kDouble && (kFar || kWaves != 4)), "fp64 weights: workgroups of four waves, in LDS");
     typedef typename std::conditional<kDouble, double, float>::type Weight;
     // (what a staged weight, and a sum over a row, carry as a factor)
     constexpr double kStagedScale = kDouble ? kWeightScale : 1.0, kRowScale = kDouble ? kSumScale : 1.0;

@@ -56,9 +56,9 @@ constexpr size_t kSlotAlign = 64;     // theta row slot alignment (bytes)
 // (twelve: two such workgroups fill a CU's six waves per SIMD, and their LDS fits twice)
 int sample_waves_for(int32_t K) { return K <= 2048 ? 4 : 12; }
 
-// How a chunk's theta rows are laid out: 4-byte entries of any K for the workgroups of twelve
-// waves; for those of four (K <= 2048) 2-byte entries with 3, 5 or 6 bits of count, or 4-byte
-// entries with long counts.
+// How a chunk's theta rows are laid out: 4-byte entries of any K for the workgroups of twelve waves,
+// and for those of four (K <= 2048) where rows are shortest; else for these 2-byte entries with 3, 5 or
+// 6 bits of count, or 4-byte entries with long counts.
 enum class RowKind { packed, tiny3, tiny5, tiny6, counted };
 
 // f(layout) for the layout of that kind.
@@ -86,7 +86,7 @@ int32_t kpad_for(int32_t K) {
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;
 constexpr int kFarStrips = 512;
 bool far_weights_for(int32_t K) {
-    return mlda::sample_lds_bytes(kpad_for(K), sample_waves_for(K)) > kLdsPerWorkgroup;
+    return mlda::sample_lds_bytes(kpad_for(K), sample_waves_for(K), 4) > kLdsPerWorkgroup;
 }
 
 // short_docs: no document has more tokens than a 4-byte entry counts; near: the theta slots of
@@ -94,6 +94,7 @@ bool far_weights_for(int32_t K) {
 template <bool kNear>
 const void* sample_kernel_of(int32_t K, RowKind rows, bool short_docs) {
     if (far_weights_for(K)) return (const void*)mlda::sample_kernel<12, mlda::PackedRows, true, kNear>;
+    if (rows == RowKind::packed && sample_waves_for(K) == 4) return (const void*)mlda::sample_kernel<4, mlda::PackedRowsShort, false, kNear>;
     if (rows == RowKind::packed && short_docs) return (const void*)mlda::sample_kernel<12, mlda::PackedRowsShort, false, kNear>;
     return with_layout(rows, [](auto layout) {
         typedef decltype(layout) Layout;
@@ -129,10 +130,7 @@ const void* theta_kernel_for(RowKind rows, bool wide_counters, bool long_docs) {
 }
 // (two documents per wave; K <= kPairMaxK)
 const void* theta_pair_kernel_for(RowKind rows) {
-    return with_layout(rows, [](auto layout) -> const void* {
-        if constexpr (layout.kDoubleWeights) return (const void*)mlda::theta_rows_pair_kernel<decltype(layout)>;
-        return nullptr;
-    });
+    return with_layout(rows, [](auto layout) { return (const void*)mlda::theta_rows_pair_kernel<decltype(layout)>; });
 }
 constexpr int kMaxTimedIters = 1024;
 constexpr int kRunTiles = 16;           // small tiles a workgroup of the large-K sampler takes one after the other
@@ -157,7 +155,7 @@ size_t slot_bytes_for(int64_t n, int32_t K, int entry_bytes, int max_count) {
     return align_up((size_t)mlda::kRowHeader + align_up((size_t)cap * (size_t)entry_bytes, 16), kSlotAlign);
 }
 
-// Layout of the theta rows of D documents (K <= 2048), from their lengths: the rows themselves change
+// Layout of the theta rows of D documents over V words (K <= 2048), from their lengths: the rows themselves change
 // with every iteration, from spread over many topics at a random start to counts of many tokens.
 // 2-byte entries read half the bytes and, eight to a unit, take fewer passes; but a count beyond its
 // field takes several of them.  Measured, sampling launch on 5e6 tokens in equal documents, from a random
@@ -175,24 +173,39 @@ size_t slot_bytes_for(int64_t n, int32_t K, int entry_bytes, int max_count) {
 // length that a token meets) and few counts can outgrow them.  4 bytes where a row could have so
 // many more of the 2-byte entries (of six bits a quarter, of five 0.15 times as many), or where the topics
 // are so few that a row of either kind is worked on by four lanes.
-constexpr int kShortDocs = 400, kFewTopics = 32;
+// The shortest documents at K >= 1,024, and somewhat longer ones where the words have so few tokens that staging
+// p* is most of the work, keep 4-byte entries and fp32 weights (six waves per SIMD instead of five, half
+// the LDS, the new topic found in the walk itself).  fp64 walk / this, sampling launch:
+//   tokens per word:        62      125      333    1,000
+//   K = 2,048,  10 tokens  1.34     1.25     1.20    1.11
+//               40         1.29     1.18     1.09    1.03
+//               60         1.14     1.07     0.97    0.89
+//              200         1.03     0.98     0.88    0.82
+//   K = 1,025,  40         1.14     1.10     1.04    1.03
+//               60         1.04     0.99     0.92    0.89
+constexpr int kShortestDocs = 50, kShortDocs = 400, kFewTopics = 32;
 constexpr double kTinyGrowth = 1.25, kTinyGrowth5 = 1.15;
-RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t K) {
+RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t V, int32_t K) {
     if (sample_waves_for(K) != 4) return RowKind::packed;
     const RowKind tiny = K <= mlda::TinyRows<6>::kMaxK ? RowKind::tiny6 : K <= mlda::TinyRows<5>::kMaxK ? RowKind::tiny5 : RowKind::tiny3;
     const int max_count = with_layout(tiny, [](auto layout) { return layout.kMaxCount; });
     auto most_entries = [&](int64_t n, int max) { return (double)(n <= K ? n : std::min<int64_t>(n, (int64_t)K + n / max)); };
     // sums over the tokens: 1, their document's length, and the most entries its row can have
     double tokens = 0.0, length = 0.0, counted = 0.0, tiny3 = 0.0, wider = 0.0;
+    int64_t longest = 0;
     for (int64_t d = 0; d < D; ++d) {
         const int64_t n = doc_ptr[d + 1] - doc_ptr[d];
         const double w = (double)n;
+        longest = std::max(longest, n);
         tokens += w;
         length += w * (double)n;
         counted += w * (double)std::min<int64_t>(n, K);
         tiny3 += w * most_entries(n, mlda::TinyRows<3>::kMaxCount);
         wider += w * most_entries(n, max_count);
     }
+    if (K > mlda::TinyRows<6>::kMaxK && longest <= mlda::PackedRowsShort::kMaxCount &&
+        length <= std::max(kShortestDocs * tokens, std::min(200.0 * tokens, 6.0 * K * V)))
+        return RowKind::packed;
     if (length <= kShortDocs * tokens && tiny3 <= kTinyGrowth * counted) return RowKind::tiny3;
     if (K <= kFewTopics) return RowKind::counted;
     return wider > (tiny == RowKind::tiny6 ? kTinyGrowth : kTinyGrowth5) * counted ? RowKind::counted : tiny;
@@ -357,7 +370,7 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
     // they hold it
     h.wide_counters = longest_doc >= 65536;
     h.short_docs = longest_doc <= mlda::PackedRows::kMaxCount;
-    h.rows = row_kind_for(doc_ptr_all + d_begin, D, K);
+    h.rows = row_kind_for(doc_ptr_all + d_begin, D, V, K);
     const int entry_bytes = with_layout(h.rows, [](auto layout) { return layout.kEntryBytes; });
     const int max_count = with_layout(h.rows, [](auto layout) { return layout.kMaxCount; });
 
@@ -923,11 +936,12 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     const int waves = sample_waves_for(c->K);
     const int32_t grid = c->far_weights ? std::min<int32_t>(a.n_tiles, kFarStrips)
                                         : a.n_single + (a.n_tiles - a.n_single + a.run_tiles - 1) / a.run_tiles;
+    const size_t lds = waves == 4 ? mlda::sample_lds_bytes(c->Kpad, waves, c->rows == RowKind::packed ? 4 : 8) : c->sample_lds;
     void* kernel_args[] = {&a};
     HIP_TRY(hipLaunchKernel(sample_kernel_for(c->K, c->rows, c->short_docs,
                                               slots_near(c->slots_bytes) && !c->wide_slot_offsets),
                             dim3((unsigned)grid),
-                            dim3((unsigned)(waves * mlda::kWave)), kernel_args, c->sample_lds, c->stream));
+                            dim3((unsigned)(waves * mlda::kWave)), kernel_args, lds, c->stream));
     return launch_check("sample_kernel");
 }
 
@@ -1131,7 +1145,7 @@ int device_limits(mlda_ctx* c) {
     const char* wide = std::getenv("MLDA_WIDE_SLOT_OFFSETS");
     c->wide_slot_offsets = wide && wide[0] != '\0' && wide[0] != '0';
     c->sample_lds = c->far_weights ? mlda::sample_far_lds_bytes(c->Kpad, sample_waves_for(c->K))
-                                   : mlda::sample_lds_bytes(c->Kpad, sample_waves_for(c->K));
+                                   : mlda::sample_lds_bytes(c->Kpad, sample_waves_for(c->K), sample_waves_for(c->K) == 4 ? 8 : 4);
     if (c->sample_lds > (size_t)c->lds_limit)
         return fail(MLDA_ENOTSUP, "K = " + std::to_string(c->K) + " needs " + std::to_string(c->sample_lds) +
                                       " bytes of LDS per workgroup, the device allows " +

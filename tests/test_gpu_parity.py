@@ -155,6 +155,12 @@ LAYOUT_CASES = [
     ("k_largest_fp64",         25, 200,  2048, 300),
     ("k_first_fp32",           25, 200,  2049, 300),
     ("counted_longest_rows",   4,  300,  2048, 2500),   # beyond the widest pass shape
+    # 4-byte entries and fp32 weights again, workgroups of four waves: the shortest documents ...
+    ("packed_four_waves",      300, 50,  1024, 30),
+    ("packed_four_waves_2048", 300, 50,  2048, 30),
+    ("three_bits_from_here",   60, 50,   2048, 260),
+    # ... and words of few tokens
+    ("packed_small_words",     60, 3000, 1500, 150),
 ]
 
 
