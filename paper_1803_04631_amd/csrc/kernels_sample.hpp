@@ -1020,7 +1020,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     // is dealt out in smaller batches, so that all waves work on it side by side: the passes
     // of one batch follow each other, each waiting for its rows.
     // (Full batches are less work in all, which is what counts where the chip is full; at K > 2048,
-    // and where all tiles are in flight at once, it is the time of one tile.)
+    // and where there are few tiles, it is the time of one tile.)
     const int batch = min(kWave, max(kWaves == 4 ? a.min_batch : kMinBatch,
                                      ((tl.count + kWaves - 1) / kWaves + 3) & ~3));
     const int n_batches = (tl.count + batch - 1) / batch;

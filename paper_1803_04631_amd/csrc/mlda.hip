@@ -931,8 +931,16 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     a.n_single = c->run_tiles > 1 ? c->n_single : c->n_tiles;
     a.run_tiles = c->run_tiles;
     a.far_pstar = c->far_pstar;
-    // few enough tiles for all to be in flight at once: nothing is gained by full batches then
-    a.min_batch = c->n_tiles <= 8 * c->n_cus ? mlda::kMinBatch * 2 : mlda::kWave;
+    // With few tiles the launch takes the time of one tile, and a small tile is done sooner by four waves side
+    // by side than by one with a full batch; with more it is the work in all that counts, and later so where
+    // rows are long and a pass takes few of a batch's tokens anyway.  Batches of at least 16 / 64 tokens,
+    // tiles of 60 tokens (of 300: alike), us:
+    //   tiles                              768          1,400        2,040
+    //   documents of 40,  K = 100     10.2 / 11.3   14.4 / 12.6   16.6 / 14.2
+    //                300, K = 100     10.8 / 12.0   14.7 / 13.6   17.6 / 15.8
+    //                300, K = 1,000   13.9 / 18.6   20.3 / 21.8   24.0 / 25.0
+    const bool long_rows = c->K >= 200 && c->T >= 200 * c->D;
+    a.min_batch = c->n_tiles <= (long_rows ? 8 : 4) * c->n_cus ? mlda::kMinBatch * 2 : mlda::kWave;
     const int waves = sample_waves_for(c->K);
     const int32_t grid = c->far_weights ? std::min<int32_t>(a.n_tiles, kFarStrips)
                                         : a.n_single + (a.n_tiles - a.n_single + a.run_tiles - 1) / a.run_tiles;
