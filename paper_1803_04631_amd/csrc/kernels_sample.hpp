@@ -6,7 +6,8 @@
 // bound by VALU issue, not by HBM):
 //   - a workgroup owns one tile = up to 1024 (4096 for large K) consecutive tokens of ONE
 //     word and stages that word's p*(k) (Eq. 8, rounded to fp32) once in LDS, widened to fp64 where
-//     K <= 2048, with fp64 prefix sums over groups of 4 (or 16) topics (Section 6.1.2: samplers of a block share the word's data);
+//     K <= 2048 and rows are not the shortest, with fp64 prefix sums over groups of 4 (or 16) topics
+//     (Section 6.1.2: samplers of a block share the word's data);
 //     for large K, the many words of few tokens are taken in runs by one workgroup, which turns
 //     p* of one word into p* of the next; where K is too large for p* to fit the LDS at all, it
 //     is staged in a strip of device memory that the workgroup owns, and read from there;
@@ -30,8 +31,8 @@
 //     results travel between the per-lane and per-group phases through small per-wave LDS
 //     records;
 //   - a theta row is a run of entries (topic, count) in ascending topic order, 2 bytes each
-//     where K <= 2048 (3, 5 or 6 bits of count; 4 bytes for long documents over few topics),
-//     else 4 bytes (16 bits of topic, 14 of count); a count too large for its field is written
+//     where K <= 2048 (3, 5 or 6 bits of count; 4 bytes for documents long beside the topics, and
+//     for the shortest), else 4 bytes (16 bits of topic, 14 of count); a count too large for its field is written
 //     as several entries of the same topic, one after the other, which changes no sum.  Only
 //     the first entry of the token's own topic gives up the token itself;
 //   - the row walk is a chain of dependent loads (record, then a random row in HBM), so the
@@ -872,8 +873,8 @@ template <int kValue> using Int = std::integral_constant<int, kValue>;
 // kNear: every byte of the slot buffer has a 32-bit offset; a pass then finds its units with
 // 32-bit arithmetic (one offset per lane, the unit's place in the load's own offset field).
 template <int kWaves, class Layout, bool kFar = false, bool kNear = false>
-// Six waves per SIMD (80 VGPRs): the walk hides HBM latency by occupancy as well as by the
-// early loads.
+// Six waves per SIMD (80 VGPRs), five (96) with fp64 weights: the walk hides HBM latency by occupancy as
+// well as by the early loads.
 __attribute__((amdgpu_waves_per_eu(Layout::kWavesPerSimd)))
 __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];

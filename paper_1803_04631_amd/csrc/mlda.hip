@@ -285,7 +285,7 @@ ModelLayout model_layout(int32_t V, int32_t K, int64_t T, bool two_phi) {
     L.n_k[0] = put((size_t)K * 4);
     L.n_k[1] = two_phi ? put((size_t)K * 4) : L.n_k[0];
     L.ll_partial = put((size_t)(2 * kLoglikBlocks + kMaxThetaGrid) * 8);
-    L.ll_scalars = put(4 * 8);                            // value, theta sum, document term, spare
+    L.ll_scalars = put(4 * 8);                            // value, theta sum, document term, the word side's ticket
     L.lg_table = put((size_t)(mlda::kLgTable + 1) * 8 * 2);   // one for alpha, one for beta
     L.row_entries = put((size_t)kEntryRing * 8);
     L.far_pstar = put(far_weights_for(K) ? (size_t)kFarStrips * (size_t)kpad_for(K) * 4 : 0);

@@ -663,8 +663,8 @@ def test_step_with_loglik_flag_and_timing(mlda):
     lens = np.diff(c.doc_ptr)
 
     def row_entries(assignments):
-        """Entries of every theta row: K < 1024 gives 2-byte entries that hold counts up to 15,
-        so a larger count takes several."""
+        """Entries of every theta row as the byte count takes them: for K < 1024 of counts up to 15,
+        so a larger count takes several, whatever the layout in use."""
         row_ptr, _, counts = oracle.doc_topic_csr(c.doc_ptr, assignments, cfg.K)
         per_topic = -(-counts.astype(np.int64) // 15)
         return np.array([per_topic[row_ptr[d]:row_ptr[d + 1]].sum() for d in range(len(lens))])
