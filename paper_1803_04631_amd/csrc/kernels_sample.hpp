@@ -104,7 +104,7 @@ struct __align__(16) TokenRec { // per-lane phase -> per-group phase, 32 bytes
     int32_t o;                  // current topic
     float w_o;                  // p*(o) with the token itself removed
     double u;
-    double Qp;                  // alpha * sum_k p*'(k), times kSumScale where p* is fp64
+    double Qp;                  // alpha * sum_k p*'(k)
 };
 constexpr int kDrawInUnit = -1; // off = the 16-byte unit of the slot buffer that holds the draw,
                                 // u = what is left of the draw at the unit's start
@@ -137,6 +137,9 @@ constexpr int kRunTileTokens = 1024;    // a tile of a run holds a whole word of
 constexpr double kWeightScale = 0x1p1000;
 constexpr double kCountUnit = 0x1p-1042;
 constexpr double kSumScale = kWeightScale * kCountUnit;
+// Q' times kSumScale is a normal number from here on.  A smaller one (alpha below 1e-290 or so) decides
+// draws of tokens that are alone in their document only; their place in p2 is worked out without the scale.
+constexpr double kSmallestScaled = 0x1p-900;
 
 // A staged weight of either form without its scale.
 __device__ __forceinline__ double plain_weight(float w) { return (double)w; }
@@ -518,7 +521,8 @@ struct RowDraw {
     bool sparse, hit;
 };
 
-template <int kLanes>
+// (kScaled: the sums carry kSumScale, and so do the draw and what follows from it)
+template <int kLanes, bool kScaled = false>
 __device__ __forceinline__ RowDraw row_draw(double lane_sum, const TokenRec* rec, int sl, int lane) {
     RowDraw d;
     const double incl = group_inclusive_sum<kLanes>(lane_sum);
@@ -528,7 +532,7 @@ __device__ __forceinline__ RowDraw row_draw(double lane_sum, const TokenRec* rec
     asm volatile("" : "+v"(lane));
     d.S = __shfl(incl, group_last_lane<kLanes>(lane), kWave);
     const double2 uq = *reinterpret_cast<const double2*>(&rec->u);     // the uniform, and Q'
-    d.x = uq.x * (d.S + uq.y);
+    d.x = uq.x * (kScaled ? fma(uq.y, kSumScale, d.S) : d.S + uq.y);
     d.sparse = d.x < d.S;
     d.hit = d.sparse && (incl > d.x) && !(excl > d.x);
     d.y = d.x - excl;
@@ -694,7 +698,7 @@ __device__ __forceinline__ void row_pass_double(TokenRec* rec, int sl, const uin
         at_end[c] = with_own_topic(acc, n_own, itself, w_o);
     }
     acc = at_end[kUnits - 1];
-    const RowDraw d = row_draw<kLanes>(acc, rec, sl, lane);
+    const RowDraw d = row_draw<kLanes, true>(acc, rec, sl, lane);
     // first unit whose end exceeds y (the sums never decrease), and the sum before it
     int unit = kUnits - 1;
 #pragma unroll
@@ -744,7 +748,7 @@ __device__ __forceinline__ void row_pass_double_long(const unsigned char* slots,
     };
     double acc = 0.0;
     for (int c = 0; c < n; ++c) acc = next_end(load_unit(slots, off, u0 + c, u0 + c < n_units));
-    const RowDraw d = row_draw<kWave>(acc, rec, lane, lane);
+    const RowDraw d = row_draw<kWave, true>(acc, rec, lane, lane);
     if (__ballot(d.hit) != 0) {
         bool found = false;
         int unit = 0, last_unit = 0;
@@ -1063,7 +1067,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                                ((double)(ka->n_k[mine.o] - 1) + ka->beta_V));
             delta = (double)mine.w_o - plain_weight(pstar[mine.o]);
             // cp[ng - 1] = sum_k p*(k), read from LDS where it is needed; Q = alpha sum (Eq. 7)
-            mine.Qp = kRowScale * (ka->alpha * (cp[ng - 1] + delta));
+            mine.Qp = ka->alpha * (cp[ng - 1] + delta);
         }
         my_rec[lane] = mine;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1212,7 +1216,11 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             }
             if (head.y == kDrawDense) {
                 const float w_o = __int_as_float(head.w);
-                z_new = dense_bucket_search<kGroup>(pstar, cp, K, ng, ka->alpha, rec->u * (1.0 / kRowScale), head.z,
+                double y = rec->u * (1.0 / kRowScale);
+                if (kDouble && __builtin_expect(rec->Qp < kSmallestScaled, 0))
+                    y = rec->Qp * token_uniform(ka->seed, ka->iter,
+                                                (uint64_t)load_at<uint32_t>(ka->tok_id + tl.begin, (uint32_t)(b * batch + lane) << 2));
+                z_new = dense_bucket_search<kGroup>(pstar, cp, K, ng, ka->alpha, y, head.z,
                                                     w_o, (double)w_o - plain_weight(pstar[head.z]));
             }
             store_at<uint16_t>(ka->z_next + tl.begin, (uint32_t)(b * batch + lane) << 1, (uint16_t)z_new);

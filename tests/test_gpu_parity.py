@@ -268,6 +268,31 @@ def test_small_beta(mlda, case, beta):
     model.close()
 
 
+@pytest.mark.parametrize("alpha", [1e-305, 1e-307])
+@pytest.mark.parametrize("K", [16, 300])
+def test_small_alpha(mlda, K, alpha):
+    """Documents of one token, whose draw alpha alone decides, beside longer ones, under an alpha so
+    small that alpha p* would be denormal with any factor to it."""
+    D, V = 6000, 40
+    rng = np.random.default_rng(K)
+    lens = np.where(np.arange(D) % 4 == 0, 5, 1)
+
+    class C:  # minimal corpus record
+        pass
+    c = C(); c.doc_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64); c.T = int(lens.sum())
+    c.word_ids = rng.integers(V, size=c.T).astype(np.int32)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, 0.01, SEED)
+    model.init_random()
+    z = oracle.init_topics(c.T, K, SEED)
+    for it in (1, 2):
+        n_wk, n_k = oracle.count_word_topic(c.word_ids, z, V, K)
+        want = oracle.iteration(c.doc_ptr, c.word_ids, z, V, K, alpha, 0.01, SEED, it, n_wk, n_k)
+        model.step(1)
+        z = model.assignments()
+        assert np.array_equal(z, want)
+    model.close()
+
+
 @pytest.mark.parametrize("case", EDGE_CASES, ids=[c[0] for c in EDGE_CASES])
 def test_edge_shapes(mlda, case):
     name, D, V, K, mean_len = case
