@@ -112,9 +112,13 @@ bool slots_near(size_t slots_bytes) { return slots_bytes <= 0xffffffffull; }
 //   10,000    54/ 26    58/ 46    62/ 67     75/ 86    155/181
 //   30,000   137/ 49   158/ 92   214/159    298/211
 // Up to one document per CU from a few thousand tokens on, then the longer the more documents
-// there are.
-bool long_docs_for(int64_t D, int64_t T, int n_cus) {
-    return D > 0 && D <= (int64_t)n_cus * 4 && T / D >= std::max<int64_t>(4096, D * 4096 / n_cus);
+// there are; and, up to eight per CU, where the longest alone would take a wave longer (4.7 ns a token)
+// than all of them take sixteen waves each (about 8 us per document and CU and 1.2 ns per token and CU): 1,024
+// documents of 10,000 tokens, the longest of 87,000, 478/166 us; 2,040 with 84,000 787/398.
+bool long_docs_for(int64_t D, int64_t T, int64_t longest, int n_cus) {
+    if (D <= 0 || D > (int64_t)n_cus * 8 || T / D < 4096) return false;
+    return (D <= (int64_t)n_cus * 4 && T / D >= D * 4096 / n_cus) ||
+           longest >= D * 1700 / n_cus + T / (4 * n_cus);
 }
 template <int kDocWaves>
 const void* theta_kernel_with(RowKind rows, bool wide_counters) {
@@ -327,6 +331,7 @@ struct HostChunk {
     int64_t D = 0, T = 0;
     RowKind rows = RowKind::packed;     // layout of the theta rows
     bool wide_counters = false;         // some document has 2^16 tokens or more
+    int64_t longest_doc = 0;            // tokens
     bool short_docs = true;             // no document has more tokens than a 4-byte entry counts
     size_t slots_bytes = 0;
     int32_t n_tiles = 0, n_segs = 0, n_split = 0;
@@ -366,6 +371,7 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
 
     int64_t longest_doc = 0;
     for (int64_t d = 0; d < D; ++d) longest_doc = std::max(longest_doc, len_of(d));
+    h.longest_doc = longest_doc;
     // a count never exceeds the document's length: 16-bit counters in the theta rebuild if
     // they hold it
     h.wide_counters = longest_doc >= 65536;
@@ -889,7 +895,7 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
         if (c->streamed) hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, c->stream, entries);    // (else rebuild_phi did)
         // two documents per wave where a half-wave suits them: few topics, short documents
         const bool pairs = c->K <= kPairMaxK && !c->wide_counters && c->T <= 160 * c->D;
-        const bool long_docs = long_docs_for(c->D, c->T, c->n_cus);
+        const bool long_docs = long_docs_for(c->D, c->T, c->at->longest_doc, c->n_cus);
         const void* kernel =
             pairs ? theta_pair_kernel_for(c->rows) : theta_kernel_for(c->rows, c->wide_counters, long_docs);
         const size_t lds = pairs ? theta_pair_lds_bytes(c->K) : theta_lds;
