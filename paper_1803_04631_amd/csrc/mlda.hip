@@ -173,10 +173,12 @@ size_t slot_bytes_for(int64_t n, int32_t K, int entry_bytes, int max_count) {
 //          12,000           5357/5371/5244    623/ 594/ 466     865/ 409/ 206
 //   K = 2,000, 12,000        6573/5479/5562   4854/1198/1224    6294/ 854/ 949
 //   K = 24,   400             190/ 189/ 154    141/ 139/ 127     137/ 135/ 108
+//   K = 44,   400                              172/ 164/ 130     158/ 150/ 111
+//   K = 52,   400                              174/ 169/ 133     208/ 154/ 113
 // Three bits of count, an instruction less for two entries, where documents are short (what counts is the
 // length that a token meets) and few counts can outgrow them.  4 bytes where a row could have so
 // many more of the 2-byte entries (of six bits a quarter, of five 0.15 times as many), or where the topics
-// are so few that a row of either kind is worked on by four lanes.
+// are so few that a 4-byte row, too, fits four lanes (twelve units).
 // The shortest documents at K >= 1,024, and somewhat longer ones where the words have so few tokens that staging
 // p* is most of the work, keep 4-byte entries and fp32 weights (six waves per SIMD instead of five, half
 // the LDS, the new topic found in the walk itself).  fp64 walk / this, sampling launch:
@@ -187,7 +189,7 @@ size_t slot_bytes_for(int64_t n, int32_t K, int entry_bytes, int max_count) {
 //              200         1.03     0.98     0.88    0.82
 //   K = 1,025,  40         1.14     1.10     1.04    1.03
 //               60         1.04     0.99     0.92    0.89
-constexpr int kShortestDocs = 50, kShortDocs = 400, kFewTopics = 32;
+constexpr int kShortestDocs = 50, kShortDocs = 400, kFewTopics = 48;
 constexpr double kTinyGrowth = 1.25, kTinyGrowth5 = 1.15;
 RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t V, int32_t K) {
     if (sample_waves_for(K) != 4) return RowKind::packed;
