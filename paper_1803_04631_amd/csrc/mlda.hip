@@ -219,7 +219,7 @@ RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t V, int32_t K) {
 
 constexpr int kLoglikBlocks = 2048;
 constexpr int kSmallLoglikBlocks = 256;     // up to so many, the word side's last workgroup adds up
-constexpr int kMaxThetaGrid = 8192;    // workgroups of the theta rebuild (each leaves one likelihood partial)
+constexpr int kMaxThetaGrid = 4096;    // workgroups of the theta rebuild (each leaves one likelihood partial and one count)
 constexpr int kEntryRing = 2048;      // per-rebuild counters of theta row entries (> kMaxTimedIters)
 
 // Where the buffers of one chunk of documents lie inside its part of the workspace (byte
@@ -290,7 +290,7 @@ ModelLayout model_layout(int32_t V, int32_t K, int64_t T, bool two_phi) {
     L.wide_row = put((size_t)V * 4);
     L.n_k[0] = put((size_t)K * 4);
     L.n_k[1] = two_phi ? put((size_t)K * 4) : L.n_k[0];
-    L.ll_partial = put((size_t)(2 * kLoglikBlocks + kMaxThetaGrid) * 8);
+    L.ll_partial = put((size_t)(2 * kLoglikBlocks + 2 * kMaxThetaGrid) * 8);
     L.ll_scalars = put(4 * 8);                            // value, theta sum, document term, the word side's ticket
     L.lg_table = put((size_t)(mlda::kLgTable + 1) * 8 * 2);   // one for alpha, one for beta
     L.row_entries = put((size_t)kEntryRing * 8);
@@ -589,7 +589,8 @@ struct mlda_ctx {
     double *ll_partial = nullptr, *ll_scalars = nullptr;   // scalars: value, theta sum, document term
     double* lg_table = nullptr;          // lgG(c + alpha) - lgG(alpha), c < 1024, then lgG(alpha)
     double* lg_table_beta = nullptr;     // the same for beta
-    unsigned long long* row_entries = nullptr;   // ring: [r % kEntryRing] written by rebuild r
+    unsigned long long* row_entries = nullptr;   // ring: [r % kEntryRing] belongs to rebuild r
+    unsigned long long* visited = nullptr;       // the last theta rebuild's row entries, one value per workgroup
     int64_t rebuilds = 0;                        // rebuilds launched so far
     int32_t last_step_iters = 0;
     bool has_state = false, ll_fresh = false;
@@ -831,10 +832,10 @@ int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which) {
     const size_t hist_bytes = (size_t)span * 4;
     const bool ranges = c->K > kHistTopics;
     if (!c->streamed) {
-        // (the counter is that of the theta rebuild that follows)
         const dim3 grid((unsigned)c->n_split + 1u, (unsigned)blocks_for(c->K, 256));
         hipLaunchKernelGGL(zero_sums_kernel, grid, dim3(256), 0, c->stream, c->split_words, c->phi[which], c->K,
-                           c->n_k[which], c->row_entries + (c->rebuilds % kEntryRing));
+                           c->n_k[which], c->visited, c->theta_grid,
+                           c->rebuilds > 0 ? c->row_entries + ((c->rebuilds - 1) % kEntryRing) : nullptr);
     }
     if (c->n_tiles > 0) {
         if (!ranges)
@@ -893,8 +894,6 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
     const int32_t* doc_map = c->streamed ? nullptr : c->doc_map;
     if (c->D > 0) {
         const size_t theta_lds = theta_lds_bytes(c->K, c->wide_counters);
-        unsigned long long* entries = c->row_entries + (c->rebuilds % kEntryRing);
-        if (c->streamed) hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, c->stream, entries);    // (else rebuild_phi did)
         // two documents per wave where a half-wave suits them: few topics, short documents
         const bool pairs = c->K <= kPairMaxK && !c->wide_counters && c->T <= 160 * c->D;
         const bool long_docs = long_docs_for(c->D, c->T, c->at->longest_doc, c->n_cus);
@@ -909,9 +908,14 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
         double alpha = c->alpha;
         const double* lg_table = c->lg_table;
         double* ll_partial = c->ll_partial + 2 * kLoglikBlocks;
-        void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &entries, &ll_partial};
+        unsigned long long* visited = c->visited;
+        void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &visited, &ll_partial};
         HIP_TRY(hipLaunchKernel(kernel, dim3((unsigned)c->theta_grid), dim3((unsigned)(long_docs ? kWave * kLongDocWaves : kWave)),
                                 args, lds, c->stream));
+        // (one chunk: the next rebuild_phi adds the counts up; sampler bytes are asked of earlier ones only)
+        if (c->streamed)
+            hipLaunchKernelGGL(visited_sum_kernel, dim3(1), dim3(256), 0, c->stream, c->visited, c->theta_grid,
+                               c->row_entries + (c->rebuilds % kEntryRing));
     }
     c->rebuilds += 1;
     return launch_check("theta rebuild kernel");
@@ -1062,6 +1066,7 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     c->lg_table = (double*)(base + ML.lg_table);
     c->lg_table_beta = c->lg_table + (mlda::kLgTable + 1);
     c->row_entries = (unsigned long long*)(base + ML.row_entries);
+    c->visited = (unsigned long long*)(c->ll_partial + 2 * kLoglikBlocks + kMaxThetaGrid);
     c->far_pstar = (float*)(base + ML.far_pstar);
 
     hipLaunchKernelGGL(mlda::lg_table_kernel, dim3(blocks_for(mlda::kLgTable + 1, 256)), dim3(256), 0,
