@@ -31,106 +31,149 @@ __global__ __launch_bounds__(256) void visited_sum_kernel(const unsigned long lo
 }
 
 // What the rebuilds of one state add to must start at zero: the rows of words whose tokens span
-// several segments, the topic totals.  The same launch adds up what the theta rebuild before left
-// (`visited`, n_visited values; `visited_sum` null: there was none).  One launch for all (a
-// launch and the gap before it take 8 us, a third of a whole rebuild on a corpus of 1e5 tokens).
-// grid = (#split words + 1, ceil(K / blockDim)).
-__global__ __launch_bounds__(256) void zero_sums_kernel(const int32_t* split_words, PhiView phi, int32_t K, int32_t* n_k,
-                                                        const unsigned long long* visited, int n_visited,
-                                                        unsigned long long* visited_sum) {
+// several segments, and the topic totals where the theta rebuild before has not cleared them
+// (n_k null: it has).  grid = (#split words + 1, ceil(K / blockDim)).
+__global__ void zero_sums_kernel(const int32_t* split_words, PhiView phi, int32_t K, int32_t* n_k) {
     const int k = (int)(blockIdx.y * blockDim.x + threadIdx.x);
+    if (k >= K) return;
     if (blockIdx.x == 0) {
-        if (k < K) n_k[k] = 0;
-        if (blockIdx.y == 0 && visited_sum) store_visited_sum(visited, n_visited, visited_sum);
+        if (n_k) n_k[k] = 0;
         return;
     }
-    if (k >= K) return;
     const int v = split_words[blockIdx.x - 1], wide_row = phi.wide_row[v];
     if (wide_row >= 0) phi.wide[(size_t)wide_row * (size_t)K + k] = 0;
     else phi.narrow[(size_t)v * (size_t)K + k] = 0;
 }
 
-// Update phi (Section 6.2: word by word, atomics with good locality): a workgroup
-// histograms one segment (up to 16384 consecutive tokens of one word) in LDS, then stores
-// the word's row outright if the segment is the whole word, else adds its non-zero bins
-// to the row.  A 16-bit cell is added to through the aligned dword that holds it: the word has
-// fewer than 2^16 tokens, so no sum carries into the neighbouring cell.
-// kRange: K counters do not fit a workgroup's LDS; the launch then covers the topics
-// k_lo .. k_lo + kn - 1 only (one launch per such range), else all K.
-template <bool kRange>
-__global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, const uint16_t* z,
-                                                       PhiView phi, int32_t K, int32_t k_lo, int32_t kn) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    int32_t* hist = reinterpret_cast<int32_t*>(lds);
-    const Tile tl = segs[blockIdx.x];
+// f(topic) for the tokens [lo, hi) of z, by 256 threads: 16 bytes (eight tokens) per load, four loads
+// in flight per thread, single tokens only before the first and after the last aligned eight.
+template <class F>
+__device__ __forceinline__ void for_topics(const uint16_t* z, int64_t lo, int64_t hi, F&& f) {
     const int tid = (int)threadIdx.x;
-    const int lo = kRange ? k_lo : 0, n = kRange ? kn : K;
+    const int64_t lo8 = min((lo + 7) & ~(int64_t)7, hi), hi8 = max(hi & ~(int64_t)7, lo8);
+    const int n_head = (int)(lo8 - lo), n_ends = n_head + (int)(hi - hi8);      // at most 14
+    int end_topic = -1;
+    if (tid < n_ends) end_topic = (int)z[tid < n_head ? lo + tid : hi8 + (tid - n_head)];
+    auto add_pair = [&](uint32_t two) { f((int)(two & 0xffffu)); f((int)(two >> 16)); };
+    auto add_eight = [&](const uint4& v) { add_pair(v.x); add_pair(v.y); add_pair(v.z); add_pair(v.w); };
+    const uint4* eights = reinterpret_cast<const uint4*>(z + lo8);
+    const int64_t n8 = (hi8 - lo8) / 8;
+    int64_t i = tid;
+    for (; i + 768 < n8; i += 1024) {
+        const uint4 v0 = eights[i], v1 = eights[i + 256], v2 = eights[i + 512], v3 = eights[i + 768];
+        add_eight(v0); add_eight(v1); add_eight(v2); add_eight(v3);
+    }
+    for (; i < n8; i += 256) add_eight(eights[i]);
+    if (end_topic >= 0) f(end_topic);
+}
+
+// Topic totals of the tokens [lo, hi) (lo a multiple of 8) added to n_k, through 32-bit counters of the
+// topics k_lo .. k_lo + n - 1 in LDS.  (Every workgroup adds each of its topics to the same n_k, 5 ns a time
+// for one address: what counts is few workgroups.)
+template <bool kRange>
+__device__ __forceinline__ void add_topic_totals(int32_t* hist, const uint16_t* z, int64_t lo, int64_t hi, int32_t* n_k,
+                                                 int32_t k_lo, int32_t n) {
+    const int tid = (int)threadIdx.x;
     for (int k = tid; k < n; k += 256) hist[k] = 0;
     __syncthreads();
-    // four independent loads in flight per thread: the loop is bound by their latency
-    const uint16_t* zt = z + tl.begin;
-    int i = tid;
-    if (kRange) {
-        for (; i < tl.count; i += 256) {
-            const int k = (int)zt[i] - lo;
-            if ((unsigned)k < (unsigned)n) atomicAdd(&hist[k], 1);
-        }
-    } else {
-        for (; i + 768 < tl.count; i += 1024) {
-            const int k0 = zt[i], k1 = zt[i + 256], k2 = zt[i + 512], k3 = zt[i + 768];
-            atomicAdd(&hist[k0], 1); atomicAdd(&hist[k1], 1); atomicAdd(&hist[k2], 1); atomicAdd(&hist[k3], 1);
-        }
-        for (; i < tl.count; i += 256) atomicAdd(&hist[zt[i]], 1);
-    }
+    for_topics(z, lo, hi, [&](int k) {
+        if (kRange) k -= k_lo;
+        if (!kRange || (unsigned)k < (unsigned)n) atomicAdd(&hist[k], 1);
+    });
     __syncthreads();
-    const int wide_row = phi.wide_row[tl.word];
-    if (wide_row >= 0) {
-        int32_t* row = phi.wide + (size_t)wide_row * (size_t)K + lo;
-        if (tl.whole) {
-            for (int k = tid; k < n; k += 256) row[k] = hist[k];
-        } else {
-            for (int k = tid; k < n; k += 256) {
-                const int c = hist[k];
-                if (c != 0) atomicAdd(&row[k], c);
-            }
-        }
-    } else {
-        const size_t cell0 = (size_t)tl.word * (size_t)K + (size_t)lo;
-        if (tl.whole) {
-            for (int k = tid; k < n; k += 256) phi.narrow[cell0 + k] = (uint16_t)hist[k];
-        } else {
-            uint32_t* dwords = reinterpret_cast<uint32_t*>(phi.narrow);
-            for (int k = tid; k < n; k += 256) {
-                const uint32_t c = (uint32_t)hist[k];
-                const size_t cell = cell0 + k;
-                if (c != 0) atomicAdd(&dwords[cell >> 1], c << ((cell & 1) * 16));
-            }
-        }
+    for (int k = tid; k < n; k += 256) {
+        const int c = hist[k];
+        if (c != 0) atomicAdd(&n_k[k_lo + k], c);
     }
 }
 
-// n_k[k] = number of tokens with topic k.  Persistent workgroups, each over a contiguous
-// share of the tokens; n_k must be zero on entry.  kRange as above.
+// Update phi (Section 6.2: word by word, atomics with good locality): a workgroup
+// histograms one segment (up to 16384 consecutive tokens of one word) in LDS, then stores
+// the word's row outright if the segment is the whole word, else adds its non-zero bins
+// to the row.  A segment's counts fit 16 bits: two topics share a dword of LDS as they do in a
+// 16-bit row, so that a row leaves as it lies in LDS, and every K fits the LDS at once.  A narrow
+// row is added to by dwords of two cells; the word has fewer than 2^16 tokens, so no sum carries into the
+// neighbouring cell.
+// The workgroups from n_segs on do what else one launch can (each launch costs a small corpus 5 us):
+// n_totals of them add the topic totals of a share of the tokens to n_k (which is zero on entry), and the
+// last one adds up the counts that the theta rebuild before left (`visited`, to visited_sum; null: none).
+__global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t n_segs, const uint16_t* z,
+                                                       PhiView phi, int32_t K, int64_t T, int32_t n_totals, int32_t* n_k,
+                                                       const unsigned long long* visited, int n_visited,
+                                                       unsigned long long* visited_sum) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int tid = (int)threadIdx.x;
+    if ((int)blockIdx.x >= n_segs) {
+        const int part = (int)blockIdx.x - n_segs;
+        if (part < n_totals) {
+            const int64_t per = ((T + n_totals - 1) / n_totals + 7) & ~(int64_t)7;
+            const int64_t lo = min(per * part, T);
+            add_topic_totals<false>(reinterpret_cast<int32_t*>(lds), z, lo, min(lo + per, T), n_k, 0, K);
+        } else if (visited_sum) {
+            store_visited_sum(visited, n_visited, visited_sum);
+        }
+        return;
+    }
+    uint32_t* hist = reinterpret_cast<uint32_t*>(lds);
+    const Tile tl = segs[blockIdx.x];
+    const int wide_row = phi.wide_row[tl.word];
+    const int n_dwords = (K + 1) / 2;
+    for (int i = tid; i < (n_dwords + 3) / 4; i += 256) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    for_topics(z, tl.begin, (int64_t)tl.begin + tl.count,
+               [&](int k) { atomicAdd(&hist[k >> 1], 1u << ((k & 1) << 4)); });
+    __syncthreads();
+    if (wide_row >= 0) {                // (2^16 tokens or more: never a whole word)
+        int32_t* row = phi.wide + (size_t)wide_row * (size_t)K;
+        for (int i = tid; i < n_dwords; i += 256) {
+            const uint32_t two = hist[i];
+            if ((two & 0xffffu) != 0u) atomicAdd(&row[2 * i], (int)(two & 0xffffu));
+            if ((two >> 16) != 0u) atomicAdd(&row[2 * i + 1], (int)(two >> 16));
+        }
+        return;
+    }
+    const size_t cell0 = (size_t)tl.word * (size_t)K;
+    if (tl.whole && (K & 7) == 0) {     // (every row starts at a multiple of 16 bytes)
+        uint4* row = reinterpret_cast<uint4*>(phi.narrow + cell0);
+        for (int i = tid; i < K / 8; i += 256) row[i] = reinterpret_cast<const uint4*>(lds)[i];
+        return;
+    }
+    // The row's dwords: with an odd K every other row starts in the upper half of one, which then holds
+    // the row's first cell only (as the last may hold its last only; the other half is another row's).
+    const int odd = (int)(cell0 & 1);
+    uint32_t* dwords = reinterpret_cast<uint32_t*>(phi.narrow) + (cell0 >> 1);
+    for (int i = tid; i < (K + odd + 1) / 2; i += 256) {
+        uint32_t two;                   // the cells 2 i - odd and 2 i - odd + 1
+        if (odd) two = (i > 0 ? hist[i - 1] >> 16 : 0u) | (i < n_dwords ? hist[i] << 16 : 0u);
+        else two = hist[i];
+        if (!tl.whole) {
+            if (two != 0u) atomicAdd(&dwords[i], two);
+        } else if (2 * i - odd < 0) {
+            phi.narrow[cell0] = (uint16_t)(two >> 16);
+        } else if (2 * i - odd + 1 >= K) {
+            phi.narrow[cell0 + K - 1] = (uint16_t)two;
+        } else {
+            dwords[i] = two;
+        }
+    }
+}
+// LDS bytes of a launch of it.
+__host__ __device__ inline size_t phi_tile_lds_bytes(int32_t K, bool totals) {
+    return totals ? ((size_t)K * 4 + 15) & ~(size_t)15 : ((size_t)((K + 1) / 2) * 4 + 15) & ~(size_t)15;
+}
+
+// n_k[k] = number of tokens with topic k, as a launch of its own: each workgroup over a contiguous
+// share of the tokens; n_k must be zero on entry.
+// kRange: K counters do not fit a workgroup's LDS; the launch then covers the topics
+// k_lo .. k_lo + kn - 1 only (one launch per such range), else all K.
 template <bool kRange>
 __global__ __launch_bounds__(256) void topic_totals_kernel(const uint16_t* z, int64_t T, int32_t* n_k,
                                                            int32_t K, int32_t k_lo, int32_t kn) {
     extern __shared__ __align__(16) unsigned char lds[];
-    int32_t* hist = reinterpret_cast<int32_t*>(lds);
-    const int tid = (int)threadIdx.x;
-    const int lo = kRange ? k_lo : 0, n = kRange ? kn : K;
-    for (int k = tid; k < n; k += 256) hist[k] = 0;
-    __syncthreads();
-    const int64_t per = (T + gridDim.x - 1) / gridDim.x;
-    const int64_t t_lo = per * blockIdx.x, t_hi = (t_lo + per < T) ? t_lo + per : T;
-    for (int64_t t = t_lo + tid; t < t_hi; t += 256) {
-        const int k = (int)z[t] - lo;
-        if (!kRange || (unsigned)k < (unsigned)n) atomicAdd(&hist[k], 1);
-    }
-    __syncthreads();
-    for (int k = tid; k < n; k += 256) {
-        const int c = hist[k];
-        if (c != 0) atomicAdd(&n_k[lo + k], c);
-    }
+    const int64_t per = ((T + gridDim.x - 1) / gridDim.x + 7) & ~(int64_t)7;
+    const int64_t lo = min(per * blockIdx.x, T);
+    add_topic_totals<kRange>(reinterpret_cast<int32_t*>(lds), z, lo, min(lo + per, T), n_k, kRange ? k_lo : 0,
+                             kRange ? kn : K);
 }
 
 // The same totals as column sums of n_wk (cheaper than a pass over z when V K is small next to
@@ -334,6 +377,12 @@ __device__ __forceinline__ void close_row(unsigned char* head, int n_entries, in
     }
 }
 
+// The topic totals that nobody reads any more (null: there are none), for the next phi rebuild to add to.
+__device__ __forceinline__ void clear_old_totals(int32_t* old_n_k, int32_t K) {
+    if (old_n_k)
+        for (int k = (int)(blockIdx.x * blockDim.x + threadIdx.x); k < K; k += (int)(gridDim.x * blockDim.x)) old_n_k[k] = 0;
+}
+
 // Update theta (Section 6.2): document by document, (1) a dense K-long histogram of the
 // document's assignments, reached through the document->token map, (2) compaction of the
 // non-zero bins into the row (topics ascending).  One wave per document, persistent; the
@@ -360,8 +409,9 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
                                                            int32_t K, double alpha,
                                                            const double* lg_table,
                                                            unsigned long long* visited_partial,
-                                                           double* ll_partial) {
+                                                           double* ll_partial, int32_t* old_n_k) {
     typedef typename Layout::Entry Entry;
+    clear_old_totals(old_n_k, K);
     if (T == 0) {       // no token anywhere: the loads "past a document's end" still need a place that exists
         doc_map = nullptr;
         z = reinterpret_cast<const uint16_t*>(docs);
@@ -581,8 +631,9 @@ __global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* do
                                                                 int32_t K, double alpha,
                                                                 const double* lg_table,
                                                                 unsigned long long* visited_partial,
-                                                                double* ll_partial) {
+                                                                double* ll_partial, int32_t* old_n_k) {
     typedef typename Layout::Entry Entry;
+    clear_old_totals(old_n_k, K);
     extern __shared__ __align__(16) unsigned char lds[];
     const int lane = (int)threadIdx.x, half = lane >> 5, hl = lane & 31;
     const int n_counters = (K + 1) / 2, n_marks = (K + 31) / 32;

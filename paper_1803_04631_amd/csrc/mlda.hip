@@ -148,7 +148,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 int tile_tokens_for(int32_t K) { return K <= 2048 ? 1024 : 4096; }
 constexpr int kPhiSegment = 16384;    // tokens one workgroup histograms for the phi rebuild
-constexpr int32_t kHistTopics = 32768; // 32-bit counters of the phi and n_k histograms that share a workgroup's LDS
+constexpr int32_t kHistTopics = 32768; // 32-bit counters of the n_k histogram that share a workgroup's LDS
 
 // A theta row's slot: a header of kRowHeader bytes (the row's number of entries), then the
 // entries, filled up to whole 16-byte units.  A document of n tokens needs at most
@@ -220,6 +220,8 @@ RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t V, int32_t K) {
 constexpr int kLoglikBlocks = 2048;
 constexpr int kSmallLoglikBlocks = 256;     // up to so many, the word side's last workgroup adds up
 constexpr int kMaxThetaGrid = 4096;    // workgroups of the theta rebuild (each leaves one likelihood partial and one count)
+// Up to this K a resident context has a second n_k (in what loglik_word_side_kernel leaves of its partials).
+constexpr int32_t kSpareTotals = 2 * kLoglikBlocks;
 constexpr int kEntryRing = 2048;      // per-rebuild counters of theta row entries (> kMaxTimedIters)
 
 // Where the buffers of one chunk of documents lie inside its part of the workspace (byte
@@ -586,6 +588,10 @@ struct mlda_ctx {
     std::vector<int32_t> wide_row;       // [V] host copy of phi[].wide_row
     int32_t* n_k[2] = {nullptr, nullptr};
     int model_cur = 0;
+    // resident, K <= kSpareTotals: two copies of n_k, [n_k_cur] is the current one; the theta rebuild clears the
+    // other for the next phi rebuild
+    int n_k_cur = 0;
+    bool spare_n_k_cleared = false;
     double *ll_partial = nullptr, *ll_scalars = nullptr;   // scalars: value, theta sum, document term
     double* lg_table = nullptr;          // lgG(c + alpha) - lgG(alpha), c < 1024, then lgG(alpha)
     double* lg_table_beta = nullptr;     // the same for beta
@@ -695,6 +701,8 @@ int launch_check(const char* what) {
     if (e != hipSuccess) return fail(MLDA_EHIP, std::string(what) + ": " + hipGetErrorString(e));
     return MLDA_OK;
 }
+
+const int32_t* current_n_k(const mlda_ctx* c) { return c->n_k[c->streamed ? c->model_cur : c->n_k_cur]; }
 
 int blocks_for(int64_t n, int per) { return (int)((n + per - 1) / per); }
 
@@ -827,41 +835,48 @@ int store_z_and_release(mlda_ctx* c, int32_t m, bool store) {
 // zeroed before the first chunk, and n_k is formed after the last (finish_model).
 int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which) {
     using namespace mlda;
-    // one counter per topic in LDS; K beyond kHistTopics is counted range by range
-    const int32_t span = std::min<int32_t>(c->K, kHistTopics);
-    const size_t hist_bytes = (size_t)span * 4;
-    const bool ranges = c->K > kHistTopics;
+    int32_t* n_k = nullptr;
+    int32_t n_totals = 0;           // workgroups of the phi launch that count the topic totals
+    const bool from_rows = (int64_t)c->V * c->K * 2 < c->T;
     if (!c->streamed) {
-        const dim3 grid((unsigned)c->n_split + 1u, (unsigned)blocks_for(c->K, 256));
-        hipLaunchKernelGGL(zero_sums_kernel, grid, dim3(256), 0, c->stream, c->split_words, c->phi[which], c->K,
-                           c->n_k[which], c->visited, c->theta_grid,
-                           c->rebuilds > 0 ? c->row_entries + ((c->rebuilds - 1) % kEntryRing) : nullptr);
+        const bool spare = c->n_k[0] != c->n_k[1];
+        const bool cleared = spare && c->spare_n_k_cleared;
+        if (spare) { c->n_k_cur ^= 1; c->spare_n_k_cleared = false; }
+        n_k = c->n_k[c->n_k_cur];
+        if (c->n_split > 0 || !cleared) {
+            const dim3 grid((unsigned)c->n_split + 1u, (unsigned)blocks_for(c->K, 256));
+            hipLaunchKernelGGL(zero_sums_kernel, grid, dim3(256), 0, c->stream, c->split_words, c->phi[which], c->K,
+                               cleared ? (int32_t*)nullptr : n_k);
+        }
+        // n_k comes from the fresh n_wk where that is fewer bytes than z (and no LDS atomics); else from z, beside
+        // phi while the counters of both leave room for many workgroups per CU
+        if (!from_rows && c->K <= kSpareTotals) n_totals = (int32_t)std::min<int64_t>((c->T + 8191) / 8192, (int64_t)c->n_cus * 2);
     }
-    if (c->n_tiles > 0) {
-        if (!ranges)
-            hipLaunchKernelGGL(phi_tile_kernel<false>, dim3((unsigned)c->n_segs), dim3(256), hist_bytes, c->stream,
-                               c->segs, z, c->phi[which], c->K, 0, c->K);
-        else
-            for (int32_t k_lo = 0; k_lo < c->K; k_lo += span)
-                hipLaunchKernelGGL(phi_tile_kernel<true>, dim3((unsigned)c->n_segs), dim3(256), hist_bytes,
-                                   c->stream, c->segs, z, c->phi[which], c->K, k_lo, std::min(span, c->K - k_lo));
-        if (c->streamed) {
-            // n_k after the last chunk
-        } else if ((int64_t)c->V * c->K * 2 < c->T) {
-            // n_k as column sums of the fresh n_wk: fewer bytes than z and no LDS atomics
+    unsigned long long* visited_sum =
+        !c->streamed && c->rebuilds > 0 ? c->row_entries + ((c->rebuilds - 1) % kEntryRing) : nullptr;
+    const unsigned blocks = (unsigned)(c->n_segs + n_totals + (visited_sum ? 1 : 0));
+    if (blocks > 0)
+        hipLaunchKernelGGL(phi_tile_kernel, dim3(blocks), dim3(256), phi_tile_lds_bytes(c->K, n_totals > 0), c->stream,
+                           c->segs, c->n_segs, z, c->phi[which], c->K, c->T, n_totals, n_k, c->visited, c->theta_grid,
+                           visited_sum);
+    if (!c->streamed && c->T > 0 && n_totals == 0) {        // (streamed: after the last chunk)
+        if (from_rows) {
             const int words_per_slice = 64;
             dim3 grid((unsigned)blocks_for(c->K, 256), (unsigned)blocks_for(c->V, words_per_slice));
             hipLaunchKernelGGL(topic_totals_from_rows_kernel, grid, dim3(256), 0, c->stream,
-                               c->phi[which], c->V, c->n_wide, c->K, words_per_slice, c->n_k[which]);
+                               c->phi[which], c->V, c->n_wide, c->K, words_per_slice, n_k);
         } else {
-            const int grid = (int)std::min<int64_t>((c->T + 4095) / 4096, (int64_t)c->n_cus * 8);
-            if (!ranges)
+            // one counter per topic in LDS; K beyond kHistTopics is counted range by range
+            const int32_t span = std::min<int32_t>(c->K, kHistTopics);
+            const size_t hist_bytes = (size_t)span * 4;
+            const int grid = (int)std::min<int64_t>((c->T + 8191) / 8192, (int64_t)c->n_cus * 2);
+            if (c->K <= kHistTopics)
                 hipLaunchKernelGGL(topic_totals_kernel<false>, dim3((unsigned)grid), dim3(256), hist_bytes,
-                                   c->stream, z, c->T, c->n_k[which], c->K, 0, c->K);
+                                   c->stream, z, c->T, n_k, c->K, 0, c->K);
             else
                 for (int32_t k_lo = 0; k_lo < c->K; k_lo += span)
                     hipLaunchKernelGGL(topic_totals_kernel<true>, dim3((unsigned)grid), dim3(256), hist_bytes,
-                                       c->stream, z, c->T, c->n_k[which], c->K, k_lo, std::min(span, c->K - k_lo));
+                                       c->stream, z, c->T, n_k, c->K, k_lo, std::min(span, c->K - k_lo));
         }
     }
     return launch_check("phi rebuild kernels");
@@ -909,9 +924,11 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
         const double* lg_table = c->lg_table;
         double* ll_partial = c->ll_partial + 2 * kLoglikBlocks;
         unsigned long long* visited = c->visited;
-        void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &visited, &ll_partial};
+        int32_t* old_n_k = !c->streamed && c->n_k[0] != c->n_k[1] ? c->n_k[c->n_k_cur ^ 1] : nullptr;
+        void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &visited, &ll_partial, &old_n_k};
         HIP_TRY(hipLaunchKernel(kernel, dim3((unsigned)c->theta_grid), dim3((unsigned)(long_docs ? kWave * kLongDocWaves : kWave)),
                                 args, lds, c->stream));
+        c->spare_n_k_cleared = old_n_k != nullptr;
         // (one chunk: the next rebuild_phi adds the counts up; sampler bytes are asked of earlier ones only)
         if (c->streamed)
             hipLaunchKernelGGL(visited_sum_kernel, dim3(1), dim3(256), 0, c->stream, c->visited, c->theta_grid,
@@ -931,7 +948,7 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     a.z_next = z_next;
     a.slots = c->slots;
     a.phi = c->phi[c->model_cur];
-    a.n_k = c->n_k[c->model_cur];
+    a.n_k = current_n_k(c);
     a.K = c->K;
     a.Kpad = c->Kpad;
     a.alpha = c->alpha;
@@ -979,7 +996,7 @@ int launch_loglik(mlda_ctx* c) {
     const double* theta_sum = c->streamed ? c->ll_scalars + 1 : nullptr;
     const double* doc_term = c->ll_scalars + 2;
     hipLaunchKernelGGL(loglik_word_side_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream,
-                       c->phi[c->model_cur], cells, wide_cells, c->n_k[c->model_cur], c->K, c->beta,
+                       c->phi[c->model_cur], cells, wide_cells, current_n_k(c), c->K, c->beta,
                        (double)c->V * c->beta, c->lg_table_beta, c->ll_partial, theta_partial, n_theta, theta_sum,
                        doc_term, small ? (unsigned int*)(c->ll_scalars + 3) : (unsigned int*)nullptr, c->ll_scalars);
     if (!small)
@@ -1062,6 +1079,7 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     c->n_k[0] = (int32_t*)(base + ML.n_k[0]);
     c->n_k[1] = (int32_t*)(base + ML.n_k[1]);
     c->ll_partial = (double*)(base + ML.ll_partial);
+    if (!c->streamed && c->K <= kSpareTotals) c->n_k[1] = (int32_t*)(c->ll_partial + kLoglikBlocks);
     c->ll_scalars = (double*)(base + ML.ll_scalars);
     c->lg_table = (double*)(base + ML.lg_table);
     c->lg_table_beta = c->lg_table + (mlda::kLgTable + 1);
@@ -1089,11 +1107,13 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
                                             hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit));
     if ((size_t)c->K * 4 > 48 * 1024) {
         const int hist_bytes = std::min<int32_t>(c->K, kHistTopics) * 4;
-        for (const void* kernel : {(const void*)mlda::phi_tile_kernel<false>, (const void*)mlda::phi_tile_kernel<true>,
-                                   (const void*)mlda::topic_totals_kernel<false>,
+        for (const void* kernel : {(const void*)mlda::topic_totals_kernel<false>,
                                    (const void*)mlda::topic_totals_kernel<true>})
             HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, hist_bytes));
     }
+    if (mlda::phi_tile_lds_bytes(c->K, false) > 48 * 1024)
+        HIP_TRY(hipFuncSetAttribute((const void*)mlda::phi_tile_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)mlda::phi_tile_lds_bytes(65535, false)));
     for (bool wide : {false, true})         // (large K only: 4-byte rows of any K)
         if (mlda::theta_lds_bytes(c->K, wide) > 48 * 1024 &&
             mlda::theta_lds_bytes(c->K, wide) <= (size_t)c->lds_limit)      // (else see check_theta_lds)
@@ -1851,7 +1871,7 @@ int mlda_get_word_topic(mlda_ctx* c, int32_t* n_wk) {
 int mlda_get_topic_totals(mlda_ctx* c, int32_t* n_k) {
     RC_TRY(need_state(c));
     if (!n_k) return fail(MLDA_EINVAL, "n_k is null");
-    HIP_TRY(hipMemcpyAsync(n_k, c->n_k[c->model_cur], (size_t)c->K * 4, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipMemcpyAsync(n_k, current_n_k(c), (size_t)c->K * 4, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return MLDA_OK;
 }

@@ -595,6 +595,32 @@ def test_phi_cell_widths(mlda):
         model.close()
 
 
+@pytest.mark.parametrize("K", [1, 7, 8, 4095, 4096, 4097, 33001])
+def test_phi_segment_edges(mlda, K):
+    """phi and n_k of words whose tokens begin and end anywhere between the aligned eights that are read
+    at a time, with rows that start in either half of a dword, whole words and words of several
+    segments; totals counted beside phi (K <= 4096), in a launch of their own and in ranges of
+    topics.  Three states in a row: the totals of one are cleared while the next is counted."""
+    word_counts = np.array([1, 7, 0, 8, 9, 15, 16, 17, 1023, 16383, 1, 16384, 16385, 0, 33000, 3])
+    V, alpha, beta = len(word_counts), 0.5, 0.01
+    rng = np.random.default_rng(K)
+
+    class C:
+        pass
+    c = C(); c.word_ids = rng.permutation(np.repeat(np.arange(V, dtype=np.int32), word_counts)); c.T = len(c.word_ids)
+    lens = rng.multinomial(c.T, np.ones(300) / 300).astype(np.int64)
+    c.doc_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    for chunks in (1, 2):
+        model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, beta, SEED, chunks=chunks)
+        for _ in range(3):
+            z = rng.integers(K, size=c.T).astype(np.uint16)
+            model.set_assignments(z)
+            check_counts(model, c, z, V, K)
+        if K < 5000:
+            check_step(model, c, z, V, K, alpha, beta, SEED, 1)
+        model.close()
+
+
 @pytest.mark.parametrize("how", ["own_stream", "stream_per_thread", "streamed"])
 def test_large_transfers(mlda, how):
     """Transfers of 8 MB and more go through eight pinned pieces of 2 MB, each with a thread of its own:
