@@ -90,13 +90,18 @@ __device__ __forceinline__ void add_topic_totals(int32_t* hist, const uint16_t* 
 // Update phi (Section 6.2: word by word, atomics with good locality): a workgroup
 // histograms one segment (up to 16384 consecutive tokens of one word) in LDS, then stores
 // the word's row outright if the segment is the whole word, else adds its non-zero bins
-// to the row.  A segment's counts fit 16 bits: two topics share a dword of LDS as they do in a
-// 16-bit row, so that a row leaves as it lies in LDS, and every K fits the LDS at once.  A narrow
-// row is added to by dwords of two cells; the word has fewer than 2^16 tokens, so no sum carries into the
-// neighbouring cell.
+// to the row.  A narrow row is written by dwords of two cells and more, and added to by dwords; the word
+// has fewer than 2^16 tokens, so no sum carries into the neighbouring cell.
+// Bound by the LDS atomics, 33 to 50 cycles of a CU for a wave's 64 tokens: 7.4e8 tokens at K = 1,000
+// take 0.52 ms, 3.4 TB/s (0.62 with 2-byte loads and stores; 0.79 with a wide row's cells added in pairs).
+// kPacked: two topics share a dword of LDS (a segment's counts fit 16 bits), so that every K fits at once.
+// More atomics then meet at one address: 1e6 to 1e7 tokens at K = 128 ... 1,537 take 3 to 9 % longer than
+// with a dword per topic.  Where that takes so much LDS that fewer workgroups fit a CU it is the slower one:
+// 2e7 tokens at K = 4,200 90 us (packed 92), 8,000 131 (123), 16,000 158 (147), 30,000 290 (250).
 // The workgroups from n_segs on do what else one launch can (each launch costs a small corpus 5 us):
 // n_totals of them add the topic totals of a share of the tokens to n_k (which is zero on entry), and the
 // last one adds up the counts that the theta rebuild before left (`visited`, to visited_sum; null: none).
+template <bool kPacked>
 __global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t n_segs, const uint16_t* z,
                                                        PhiView phi, int32_t K, int64_t T, int32_t n_totals, int32_t* n_k,
                                                        const unsigned long long* visited, int n_visited,
@@ -117,25 +122,38 @@ __global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t
     uint32_t* hist = reinterpret_cast<uint32_t*>(lds);
     const Tile tl = segs[blockIdx.x];
     const int wide_row = phi.wide_row[tl.word];
-    const int n_dwords = (K + 1) / 2;
-    for (int i = tid; i < (n_dwords + 3) / 4; i += 256) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+    const int n_counters = kPacked ? (K + 1) / 2 : K;
+    for (int i = tid; i < (n_counters + 3) / 4; i += 256) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    for_topics(z, tl.begin, (int64_t)tl.begin + tl.count,
-               [&](int k) { atomicAdd(&hist[k >> 1], 1u << ((k & 1) << 4)); });
+    for_topics(z, tl.begin, (int64_t)tl.begin + tl.count, [&](int k) {
+        if (kPacked) atomicAdd(&hist[k >> 1], 1u << ((k & 1) << 4));
+        else atomicAdd(&hist[k], 1u);
+    });
     __syncthreads();
+    auto count_of = [&](int k) -> uint32_t {        // (0 outside the row)
+        if ((unsigned)k >= (unsigned)K) return 0u;
+        return kPacked ? (hist[k >> 1] >> ((k & 1) << 4)) & 0xffffu : hist[k];
+    };
     if (wide_row >= 0) {                // (2^16 tokens or more: never a whole word)
         int32_t* row = phi.wide + (size_t)wide_row * (size_t)K;
-        for (int i = tid; i < n_dwords; i += 256) {
-            const uint32_t two = hist[i];
-            if ((two & 0xffffu) != 0u) atomicAdd(&row[2 * i], (int)(two & 0xffffu));
-            if ((two >> 16) != 0u) atomicAdd(&row[2 * i + 1], (int)(two >> 16));
+        for (int k = tid; k < K; k += 256) {
+            const int c = (int)count_of(k);
+            if (c != 0) atomicAdd(&row[k], c);
         }
         return;
     }
     const size_t cell0 = (size_t)tl.word * (size_t)K;
     if (tl.whole && (K & 7) == 0) {     // (every row starts at a multiple of 16 bytes)
         uint4* row = reinterpret_cast<uint4*>(phi.narrow + cell0);
-        for (int i = tid; i < K / 8; i += 256) row[i] = reinterpret_cast<const uint4*>(lds)[i];
+        const uint4* counts = reinterpret_cast<const uint4*>(lds);
+        for (int i = tid; i < K / 8; i += 256) {
+            if (kPacked) {
+                row[i] = counts[i];
+            } else {
+                const uint4 a = counts[2 * i], b = counts[2 * i + 1];
+                row[i] = make_uint4(a.x | a.y << 16, a.z | a.w << 16, b.x | b.y << 16, b.z | b.w << 16);
+            }
+        }
         return;
     }
     // The row's dwords: with an odd K every other row starts in the upper half of one, which then holds
@@ -143,23 +161,23 @@ __global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t
     const int odd = (int)(cell0 & 1);
     uint32_t* dwords = reinterpret_cast<uint32_t*>(phi.narrow) + (cell0 >> 1);
     for (int i = tid; i < (K + odd + 1) / 2; i += 256) {
-        uint32_t two;                   // the cells 2 i - odd and 2 i - odd + 1
-        if (odd) two = (i > 0 ? hist[i - 1] >> 16 : 0u) | (i < n_dwords ? hist[i] << 16 : 0u);
-        else two = hist[i];
+        const int k = 2 * i - odd;
+        const uint32_t two = count_of(k) | count_of(k + 1) << 16;
         if (!tl.whole) {
             if (two != 0u) atomicAdd(&dwords[i], two);
-        } else if (2 * i - odd < 0) {
+        } else if (k < 0) {
             phi.narrow[cell0] = (uint16_t)(two >> 16);
-        } else if (2 * i - odd + 1 >= K) {
-            phi.narrow[cell0 + K - 1] = (uint16_t)two;
+        } else if (k + 1 >= K) {
+            phi.narrow[cell0 + k] = (uint16_t)two;
         } else {
             dwords[i] = two;
         }
     }
 }
-// LDS bytes of a launch of it.
-__host__ __device__ inline size_t phi_tile_lds_bytes(int32_t K, bool totals) {
-    return totals ? ((size_t)K * 4 + 15) & ~(size_t)15 : ((size_t)((K + 1) / 2) * 4 + 15) & ~(size_t)15;
+// Up to which K a topic has a dword, and the LDS bytes of a launch (the totals' counters are dwords).
+constexpr int32_t kPhiDwordTopics = 4096;
+__host__ __device__ inline size_t phi_tile_lds_bytes(int32_t K) {
+    return ((K <= kPhiDwordTopics ? (size_t)K * 4 : (size_t)((K + 1) / 2) * 4) + 15) & ~(size_t)15;
 }
 
 // n_k[k] = number of tokens with topic k, as a launch of its own: each workgroup over a contiguous

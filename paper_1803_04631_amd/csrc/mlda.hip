@@ -222,6 +222,7 @@ constexpr int kSmallLoglikBlocks = 256;     // up to so many, the word side's la
 constexpr int kMaxThetaGrid = 4096;    // workgroups of the theta rebuild (each leaves one likelihood partial and one count)
 // Up to this K a resident context has a second n_k (in what loglik_word_side_kernel leaves of its partials).
 constexpr int32_t kSpareTotals = 2 * kLoglikBlocks;
+static_assert(kSpareTotals <= mlda::kPhiDwordTopics, "phi and the totals share a launch's LDS");
 constexpr int kEntryRing = 2048;      // per-rebuild counters of theta row entries (> kMaxTimedIters)
 
 // Where the buffers of one chunk of documents lie inside its part of the workspace (byte
@@ -856,7 +857,8 @@ int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which) {
         !c->streamed && c->rebuilds > 0 ? c->row_entries + ((c->rebuilds - 1) % kEntryRing) : nullptr;
     const unsigned blocks = (unsigned)(c->n_segs + n_totals + (visited_sum ? 1 : 0));
     if (blocks > 0)
-        hipLaunchKernelGGL(phi_tile_kernel, dim3(blocks), dim3(256), phi_tile_lds_bytes(c->K, n_totals > 0), c->stream,
+        hipLaunchKernelGGL((c->K <= kPhiDwordTopics ? phi_tile_kernel<false> : phi_tile_kernel<true>), dim3(blocks),
+                           dim3(256), phi_tile_lds_bytes(c->K), c->stream,
                            c->segs, c->n_segs, z, c->phi[which], c->K, c->T, n_totals, n_k, c->visited, c->theta_grid,
                            visited_sum);
     if (!c->streamed && c->T > 0 && n_totals == 0) {        // (streamed: after the last chunk)
@@ -1111,9 +1113,9 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
                                    (const void*)mlda::topic_totals_kernel<true>})
             HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, hist_bytes));
     }
-    if (mlda::phi_tile_lds_bytes(c->K, false) > 48 * 1024)
-        HIP_TRY(hipFuncSetAttribute((const void*)mlda::phi_tile_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)mlda::phi_tile_lds_bytes(65535, false)));
+    if (mlda::phi_tile_lds_bytes(c->K) > 48 * 1024)
+        HIP_TRY(hipFuncSetAttribute((const void*)mlda::phi_tile_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)mlda::phi_tile_lds_bytes(65535)));
     for (bool wide : {false, true})         // (large K only: 4-byte rows of any K)
         if (mlda::theta_lds_bytes(c->K, wide) > 48 * 1024 &&
             mlda::theta_lds_bytes(c->K, wide) <= (size_t)c->lds_limit)      // (else see check_theta_lds)
