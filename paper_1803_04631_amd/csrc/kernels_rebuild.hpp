@@ -629,50 +629,62 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
     block_partial_store(ll, ll_partial);
 }
 
-// The same for K <= 1024 and documents of fewer than 2^16 tokens, two documents per wave: the
-// mark bits of a document then fit one word per lane of a half-wave (32 lanes x 32 topics), so
-// lanes 0..31 rebuild one document and lanes 32..63 the next one with the same instructions,
-// which halves the instructions per document.  Documents 2 p and 2 p + 1 (neighbours in the
-// working order, so of similar length) make pair p; the topics of the first 128 tokens of each
-// document of the next pair are on their way while the current pair is counted.
+// The same for documents of fewer than 2^16 tokens, without a dense row.  One bit per topic marks the topics
+// of the document; a prefix sum over the mark words tells every marked topic its place among them
+// (its rank); the tokens then add to a cell per rank, {topic, count}, and the cells leave as the row,
+// one per lane in whole consecutive stores.  Against compacting a dense row of K counters: LDS of K / 4 bytes and a cell per
+// topic of a row instead of 2 K (K = 40,000: 17 KB and nine waves per CU instead of 92 KB and one), and every step
+// takes all lanes, where the lane that owns 32 topics walked its non-zero bins one by one.
+// kDocs = 2 (K <= 1024): lanes 0 .. 31 rebuild one document and lanes 32 .. 63 the next one in the working order
+// (of similar length) with the same instructions: a document's mark words are one per lane then.
+// n_cells: a row with more topics is made in several rounds of so many; n_stage: so many of the
+// topics of the tokens beyond those in registers are kept in LDS, the rest is read again.
+// Tokens per lane whose topics are in registers: 128 of each document (256 with one document per wave
+// took 6 to 9 % longer on 1e8 tokens in documents of 330: more lines of z in use at once).
+__host__ __device__ constexpr int rank_keep(int docs) { return docs == 1 ? 2 : 4; }
 constexpr int kPairMaxK = 1024;
-constexpr int kPairStage = 256;         // entries of a row that are lined up in LDS before they are stored
-__host__ __device__ inline size_t theta_pair_lds_bytes(int32_t K) {
-    return 2 * theta_hist_bytes(K, false) + (size_t)kThetaLgTable * 8 + 2 * (size_t)kPairStage * 4 + kWave * 4;
+__host__ __device__ inline int theta_rank_words(int32_t K) { return ((K + 31) / 32 + 3) & ~3; }
+__host__ __device__ inline int theta_rank_cells(int32_t K, int64_t longest, int docs) {
+    const int64_t most = docs == 1 ? 1024 : 512, n = K < longest ? K : longest;
+    return (int)(((n < most ? n : most) + 3) & ~(int64_t)3);
+}
+__host__ __device__ inline int theta_rank_stage(int64_t longest, int docs) {
+    const int64_t most = docs == 1 ? 2048 : 256, n = longest - rank_keep(docs) * (kWave / docs);
+    return n <= 0 ? 0 : (int)(((n < most ? n : most) + 3) & ~(int64_t)3);
+}
+__host__ __device__ inline size_t theta_rank_lds_bytes(int32_t K, int64_t longest, int docs) {
+    return (size_t)docs * ((size_t)theta_rank_words(K) * 8 + (size_t)theta_rank_cells(K, longest, docs) * 4 +
+                           (size_t)theta_rank_stage(longest, docs) * 2) + (size_t)kThetaLgTable * 8;
 }
 
-template <class Layout>
-__global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* docs,
-                                                                const int32_t* doc_map,
-                                                                const uint16_t* z, uint2* row_rec,
-                                                                unsigned char* slots, int64_t D, int64_t T,
-                                                                int32_t K, double alpha,
-                                                                const double* lg_table,
-                                                                unsigned long long* visited_partial,
-                                                                double* ll_partial, int32_t* old_n_k) {
+template <class Layout, int kDocs>
+__global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs, const int32_t* doc_map,
+                                                             const uint16_t* z, uint2* row_rec,
+                                                             unsigned char* slots, int64_t D, int64_t T,
+                                                             int32_t K, double alpha, const double* lg_table,
+                                                             unsigned long long* visited_partial,
+                                                             double* ll_partial, int32_t* old_n_k,
+                                                             int32_t n_cells, int32_t n_stage) {
     typedef typename Layout::Entry Entry;
+    constexpr int W = kWave / kDocs, kKeep = rank_keep(kDocs);      // lanes per document
     clear_old_totals(old_n_k, K);
+    if (T == 0) {       // no token anywhere: the loads "past a document's end" still need a place that exists
+        doc_map = nullptr;
+        z = reinterpret_cast<const uint16_t*>(docs);
+    }
     extern __shared__ __align__(16) unsigned char lds[];
-    const int lane = (int)threadIdx.x, half = lane >> 5, hl = lane & 31;
-    const int n_counters = (K + 1) / 2, n_marks = (K + 31) / 32;
-    const size_t one = theta_hist_bytes(K, false);
-    // per half: paired 16-bit counters, then one mark bit per topic
-    uint32_t* hist = reinterpret_cast<uint32_t*>(lds + (size_t)half * one);
-    uint32_t* marks = reinterpret_cast<uint32_t*>(lds + (size_t)half * one + theta_counter_bytes(K, false));
-    double* table = reinterpret_cast<double*>(lds + 2 * one);
-    // per half: room to line up a row's entries before they are stored; a 2-byte entry with its
-    // topic's count above it (0 in the entries after the topic's first)
-    uint32_t* stage = reinterpret_cast<uint32_t*>(lds + 2 * one + (size_t)kThetaLgTable * 8) + half * kPairStage;
-    constexpr bool kMore = sizeof(Entry) == 2;
-    [[maybe_unused]] uint32_t* more = reinterpret_cast<uint32_t*>(lds + 2 * one + (size_t)kThetaLgTable * 8) +
-                                      2 * kPairStage + half * 32;
+    const int lane = (int)threadIdx.x, part = lane / W, hl = lane % W;
+    const int n_words = theta_rank_words(K);
+    // per document: {marks of 32 topics, topics marked before them}, the cells, the topics of further tokens
+    uint2* words = reinterpret_cast<uint2*>(lds) + part * n_words;
+    uint32_t* cells = reinterpret_cast<uint32_t*>(lds + (size_t)kDocs * n_words * 8) + part * n_cells;
+    uint16_t* stage = reinterpret_cast<uint16_t*>(lds + (size_t)kDocs * (n_words * 8 + n_cells * 4)) + part * n_stage;
+    double* table = reinterpret_cast<double*>(lds + (size_t)kDocs * (n_words * 8 + n_cells * 4 + n_stage * 2));
     const double lg_alpha = lg_table[kLgTable];
-    for (int k = hl; k < n_counters; k += 32) hist[k] = 0u;
-    for (int k = hl; k < n_marks; k += 32) marks[k] = 0u;
-    if constexpr (kMore) more[hl] = 0u;
+    for (int i = lane; i < kDocs * n_words / 2; i += kWave) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
     for (int c = lane; c < kThetaLgTable; c += kWave) table[c] = lg_table[c];
     __syncthreads();
-    unsigned long long visited = 0;      // sum of N_d * (nominal entries of row d) over this half's documents
+    unsigned long long visited = 0;      // sum of N_d * (nominal entries of row d) over this part's documents
     double ll = 0.0;
     auto add_ll = [&](int c) {
         if (c > 0 && c < kThetaLgTable) ll += table[c];
@@ -681,150 +693,204 @@ __global__ __launch_bounds__(kWave) void theta_rows_pair_kernel(const DocRec* do
                 ll += c < kLgTable ? lg_table[c] : lgamma_large((double)c + alpha) - lg_alpha;
         }
     };
-    // one more token of topic k; true if the topic's count has outgrown one entry (kPlainCount)
-    auto count_topic = [&](int k) -> bool {
-        const uint32_t both = atomicAdd(&hist[k >> 1], 1u << ((k & 1) << 4));
-        atomicOr(&marks[k >> 5], 1u << (k & 31));
-        const int before = (int)((both >> ((k & 1) << 4)) & 0xffffu);
-        if constexpr (kMore) more_entries<Layout>(more, k, before, K);
-        return before >= kPlainCount<Layout>;
+    // inclusive sum over the lanes of a document, and the last lane's value
+    auto part_sums = [](int v) {
+        if constexpr (kDocs == 1) return wave_inclusive_sum(v);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+        return v;
     };
-    auto topic_at = [&](const DocRec& r, int j) {       // topic of the document's token j, -1 past its end
-        const int p = doc_token_position(doc_map, r, j);
-        return p >= 0 ? (int)z[p] : -1;
+    auto part_last = [&](int sums) {
+        if constexpr (kDocs == 1) return read_lane(sums, kWave - 1);
+        const int a = read_lane(sums, W - 1), b = read_lane(sums, kWave - 1);
+        return part ? b : a;
     };
-    const int64_t n_pairs = (D + 1) / 2, step = gridDim.x;
+    auto most_of_parts = [&](int v) {       // (v the same in all lanes of a part)
+        if constexpr (kDocs == 1) return v;
+        return max(read_lane(v, 0), read_lane(v, W));
+    };
+    // counts up to this one are one entry, and one nominal entry, each
+    constexpr bool kNominal = Layout::kDoubleWeights;
+    const int plain = min(Layout::kMaxCount, kNominal && K < 1024 ? 15 : 16383);
+
+    const int64_t n_rounds = (D + kDocs - 1) / kDocs, step = gridDim.x;
     const DocRec none = {0, 0, 0u, 0};
-    auto record = [&](int64_t p) { return (p < n_pairs && 2 * p + half < D) ? docs[2 * p + half] : none; };
-    // each XCD takes a contiguous run of pairs (see theta_rows_kernel)
+    auto record = [&](int64_t r) {      // (the load is made for every r, from the last record if need be)
+        const int64_t d = r * kDocs + part;
+        const DocRec rec = docs[d < D ? d : D - 1];
+        return d < D ? rec : none;
+    };
+    // each XCD takes a contiguous run of documents (see theta_rows_kernel)
     const int per_xcd = (int)gridDim.x / kXcds;
     int64_t i = (int)blockIdx.x < per_xcd * kXcds
                     ? (int64_t)((int)blockIdx.x % kXcds) * per_xcd + (int)blockIdx.x / kXcds
                     : (int64_t)blockIdx.x;
-    DocRec cur = record(i), nxt = record(i + step);
-    int k0 = topic_at(cur, hl), k1 = topic_at(cur, hl + 32), k2 = topic_at(cur, hl + 64),
-        k3 = topic_at(cur, hl + 96);
-    for (; i < n_pairs; i += step) {
-        const int n0 = topic_at(nxt, hl), n1 = topic_at(nxt, hl + 32), n2 = topic_at(nxt, hl + 64),
-                  n3 = topic_at(nxt, hl + 96);
-        const DocRec after = record(i + 2 * step);
-        bool outgrown = false;
-        if (k0 >= 0) outgrown |= count_topic(k0);
-        if (k1 >= 0) outgrown |= count_topic(k1);
-        if (k2 >= 0) outgrown |= count_topic(k2);
-        if (k3 >= 0) outgrown |= count_topic(k3);
-        for (int j = 128 + hl; j < cur.n; j += 32) outgrown |= count_topic(topic_at(cur, j));
-        __syncthreads();
-        unsigned char* head = slots + (size_t)cur.slot * 16u;
-        Entry* ent = reinterpret_cast<Entry*>(head + kRowHeader);
-        // lane hl of a half owns mark word hl: 32 topics = 16 counter pairs
-        const uint32_t w = hl < n_marks ? marks[hl] : 0u;
-        const int distinct = __popc(w);
-        int mine = distinct, nominal = kMore ? distinct : 0;
-        const bool any_outgrown = __ballot(outgrown) != 0;
-        if (kMore && any_outgrown) {                 // some count of the pair takes several entries
-            const uint32_t m = more[hl];
-            mine += (int)(m & 0xffffu);
-            nominal += (int)(m >> 16);
-            if (m != 0u) more[hl] = 0u;
-        } else if (any_outgrown) {
-            mine = 0;
-            for (uint32_t rest = w; rest != 0u; rest &= rest - 1u) {
-                const int k = hl * 32 + __ffs((int)rest) - 1;
-                mine += entries_of<Layout>((int)((hist[k >> 1] >> ((k & 1) << 4)) & 0xffffu));
+    // One document per wave: three loads deep, as in theta_rows_kernel, every lane making every load.  Two
+    // per wave: the topics of the next two documents are on their way while these are counted (positions and
+    // topics of one token after the other: many gathers of a wave in flight at once measured slower).
+    auto topic_at = [&](const DocRec& r, int j) {
+        const int p = doc_token_position(doc_map, r, j);
+        return p >= 0 ? (int)z[p] : -1;
+    };
+    DocRec cur = record(i), nxt = record(i + step), after = record(i + 2 * step);
+    int topic[kKeep], next_at[kKeep];
+#pragma unroll
+    for (int t = 0; t < kKeep; ++t) {
+        if constexpr (kDocs == 1) {
+            topic[t] = doc_token_topic(z, doc_token_position_any(doc_map, cur, hl + t * W), cur, hl + t * W);
+            next_at[t] = doc_token_position_any(doc_map, nxt, hl + t * W);
+        } else {
+            topic[t] = topic_at(cur, hl + t * W);
+        }
+    }
+    for (; i < n_rounds; i += step) {
+        int next_topic[kKeep], after_at[kKeep];
+#pragma unroll
+        for (int t = 0; t < kKeep; ++t) {
+            if constexpr (kDocs == 1) next_topic[t] = doc_token_topic(z, next_at[t], nxt, hl + t * W);
+            else next_topic[t] = topic_at(nxt, hl + t * W);
+        }
+        if constexpr (kDocs == 1) {
+#pragma unroll
+            for (int t = 0; t < kKeep; ++t) after_at[t] = doc_token_position_any(doc_map, after, hl + t * W);
+        }
+        const DocRec later = record(i + 3 * step);
+
+        // ---- mark the topics
+        auto mark = [&](int k) {
+            if (k >= 0) atomicOr(&words[k >> 5].x, 1u << (k & 31));
+        };
+#pragma unroll
+        for (int t = 0; t < kKeep; ++t) mark(topic[t]);
+        const int rest = most_of_parts(cur.n) - kKeep * W;      // tokens beyond those, of the longer document
+        for (int s = hl; s - hl < rest; s += 4 * W) {
+            int at[4], k[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) at[t] = doc_token_position_any(doc_map, cur, kKeep * W + s + t * W);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) k[t] = doc_token_topic(z, at[t], cur, kKeep * W + s + t * W);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                mark(k[t]);
+                if (s + t * W < n_stage) stage[s + t * W] = (uint16_t)k[t];
             }
         }
-        // prefix over the 32 lanes of each half: the wave-wide scan without its last step
-        auto half_inclusive_sum = [](int v) {
-            v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
-            v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-            v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-            v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-            v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
-            return v;
+        __syncthreads();
+        // ---- topics marked before every word
+        int n_topics;
+        if constexpr (kDocs == 2) {
+            const int mine = hl < n_words ? __popc(words[hl].x) : 0;
+            const int upto = part_sums(mine);
+            if (hl < n_words) words[hl].y = (uint32_t)(upto - mine);
+            n_topics = part_last(upto);
+        } else {
+            n_topics = 0;
+            for (int base = 0; base < n_words; base += 4 * kWave) {
+                const int at = base + 4 * lane;         // four words per lane; n_words is a multiple of four
+                uint4* two = reinterpret_cast<uint4*>(words + at);
+                uint4 a = make_uint4(0u, 0u, 0u, 0u), b = a;
+                if (at < n_words) { a = two[0]; b = two[1]; }
+                const int c0 = __popc(a.x), c1 = __popc(a.z), c2 = __popc(b.x), mine = c0 + c1 + c2 + __popc(b.z);
+                const int upto = part_sums(mine);
+                a.y = (uint32_t)(n_topics + upto - mine);
+                a.w = a.y + (uint32_t)c0;
+                b.y = a.w + (uint32_t)c1;
+                b.w = b.y + (uint32_t)c2;
+                if (at < n_words) { two[0] = a; two[1] = b; }
+                n_topics += part_last(upto);
+            }
+        }
+        __syncthreads();
+        auto rank_of = [&](int k) {         // k >= 0, marked
+            const uint2 w = words[k >> 5];
+            return (int)(w.y + (uint32_t)__popc(w.x & ((1u << (k & 31)) - 1u)));
         };
-        const int upto = half_inclusive_sum(mine);
-        const int n_a = read_lane(upto, 31), n_b = read_lane(upto, 63);
-        const int n_entries = half ? n_b : n_a;
-        auto half_sum = [&](int v) {
-            const int v_upto = half_inclusive_sum(v), v_a = read_lane(v_upto, 31), v_b = read_lane(v_upto, 63);
-            return half ? v_b : v_a;
-        };
-        const bool any_split = __ballot(mine != distinct) != 0;
-        const int nnz = any_split ? half_sum(distinct) : n_entries;       // distinct topics of the row
-        int at = upto - mine;
-        if (w != 0u) marks[hl] = 0u;
-        uint32_t pairs = (w | (w >> 1)) & 0x55555555u;
-        const bool real = 2 * i + half < D;              // the last pair may lack its second document
-        const int n_longer = max(n_a, n_b);
-        if ((kMore || !any_split) && n_longer <= kPairStage) {
-            // The usual case: the lanes that own the bins only line the
-            // entries up in LDS; the lanes then take them one each, so that the row leaves in
-            // whole consecutive stores and the likelihood's term is added with all lanes busy.
-            auto line_up = [&](int place, int k, int c) {
-                if constexpr (!kMore) {
-                    stage[place++] = (uint32_t)Layout::make(c, k);
-                } else {
-                    uint32_t whole = (uint32_t)c << 16;
-                    for (; c > Layout::kMaxCount; c -= Layout::kMaxCount) {
-                        stage[place++] = Layout::make(Layout::kMaxCount, k) | whole;
-                        whole = 0u;
-                    }
-                    stage[place++] = Layout::make(c, k) | whole;
+        int rank[kKeep];
+#pragma unroll
+        for (int t = 0; t < kKeep; ++t) rank[t] = topic[t] >= 0 ? rank_of(topic[t]) : -1;
+        // ---- the row, n_cells topics at a time
+        unsigned char* head = slots + (size_t)cur.slot * 16u;
+        Entry* ent = reinterpret_cast<Entry*>(head + kRowHeader);
+        int filled = 0, further = 0;        // entries so far; nominal entries beyond one per topic (this lane's)
+        bool any_further = false;
+        const int most_topics = most_of_parts(n_topics);
+        for (int first = 0; first < most_topics; first += n_cells) {
+            const int cleared = min(n_topics - first, n_cells);
+            for (int e = 4 * hl; e < cleared; e += 4 * W) *reinterpret_cast<uint4*>(cells + e) = make_uint4(0u, 0u, 0u, 0u);
+            // a cell: the count below, the topic above (written by every token of the topic)
+            auto add_token = [&](int k, int at) {
+                if ((unsigned)at < (unsigned)n_cells) {
+                    reinterpret_cast<uint16_t*>(cells + at)[1] = (uint16_t)k;
+                    atomicAdd(&cells[at], 1u);
                 }
-                return place;
             };
-            while (__ballot(pairs != 0u) != 0) {
-                if (pairs != 0u) {
-                    const int k = hl * 32 + __ffs((int)pairs) - 1;    // even topic of the pair
-                    pairs &= pairs - 1u;
-                    const uint32_t both = hist[k >> 1];
-                    hist[k >> 1] = 0u;
-                    const int lo = (int)(both & 0xffffu), hi = (int)(both >> 16);
-                    if (lo != 0) at = line_up(at, k, lo);
-                    if (hi != 0) at = line_up(at, k + 1, hi);
-                    if (!kMore) nominal += nominal_entries(lo, K) + nominal_entries(hi, K);
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < kKeep; ++t) add_token(topic[t], rank[t] < 0 ? -1 : rank[t] - first);
+            // the tokens beyond those in registers, four per lane at a time
+            const int n_rest = cur.n - kKeep * W;
+            for (int s = hl; s - hl < rest; s += 4 * W) {
+                int k[4], at[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int j = s + t * W;
+                    k[t] = j < n_rest && j < n_stage ? (int)stage[j] : -1;
                 }
+                if (s - hl + 4 * W > n_stage) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int j = s + t * W;
+                        if (j >= n_stage) k[t] = topic_at(cur, kKeep * W + j);
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) at[t] = k[t] >= 0 ? rank_of(k[t]) - first : -1;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) add_token(k[t], at[t]);
             }
             __syncthreads();
-            for (int first = 0; first < n_longer; first += 32) {
-                const int e = first + hl;
-                int c = 0;
-                if (e < n_entries) {
-                    const uint32_t v = stage[e];
-                    ent[e] = (Entry)v;
-                    c = kMore ? (int)(v >> 16) : Layout::entry_count((Entry)v);
+            const int here = min(n_topics - first, n_cells), most_here = min(most_topics - first, n_cells);
+            for (int e0 = 0; e0 < most_here; e0 += W) {
+                const uint32_t cell = e0 + hl < here ? cells[e0 + hl] : 0u;
+                const int c = (int)(cell & 0xffffu), k = (int)(cell >> 16);
+                if (__ballot(c > plain) == 0) {
+                    if (c > 0) ent[filled + hl] = Layout::make(c, k);
+                    filled += max(min(here - e0, W), 0);
+                } else {                    // some count takes several entries
+                    any_further = true;
+                    const int mine = c > 0 ? entries_of<Layout>(c) : 0;
+                    const int upto = part_sums(mine);
+                    if (c > 0) {
+                        write_entries<Layout>(ent, filled + upto - mine, k, c);
+                        if (kNominal) further += nominal_entries(c, K) - 1;
+                    }
+                    filled += part_last(upto);
                 }
                 add_ll(c);
             }
-        } else {
-            while (__ballot(pairs != 0u) != 0) {
-                int lo = 0, hi = 0;
-                if (pairs != 0u) {
-                    const int k = hl * 32 + __ffs((int)pairs) - 1;    // even topic of the pair
-                    pairs &= pairs - 1u;
-                    const uint32_t both = hist[k >> 1];
-                    hist[k >> 1] = 0u;
-                    lo = (int)(both & 0xffffu);
-                    hi = (int)(both >> 16);
-                    if (lo != 0) at = write_entries<Layout>(ent, at, k, lo);
-                    if (hi != 0) at = write_entries<Layout>(ent, at, k + 1, hi);
-                    if (!kMore) nominal += nominal_entries(lo, K) + nominal_entries(hi, K);
-                }
-                add_ll(lo);
-                add_ll(hi);
-            }
+            __syncthreads();
         }
-        close_row<Layout>(head, n_entries, K, hl, real);
-        const int n_nominal = kMore && !any_outgrown ? n_entries : half_sum(nominal);
+        for (int w = 2 * hl; w < n_words; w += 2 * W) *reinterpret_cast<uint4*>(words + w) = make_uint4(0u, 0u, 0u, 0u);
+        const bool real = i * kDocs + part < D;          // the last round may lack its second document
+        close_row<Layout>(head, filled, K, hl, real);
+        int nominal = filled;
+        if (kNominal && any_further) nominal = n_topics + part_last(part_sums(further));
         if (real && hl == 0) {
-            row_rec[cur.doc].y = (uint32_t)nnz;          // distinct topics, for the getters
-            visited += (unsigned long long)cur.n * (unsigned long long)n_nominal;
+            row_rec[cur.doc].y = (uint32_t)n_topics;     // distinct topics, for the getters
+            visited += (unsigned long long)cur.n * (unsigned long long)nominal;
         }
         __syncthreads();
-        cur = nxt; nxt = after; k0 = n0; k1 = n1; k2 = n2; k3 = n3;
+        cur = nxt; nxt = after; after = later;
+#pragma unroll
+        for (int t = 0; t < kKeep; ++t) {
+            topic[t] = next_topic[t];
+            if constexpr (kDocs == 1) next_at[t] = after_at[t];
+        }
     }
-    visited += __shfl_xor(visited, 32, kWave);           // the other half's documents
+    if (kDocs == 2) visited += __shfl_xor(visited, W, kWave);       // the other part's documents
     if (lane == 0) visited_partial[blockIdx.x] = visited;
     block_partial_store(ll, ll_partial);
 }

@@ -120,21 +120,23 @@ bool long_docs_for(int64_t D, int64_t T, int64_t longest, int n_cus) {
     return (D <= (int64_t)n_cus * 4 && T / D >= D * 4096 / n_cus) ||
            longest >= D * 1700 / n_cus + T / (4 * n_cus);
 }
-template <int kDocWaves>
-const void* theta_kernel_with(RowKind rows, bool wide_counters) {
+// (with a dense row)
+const void* theta_kernel_for(RowKind rows, bool wide_counters, bool long_docs) {
     return with_layout(rows, [&](auto layout) {
         typedef decltype(layout) Layout;
-        return wide_counters ? (const void*)mlda::theta_rows_kernel<Layout, true, kDocWaves>
-                             : (const void*)mlda::theta_rows_kernel<Layout, false, kDocWaves>;
+        if (long_docs)
+            return wide_counters ? (const void*)mlda::theta_rows_kernel<Layout, true, mlda::kLongDocWaves>
+                                 : (const void*)mlda::theta_rows_kernel<Layout, false, mlda::kLongDocWaves>;
+        return wide_counters ? (const void*)mlda::theta_rows_kernel<Layout, true, 1>
+                             : (const void*)mlda::theta_rows_kernel<Layout, false, 1>;
     });
 }
-const void* theta_kernel_for(RowKind rows, bool wide_counters, bool long_docs) {
-    return long_docs ? theta_kernel_with<mlda::kLongDocWaves>(rows, wide_counters)
-                     : theta_kernel_with<1>(rows, wide_counters);
-}
-// (two documents per wave; K <= kPairMaxK)
-const void* theta_pair_kernel_for(RowKind rows) {
-    return with_layout(rows, [](auto layout) { return (const void*)mlda::theta_rows_pair_kernel<decltype(layout)>; });
+// (by ranks; `docs` documents per wave, two for K <= kPairMaxK)
+const void* theta_ranked_kernel_for(RowKind rows, int docs) {
+    return with_layout(rows, [&](auto layout) {
+        typedef decltype(layout) Layout;
+        return docs == 2 ? (const void*)mlda::theta_ranked_kernel<Layout, 2> : (const void*)mlda::theta_ranked_kernel<Layout, 1>;
+    });
 }
 constexpr int kMaxTimedIters = 1024;
 constexpr int kRunTiles = 16;           // small tiles a workgroup of the large-K sampler takes one after the other
@@ -633,6 +635,9 @@ struct mlda_ctx {
     uint2* doc_pairs = nullptr;          // streamed: {slot of the token's document, its topic}, document order
     mlda::DocRec* doc_order = nullptr;   // documents by falling length, as the theta rebuild walks them
     int32_t theta_grid = 0;
+    int theta_ranked = 0;                // documents per wave of theta_ranked_kernel, 0: theta_rows_kernel
+    bool theta_long_docs = false;
+    size_t theta_lds = 0;
     RowKind rows = RowKind::packed;
     bool wide_counters = false, short_docs = true;
     int32_t* split_words = nullptr;
@@ -734,7 +739,20 @@ void point_at(mlda_ctx* c, const HostChunk& h, unsigned char* base) {
     c->z[1] = (uint16_t*)(base + h.L.z1);
     c->slots = base + h.L.slots;
     c->cur = 0;
-    const size_t theta_lds = mlda::theta_lds_bytes(c->K, h.wide_counters);
+    c->theta_long_docs = long_docs_for(h.D, h.T, h.longest_doc, c->n_cus);
+    // Ranks, but for 32-bit counters and documents so long that reading their topics twice costs more than
+    // the dense row does; two documents per wave where a half-wave suits them: few topics, short documents.
+    // Ranks / dense row, rebuild of 3e6 tokens from random topics (trained: alike), us:
+    //   tokens       10         40        100       400      1,000     3,000
+    //   K = 100   86 / 145   35 / 94    28 / 73   25 / 65   37 / 52   70 / 51
+    //     1,000   86 / 128   35 / 82    29 / 72   28 / 66   42 / 61   79 / 57
+    //     5,000  150 / 284   47 / 123   30 / 84   28 / 60   54 / 52  155 / 59
+    //    30,000  295 / 2753  89 / 1142  49 / 568  38 / 228  65 / 154 203 / 125
+    c->theta_ranked = h.wide_counters || c->theta_long_docs || h.T > 1500 * h.D ? 0
+                      : c->K <= mlda::kPairMaxK && h.T <= 160 * h.D ? 2 : 1;
+    const size_t theta_lds = c->theta_ranked ? mlda::theta_rank_lds_bytes(c->K, h.longest_doc, c->theta_ranked)
+                                             : mlda::theta_lds_bytes(c->K, h.wide_counters);
+    c->theta_lds = theta_lds;
     // 16 one-wave workgroups per CU: enough to hide the gathers' latency; more of them
     // touch more lines of z at once than an XCD's L2 holds, and neighbours stop sharing
     const int per_cu = std::max(1, std::min(16, (int)(144 * 1024 / theta_lds)));
@@ -910,13 +928,10 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
     using namespace mlda;
     const int32_t* doc_map = c->streamed ? nullptr : c->doc_map;
     if (c->D > 0) {
-        const size_t theta_lds = theta_lds_bytes(c->K, c->wide_counters);
-        // two documents per wave where a half-wave suits them: few topics, short documents
-        const bool pairs = c->K <= kPairMaxK && !c->wide_counters && c->T <= 160 * c->D;
-        const bool long_docs = long_docs_for(c->D, c->T, c->at->longest_doc, c->n_cus);
-        const void* kernel =
-            pairs ? theta_pair_kernel_for(c->rows) : theta_kernel_for(c->rows, c->wide_counters, long_docs);
-        const size_t lds = pairs ? theta_pair_lds_bytes(c->K) : theta_lds;
+        const void* kernel = c->theta_ranked ? theta_ranked_kernel_for(c->rows, c->theta_ranked)
+                                             : theta_kernel_for(c->rows, c->wide_counters, c->theta_long_docs);
+        int32_t n_cells = theta_rank_cells(c->K, c->at->longest_doc, c->theta_ranked);
+        int32_t n_stage = theta_rank_stage(c->at->longest_doc, std::max(c->theta_ranked, 1));
         const DocRec* docs = c->doc_order;
         uint2* row_rec = c->row_rec;
         unsigned char* slots = c->slots;
@@ -927,9 +942,10 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
         double* ll_partial = c->ll_partial + 2 * kLoglikBlocks;
         unsigned long long* visited = c->visited;
         int32_t* old_n_k = !c->streamed && c->n_k[0] != c->n_k[1] ? c->n_k[c->n_k_cur ^ 1] : nullptr;
-        void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &visited, &ll_partial, &old_n_k};
-        HIP_TRY(hipLaunchKernel(kernel, dim3((unsigned)c->theta_grid), dim3((unsigned)(long_docs ? kWave * kLongDocWaves : kWave)),
-                                args, lds, c->stream));
+        void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &visited, &ll_partial, &old_n_k,
+                        &n_cells, &n_stage};        // (the last two: theta_ranked_kernel's)
+        HIP_TRY(hipLaunchKernel(kernel, dim3((unsigned)c->theta_grid), dim3((unsigned)(c->theta_long_docs ? kWave * kLongDocWaves : kWave)),
+                                args, c->theta_lds, c->stream));
         c->spare_n_k_cleared = old_n_k != nullptr;
         // (one chunk: the next rebuild_phi adds the counts up; sampler bytes are asked of earlier ones only)
         if (c->streamed)
@@ -1116,13 +1132,15 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     if (mlda::phi_tile_lds_bytes(c->K) > 48 * 1024)
         HIP_TRY(hipFuncSetAttribute((const void*)mlda::phi_tile_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)mlda::phi_tile_lds_bytes(65535)));
-    for (bool wide : {false, true})         // (large K only: 4-byte rows of any K)
-        if (mlda::theta_lds_bytes(c->K, wide) > 48 * 1024 &&
-            mlda::theta_lds_bytes(c->K, wide) <= (size_t)c->lds_limit)      // (else see check_theta_lds)
-            for (bool long_docs : {false, true})
-                HIP_TRY(hipFuncSetAttribute(theta_kernel_for(RowKind::packed, wide, long_docs),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)mlda::theta_lds_bytes(c->K, wide)));
+    // (large K only: 4-byte rows of any K; the forms with a dense row)
+    auto raise_theta = [&](bool wide, bool long_docs) {
+        const size_t bytes = mlda::theta_lds_bytes(c->K, wide);
+        if (bytes <= 48 * 1024 || bytes > (size_t)c->lds_limit) return hipSuccess;      // (too large: see check_theta_lds)
+        return hipFuncSetAttribute(theta_kernel_for(RowKind::packed, wide, long_docs),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    };
+    for (bool wide : {false, true})
+        for (bool long_docs : {false, true}) HIP_TRY(raise_theta(wide, long_docs));
     return MLDA_OK;
 }
 

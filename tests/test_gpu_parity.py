@@ -621,6 +621,41 @@ def test_phi_segment_edges(mlda, K):
         model.close()
 
 
+# (topics, lengths of the first documents, further documents of 3 tokens each)
+RANKED_CASES = [("two_per_wave", 1000, [0, 1, 31, 32, 33, 127, 128, 129, 383, 384, 385, 1500, 4000, 0, 700], 60),
+                ("two_per_wave_33", 33, [0, 1, 127, 128, 129, 383, 384, 385, 3000], 60),
+                ("two_per_wave_1024", 1024, [2500, 1, 600, 3], 40),
+                ("one_per_wave", 3000, [0, 1, 63, 64, 65, 127, 128, 129, 2175, 2176, 2177, 5000, 1153, 1152], 0),
+                ("one_per_wave_2048", 2048, [4096, 128, 129, 2000, 0], 0),
+                ("one_per_wave_largest", 65535, [3000, 1, 128, 1500, 300], 0)]
+
+
+@pytest.mark.parametrize("case", RANKED_CASES, ids=[c[0] for c in RANKED_CASES])
+def test_rows_by_ranks(mlda, case):
+    """Rows of theta from topics' ranks: documents at the edges of what registers, the staged topics and
+    one round of cells hold, rows of several rounds, counts of several entries in any of them,
+    empty documents, an odd number of documents."""
+    _, K, lens, short = case
+    rng = np.random.default_rng(K)
+    lens = np.array(lens + [3] * short, dtype=np.int64)
+
+    class C:
+        pass
+    c = C(); V = 40
+    c.doc_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    c.T = int(lens.sum())
+    c.word_ids = rng.integers(V, size=c.T).astype(np.int32)
+    spread = rng.integers(K, size=c.T).astype(np.uint16)
+    few = np.where(rng.random(c.T) < 0.7, rng.choice([0, K // 2, K - 1], size=c.T), spread).astype(np.uint16)
+    for chunks in (1, 2):
+        model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, 50.0 / K, 0.01, SEED, chunks=chunks)
+        for it, z in enumerate((spread, few)):
+            model.set_assignments(z, it=it)
+            check_counts(model, c, z, V, K)
+            check_step(model, c, z, V, K, 50.0 / K, 0.01, SEED, it + 1)
+        model.close()
+
+
 @pytest.mark.parametrize("how", ["own_stream", "stream_per_thread", "streamed"])
 def test_large_transfers(mlda, how):
     """Transfers of 8 MB and more go through eight pinned pieces of 2 MB, each with a thread of its own:
