@@ -4,7 +4,8 @@
 // Mapping to gfx950 (the paper's own mapping, one 32-wide warp per sampler with 32-way
 // index trees, was made for NVIDIA warps; measured here, a whole 64-lane wave per token is
 // bound by VALU issue, not by HBM):
-//   - a workgroup owns one tile = up to 1024 (4096 for large K) consecutive tokens of ONE
+//   - a workgroup of four (twelve for large K) waves, or a single wave where the tile is small and the
+//     column of topics short, owns one tile = up to 1024 (4096 for large K) consecutive tokens of ONE
 //     word and stages that word's p*(k) (Eq. 8, rounded to fp32) once in LDS, widened to fp64 where
 //     K <= 2048 and rows are not the shortest, with fp64 prefix sums over groups of 4 (or 16) topics
 //     (Section 6.1.2: samplers of a block share the word's data);
@@ -86,13 +87,13 @@ struct SampleArgs {
     // K too large for p* to fit a workgroup's LDS (sample_kernel<12, .., true>): workgroup b keeps
     // p* of its current tile in far_pstar[b * Kpad ..] and takes the tiles b, b + grid, ...
     float* far_pstar;
-    int32_t min_batch;          // workgroups of four waves: tokens a wave takes at a time at least
+    int32_t min_batch;          // K <= 2048: tokens a wave takes at a time at least
 };
 
 constexpr int kRowHeader = 16;  // bytes before a theta row's entries
-// Topics per fp64 prefix group of the dense bucket: 4 where LDS has room (workgroups of four
+// Topics per fp64 prefix group of the dense bucket: 4 where LDS has room (workgroups of up to four
 // waves, K <= 2048), 16 for the large-K workgroups of twelve waves.
-__host__ __device__ constexpr int dense_group(int waves) { return waves == 4 ? 4 : 16; }
+__host__ __device__ constexpr int dense_group(int waves) { return waves <= 4 ? 4 : 16; }
 constexpr int kKeptUnits = 3;   // 16-byte units of entries a lane keeps in registers at most
 constexpr int kMinBatch = 8;    // tokens a wave takes at a time at least
 
@@ -885,7 +886,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     constexpr int kGroup = dense_group(kWaves);
     const int K = a.K, Kpad = a.Kpad, ng = Kpad / kGroup;
     constexpr bool kDouble = Layout::kDoubleWeights;
-    static_assert(!(kDouble && (kFar || kWaves != 4)), "fp64 weights: workgroups of four waves, in LDS");
+    static_assert(!(kDouble && (kFar || kWaves > 4)), "fp64 weights: workgroups of up to four waves, in LDS");
     typedef typename std::conditional<kDouble, double, float>::type Weight;
     // (what a staged weight, and a sum over a row, carry as a factor)
     constexpr double kStagedScale = kDouble ? kWeightScale : 1.0, kRowScale = kDouble ? kSumScale : 1.0;
@@ -1026,7 +1027,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     // of one batch follow each other, each waiting for its rows.
     // (Full batches are less work in all, which is what counts where the chip is full; at K > 2048,
     // and where there are few tiles, it is the time of one tile.)
-    const int batch = min(kWave, max(kWaves == 4 ? a.min_batch : kMinBatch,
+    const int batch = min(kWave, max(kWaves <= 4 ? a.min_batch : kMinBatch,
                                      ((tl.count + kWaves - 1) / kWaves + 3) & ~3));
     const int n_batches = (tl.count + batch - 1) / batch;
     for (int b = wave; b < n_batches; b += kWaves) {

@@ -104,6 +104,16 @@ const void* sample_kernel_of(int32_t K, RowKind rows, bool short_docs) {
 const void* sample_kernel_for(int32_t K, RowKind rows, bool short_docs, bool near) {
     return near ? sample_kernel_of<true>(K, rows, short_docs) : sample_kernel_of<false>(K, rows, short_docs);
 }
+// (a wave per tile, K <= 2048)
+template <bool kNear>
+const void* sample_solo_kernel_of(RowKind rows) {
+    if (rows == RowKind::packed) return (const void*)mlda::sample_kernel<1, mlda::PackedRowsShort, false, kNear>;
+    return with_layout(rows, [](auto layout) {
+        typedef decltype(layout) Layout;
+        typedef typename std::conditional<Layout::kDoubleWeights, Layout, mlda::PackedRowsShort>::type Rows;
+        return (const void*)mlda::sample_kernel<1, Rows, false, kNear>;
+    });
+}
 bool slots_near(size_t slots_bytes) { return slots_bytes <= 0xffffffffull; }
 // Few long documents are counted by kLongDocWaves waves each.  Measured, theta rebuild of D equal
 // documents at K = 500 with one wave each / sixteen, us (24 and 3,000 topics alike):
@@ -149,6 +159,34 @@ constexpr int kMaxTimedVisits = 4096;
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 int tile_tokens_for(int32_t K) { return K <= 2048 ? 1024 : 4096; }
+// K <= 2048: the tokens of a sampling tile, and up to how many of them a wave takes the tile alone.  A workgroup
+// of four waves keeps three of them idle over a word of few tokens, and on a small corpus the launch takes the time
+// of one tile's batches; a wave per tile stages p* of the word by itself, which the longer the column and the smaller
+// the tile is the larger part of its work.  Measured, sampling launch (us) by "tile / alone up to", documents of 150:
+//                       1024/0  1024/64  256/64  128/128  64/64
+//   K = 16,     1e5       24      28       17      15       11
+//               3e6      110      99       94      85       86
+//               4e7      926     911      961     865      961
+//   K = 128,    1e5       34      41       25      22       16
+//               1e6      106      92       76      73       67
+//               4e7     1538    1439     1507    1427     1518
+//   K = 512,    1e6      171     145      117     119      112
+//               3e6      321     258      248     244      250      1024/128: 254
+//               4e7     2031    1859     1979    1923     2142                1805
+//   K = 1,000,  1e5       57      65       39      40       34
+//               1e6      188     190      166     183      186
+//               4e7     2251    2184     2358    3136     3852
+//   K = 2,000,  1e5       66      90       64      62       55
+//               1e6      272     338      315     388      415
+struct TileShape { int32_t tokens, alone; };
+TileShape tile_shape_for(int32_t K, int64_t T) {
+    if (K > 2048) return {4096, 0};
+    if (T <= (K <= 512 ? 2000000 : K <= 1024 ? 200000 : 100000)) return {64, 64};
+    if (K <= 256 && T <= 100000000) return {128, 128};
+    if (K <= 512) return {1024, 128};
+    if (K <= 1024) return {T <= 4000000 ? 256 : 1024, 64};
+    return {1024, 0};
+}
 constexpr int kPhiSegment = 16384;    // tokens one workgroup histograms for the phi rebuild
 constexpr int32_t kHistTopics = 32768; // 32-bit counters of the n_k histogram that share a workgroup's LDS
 
@@ -343,8 +381,10 @@ struct HostChunk {
     size_t slots_bytes = 0;
     int32_t n_tiles = 0, n_segs = 0, n_split = 0;
     int32_t n_single = 0;               // the tiles from this one on hold whole small words: taken in runs
+    int32_t n_shared = 0;               // K <= 2048: the tiles from this one on are taken by a wave each
+    int32_t counted_tiles = 0;          // tiles of tile_tokens_for(K) tokens that the words have, as the sampler's bytes count them
     int64_t run_tokens = 0;             // their tokens
-    int32_t n_wide_tiles = 0;           // sampling tiles of words whose row of phi is int32
+    int32_t n_wide_tiles = 0;           // counted tiles of words whose row of phi is int32
     ChunkLayout L;
     unsigned char* arena = nullptr;     // L.static_bytes bytes
     bool pinned = false;
@@ -367,7 +407,7 @@ struct HostChunk {
 // result, because the uniforms are keyed by the caller's token index.  `accumulate`: the
 // chunk's counts will be added to phi (several chunks) instead of stored.
 int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64_t d_begin,
-                  int64_t d_end, int32_t V, int32_t K, bool accumulate, bool pinned, bool runs, HostChunk& h) {
+                  int64_t d_end, int32_t V, int32_t K, bool accumulate, bool pinned, bool runs, const TileShape* forced, HostChunk& h) {
     const int64_t D = d_end - d_begin;
     const int64_t tok_begin = doc_ptr_all[d_begin];
     const int64_t T = doc_ptr_all[d_end] - tok_begin;
@@ -444,8 +484,7 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
     for (int p = 0; p < n_parts; ++p)
         if (part_bad[p]) return fail(MLDA_EINVAL, "word id outside [0, V)");
 
-    const int32_t tile = tile_tokens_for(K);
-    size_t n_tiles = 0, n_segs = 0, n_split = 0;
+    size_t n_tiles = 0, n_counted = 0, n_segs = 0, n_split = 0;
     for (int32_t v = 0; v < V; ++v) {
         int32_t n = 0;
         for (int p = 0; p < n_parts; ++p) {
@@ -454,12 +493,22 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
             n += c;
         }
         word_ptr[v + 1] = word_ptr[v] + n;
-        n_tiles += (size_t)((n + tile - 1) / tile);
+        n_counted += (size_t)((n + tile_tokens_for(K) - 1) / tile_tokens_for(K));
         n_segs += (size_t)((n + kPhiSegment - 1) / kPhiSegment);
         if (!accumulate && n > kPhiSegment) ++n_split;
     }
+    TileShape shape = forced ? *forced : tile_shape_for(K, T);
+    for (;;) {
+        n_tiles = 0;
+        for (int32_t v = 0; v < V; ++v) n_tiles += (size_t)((word_ptr[v + 1] - word_ptr[v] + shape.tokens - 1) / shape.tokens);
+        h.L = chunk_layout(D, T, h.slots_bytes, n_tiles, n_segs, n_split, accumulate);
+        // (the bound that a workspace is sized by knows tiles of tile_tokens_for(K))
+        if (shape.tokens >= tile_tokens_for(K) || h.L.total <= chunk_layout_bound(D, T, V, K, accumulate).total) break;
+        shape.tokens = tile_tokens_for(K);
+    }
+    const int32_t tile = shape.tokens;
     h.n_tiles = (int32_t)n_tiles; h.n_segs = (int32_t)n_segs; h.n_split = (int32_t)n_split;
-    h.L = chunk_layout(D, T, h.slots_bytes, n_tiles, n_segs, n_split, accumulate);
+    h.counted_tiles = (int32_t)n_counted;
 
     h.release();
     h.pinned = pinned;
@@ -546,7 +595,11 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
                          [](const mlda::Tile& a, const mlda::Tile& b) { return a.count > b.count; });
         // tiles that hold a whole word of few tokens go last, to be taken in runs by one
         // workgroup each (their order among themselves stays)
-        h.n_single = h.n_tiles;
+        h.n_single = h.n_shared = h.n_tiles;
+        if (shape.alone > 0) {
+            mlda::Tile* first_solo = std::stable_partition(tiles, tiles + n_tiles, [&](const mlda::Tile& t) { return t.count > shape.alone; });
+            h.n_shared = (int32_t)(first_solo - tiles);
+        }
         if (runs) {
             mlda::Tile* first_small = std::stable_partition(tiles, tiles + n_tiles, [&](const mlda::Tile& t) {
                 const bool whole_word = word_ptr[t.word + 1] - word_ptr[t.word] == t.count;
@@ -583,6 +636,8 @@ struct mlda_ctx {
     int n_cus = 0, lds_limit = 0;
     bool far_weights = false;           // p* of the sampler's tiles in device memory (large K)
     bool wide_slot_offsets = false;     // MLDA_WIDE_SLOT_OFFSETS: 64-bit unit addresses whatever the buffer's size
+    TileShape shape = {0, 0};           // MLDA_TILE_SHAPE="tokens,alone": this one whatever the sizes
+    const TileShape* forced_shape() const { return shape.tokens > 0 ? &shape : nullptr; }
     float* far_pstar = nullptr;
     size_t sample_lds = 0;
     mlda::PhiView phi[2];                // [model_cur] is the current phi; two copies when streamed
@@ -651,6 +706,8 @@ struct mlda_ctx {
     mlda::Tile* segs = nullptr;          // phi rebuild segments
     int32_t n_tiles = 0, n_segs = 0, n_split = 0, n_wide_tiles = 0;
     int32_t n_single = 0;                // tiles taken one per workgroup; the rest in runs of run_tiles
+    int32_t n_shared = 0;                // tiles taken by workgroups of several waves, the rest by a wave each
+    int32_t counted_tiles = 0;           // see HostChunk
     int32_t run_tiles = 1;
     int64_t run_tokens = 0;              // tokens of the tiles taken in runs
 
@@ -723,6 +780,8 @@ void point_at(mlda_ctx* c, const HostChunk& h, unsigned char* base) {
     c->n_tiles = h.n_tiles; c->n_segs = h.n_segs; c->n_split = h.n_split;
     c->n_wide_tiles = h.n_wide_tiles;
     c->n_single = h.n_single;
+    c->n_shared = h.n_shared;
+    c->counted_tiles = h.counted_tiles;
     c->run_tokens = h.run_tokens;
     c->tok_slot = (uint32_t*)(base + h.L.tok_slot);
     c->tok_id = (int32_t*)(base + h.L.tok_id);
@@ -974,8 +1033,8 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     a.beta_V = c->beta * (double)c->V;
     a.seed = c->seed;
     a.iter = (uint32_t)(c->iter + 1);
-    a.n_tiles = c->n_tiles;
-    a.n_single = c->run_tiles > 1 ? c->n_single : c->n_tiles;
+    a.n_tiles = c->n_shared;
+    a.n_single = c->run_tiles > 1 ? c->n_single : c->n_shared;
     a.run_tiles = c->run_tiles;
     a.far_pstar = c->far_pstar;
     // With few tiles the launch takes the time of one tile, and a small tile is done sooner by four waves side
@@ -987,16 +1046,25 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     //                300, K = 100     10.8 / 12.0   14.7 / 13.6   17.6 / 15.8
     //                300, K = 1,000   13.9 / 18.6   20.3 / 21.8   24.0 / 25.0
     const bool long_rows = c->K >= 200 && c->T >= 200 * c->D;
-    a.min_batch = c->n_tiles <= (long_rows ? 8 : 4) * c->n_cus ? mlda::kMinBatch * 2 : mlda::kWave;
+    a.min_batch = c->n_shared <= (long_rows ? 8 : 4) * c->n_cus ? mlda::kMinBatch * 2 : mlda::kWave;
     const int waves = sample_waves_for(c->K);
     const int32_t grid = c->far_weights ? std::min<int32_t>(a.n_tiles, kFarStrips)
                                         : a.n_single + (a.n_tiles - a.n_single + a.run_tiles - 1) / a.run_tiles;
-    const size_t lds = waves == 4 ? mlda::sample_lds_bytes(c->Kpad, waves, c->rows == RowKind::packed ? 4 : 8) : c->sample_lds;
+    const bool near = slots_near(c->slots_bytes) && !c->wide_slot_offsets;
+    const int weight_bytes = c->rows == RowKind::packed ? 4 : 8;
+    const size_t lds = waves == 4 ? mlda::sample_lds_bytes(c->Kpad, waves, weight_bytes) : c->sample_lds;
     void* kernel_args[] = {&a};
-    HIP_TRY(hipLaunchKernel(sample_kernel_for(c->K, c->rows, c->short_docs,
-                                              slots_near(c->slots_bytes) && !c->wide_slot_offsets),
-                            dim3((unsigned)grid),
-                            dim3((unsigned)(waves * mlda::kWave)), kernel_args, lds, c->stream));
+    if (grid > 0)
+        HIP_TRY(hipLaunchKernel(sample_kernel_for(c->K, c->rows, c->short_docs, near), dim3((unsigned)grid),
+                                dim3((unsigned)(waves * mlda::kWave)), kernel_args, lds, c->stream));
+    const int32_t n_solo = c->n_tiles - c->n_shared;
+    if (n_solo > 0) {
+        a.tiles += c->n_shared;
+        a.n_tiles = a.n_single = n_solo;
+        HIP_TRY(hipLaunchKernel(near ? sample_solo_kernel_of<true>(c->rows) : sample_solo_kernel_of<false>(c->rows),
+                                dim3((unsigned)n_solo), dim3((unsigned)mlda::kWave), kernel_args,
+                                mlda::sample_lds_bytes(c->Kpad, 1, weight_bytes), c->stream));
+    }
     return launch_check("sample_kernel");
 }
 
@@ -1186,13 +1254,18 @@ int find_wide_rows(mlda_ctx* c, const int32_t* word_ids) {
 }
 
 // Every sampling tile carries its word's row among the wide rows of phi (or -1).
-void mark_wide_tiles(const mlda_ctx* c, HostChunk& h) {
+int mark_wide_tiles(const mlda_ctx* c, HostChunk& h) {
     mlda::Tile* tiles = (mlda::Tile*)(h.arena + h.L.tiles);
-    h.n_wide_tiles = 0;
+    std::vector<int64_t> tokens;            // of every wide row's word in this chunk
+    try { tokens.resize((size_t)c->n_wide); } catch (const std::bad_alloc&) { return fail(MLDA_ENOMEM, "out of host memory"); }
     for (int32_t i = 0; i < h.n_tiles; ++i) {
         tiles[i].whole = c->wide_row[(size_t)tiles[i].word];
-        if (tiles[i].whole >= 0) h.n_wide_tiles += 1;
+        if (tiles[i].whole >= 0) tokens[(size_t)tiles[i].whole] += tiles[i].count;
     }
+    const int64_t tile = tile_tokens_for(c->K);
+    h.n_wide_tiles = 0;
+    for (int64_t n : tokens) h.n_wide_tiles += (int32_t)((n + tile - 1) / tile);
+    return MLDA_OK;
 }
 
 int device_limits(mlda_ctx* c) {
@@ -1205,6 +1278,12 @@ int device_limits(mlda_ctx* c) {
     // (a switch for tests: the 64-bit form is otherwise only reached by theta slots beyond 4 GiB)
     const char* wide = std::getenv("MLDA_WIDE_SLOT_OFFSETS");
     c->wide_slot_offsets = wide && wide[0] != '\0' && wide[0] != '0';
+    // (likewise: most shapes are otherwise only reached by corpora of millions of tokens)
+    const char* shape = std::getenv("MLDA_TILE_SHAPE");
+    int tokens = 0, alone = 0;
+    if (shape && c->K <= 2048 && std::sscanf(shape, "%d,%d", &tokens, &alone) == 2 && tokens >= 16 && tokens <= 1024 &&
+        alone >= 0 && alone <= tokens)
+        c->shape = {tokens, alone};
     c->sample_lds = c->far_weights ? mlda::sample_far_lds_bytes(c->Kpad, sample_waves_for(c->K))
                                    : mlda::sample_lds_bytes(c->Kpad, sample_waves_for(c->K), sample_waves_for(c->K) == 4 ? 8 : 4);
     if (c->sample_lds > (size_t)c->lds_limit)
@@ -1555,9 +1634,9 @@ static int create_resident(mlda_ctx** out, const int64_t* doc_ptr, const int32_t
     if (rc == MLDA_OK) {
         try { c->chunks = std::vector<HostChunk>(1); } catch (const std::bad_alloc&) { rc = fail(MLDA_ENOMEM, "out of host memory"); }
     }
-    if (rc == MLDA_OK) rc = prepare_chunk(doc_ptr, word_ids, 0, D, V, K, false, false, c->run_tiles > 1, c->chunks[0]);
+    if (rc == MLDA_OK) rc = prepare_chunk(doc_ptr, word_ids, 0, D, V, K, false, false, c->run_tiles > 1, c->forced_shape(), c->chunks[0]);
     if (rc == MLDA_OK) rc = check_theta_lds(c, c->chunks[0]);
-    if (rc == MLDA_OK) mark_wide_tiles(c, c->chunks[0]);
+    if (rc == MLDA_OK) rc = mark_wide_tiles(c, c->chunks[0]);
     const ModelLayout ML = model_layout(V, K, T, false);
     if (rc == MLDA_OK && ML.total + c->chunks[0].L.total > workspace_bytes)
         rc = fail(MLDA_ENOMEM, "workspace has " + std::to_string(workspace_bytes) + " bytes, need " +
@@ -1632,9 +1711,9 @@ int mlda_create_streamed(mlda_ctx** out, const int64_t* doc_ptr, const int32_t* 
     size_t chunk_bytes = 0;
     for (int32_t m = 0; rc == MLDA_OK && m < n_chunks; ++m) {
         rc = prepare_chunk(doc_ptr, word_ids, chunk_first(doc_ptr, D, n_chunks, m),
-                           chunk_first(doc_ptr, D, n_chunks, m + 1), V, K, true, true, false, c->chunks[(size_t)m]);
+                           chunk_first(doc_ptr, D, n_chunks, m + 1), V, K, true, true, false, c->forced_shape(), c->chunks[(size_t)m]);
         if (rc == MLDA_OK) rc = check_theta_lds(c, c->chunks[(size_t)m]);
-        if (rc == MLDA_OK) mark_wide_tiles(c, c->chunks[(size_t)m]);
+        if (rc == MLDA_OK) rc = mark_wide_tiles(c, c->chunks[(size_t)m]);
         if (rc == MLDA_OK) chunk_bytes = std::max(chunk_bytes, c->chunks[(size_t)m].L.total);
     }
     const ModelLayout ML = model_layout(V, K, T, true);
@@ -1757,7 +1836,7 @@ static int step_streamed(mlda_ctx* c, bool loglik, int32_t timed_row) {
         RC_TRY(attach(c, m, true, ev));
         if (ev) {
             try {
-                c->visit_log.push_back({timed_row, c->T, c->n_tiles, c->n_wide_tiles, c->rebuilds,
+                c->visit_log.push_back({timed_row, c->T, c->counted_tiles, c->n_wide_tiles, c->rebuilds,
                                         (size_t)(ev - c->events.data())});
             } catch (const std::bad_alloc&) { return fail(MLDA_ENOMEM, "out of host memory"); }
         }
@@ -2034,7 +2113,7 @@ int mlda_get_sampler_bytes(mlda_ctx* c, double* bytes, int32_t capacity_iters, i
         // per token, counted as if both tiles had this tile's tokens
         const int32_t n_run_tiles = c->run_tiles > 1 ? c->n_tiles - c->n_single : 0;
         const int32_t n_runs = n_run_tiles > 0 ? (n_run_tiles + c->run_tiles - 1) / c->run_tiles : 0;
-        const double staged_rows = (double)(c->n_tiles - n_run_tiles + n_runs);
+        const double staged_rows = (double)(c->counted_tiles - n_run_tiles + n_runs);
         bytes[i] = 16.0 * (double)c->T + entry_bytes * row_entries +
                    (double)c->K * (2.0 * staged_rows + 2.0 * (double)c->n_wide_tiles) +
                    6.0 * (double)c->run_tokens;

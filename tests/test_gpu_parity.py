@@ -233,6 +233,41 @@ def test_counts_at_the_ends_of_their_fields(mlda, case, wide_offsets, monkeypatc
     model.close()
 
 
+# (MLDA_TILE_SHAPE: tokens of a tile, and up to how many of them one wave takes a tile alone)
+@pytest.mark.parametrize("shape", ["1024,0", "128,128", "256,40"])
+@pytest.mark.parametrize("case", [c for c in LAYOUT_CASES if c[3] <= 2048], ids=lambda c: c[0])
+def test_row_layouts_in_every_tile_shape(mlda, case, shape, monkeypatch):
+    """Workgroups of four waves, of one, and both side by side, on corpora that would take another shape."""
+    monkeypatch.setenv("MLDA_TILE_SHAPE", shape)
+    test_row_layouts(mlda, case, "1" if shape == "128,128" else "0", monkeypatch)
+
+
+@pytest.mark.parametrize("case", [c for c in SPLIT_CASES if c[1] <= 2048], ids=lambda c: c[0])
+def test_counts_at_the_ends_of_their_fields_with_four_waves(mlda, case, monkeypatch):
+    monkeypatch.setenv("MLDA_TILE_SHAPE", "1024,0")
+    test_counts_at_the_ends_of_their_fields(mlda, case, "0", monkeypatch)
+
+
+@pytest.mark.parametrize("chunks", [1, 3])
+def test_tile_shapes_agree(mlda, chunks, monkeypatch):
+    """Words of 1 .. 2,100 tokens (tiles of every size), the same assignments and byte counts in every shape."""
+    V, K = 120, 200
+    rng = np.random.default_rng(3)
+    per_word = np.concatenate([np.arange(1, 100), [127, 128, 129, 255, 256, 257, 1023, 1024, 1025, 2100], np.zeros(11, int)])
+    words = rng.permutation(np.repeat(np.arange(V, dtype=np.int32), per_word))
+    doc_ptr = np.concatenate([[0], np.sort(rng.choice(np.arange(1, len(words)), 150, replace=False)), [len(words)]]).astype(np.int64)
+    got = []
+    for shape in ("1024,0", "64,64", "128,128", "256,64", "1024,64", ""):
+        monkeypatch.setenv("MLDA_TILE_SHAPE", shape)
+        model = mlda.Mlda(doc_ptr, words, V, K, 50.0 / K, 0.01, SEED, chunks=chunks)
+        model.init_random(); model.step(3)
+        got.append((model.assignments(), model.sampler_bytes(), model.loglik()))
+        model.close()
+    for z, moved, ll in got[1:]:
+        assert np.array_equal(z, got[0][0]) and np.array_equal(moved, got[0][1]) and ll == got[0][2]
+
+
+
 # Rows of every way the walk over fp64 weights goes: (name, K, documents, tokens each).
 SMALL_BETA_CASES = [
     ("two_byte_rows",         60,   400, 50),
