@@ -88,6 +88,9 @@ struct SampleArgs {
     // p* of its current tile in far_pstar[b * Kpad ..] and takes the tiles b, b + grid, ...
     float* far_pstar;
     int32_t min_batch;          // K <= 2048: tokens a wave takes at a time at least
+    // fp64 weights, tokens that share the walks over their rows: how many passes, and units of them, a wave
+    // keeps the sums of at a time
+    int32_t kept_passes, kept_sums;
 };
 
 constexpr int kRowHeader = 16;  // bytes before a theta row's entries
@@ -95,6 +98,7 @@ constexpr int kRowHeader = 16;  // bytes before a theta row's entries
 // waves, K <= 2048), 16 for the large-K workgroups of twelve waves.
 __host__ __device__ constexpr int dense_group(int waves) { return waves <= 4 ? 4 : 16; }
 constexpr int kKeptUnits = 3;   // 16-byte units of entries a lane keeps in registers at most
+constexpr int kMostKeptUnits = kWave * kKeptUnits;  // of a row that is walked once
 constexpr int kMinBatch = 8;    // tokens a wave takes at a time at least
 
 // Once a token's pass has read its record, the record takes the result back to the per-lane
@@ -115,10 +119,16 @@ constexpr int kDrawTopic = -3;  // off = the new topic itself
 // p* of the tile's word is staged as fp64 or fp32 (Layout::kDoubleWeights), as fp32 always in the
 // workgroups of twelve waves, where fp64 would cost a CU its second workgroup.
 //
+// What a wave keeps in LDS: the records of its tokens, or (shared walks) the sums of up to kept_sums units
+// and the first topics of the lanes of kept_passes passes, then 64 rows' slots and lengths.
+__host__ __device__ constexpr int sample_wave_bytes(int kept_passes, int kept_sums) {
+    const int shared = kept_sums * 8 + kept_passes * kWave * 2 + kWave * 5, records = kWave * (int)sizeof(TokenRec);
+    return shared > records ? shared : records;
+}
 // LDS bytes of sample_kernel<kWaves> for a given Kpad and bytes of a staged weight.
-__host__ __device__ constexpr size_t sample_lds_bytes(int Kpad, int waves, int weight_bytes) {
+__host__ __device__ constexpr size_t sample_lds_bytes(int Kpad, int waves, int weight_bytes, int kept_passes = 0, int kept_sums = 0) {
     return (size_t)Kpad * weight_bytes + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 +
-           (size_t)waves * kWave * sizeof(TokenRec);
+           (size_t)waves * sample_wave_bytes(kept_passes, kept_sums);
 }
 // The same when p* stays in device memory: the prefix sums and the waves' records only.
 __host__ __device__ constexpr size_t sample_far_lds_bytes(int Kpad, int waves) { return sample_lds_bytes(Kpad, waves, 0); }
@@ -141,6 +151,8 @@ constexpr double kSumScale = kWeightScale * kCountUnit;
 // Q' times kSumScale is a normal number from here on.  A smaller one (alpha below 1e-290 or so) decides
 // draws of tokens that are alone in their document only; their place in p2 is worked out without the scale.
 constexpr double kSmallestScaled = 0x1p-900;
+// Shared walks: how many times a token's total a row's sum may be in which its own topic still counts in full.
+constexpr double kMostTakenOff = 2.0;
 
 // A staged weight of either form without its scale.
 __device__ __forceinline__ double plain_weight(float w) { return (double)w; }
@@ -327,6 +339,13 @@ struct TinyRows {
             d -= __builtin_bit_cast(uint32_t, own);         // (no half below zero: own is its count, or 0)
         }
     }
+    // n += the tokens of topic o (as take_out, the entries stay)
+    static __device__ __forceinline__ void count_own(const uint4& u, int o, uint32_t& n) {
+        const Pair most = Pair((uint16_t)make(kMaxCount, o)), one = Pair(1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            n = __builtin_amdgcn_udot2(__builtin_elementwise_sub_sat(Pair(kMaxCount), most - __builtin_bit_cast(Pair, word(u, i))), one, n, false);
+    }
     // acc += count * weight over the eight entries, in their order
     static __device__ __forceinline__ void add_products(const uint4& u, const double* w, double& acc) {
         add_four(u.x, u.y, w, acc);
@@ -372,6 +391,11 @@ struct CountedRows {
             n += own;
             d -= own;
         }
+    }
+    static __device__ __forceinline__ void count_own(const uint4& u, int o, uint32_t& n) {
+        const uint32_t most = make(kMaxCount, o);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) n += __builtin_elementwise_sub_sat((uint32_t)kMaxCount, most - word(u, i));
     }
     static __device__ __forceinline__ void add_products(const uint4& u, const double* w, double& acc) {
         asm("v_mov_b32 v72, 0\n\tv_mov_b32 v74, 0\n\t"
@@ -728,6 +752,27 @@ __device__ __forceinline__ void row_pass_double(TokenRec* rec, int sl, const uin
     record_dense(rec, sl, d);
 }
 
+// The walk over a row for all the tokens that share it: what the row's sub-lanes have summed up at the end
+// of each of their units, every entry with p*, goes to LDS (`sums`, the row's units one after the other),
+// with the topic of each sub-lane's first entry.  Three instructions per entry and no draw.
+template <class Layout, int kLanes, int kUnits>
+__device__ __forceinline__ void row_pass_shared(double* sums, uint16_t* first_topic, int rel, int sl, const uint4* raw) {
+    double at_end[kUnits];
+    double acc = 0.0;
+#pragma unroll
+    for (int c = 0; c < kUnits; ++c) {
+        unit_sum_plain<Layout>(raw[c], acc);
+        at_end[c] = acc;
+    }
+    const double incl = group_inclusive_sum<kLanes>(acc);
+    const double excl = group_previous<kLanes>(incl, sl);
+    const int lane_at = rel * kLanes + sl;
+#pragma unroll
+    for (int c = 0; c + 1 < kUnits; ++c) sums[lane_at * kUnits + c] = excl + at_end[c];
+    sums[lane_at * kUnits + kUnits - 1] = incl;
+    first_topic[lane_at] = (uint16_t)Layout::entry_topic((typename Layout::Entry)raw[0].x);
+}
+
 // The same for rows too long for the kept shapes, one per wave (sub-lane = lane): one walk for
 // the sums, a second one over the hit lane's units.  Lane l owns the units [n l, n (l + 1)).
 template <class Layout>
@@ -897,7 +942,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);      // wave-uniform, in an SGPR
     unsigned char* wave_base = lds + pstar_lds + (size_t)((ng + 1) & ~1) * 8;
-    TokenRec* my_rec = reinterpret_cast<TokenRec*>(wave_base) + wave * kWave;
+    TokenRec* my_rec = reinterpret_cast<TokenRec*>(wave_base + wave * (kDouble ? sample_wave_bytes(a.kept_passes, a.kept_sums) : kWave * (int)sizeof(TokenRec)));
     typedef typename std::conditional<kFar, FarWeights, LdsWeights>::type Weights;
     [[maybe_unused]] Weights weight_at;
     if constexpr (kFar) weight_at.base = reinterpret_cast<const unsigned char*>(pstar);
@@ -1070,29 +1115,22 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             // cp[ng - 1] = sum_k p*(k), read from LDS where it is needed; Q = alpha sum (Eq. 7)
             mine.Qp = ka->alpha * (cp[ng - 1] + delta);
         }
-        my_rec[lane] = mine;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-        // ---- one token per group of 4 .. 64 lanes.  A pass takes the next 16, 8, 4, 2 or 1
-        // tokens, as many as lets every lane own at most kKeptUnits units; the rows of the
-        // following pass are requested from memory before this one is worked on.
-        // Shapes of a pass (lanes per token, units per lane); a row may have up to
-        // lanes * units * (entries per unit) entries:
+        // Which rows of the batch (tokens, or rows that tokens share) are beyond each of the pass shapes'
+        // lengths: the shape of every pass follows from these masks.
         //   0 (4,1)   1 (4,2)   2 (4,3)   3 (8,2)   4 (8,3)   5 (16,2)   6 (16,3)
-        //   7 (32,2)   8 (32,3)   9 (64,2)   10 (64,3)   11 = one longer row, walked twice by the wave
-        // Which tokens of the batch have rows beyond each of these lengths (lanes past the
-        // batch's end hold nnz = 0): the shape of every pass follows from these masks.
-        const int n_here = min(batch, tl.count - b * batch);
+        //   7 (32,2)   8 (32,3)   9 (64,2)   10 (64,3)   11 = one longer row
+        // (lanes per row, units per lane: a row may have up to lanes * units * (entries per unit) entries)
         static_assert(kKeptUnits == 3, "the pass shapes assume three kept units per lane");
-        const uint64_t over_4_1 = __ballot(mine.nnz > 4), over_4_2 = __ballot(mine.nnz > 8);
-        const uint64_t over_4_3 = __ballot(mine.nnz > 12), over_8_2 = __ballot(mine.nnz > 16);
-        const uint64_t over_8_3 = __ballot(mine.nnz > 24), over_16_2 = __ballot(mine.nnz > 32);
-        const uint64_t over_16_3 = __ballot(mine.nnz > 48), over_32_2 = __ballot(mine.nnz > 64);
-        const uint64_t over_32_3 = __ballot(mine.nnz > 96), over_64_2 = __ballot(mine.nnz > 128);
-        const uint64_t over_64_3 = __ballot(mine.nnz > 192);
-        auto any = [](uint64_t mask, int t0, uint32_t window) {      // 1 if a token of the window is set
+        uint64_t over_4_1, over_4_2, over_4_3, over_8_2, over_8_3, over_16_2, over_16_3, over_32_2, over_32_3, over_64_2, over_64_3;
+        auto learn_shapes = [&](int units) {
+            over_4_1 = __ballot(units > 4); over_4_2 = __ballot(units > 8);
+            over_4_3 = __ballot(units > 12); over_8_2 = __ballot(units > 16);
+            over_8_3 = __ballot(units > 24); over_16_2 = __ballot(units > 32);
+            over_16_3 = __ballot(units > 48); over_32_2 = __ballot(units > 64);
+            over_32_3 = __ballot(units > 96); over_64_2 = __ballot(units > 128);
+            over_64_3 = __ballot(units > 192);
+        };
+        auto any = [](uint64_t mask, int t0, uint32_t window) {      // 1 if a row of the window is set
             const uint32_t w = (uint32_t)(mask >> t0) & window;
             return min(1, (int)__builtin_popcount(w));      // stays scalar arithmetic
         };
@@ -1107,19 +1145,225 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         constexpr int kNoPass = 12;
         auto lanes_log2 = [](int shape) { return (int)((0x666554433222ull >> (4 * shape)) & 0xfull); };
         auto units_of = [](int shape) { return (int)((0x032323232321ull >> (4 * shape)) & 0xfull); };
+        auto place_lanes = [&](int shape) {     // the lanes' places change only with the shape
+            if (shape == geo_shape) return;
+            const int lg = lanes_log2(shape);
+            const int g = lg < 4 ? 4 - lg : 0, hs = lg < 4 ? 4 : lg;    // interleave, run length
+            geo_shape = shape;
+            geo_rel = ((lane >> hs) << g) | (lane & ((1 << g) - 1));
+            geo_sl = (lane & ((1 << hs) - 1)) >> g;
+            geo_q0 = geo_sl * units_of(shape);        // the lane's first unit
+        };
+
+        // ---- one token per lane at last: the entry inside the unit that holds the draw, or the
+        // dense bucket; store
+        auto finish = [&](int found, int kind, int o, float w_o, double u, double Qp) {
+            int z_new = found;
+            if (kind == kDrawInUnit) {
+                if constexpr (kDouble)
+                    z_new = topic_in_unit_double<Layout, kNear>(a.slots, (uint32_t)found, o, w_o, u);
+                else
+                    z_new = topic_in_unit<Layout, kNear>(weight_at, a.slots, (uint32_t)found, o << 2, w_o, u);
+            }
+            if (kind == kDrawDense) {
+                double y = u * (1.0 / kRowScale);
+                if (kDouble && __builtin_expect(Qp < kSmallestScaled, 0))
+                    y = Qp * token_uniform(ka->seed, ka->iter,
+                                           (uint64_t)load_at<uint32_t>(ka->tok_id + tl.begin, (uint32_t)(b * batch + lane) << 2));
+                z_new = dense_bucket_search<kGroup>(pstar, cp, K, ng, ka->alpha, y, o,
+                                                    w_o, (double)w_o - plain_weight(pstar[o]));
+            }
+            store_at<uint16_t>(ka->z_next + tl.begin, (uint32_t)(b * batch + lane) << 1, (uint16_t)z_new);
+        };
+
+        // ---- Tokens of one document and word stand next to each other and walk the same row with the same
+        // p*: where rows are shared, a row is walked once for all its tokens of the batch.  The sums at the
+        // ends of its units go to LDS, and each token, one per lane, then finds its topic among the row's
+        // sub-lanes, counts it, corrects the sums from there on and looks its draw up among them.
+        // A correction that takes off more than it leaves would cost bits: such tokens, and those
+        // with their topic spread over several units, take the walk of their own below.
+        bool in_rest = valid;
+        // (lane 0 is given slot 0, which no document has)
+        const bool head = valid && mine.off != (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine.off, 0x138, 0xf, 0xf, true);
+        const uint64_t heads = kDouble ? __ballot(head) : 0;
+        const int n_rows = __popcll(heads);
+        // Sharing costs a search per token among its row's sums and a wait for a unit of the row, once for
+        // every kept_sums units that the batch's rows have; it saves the walks that are not made, and a
+        // quarter of each that is.  So: at most two rows for three tokens, and two passes saved.  Sampling
+        // launch, ms, no sharing / rows up to 16 of 16, 16 of 20, 16 of 24 (and two passes saved):
+        //   9.9e7 tokens, K = 1,000, late       6.26   6.04   5.16   5.16      1.8e8, K = 1,000   7.47   8.20   7.15   7.14
+        //   6.3e6, K = 1,537                    0.62   0.78   0.55   0.55      1e6, K = 128      0.058  0.071  0.056  0.056
+        //   8.6e6, documents of 30,000, K = 299 1.42   0.53   0.47   0.47      1e5, K = 32       12.3us 16.0   12.4   12.4
+        //   1.2e7, documents of 4,000, K = 2,000 5.76  5.36   3.93   3.87
+        auto share_walks = [&]() {
+            const int n = min(batch, tl.count - b * batch);
+            if (3 * n_rows > 2 * n || __ballot(mine.nnz > kMostKeptUnits) != 0) return false;
+            const int rows_per_pass = __ballot(mine.nnz > 12) == 0 ? 16 : __ballot(mine.nnz > 24) == 0 ? 8 : __ballot(mine.nnz > 48) == 0 ? 4 : 1;
+            return 4 * n - 3 * n_rows >= 8 * rows_per_pass;
+        };
+        if constexpr (kDouble) if (share_walks()) {
+            in_rest = false;
+            double* sums = reinterpret_cast<double*>(my_rec);
+            uint16_t* first_topic = reinterpret_cast<uint16_t*>(sums + a.kept_sums);
+            uint32_t* row_slot = reinterpret_cast<uint32_t*>(first_topic + a.kept_passes * kWave);
+            unsigned char* row_units = reinterpret_cast<unsigned char*>(row_slot + kWave);
+            const int row = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(heads >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)heads, 0u)) +
+                            (head ? 0 : -1);
+            if (head) {
+                row_slot[row] = mine.off;
+                row_units[row] = (unsigned char)mine.nnz;
+            }
+            if (lane >= n_rows) {
+                row_slot[lane] = 0;
+                row_units[lane] = 0;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            learn_shapes((int)row_units[lane]);
+            auto request = [&](int t0, int shape, uint4* raw, bool live) {
+                place_lanes(shape);
+                const int r = min(t0 + geo_rel, kWave - 1);
+                const uint32_t off = row_slot[r];
+                const int n_mine = live ? min((int)row_units[r] - geo_q0, units_of(shape)) : 0;
+                if constexpr (kNear) {
+                    const uint32_t row_bytes = (off + 1u + (uint32_t)geo_q0) << 4;
+#pragma unroll
+                    for (int c = 0; c < kKeptUnits; ++c) raw[c] = load_unit_near(a.slots, row_bytes, c, c < n_mine);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < kKeptUnits; ++c) raw[c] = load_unit(a.slots, off, geo_q0 + c, c < n_mine);
+                }
+            };
+            uint4 raw_next[kKeptUnits];
+            int t_next = 0, shape_next = shape_at(0);
+            request(0, shape_next, raw_next, true);
+            do {                // as many passes as there is room for, then the tokens of their rows
+                const int row0 = t_next;
+                int n_passes = 0, n_sums = 0, most_lanes = 4, most_units = 1;
+                do {
+                    const int shape = shape_next, rel = geo_rel, sl = geo_sl, t0 = t_next;
+                    uint4 raw[kKeptUnits];
+#pragma unroll
+                    for (int c = 0; c < kKeptUnits; ++c) raw[c] = raw_next[c];
+                    const int lanes = 1 << lanes_log2(shape), nu = units_of(shape);
+                    t_next += kWave / lanes;
+                    most_lanes = max(most_lanes, lanes);
+                    most_units = max(most_units, lanes * nu);
+                    const int t_req = min(t_next, kWave - 1);
+                    shape_next = shape_at(t_req);
+                    request(t_req, shape_next, raw_next, t_next < n_rows);
+                    double* s = sums + n_sums;
+                    uint16_t* ft = first_topic + n_passes * kWave;
+                    switch (shape) {
+                    case 0: row_pass_shared<Layout, 4, 1>(s, ft, rel, sl, raw); break;
+                    case 1: row_pass_shared<Layout, 4, 2>(s, ft, rel, sl, raw); break;
+                    case 2: row_pass_shared<Layout, 4, 3>(s, ft, rel, sl, raw); break;
+                    case 3: row_pass_shared<Layout, 8, 2>(s, ft, rel, sl, raw); break;
+                    case 4: row_pass_shared<Layout, 8, 3>(s, ft, rel, sl, raw); break;
+                    case 5: row_pass_shared<Layout, 16, 2>(s, ft, rel, sl, raw); break;
+                    case 6: row_pass_shared<Layout, 16, 3>(s, ft, rel, sl, raw); break;
+                    case 7: row_pass_shared<Layout, 32, 2>(s, ft, rel, sl, raw); break;
+                    case 8: row_pass_shared<Layout, 32, 3>(s, ft, rel, sl, raw); break;
+                    case 9: row_pass_shared<Layout, 64, 2>(s, ft, rel, sl, raw); break;
+                    case 10: row_pass_shared<Layout, 64, 3>(s, ft, rel, sl, raw); break;
+                    }
+                    // where the row's sums are | its first sub-lane's place | units per lane | log2 of its lanes
+                    if (sl == 0 && t0 + rel < n_rows)
+                        row_slot[t0 + rel] = (uint32_t)(n_sums + rel * lanes * nu) | (uint32_t)(n_passes * kWave + rel * lanes) << 12 |
+                                             (uint32_t)nu << 24 | (uint32_t)lanes_log2(shape) << 28;
+                    ++n_passes;
+                    n_sums += kWave * nu;
+                } while (t_next < n_rows && n_passes < a.kept_passes && n_sums + kWave * units_of(shape_next) <= a.kept_sums);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                if (valid && row >= row0 && row < t_next) {
+                    const uint32_t info = row_slot[row];
+                    const int lane0 = (int)((info >> 12) & 0xfffu), nu = (int)((info >> 24) & 3u), lanes = 1 << (info >> 28);
+                    const double* row_sums = sums + (info & 0xfffu);
+                    const int n_units = mine.nnz, o = mine.o;
+                    // the last sub-lane whose first topic is not above o
+                    int holder = 0;
+                    for (int step = most_lanes >> 1; step > 0; step >>= 1) {
+                        const int at = min(holder + step, lanes - 1);
+                        if (holder + step < lanes && (int)first_topic[lane0 + at] <= o) holder = at;
+                    }
+                    // its units: where o is, and o's tokens
+                    const int q0 = holder * nu;
+                    uint32_t n_to[kKeptUnits], n_o = 0;
+                    uint4 held[kKeptUnits];
+#pragma unroll
+                    for (int c = 0; c < kKeptUnits; ++c) held[c] = load_unit(a.slots, mine.off, q0 + c, c < nu && q0 + c < n_units);
+#pragma unroll
+                    for (int c = 0; c < kKeptUnits; ++c) {
+                        Layout::count_own(held[c], o, n_o);
+                        n_to[c] = n_o;
+                    }
+                    const int c_o = n_to[0] > 0 ? 0 : n_to[1] > 0 ? 1 : 2, q_o = q0 + c_o;
+                    if ((n_to[0] > 0 ? n_to[0] : n_to[1] > 0 ? n_to[1] : n_to[2]) != n_o) in_rest = true;
+                    if (holder > 0 && (int)first_topic[lane0 + holder] == o &&
+                        key_before_unit<Layout>(a.slots + ((size_t)mine.off + 1u + (size_t)q0) * 16u) == Layout::key_of_topic(o))
+                        in_rest = true;
+                    const double w_o = kWeightScale * (double)mine.w_o;
+                    const double shift = fma(__hiloint2double((int)n_o - 1, 0), w_o,
+                                             -(__hiloint2double((int)n_o, 0) * (double)pstar[o]));
+                    const double S_all = row_sums[n_units - 1];
+                    const double S = S_all + shift, total = fma(mine.Qp, kSumScale, S);
+                    if (!(S_all <= kMostTakenOff * total) || !(mine.Qp >= kSmallestScaled)) in_rest = true;
+                    const double x = mine.u * total;
+                    int unit = 0;           // units known to lie before the draw
+                    double before = 0.0;
+                    for (int step = 1 << (31 - __builtin_clz(most_units)); step > 0; step >>= 1) {
+                        const int upto = unit + step;
+                        if (upto <= n_units) {
+                            const double e = row_sums[upto - 1] + (upto > q_o ? shift : 0.0);
+                            if (!(e > x)) { unit = upto; before = e; }
+                        }
+                    }
+                    if (!in_rest) {
+                        const bool sparse = x < S;
+                        mine.nnz = sparse ? kDrawInUnit : kDrawDense;
+                        mine.off += 1u + (uint32_t)min(unit, n_units - 1);      // (the last unit's sum is S: above x)
+                        mine.u = x - (sparse ? before : S);
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            } while (t_next < n_rows);
+            if (valid && !in_rest) finish((int)mine.off, mine.nnz, mine.o, mine.w_o, mine.u, mine.Qp);
+        }
+        int n_here, my_place;
+        if constexpr (kDouble) {
+            const uint64_t rest = __ballot(in_rest);
+            n_here = __popcll(rest);
+            if (n_here == 0) continue;
+            my_place = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(rest >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)rest, 0u));
+            if (!in_rest) {             // (behind the records in use)
+                mine.off = 0; mine.nnz = 0;
+                my_rec[n_here + lane - my_place] = mine;
+            } else {
+                my_rec[my_place] = mine;
+            }
+        } else {
+            n_here = min(batch, tl.count - b * batch);
+            my_place = lane;
+            my_rec[lane] = mine;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+        // ---- one token per group of 4 .. 64 lanes.  A pass takes the next 16, 8, 4, 2 or 1
+        // tokens, as many as lets every lane own at most kKeptUnits units; the rows of the
+        // following pass are requested from memory before this one is worked on.
+        learn_shapes(kDouble ? my_rec[lane].nnz : mine.nnz);
         // where a pass's rows are, and the loads of the units its lanes keep.  `rec` is the
         // record of the lane's token, `sl` the lane's place inside its group.  A pass that
         // would run past the batch's 64 records works on the last one several times over.
         auto request = [&](int t0, int shape, TokenRec*& rec, int& sl, uint4* raw, bool live) {
             const int nu = units_of(shape);
-            if (shape != geo_shape) {       // the lanes' places change only with the shape
-                const int lg = lanes_log2(shape);
-                const int g = lg < 4 ? 4 - lg : 0, hs = lg < 4 ? 4 : lg;    // interleave, run length
-                geo_shape = shape;
-                geo_rel = ((lane >> hs) << g) | (lane & ((1 << g) - 1));
-                geo_sl = (lane & ((1 << hs) - 1)) >> g;
-                geo_q0 = geo_sl * nu;        // the lane's first unit
-            }
+            place_lanes(shape);
             sl = geo_sl;
             rec = my_rec + min(t0 + geo_rel, kWave - 1);
             const uint2 where = *reinterpret_cast<const uint2*>(rec);
@@ -1199,32 +1443,12 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-        // ---- one token per lane again: the entry inside the unit that holds the draw, or the
-        // dense bucket; store
         // (the token's topic and corrected weight are read back from its record rather than
         // kept in registers across the passes)
-        if (lane < batch && b * batch + lane < tl.count) {
-            const TokenRec* rec = &my_rec[lane];
-            const int4 head = *reinterpret_cast<const int4*>(rec);     // off, kind, o, w_o
-            int z_new = head.x;
-            if (head.y == kDrawInUnit) {
-                if constexpr (kDouble)
-                    z_new = topic_in_unit_double<Layout, kNear>(a.slots, (uint32_t)head.x, head.z,
-                                                                __int_as_float(head.w), rec->u);
-                else
-                    z_new = topic_in_unit<Layout, kNear>(weight_at, a.slots, (uint32_t)head.x, head.z << 2,
-                                                         __int_as_float(head.w), rec->u);
-            }
-            if (head.y == kDrawDense) {
-                const float w_o = __int_as_float(head.w);
-                double y = rec->u * (1.0 / kRowScale);
-                if (kDouble && __builtin_expect(rec->Qp < kSmallestScaled, 0))
-                    y = rec->Qp * token_uniform(ka->seed, ka->iter,
-                                                (uint64_t)load_at<uint32_t>(ka->tok_id + tl.begin, (uint32_t)(b * batch + lane) << 2));
-                z_new = dense_bucket_search<kGroup>(pstar, cp, K, ng, ka->alpha, y, head.z,
-                                                    w_o, (double)w_o - plain_weight(pstar[head.z]));
-            }
-            store_at<uint16_t>(ka->z_next + tl.begin, (uint32_t)(b * batch + lane) << 1, (uint16_t)z_new);
+        if (kDouble ? in_rest : lane < batch && b * batch + lane < tl.count) {
+            const TokenRec* rec = &my_rec[my_place];
+            const int4 head_of = *reinterpret_cast<const int4*>(rec);     // off, kind, o, w_o
+            finish(head_of.x, head_of.y, head_of.z, __int_as_float(head_of.w), rec->u, rec->Qp);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();

@@ -148,6 +148,20 @@ const void* theta_ranked_kernel_for(RowKind rows, int docs) {
         return docs == 2 ? (const void*)mlda::theta_ranked_kernel<Layout, 2> : (const void*)mlda::theta_ranked_kernel<Layout, 1>;
     });
 }
+// What a wave of the sampler with fp64 weights keeps of shared walks: as much as leaves a CU its twenty waves
+// (five per SIMD; LDS is dealt out in 128 pieces of 1,280 bytes), where that is at least one pass.  Units,
+// sampling launch, ms:            192    384    576    768
+//   K = 299, documents of 30,000 0.632  0.549  0.520  0.519
+//   K = 1,000, 3.3e7 tokens       2.63   2.46   2.47   2.69   (four workgroups a CU)
+//   K = 1,537, 6.3e6             0.549  0.557  0.630  0.783   (four from 448 on)
+//   K = 2,000, 1.1e7             0.960  1.053  1.279  1.258   (four from 320 on)
+struct KeptSums { int32_t passes, sums; };
+KeptSums kept_sums_for(int32_t Kpad, int waves) {
+    const size_t budget = (size_t)(128 * waves / 20) * 1280;
+    for (int32_t sums = 768; sums > 192; sums -= 64)
+        if (mlda::sample_lds_bytes(Kpad, waves, 8, sums / 192 + 1, sums) <= budget) return {sums / 192 + 1, sums};
+    return {2, 192};
+}
 constexpr int kMaxTimedIters = 1024;
 constexpr int kRunTiles = 16;           // small tiles a workgroup of the large-K sampler takes one after the other
 // events of a streamed chunk visit: its uploads have arrived | topics and slots in word-major
@@ -1052,7 +1066,11 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
                                         : a.n_single + (a.n_tiles - a.n_single + a.run_tiles - 1) / a.run_tiles;
     const bool near = slots_near(c->slots_bytes) && !c->wide_slot_offsets;
     const int weight_bytes = c->rows == RowKind::packed ? 4 : 8;
-    const size_t lds = waves == 4 ? mlda::sample_lds_bytes(c->Kpad, waves, weight_bytes) : c->sample_lds;
+    const KeptSums kept = kept_sums_for(c->Kpad, 4), kept_solo = kept_sums_for(c->Kpad, 1);
+    a.kept_passes = kept.passes;
+    a.kept_sums = kept.sums;
+    if (weight_bytes != 8) a.kept_passes = a.kept_sums = 0;
+    const size_t lds = waves == 4 ? mlda::sample_lds_bytes(c->Kpad, waves, weight_bytes, a.kept_passes, a.kept_sums) : c->sample_lds;
     void* kernel_args[] = {&a};
     if (grid > 0)
         HIP_TRY(hipLaunchKernel(sample_kernel_for(c->K, c->rows, c->short_docs, near), dim3((unsigned)grid),
@@ -1060,10 +1078,14 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     const int32_t n_solo = c->n_tiles - c->n_shared;
     if (n_solo > 0) {
         a.tiles += c->n_shared;
+        if (weight_bytes == 8) {
+            a.kept_passes = kept_solo.passes;
+            a.kept_sums = kept_solo.sums;
+        }
         a.n_tiles = a.n_single = n_solo;
         HIP_TRY(hipLaunchKernel(near ? sample_solo_kernel_of<true>(c->rows) : sample_solo_kernel_of<false>(c->rows),
                                 dim3((unsigned)n_solo), dim3((unsigned)mlda::kWave), kernel_args,
-                                mlda::sample_lds_bytes(c->Kpad, 1, weight_bytes), c->stream));
+                                mlda::sample_lds_bytes(c->Kpad, 1, weight_bytes, a.kept_passes, a.kept_sums), c->stream));
     }
     return launch_check("sample_kernel");
 }

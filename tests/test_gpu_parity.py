@@ -303,6 +303,60 @@ def test_small_beta(mlda, case, beta):
     model.close()
 
 
+# (topics, tokens of a document, documents, words): many tokens of a document share a word, so their rows are walked
+# once.  Rows of every pass shape: up to 4, 8, 12 units of a row on 4 lanes, 16, 24 on 8, 32, 48 on 16, 64, 96 on
+# 32, 128, 192 on 64 (2-byte entries: 8 to a unit), and longer ones, which are not shared.
+SHARED_CASES = [(2000, n, D, 4) for n, D in [(60, 300), (90, 250), (125, 200), (185, 150), (250, 100), (370, 70),
+                                             (500, 50), (780, 40), (1200, 30), (2000, 20), (4000, 8)]] + [
+    (24, 200, 150, 4), (24, 30, 400, 2), (300, 28, 600, 2), (300, 500, 40, 5), (1023, 700, 30, 5), (1, 64, 40, 2)]
+
+
+@pytest.mark.parametrize("shape", ["1024,0", "128,128"])
+@pytest.mark.parametrize("case", SHARED_CASES, ids=lambda c: "k%d_n%d" % c[:2])
+def test_walks_shared_by_tokens(mlda, case, shape, monkeypatch):
+    monkeypatch.setenv("MLDA_TILE_SHAPE", shape)
+    monkeypatch.setenv("MLDA_WIDE_SLOT_OFFSETS", "1" if shape == "128,128" else "0")
+    K, length, D, V = case
+    rng = np.random.default_rng(K + length)
+    lens = np.maximum(1, length + rng.integers(-3, 4, size=D))
+
+    class C:  # minimal corpus record
+        pass
+    c = C(); c.doc_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64); c.T = int(lens.sum())
+    c.word_ids = rng.integers(V, size=c.T).astype(np.int32)
+    spread = rng.integers(K, size=c.T).astype(np.uint16)
+    # topics whose counts take many entries, which then cross units and lanes
+    few = np.where(rng.random(c.T) < 0.8, rng.choice([0, K // 3, K // 2, K - 1], size=c.T), spread).astype(np.uint16)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, 50.0 / K, 0.01, SEED)
+    for it, z in enumerate((spread, few)):
+        model.set_assignments(z, it=it)
+        check_step(model, c, z, V, K, 50.0 / K, 0.01, SEED, it + 1)
+    model.close()
+
+
+@pytest.mark.parametrize("beta", [0.01, 1e-14, 1e-30])
+@pytest.mark.parametrize("K", [30, 500])
+def test_shared_walks_with_little_left(mlda, K, beta):
+    """Documents with one token of a word, its only one of its topic, among documents with forty: without the
+    token nothing of the row's sum is left but beta, and alpha is too small to matter."""
+    V, pairs = 3, 11
+    words, z = [], []
+    for i in range(pairs):
+        words += [0] * 40 + [0] + [1] * 39
+        z += [0] * 40 + [2 + i] + [K - 1] * 20 + [K - 2] * 19
+
+    class C:  # minimal corpus record
+        pass
+    c = C(); c.doc_ptr = np.arange(2 * pairs + 1, dtype=np.int64) * 40; c.T = 80 * pairs
+    c.word_ids = np.array(words, dtype=np.int32)
+    z = np.array(z, dtype=np.uint16)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, 1e-30, beta, SEED)
+    for it in range(6):
+        model.set_assignments(z, it=it)
+        check_step(model, c, z, V, K, 1e-30, beta, SEED, it + 1)
+    model.close()
+
+
 @pytest.mark.parametrize("alpha", [1e-305, 1e-307])
 @pytest.mark.parametrize("K", [16, 300])
 def test_small_alpha(mlda, K, alpha):
