@@ -978,6 +978,36 @@ __global__ void pairs_to_word_major_kernel(const uint2* pairs, const int32_t* to
 }
 
 // Boundary order changes.  tok_id[pos] = document-major index of word-major position pos.
+// By sampling tiles, in their order, every XCD a run of them: the tiles in flight then hold the same documents,
+// and a line of z_doc gathers its tokens in the XCD's L2.  One workgroup per tile; for large corpora
+// (kReorderByTiles has both sides).
+template <bool kToDocuments>
+__global__ __launch_bounds__(256) void reorder_by_tiles_kernel(const Tile* tiles, int32_t n_tiles, uint16_t* z_word,
+                                                               const int32_t* tok_id, uint16_t* z_doc, int64_t first) {
+    const int per_xcd = (int)gridDim.x / 8;
+    const int ti = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    if (ti >= n_tiles) return;
+    const Tile tl = tiles[ti];
+    for (int i = (int)threadIdx.x; i < tl.count; i += 4 * 256) {
+        int64_t id[4];
+        uint16_t z[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int j = min(i + e * 256, tl.count - 1);
+            id[e] = (int64_t)tok_id[(int64_t)tl.begin + j] - first;
+            if (kToDocuments) z[e] = z_word[(int64_t)tl.begin + j];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) if (!kToDocuments) z[e] = z_doc[id[e]];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (i + e * 256 >= tl.count) break;
+            if (kToDocuments) z_doc[id[e]] = z[e];
+            else z_word[(int64_t)tl.begin + i + e * 256] = z[e];
+        }
+    }
+}
+
 __global__ void to_doc_major_scatter_kernel(const uint16_t* z_word, const int32_t* tok_id,
                                             uint16_t* z_doc, int64_t T, int64_t first) {
     const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -162,6 +162,11 @@ KeptSums kept_sums_for(int32_t Kpad, int waves) {
         if (mlda::sample_lds_bytes(Kpad, waves, 8, sums / 192 + 1, sums) <= budget) return {sums / 192 + 1, sums};
     return {2, 192};
 }
+// Tokens from which assignments change their order tile by tile: where the caller's array outgrows the 256 MB
+// of last-level cache, in which the plain scatter's lines otherwise meet.  The whole getter, plain / by tiles, ms:
+//   1.35e8 tokens 8.6 / 9.8   1.8e8 12.1 / 12.5   2.7e8 20.4 / 18.0   3.8e8 29.8 / 24.8   7.4e8 60.8 / 48.0
+// (7.4e8: the scatter itself 24.05 / 11.2, the gather of the setter 12.55 / 7.5; 9.9e7: 1.00 / 1.95 and 1.36 / 1.15.)
+constexpr int64_t kReorderByTiles = 200000000;
 constexpr int kMaxTimedIters = 1024;
 constexpr int kRunTiles = 16;           // small tiles a workgroup of the large-K sampler takes one after the other
 // events of a streamed chunk visit: its uploads have arrived | topics and slots in word-major
@@ -649,6 +654,7 @@ struct mlda_ctx {
     hipStream_t stream = nullptr;
     int n_cus = 0, lds_limit = 0;
     bool far_weights = false;           // p* of the sampler's tiles in device memory (large K)
+    int64_t reorder_by_tiles = kReorderByTiles;         // MLDA_REORDER_BY_TILES: other tokens than these
     bool wide_slot_offsets = false;     // MLDA_WIDE_SLOT_OFFSETS: 64-bit unit addresses whatever the buffer's size
     TileShape shape = {0, 0};           // MLDA_TILE_SHAPE="tokens,alone": this one whatever the sizes
     const TileShape* forced_shape() const { return shape.tokens > 0 ? &shape : nullptr; }
@@ -1300,6 +1306,7 @@ int device_limits(mlda_ctx* c) {
     // (a switch for tests: the 64-bit form is otherwise only reached by theta slots beyond 4 GiB)
     const char* wide = std::getenv("MLDA_WIDE_SLOT_OFFSETS");
     c->wide_slot_offsets = wide && wide[0] != '\0' && wide[0] != '0';
+    if (const char* from = std::getenv("MLDA_REORDER_BY_TILES")) c->reorder_by_tiles = std::atoll(from);
     // (likewise: most shapes are otherwise only reached by corpora of millions of tokens)
     const char* shape = std::getenv("MLDA_TILE_SHAPE");
     int tokens = 0, alone = 0;
@@ -1823,8 +1830,12 @@ int mlda_set_assignments(mlda_ctx* c, const uint16_t* z, int32_t iter) {
         if (c->T > 0) {
             uint16_t* tmp = c->z[c->cur ^ 1];
             RC_TRY(send(c, tmp, z, (size_t)c->T * 2));    // (done: the caller's z may go away)
-            hipLaunchKernelGGL(mlda::to_word_major_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0,
-                               c->stream, tmp, c->tok_id, c->z[c->cur], c->T, (int64_t)0);
+            if (c->T >= c->reorder_by_tiles)
+                hipLaunchKernelGGL(mlda::reorder_by_tiles_kernel<false>, dim3((unsigned)((c->n_tiles + 7) / 8 * 8)), dim3(256), 0,
+                                   c->stream, c->tiles, c->n_tiles, c->z[c->cur], c->tok_id, tmp, (int64_t)0);
+            else
+                hipLaunchKernelGGL(mlda::to_word_major_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0,
+                                   c->stream, tmp, c->tok_id, c->z[c->cur], c->T, (int64_t)0);
         }
         RC_TRY(rebuild_phi(c, c->z[c->cur], 0));
         RC_TRY(rebuild_theta(c, c->z[c->cur]));
@@ -1956,9 +1967,13 @@ int mlda_get_assignments(mlda_ctx* c, uint16_t* z) {
         return MLDA_OK;
     }
     uint16_t* tmp = c->z[c->cur ^ 1];      // free between steps
-    hipLaunchKernelGGL(mlda::to_doc_major_scatter_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0, c->stream,
-                       c->z[c->cur], c->tok_id, tmp, c->T, c->at->tok_begin);
-    RC_TRY(launch_check("to_doc_major_scatter_kernel"));
+    if (c->T >= c->reorder_by_tiles)
+        hipLaunchKernelGGL(mlda::reorder_by_tiles_kernel<true>, dim3((unsigned)((c->n_tiles + 7) / 8 * 8)), dim3(256), 0,
+                           c->stream, c->tiles, c->n_tiles, c->z[c->cur], c->tok_id, tmp, c->at->tok_begin);
+    else
+        hipLaunchKernelGGL(mlda::to_doc_major_scatter_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0, c->stream,
+                           c->z[c->cur], c->tok_id, tmp, c->T, c->at->tok_begin);
+    RC_TRY(launch_check("assignments to document order"));
     return fetch(c, z, tmp, (size_t)c->T * 2);
 }
 

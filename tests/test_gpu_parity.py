@@ -710,6 +710,26 @@ def test_phi_segment_edges(mlda, K):
         model.close()
 
 
+@pytest.mark.parametrize("K", [40, 3000])
+def test_assignments_change_order_tile_by_tile(mlda, K, monkeypatch):
+    """Both directions, tiles of every size up to the largest and one more, and a number of them that eight does not divide."""
+    monkeypatch.setenv("MLDA_REORDER_BY_TILES", "0")
+    V = 61
+    rng = np.random.default_rng(K)
+    per_word = np.concatenate([np.arange(1, V - 7), [255, 256, 257, 1023, 1024, 1025, 4097, 0]])
+    words = rng.permutation(np.repeat(np.arange(V, dtype=np.int32), per_word))
+    doc_ptr = np.concatenate([[0], np.sort(rng.choice(np.arange(1, len(words)), 90, replace=False)), [len(words)]]).astype(np.int64)
+    for shape in ("1024,0", "64,64"):
+        monkeypatch.setenv("MLDA_TILE_SHAPE", shape)
+        model = mlda.Mlda(doc_ptr, words, V, K, 50.0 / K, 0.01, SEED)
+        z = rng.integers(K, size=len(words)).astype(np.uint16)
+        model.set_assignments(z)
+        assert np.array_equal(model.assignments(), z)
+        n_wk, n_k = oracle.count_word_topic(words, z, V, K)
+        assert np.array_equal(model.word_topic(), n_wk) and np.array_equal(model.topic_totals(), n_k)
+        model.close()
+
+
 # (topics, lengths of the first documents, further documents of 3 tokens each)
 RANKED_CASES = [("two_per_wave", 1000, [0, 1, 31, 32, 33, 127, 128, 129, 383, 384, 385, 1500, 4000, 0, 700], 60),
                 ("two_per_wave_33", 33, [0, 1, 127, 128, 129, 383, 384, 385, 3000], 60),
