@@ -31,6 +31,9 @@
 //     units per lane of a whole wave are walked twice by the wave.  Token parameters and
 //     results travel between the per-lane and per-group phases through small per-wave LDS
 //     records;
+//   - tokens of one document and word stand next to each other; where most tokens of a batch have such
+//     company, a row is walked once for all of them, its prefix sums go to LDS, and every token
+//     corrects them for its own topic and looks its draw up there, one token per lane;
 //   - a theta row is a run of entries (topic, count) in ascending topic order, 2 bytes each
 //     where K <= 2048 (3, 5 or 6 bits of count; 4 bytes for documents long beside the topics, and
 //     for the shortest), else 4 bytes (16 bits of topic, 14 of count); a count too large for its field is written
@@ -88,8 +91,8 @@ struct SampleArgs {
     // p* of its current tile in far_pstar[b * Kpad ..] and takes the tiles b, b + grid, ...
     float* far_pstar;
     int32_t min_batch;          // K <= 2048: tokens a wave takes at a time at least
-    // fp64 weights, tokens that share the walks over their rows: how many passes, and units of them, a wave
-    // keeps the sums of at a time
+    // Tokens that share the walks over their rows: how many passes, and (fp64 weights) units of them, a wave keeps
+    // the sums of at a time.  (fp32 weights: a sum per lane and pass)
     int32_t kept_passes, kept_sums;
 };
 
@@ -119,6 +122,10 @@ constexpr int kDrawTopic = -3;  // off = the new topic itself
 // p* of the tile's word is staged as fp64 or fp32 (Layout::kDoubleWeights), as fp32 always in the
 // workgroups of twelve waves, where fp64 would cost a CU its second workgroup.
 //
+// Large K: a wave keeps the sums of at least so many passes, which takes no more than its records do.
+constexpr int kLeastKeptPasses = 2;
+// (a sum per lane and pass; the rows' lengths take two bytes each, 64 bytes more than the shorter ones below)
+__host__ __device__ constexpr int lane_sums_for(int kept_passes) { return kept_passes * kWave + 8; }
 // What a wave keeps in LDS: the records of its tokens, or (shared walks) the sums of up to kept_sums units
 // and the first topics of the lanes of kept_passes passes, then 64 rows' slots and lengths.
 __host__ __device__ constexpr int sample_wave_bytes(int kept_passes, int kept_sums) {
@@ -131,7 +138,7 @@ __host__ __device__ constexpr size_t sample_lds_bytes(int Kpad, int waves, int w
            (size_t)waves * sample_wave_bytes(kept_passes, kept_sums);
 }
 // The same when p* stays in device memory: the prefix sums and the waves' records only.
-__host__ __device__ constexpr size_t sample_far_lds_bytes(int Kpad, int waves) { return sample_lds_bytes(Kpad, waves, 0); }
+__host__ __device__ constexpr size_t sample_far_lds_bytes(int Kpad, int waves) { return sample_lds_bytes(Kpad, waves, 0, kLeastKeptPasses, lane_sums_for(kLeastKeptPasses)); }
 // What runs of small tiles keep in LDS besides: the groups' own sums (the prefix sums are made
 // from them again after every change) and one bit per group for "changed".
 __host__ __device__ constexpr size_t sample_run_lds_bytes(int Kpad, int waves) {
@@ -266,7 +273,7 @@ struct PackedRows {
     static constexpr int kEntryBytes = 4, kUnitEntries = 4;
     static constexpr int kMaxCount = (1 << 14) - 1;
     static constexpr int kWavesPerSimd = 6;
-    static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = false;
+    static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = false, kShares = true;
     static __host__ __device__ __forceinline__ Entry make(int count, int topic) {
         return ((uint32_t)count << 18) | ((uint32_t)topic << 2);
     }
@@ -286,6 +293,10 @@ struct PackedRows {
 struct PackedRowsShort : PackedRows {
     static constexpr bool kOneEntryPerTopic = true;
 };
+// The same for documents so short that tokens hardly share a walk over their row.
+struct PackedRowsAlone : PackedRowsShort {
+    static constexpr bool kShares = false;
+};
 
 // The two layouts of K <= 2048, whose p* is staged in fp64.  An entry holds its topic above its
 // count: entries of a row rise as numbers, and "(o, kMaxCount) - entry", as an unsigned number, is at
@@ -302,7 +313,7 @@ struct TinyRows {
     static constexpr int kMaxCount = (1 << kCountBits) - 1;
     static constexpr int kMaxK = (1 << (16 - kCountBits)) - 1;      // topics 0 .. K, K being the padding entries'
     static constexpr int kWavesPerSimd = 5;
-    static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = true;
+    static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = true, kShares = true;
     typedef uint16_t Pair __attribute__((ext_vector_type(2)));
     static __host__ __device__ __forceinline__ Entry make(int count, int topic) {
         return (Entry)(((uint32_t)topic << kCountBits) | (uint32_t)count);
@@ -370,7 +381,7 @@ struct CountedRows {
     static constexpr int kEntryBytes = 4, kUnitEntries = 4;
     static constexpr int kMaxCount = (1 << 13) - 1;
     static constexpr int kWavesPerSimd = 5;
-    static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = true;
+    static constexpr bool kOneEntryPerTopic = false, kDoubleWeights = true, kShares = true;
     static __host__ __device__ __forceinline__ Entry make(int count, int topic) {
         return ((uint32_t)topic << 16) | (uint32_t)count;
     }
@@ -871,6 +882,52 @@ __device__ __forceinline__ int topic_in_unit(const Weights& weight_at, const uns
     return (found >= 0 ? found : last) >> 2;
 }
 
+// The walk over a row for all the tokens that share it, fp32 weights: the sums at the ends of the sub-lanes,
+// every entry with p*, go to LDS with the topic of each sub-lane's first entry.
+template <class Layout, class Weights>
+__device__ __forceinline__ void unit_sum_shared(const Weights& weight_at, const uint4& raw, double& acc) {
+    float w[Layout::kUnitEntries];
+#pragma unroll
+    for (int j = 0; j < Layout::kUnitEntries; ++j) w[j] = weight_at((uint32_t)Layout::key(raw, j));
+#pragma unroll
+    for (int j = 0; j < Layout::kUnitEntries; ++j) acc = fma((double)Layout::count(raw, j), (double)w[j], acc);
+}
+template <class Layout, int kLanes, int kUnits, class Weights>
+__device__ __forceinline__ void row_pass_lanes(const Weights& weight_at, double* sums, uint16_t* first_topic, int rel, int sl,
+                                               const uint4* raw) {
+    double acc = 0.0;
+#pragma unroll
+    for (int c = 0; c < kUnits; ++c) unit_sum_shared<Layout>(weight_at, raw[c], acc);
+    const double incl = group_inclusive_sum<kLanes>(acc);
+    sums[rel * kLanes + sl] = incl;
+    first_topic[rel * kLanes + sl] = (uint16_t)Layout::entry_topic((typename Layout::Entry)raw[0].x);
+}
+
+// The entry that holds the draw y (measured from the first unit's start) among the `n_units` units from `unit`
+// on, which have all entries of o or none: as topic_in_unit.  One token per lane.
+template <class Layout, class Weights>
+__device__ __forceinline__ int topic_in_units(const Weights& weight_at, const unsigned char* slots, uint32_t unit, int n_units,
+                                              int o, float w_o, double y) {
+    const int o_key = Layout::key_of_topic(o);
+    bool own_before = false;
+    double acc = 0.0;
+    int found = -1, last = -1;
+    for (int c = 0; c < n_units && found < 0; ++c) {
+        const uint4 raw = *reinterpret_cast<const uint4*>(slots + ((size_t)unit + (size_t)c) * 16u);
+#pragma unroll
+        for (int j = 0; j < Layout::kUnitEntries; ++j) {
+            const int key = Layout::key(raw, j);
+            const bool own = key == o_key, first = own && !own_before;
+            own_before = own_before || own;
+            const double before = acc;
+            acc = fma((double)(Layout::count(raw, j) - (first ? 1 : 0)), (double)(own ? w_o : weight_at((uint32_t)key)), acc);
+            if (acc > before || last < 0) last = key;
+            if (found < 0 && acc > y) found = key;
+        }
+    }
+    return (found >= 0 ? found : last) >> 2;
+}
+
 // Rows too long for the kept shapes, one per wave (sub-lane = lane): one walk for the sums, a
 // second one over the hit lane's entries.  Lane l owns the units [n l, n (l + 1)).
 template <class Layout, class Weights>
@@ -942,7 +999,9 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);      // wave-uniform, in an SGPR
     unsigned char* wave_base = lds + pstar_lds + (size_t)((ng + 1) & ~1) * 8;
-    TokenRec* my_rec = reinterpret_cast<TokenRec*>(wave_base + wave * (kDouble ? sample_wave_bytes(a.kept_passes, a.kept_sums) : kWave * (int)sizeof(TokenRec)));
+    constexpr bool kShares = Layout::kShares;
+    const int wave_bytes = kShares ? sample_wave_bytes(a.kept_passes, a.kept_sums) : kWave * (int)sizeof(TokenRec);
+    TokenRec* my_rec = reinterpret_cast<TokenRec*>(wave_base + wave * wave_bytes);
     typedef typename std::conditional<kFar, FarWeights, LdsWeights>::type Weights;
     [[maybe_unused]] Weights weight_at;
     if constexpr (kFar) weight_at.base = reinterpret_cast<const unsigned char*>(pstar);
@@ -964,7 +1023,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         return in_run() ? a.n_single + before * a.run_tiles : (int)blockIdx.x - before;
     };
     auto last_tile = [&]() { return in_run() ? min(first_tile() + a.run_tiles, a.n_tiles) : first_tile() + 1; };
-    double* group_sum = reinterpret_cast<double*>(wave_base + (size_t)kWaves * kWave * sizeof(TokenRec));
+    double* group_sum = reinterpret_cast<double*>(wave_base + (size_t)kWaves * wave_bytes);
     uint32_t* changed = reinterpret_cast<uint32_t*>(group_sum + ((ng + 1) & ~1));
     if (in_run()) {
         for (int w = tid; w < (ng + 31) / 32; w += kWaves * kWave) changed[w] = 0u;
@@ -1182,14 +1241,14 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         // sub-lanes, counts it, corrects the sums from there on and looks its draw up among them.
         // A correction that takes off more than it leaves would cost bits: such tokens, and those
         // with their topic spread over several units, take the walk of their own below.
-        bool in_rest = valid;
+        bool in_rest = valid, shared = false;
         // (lane 0 is given slot 0, which no document has)
         const bool head = valid && mine.off != (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine.off, 0x138, 0xf, 0xf, true);
-        const uint64_t heads = kDouble ? __ballot(head) : 0;
+        const uint64_t heads = kShares ? __ballot(head) : 0;
         const int n_rows = __popcll(heads);
-        // Sharing costs a search per token among its row's sums and a wait for a unit of the row, once for
-        // every kept_sums units that the batch's rows have; it saves the walks that are not made, and a
-        // quarter of each that is.  So: at most two rows for three tokens, and two passes saved.  Sampling
+        // Sharing costs a search per token among its row's sums and a wait for units of the row, once for every
+        // time that the kept sums fill up; it saves the walks that are not made, and a quarter of each that
+        // is.  So: at most two rows for three tokens, and two passes saved.  Sampling
         // launch, ms, no sharing / rows up to 16 of 16, 16 of 20, 16 of 24 (and two passes saved):
         //   9.9e7 tokens, K = 1,000, late       6.26   6.04   5.16   5.16      1.8e8, K = 1,000   7.47   8.20   7.15   7.14
         //   6.3e6, K = 1,537                    0.62   0.78   0.55   0.55      1e6, K = 128      0.058  0.071  0.056  0.056
@@ -1197,12 +1256,13 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         //   1.2e7, documents of 4,000, K = 2,000 5.76  5.36   3.93   3.87
         auto share_walks = [&]() {
             const int n = min(batch, tl.count - b * batch);
-            if (3 * n_rows > 2 * n || __ballot(mine.nnz > kMostKeptUnits) != 0) return false;
+            if (3 * n_rows > 2 * n || (kDouble && __ballot(mine.nnz > kMostKeptUnits) != 0)) return false;
             const int rows_per_pass = __ballot(mine.nnz > 12) == 0 ? 16 : __ballot(mine.nnz > 24) == 0 ? 8 : __ballot(mine.nnz > 48) == 0 ? 4 : 1;
             return 4 * n - 3 * n_rows >= 8 * rows_per_pass;
         };
         if constexpr (kDouble) if (share_walks()) {
             in_rest = false;
+            shared = true;
             double* sums = reinterpret_cast<double*>(my_rec);
             uint16_t* first_topic = reinterpret_cast<uint16_t*>(sums + a.kept_sums);
             uint32_t* row_slot = reinterpret_cast<uint32_t*>(first_topic + a.kept_passes * kWave);
@@ -1333,23 +1393,158 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             } while (t_next < n_rows);
             if (valid && !in_rest) finish((int)mine.off, mine.nnz, mine.o, mine.w_o, mine.u, mine.Qp);
         }
-        int n_here, my_place;
-        if constexpr (kDouble) {
+        if constexpr (kShares && !kDouble) if (share_walks()) {
+            // The same with a sum per sub-lane: a unit has four entries here, and a token looks through the units of
+            // its sub-lane itself.  Rows of any length: beyond the kept shapes a lane of the whole wave owns as many
+            // units as it takes, read in threes.  Sampling launch, random topics, before / after:
+            //   1.5e5 tokens in documents of 3,000, K = 4,983   4.28 / 0.97 ms     5e6 of 286, K = 2,218    0.84 / 0.49 ms
+            //   9.9e7 of 330, K = 10,000                        39.3 / 32.6        2e6 of 250, K = 40,000   4.38 / 3.75
+            in_rest = false;
+            shared = true;
+            double* sums = reinterpret_cast<double*>(my_rec);
+            uint16_t* first_topic = reinterpret_cast<uint16_t*>(sums + a.kept_passes * kWave);
+            uint32_t* row_slot = reinterpret_cast<uint32_t*>(first_topic + a.kept_passes * kWave);
+            uint16_t* row_units = reinterpret_cast<uint16_t*>(row_slot + kWave);
+            const int row = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(heads >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)heads, 0u)) +
+                            (head ? 0 : -1);
+            if (head) {
+                row_slot[row] = mine.off;
+                row_units[row] = (uint16_t)mine.nnz;
+            }
+            if (lane >= n_rows) {
+                row_slot[lane] = 0;
+                row_units[lane] = 0;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            learn_shapes((int)row_units[lane]);
+            int t_next = 0, scan_units = 0;
+            do {                // as many passes as there is room for, then the tokens of their rows
+                const int row0 = t_next;
+                int n_passes = 0, most_lanes = 4, most_units = 1;
+                do {
+                    const int shape = shape_at(t_next), t0 = t_next;
+                    place_lanes(shape);
+                    const int lanes = 1 << lanes_log2(shape);
+                    const int r = min(t0 + geo_rel, kWave - 1);
+                    const uint32_t off = row_slot[r];
+                    const int n_units = (int)row_units[r];
+                    const int nu = shape < 11 ? units_of(shape) : __builtin_amdgcn_readfirstlane((n_units + kWave - 1) / kWave);
+                    const int q0 = geo_sl * nu;
+                    t_next += kWave / lanes;
+                    most_lanes = max(most_lanes, lanes);
+                    most_units = max(most_units, nu);
+                    double* s = sums + n_passes * kWave;
+                    uint16_t* ft = first_topic + n_passes * kWave;
+                    uint4 raw[kKeptUnits];
+#pragma unroll
+                    for (int c = 0; c < kKeptUnits; ++c) raw[c] = load_unit(a.slots, off, q0 + c, c < nu && q0 + c < n_units);
+                    switch (shape) {
+                    case 0: row_pass_lanes<Layout, 4, 1>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 1: row_pass_lanes<Layout, 4, 2>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 2: row_pass_lanes<Layout, 4, 3>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 3: row_pass_lanes<Layout, 8, 2>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 4: row_pass_lanes<Layout, 8, 3>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 5: row_pass_lanes<Layout, 16, 2>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 6: row_pass_lanes<Layout, 16, 3>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 7: row_pass_lanes<Layout, 32, 2>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 8: row_pass_lanes<Layout, 32, 3>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 9: row_pass_lanes<Layout, 64, 2>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    case 10: row_pass_lanes<Layout, 64, 3>(weight_at, s, ft, geo_rel, geo_sl, raw); break;
+                    default: {
+                        ft[lane] = (uint16_t)Layout::entry_topic((typename Layout::Entry)raw[0].x);
+                        double acc = 0.0;
+                        for (int c0 = 0; c0 < nu; c0 += kKeptUnits) {
+                            uint4 ahead[kKeptUnits];
+#pragma unroll
+                            for (int c = 0; c < kKeptUnits; ++c) {
+                                const int q = c0 + kKeptUnits + c;
+                                ahead[c] = load_unit(a.slots, off, q0 + q, q < nu && q0 + q < n_units);
+                            }
+#pragma unroll
+                            for (int c = 0; c < kKeptUnits; ++c) {
+                                unit_sum_shared<Layout>(weight_at, raw[c], acc);
+                                raw[c] = ahead[c];
+                            }
+                        }
+                        s[lane] = group_inclusive_sum<kWave>(acc);
+                        break;
+                    }
+                    }
+                    // where the row's sums are | units per lane | log2 of its lanes
+                    if (geo_sl == 0 && t0 + geo_rel < n_rows)
+                        row_slot[t0 + geo_rel] = (uint32_t)(n_passes * kWave + geo_rel * lanes) | (uint32_t)nu << 12 |
+                                                 (uint32_t)lanes_log2(shape) << 28;
+                    ++n_passes;
+                } while (t_next < n_rows && n_passes < a.kept_passes);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                if (valid && row >= row0 && row < t_next) {
+                    const uint32_t info = row_slot[row];
+                    const int lane0 = (int)(info & 0xfffu), nu = (int)((info >> 12) & 0xffffu), lanes = 1 << (info >> 28);
+                    const int n_units = mine.nnz, o = mine.o, n_lanes = (n_units + nu - 1) / nu;
+                    int holder = 0;             // the last sub-lane whose first topic is not above o
+                    for (int step = most_lanes >> 1; step > 0; step >>= 1) {
+                        const int at = min(holder + step, lanes - 1);
+                        if (holder + step < lanes && (int)first_topic[lane0 + at] <= o) holder = at;
+                    }
+                    const int q0 = holder * nu, o_key = Layout::key_of_topic(o);
+                    int n_o = 0;
+                    for (int c = 0; c < most_units; ++c) {
+                        const uint4 unit = load_unit(a.slots, mine.off, q0 + c, c < nu && q0 + c < n_units);
+#pragma unroll
+                        for (int j = 0; j < Layout::kUnitEntries; ++j)
+                            n_o += Layout::key(unit, j) == o_key ? Layout::count(unit, j) : 0;
+                    }
+                    if (!Layout::kOneEntryPerTopic && holder > 0 && (int)first_topic[lane0 + holder] == o &&
+                        key_before_unit<Layout>(a.slots + ((size_t)mine.off + 1u + (size_t)q0) * 16u) == o_key)
+                        in_rest = true;         // the sub-lane before has some of o's entries, too
+                    const double shift = fma((double)(n_o - 1), (double)mine.w_o, -((double)n_o * (double)pstar[o]));
+                    const double S_all = sums[lane0 + n_lanes - 1];
+                    const double S = S_all + shift, total = mine.Qp + S;
+                    if (!(S_all <= kMostTakenOff * total)) in_rest = true;
+                    const double x = mine.u * total;
+                    int sub = 0;                // sub-lanes known to lie before the draw
+                    double before = 0.0;
+                    for (int step = most_lanes; step > 0; step >>= 1) {
+                        const int upto = sub + step;
+                        if (upto <= n_lanes) {
+                            const double e = sums[lane0 + upto - 1] + (upto > holder ? shift : 0.0);
+                            if (!(e > x)) { sub = upto; before = e; }
+                        }
+                    }
+                    if (!in_rest) {
+                        const bool sparse = x < S;
+                        sub = min(sub, n_lanes - 1);        // (the last sum is S: above x)
+                        scan_units = sparse ? min(nu, n_units - sub * nu) : 0;
+                        mine.off += 1u + (uint32_t)(sub * nu);
+                        mine.u = x - (sparse ? before : S);
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            } while (t_next < n_rows);
+            if (valid && !in_rest) {
+                if (scan_units > 0) finish(topic_in_units<Layout>(weight_at, a.slots, mine.off, scan_units, mine.o, mine.w_o, mine.u),
+                                           kDrawTopic, mine.o, mine.w_o, 0.0, 0.0);
+                else finish(0, kDrawDense, mine.o, mine.w_o, mine.u, mine.Qp);
+            }
+        }
+        // (the tokens that have no result yet, side by side)
+        int n_here = min(batch, tl.count - b * batch), my_place = lane;
+        if (kShares && shared) {
             const uint64_t rest = __ballot(in_rest);
             n_here = __popcll(rest);
             if (n_here == 0) continue;
             my_place = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(rest >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)rest, 0u));
             if (!in_rest) {             // (behind the records in use)
                 mine.off = 0; mine.nnz = 0;
-                my_rec[n_here + lane - my_place] = mine;
-            } else {
-                my_rec[my_place] = mine;
+                my_place = n_here + lane - my_place;
             }
-        } else {
-            n_here = min(batch, tl.count - b * batch);
-            my_place = lane;
-            my_rec[lane] = mine;
         }
+        my_rec[my_place] = mine;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1357,7 +1552,9 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         // ---- one token per group of 4 .. 64 lanes.  A pass takes the next 16, 8, 4, 2 or 1
         // tokens, as many as lets every lane own at most kKeptUnits units; the rows of the
         // following pass are requested from memory before this one is worked on.
-        learn_shapes(kDouble ? my_rec[lane].nnz : mine.nnz);
+        int units = mine.nnz;
+        if (kShares && shared) units = my_rec[lane].nnz;
+        learn_shapes(units);
         // where a pass's rows are, and the loads of the units its lanes keep.  `rec` is the
         // record of the lane's token, `sl` the lane's place inside its group.  A pass that
         // would run past the batch's 64 records works on the last one several times over.
@@ -1445,7 +1642,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
 
         // (the token's topic and corrected weight are read back from its record rather than
         // kept in registers across the passes)
-        if (kDouble ? in_rest : lane < batch && b * batch + lane < tl.count) {
+        if (kShares ? in_rest : lane < batch && b * batch + lane < tl.count) {
             const TokenRec* rec = &my_rec[my_place];
             const int4 head_of = *reinterpret_cast<const int4*>(rec);     // off, kind, o, w_o
             finish(head_of.x, head_of.y, head_of.z, __int_as_float(head_of.w), rec->u, rec->Qp);

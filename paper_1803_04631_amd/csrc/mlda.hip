@@ -92,25 +92,26 @@ bool far_weights_for(int32_t K) {
 // short_docs: no document has more tokens than a 4-byte entry counts; near: the theta slots of
 // the chunk end below 4 GiB, so that 32-bit byte offsets reach them
 template <bool kNear>
-const void* sample_kernel_of(int32_t K, RowKind rows, bool short_docs) {
+const void* sample_kernel_of(int32_t K, RowKind rows, bool short_docs, bool alone) {
     if (far_weights_for(K)) return (const void*)mlda::sample_kernel<12, mlda::PackedRows, true, kNear>;
-    if (rows == RowKind::packed && sample_waves_for(K) == 4) return (const void*)mlda::sample_kernel<4, mlda::PackedRowsShort, false, kNear>;
+    if (rows == RowKind::packed && sample_waves_for(K) == 4) return (const void*)mlda::sample_kernel<4, mlda::PackedRowsAlone, false, kNear>;
+    if (rows == RowKind::packed && short_docs && alone) return (const void*)mlda::sample_kernel<12, mlda::PackedRowsAlone, false, kNear>;
     if (rows == RowKind::packed && short_docs) return (const void*)mlda::sample_kernel<12, mlda::PackedRowsShort, false, kNear>;
     return with_layout(rows, [](auto layout) {
         typedef decltype(layout) Layout;
         return (const void*)mlda::sample_kernel<Layout::kDoubleWeights ? 4 : 12, Layout, false, kNear>;
     });
 }
-const void* sample_kernel_for(int32_t K, RowKind rows, bool short_docs, bool near) {
-    return near ? sample_kernel_of<true>(K, rows, short_docs) : sample_kernel_of<false>(K, rows, short_docs);
+const void* sample_kernel_for(int32_t K, RowKind rows, bool short_docs, bool alone, bool near) {
+    return near ? sample_kernel_of<true>(K, rows, short_docs, alone) : sample_kernel_of<false>(K, rows, short_docs, alone);
 }
 // (a wave per tile, K <= 2048)
 template <bool kNear>
 const void* sample_solo_kernel_of(RowKind rows) {
-    if (rows == RowKind::packed) return (const void*)mlda::sample_kernel<1, mlda::PackedRowsShort, false, kNear>;
+    if (rows == RowKind::packed) return (const void*)mlda::sample_kernel<1, mlda::PackedRowsAlone, false, kNear>;
     return with_layout(rows, [](auto layout) {
         typedef decltype(layout) Layout;
-        typedef typename std::conditional<Layout::kDoubleWeights, Layout, mlda::PackedRowsShort>::type Rows;
+        typedef typename std::conditional<Layout::kDoubleWeights, Layout, mlda::PackedRowsAlone>::type Rows;
         return (const void*)mlda::sample_kernel<1, Rows, false, kNear>;
     });
 }
@@ -162,6 +163,14 @@ KeptSums kept_sums_for(int32_t Kpad, int waves) {
         if (mlda::sample_lds_bytes(Kpad, waves, 8, sums / 192 + 1, sums) <= budget) return {sums / 192 + 1, sums};
     return {2, 192};
 }
+// K > 2048: documents of fewer tokens than these have too few words several times for shared walks, which the
+// kernel then leaves out.  1e6 tokens at K = 5,000, sampling launch without / with, us:
+//   documents of 15  190/198   30  172/180   50  191/202   80  193/200   120  221/207
+//   8e6, K = 3,000, 300 words: of 20  277/287   of 40  320/338
+constexpr int kAloneDocs = 90;
+// K > 2048: passes whose sums a wave keeps at most.  2 / 8: 5e6 tokens at K = 2,218 358/309 us, 1.5e5 at
+// K = 4,983 521/504, 9.9e7 at K = 10,000 22.5/22.2 ms.
+constexpr int kMostKeptPasses = 8;
 // Tokens from which assignments change their order tile by tile: where the caller's array outgrows the 256 MB
 // of last-level cache, in which the plain scatter's lines otherwise meet.  The whole getter, plain / by tiles, ms:
 //   1.35e8 tokens 8.6 / 9.8   1.8e8 12.1 / 12.5   2.7e8 20.4 / 18.0   3.8e8 29.8 / 24.8   7.4e8 60.8 / 48.0
@@ -660,6 +669,7 @@ struct mlda_ctx {
     const TileShape* forced_shape() const { return shape.tokens > 0 ? &shape : nullptr; }
     float* far_pstar = nullptr;
     size_t sample_lds = 0;
+    int32_t kept_passes = mlda::kLeastKeptPasses;       // K > 2048: of shared walks, see device_limits
     mlda::PhiView phi[2];                // [model_cur] is the current phi; two copies when streamed
     size_t phi_bytes = 0;                // bytes of one copy
     int32_t n_wide = 0;                  // words with an int32 row
@@ -1075,11 +1085,17 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     const KeptSums kept = kept_sums_for(c->Kpad, 4), kept_solo = kept_sums_for(c->Kpad, 1);
     a.kept_passes = kept.passes;
     a.kept_sums = kept.sums;
-    if (weight_bytes != 8) a.kept_passes = a.kept_sums = 0;
+    const bool alone = c->T < kAloneDocs * c->D;
+    if (waves == 12) {
+        a.kept_passes = c->kept_passes;
+        a.kept_sums = mlda::lane_sums_for(c->kept_passes);
+    } else if (weight_bytes != 8) {
+        a.kept_passes = a.kept_sums = 0;
+    }
     const size_t lds = waves == 4 ? mlda::sample_lds_bytes(c->Kpad, waves, weight_bytes, a.kept_passes, a.kept_sums) : c->sample_lds;
     void* kernel_args[] = {&a};
     if (grid > 0)
-        HIP_TRY(hipLaunchKernel(sample_kernel_for(c->K, c->rows, c->short_docs, near), dim3((unsigned)grid),
+        HIP_TRY(hipLaunchKernel(sample_kernel_for(c->K, c->rows, c->short_docs, alone, near), dim3((unsigned)grid),
                                 dim3((unsigned)(waves * mlda::kWave)), kernel_args, lds, c->stream));
     const int32_t n_solo = c->n_tiles - c->n_shared;
     if (n_solo > 0) {
@@ -1214,10 +1230,10 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     RC_TRY(launch_check("model set-up kernels"));
     if (c->sample_lds > 48 * 1024)          // (the workgroups of twelve waves only)
         for (bool short_docs : {false, true})
-            for (bool near : {false, true})
+            for (int form = 0; form < 4; ++form)
                 // (the attribute belongs to the kernel, not to this context: contexts of different
                 // needs may live side by side, so it is raised to what the device allows)
-                HIP_TRY(hipFuncSetAttribute(sample_kernel_for(c->K, RowKind::packed, short_docs, near),
+                HIP_TRY(hipFuncSetAttribute(sample_kernel_for(c->K, RowKind::packed, short_docs, (form & 1) != 0, (form & 2) != 0),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_limit));
     if ((size_t)c->K * 4 > 48 * 1024) {
         const int hist_bytes = std::min<int32_t>(c->K, kHistTopics) * 4;
@@ -1329,6 +1345,18 @@ int device_limits(mlda_ctx* c) {
         (2 * with_runs <= cu_lds || 2 * c->sample_lds > cu_lds)) {
         c->sample_lds = with_runs;
         c->run_tiles = kRunTiles;
+    }
+    // the sums of more passes where that leaves a CU as many workgroups
+    if (sample_waves_for(c->K) == 12) {
+        const size_t room = 2 * c->sample_lds <= cu_lds ? cu_lds / 2 : (size_t)c->lds_limit;
+        for (int passes = kMostKeptPasses; passes > mlda::kLeastKeptPasses; --passes) {
+            const size_t more = 12 * (size_t)(mlda::sample_wave_bytes(passes, mlda::lane_sums_for(passes)) -
+                                              mlda::sample_wave_bytes(mlda::kLeastKeptPasses, mlda::lane_sums_for(mlda::kLeastKeptPasses)));
+            if (c->sample_lds + more > room) continue;
+            c->sample_lds += more;
+            c->kept_passes = passes;
+            break;
+        }
     }
     return MLDA_OK;
 }

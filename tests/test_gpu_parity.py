@@ -308,6 +308,9 @@ def test_small_beta(mlda, case, beta):
 # 32, 128, 192 on 64 (2-byte entries: 8 to a unit), and longer ones, which are not shared.
 SHARED_CASES = [(2000, n, D, 4) for n, D in [(60, 300), (90, 250), (125, 200), (185, 150), (250, 100), (370, 70),
                                              (500, 50), (780, 40), (1200, 30), (2000, 20), (4000, 8)]] + [
+    # a sum per sub-lane, 4 entries to a unit; rows beyond the widest shape; counts of several entries; p* in device memory
+    (2500, 100, 200, 3), (2500, 130, 150, 3), (2500, 200, 100, 3), (2500, 300, 80, 3), (2500, 400, 60, 3), (2500, 700, 40, 3),
+    (2500, 1100, 30, 3), (2500, 3000, 12, 3), (3000, 40000, 4, 3), (40000, 300, 30, 3), (40000, 3000, 6, 3), (65535, 150, 40, 2),
     (24, 200, 150, 4), (24, 30, 400, 2), (300, 28, 600, 2), (300, 500, 40, 5), (1023, 700, 30, 5), (1, 64, 40, 2)]
 
 
@@ -335,7 +338,7 @@ def test_walks_shared_by_tokens(mlda, case, shape, monkeypatch):
 
 
 @pytest.mark.parametrize("beta", [0.01, 1e-14, 1e-30])
-@pytest.mark.parametrize("K", [30, 500])
+@pytest.mark.parametrize("K", [30, 500, 3000])
 def test_shared_walks_with_little_left(mlda, K, beta):
     """Documents with one token of a word, its only one of its topic, among documents with forty: without the
     token nothing of the row's sum is left but beta, and alpha is too small to matter."""
