@@ -739,6 +739,7 @@ struct mlda_ctx {
     int32_t n_shared = 0;                // tiles taken by workgroups of several waves, the rest by a wave each
     int32_t counted_tiles = 0;           // see HostChunk
     int32_t run_tiles = 1;
+    int32_t forced_run = 0;             // MLDA_RUN_TILES: runs of so many whatever the number of tiles
     int64_t run_tokens = 0;              // tokens of the tiles taken in runs
 
     // large transfers between the device and the caller's memory (see through_ring): pinned pieces,
@@ -1045,6 +1046,22 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
     return launch_check("theta rebuild kernel");
 }
 
+// Small tiles that a workgroup takes one after the other: kRunTiles, fewer where that leaves the chip less than three
+// workgroups a CU.  Sampling launch, us, by run length:
+//                                              1     2     4     8     16
+//   2.4e4 tokens, 580 words, K = 9,819        53    52    52    82    150
+//   1.5e5, 890 words, K = 4,983              185   193   284   515    955
+//   4.9e5, 1,000 words, K = 12,736           126   107   102   112    192
+//   1.0e6, 3,000 words, K = 5,000            142   126   111   130    191
+//   5.0e5, 20,000 words, K = 3,000           395   332   303   290    312
+//   5.0e5, 20,000 words, K = 20,000         1848  1292   995   868    797
+int run_length(const mlda_ctx* c, int32_t n_small) {
+    if (c->run_tiles <= 1) return c->run_tiles;
+    if (c->forced_run > 0) return c->forced_run;
+    const int32_t want = 3 * c->n_cus;
+    return std::max(1, std::min(c->run_tiles, (n_small + want - 1) / want));
+}
+
 int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     if (c->n_tiles == 0) return MLDA_OK;
     mlda::SampleArgs a;
@@ -1065,7 +1082,7 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
     a.iter = (uint32_t)(c->iter + 1);
     a.n_tiles = c->n_shared;
     a.n_single = c->run_tiles > 1 ? c->n_single : c->n_shared;
-    a.run_tiles = c->run_tiles;
+    a.run_tiles = run_length(c, a.n_tiles - a.n_single);
     a.far_pstar = c->far_pstar;
     // With few tiles the launch takes the time of one tile, and a small tile is done sooner by four waves side
     // by side than by one with a full batch; with more it is the work in all that counts, and later so where
@@ -1323,6 +1340,8 @@ int device_limits(mlda_ctx* c) {
     const char* wide = std::getenv("MLDA_WIDE_SLOT_OFFSETS");
     c->wide_slot_offsets = wide && wide[0] != '\0' && wide[0] != '0';
     if (const char* from = std::getenv("MLDA_REORDER_BY_TILES")) c->reorder_by_tiles = std::atoll(from);
+    // (likewise: small corpora have no runs)
+    if (const char* run = std::getenv("MLDA_RUN_TILES")) c->forced_run = std::max(0, std::min(kRunTiles, std::atoi(run)));
     // (likewise: most shapes are otherwise only reached by corpora of millions of tokens)
     const char* shape = std::getenv("MLDA_TILE_SHAPE");
     int tokens = 0, alone = 0;
@@ -2175,7 +2194,7 @@ int mlda_get_sampler_bytes(mlda_ctx* c, double* bytes, int32_t capacity_iters, i
         // per tile: the word's row of phi, 2 K bytes, or 4 K for a word with 2^16 tokens or more;
         // a tile that follows another in a run reads, instead of a row of phi, the topics of
         // the previous tile's tokens and, for its own tokens, topic and cell of phi: 6 bytes
-        // per token, counted as if both tiles had this tile's tokens
+        // per token, counted as if both tiles had this tile's tokens (and as runs of kRunTiles)
         const int32_t n_run_tiles = c->run_tiles > 1 ? c->n_tiles - c->n_single : 0;
         const int32_t n_runs = n_run_tiles > 0 ? (n_run_tiles + c->run_tiles - 1) / c->run_tiles : 0;
         const double staged_rows = (double)(c->counted_tiles - n_run_tiles + n_runs);

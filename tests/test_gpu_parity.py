@@ -733,6 +733,14 @@ def test_assignments_change_order_tile_by_tile(mlda, K, monkeypatch):
         model.close()
 
 
+@pytest.mark.parametrize("run", ["16", "3", "1"])
+@pytest.mark.parametrize("case", [c for c in EDGE_CASES if 2048 < c[3] <= 20000], ids=lambda c: c[0])
+def test_large_k_in_runs(mlda, case, run, monkeypatch):
+    """Small tiles one after the other in a workgroup, of which corpora of few words have none by themselves."""
+    monkeypatch.setenv("MLDA_RUN_TILES", run)
+    test_edge_shapes(mlda, case)
+
+
 # (topics, lengths of the first documents, further documents of 3 tokens each)
 RANKED_CASES = [("two_per_wave", 1000, [0, 1, 31, 32, 33, 127, 128, 129, 383, 384, 385, 1500, 4000, 0, 700], 60),
                 ("two_per_wave_33", 33, [0, 1, 127, 128, 129, 383, 384, 385, 3000], 60),
