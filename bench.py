@@ -28,13 +28,13 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E peak
 # this chip, WRITE_SIZE by 1.000 (same summaries).
 FETCH_SCALE, WRITE_SCALE = 2.000, 1.000
 MEASURED_TRAFFIC_KIB = {
-    ("C4", "init"): (7.00836e7, 1.66741e6, "profiles/sample_kernel_C4.md"),
-    ("C3", "init"): (1.23991e7, 2.24734e5, "profiles/sample_kernel_C3_C5.md"),
-    ("C5", "init"): (2.89505e7, 1.38495e6, "profiles/sample_kernel_C3_C5.md"),
+    ("C4", "init"): (7.05941e7, 1.71133e6, "profiles/sample_kernel_C4.md"),
+    ("C3", "init"): (1.22510e7, 2.28277e5, "profiles/sample_kernel_C3_C5.md"),
+    ("C5", "init"): (2.94472e7, 1.47728e6, "profiles/sample_kernel_C3_C5.md"),
 }
 # VALU wave-instructions per sampling launch (SQ_INSTS_VALU, same summaries): the sampler's other
 # limit is instruction issue, 1024 SIMDs x 2.4 GHz / 4 cycles per wave-instruction
-MEASURED_VALU_INSTS = {("C4", "init"): 1.50174e10, ("C3", "init"): 3.90507e9, ("C5", "init"): 6.47468e9}
+MEASURED_VALU_INSTS = {("C4", "init"): 1.41003e10, ("C3", "init"): 3.07680e9, ("C5", "init"): 4.99308e9}
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0
 
 
