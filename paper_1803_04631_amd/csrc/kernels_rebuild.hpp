@@ -250,7 +250,8 @@ __device__ __forceinline__ void store_loglik(const double* partial, int n, const
     if (threadIdx.x == 0) *out = sum;
 }
 
-__device__ __forceinline__ void block_partial_store(double v, double* partial) {
+// (n_before: so many of the partials are there already, and are added to)
+__device__ __forceinline__ void block_partial_store(double v, double* partial, int n_before = 0) {
     __shared__ double wsum[16];
     const int lane = lane_id(), wave = (int)threadIdx.x / kWave;
     const double s = wave_sum(v);
@@ -259,7 +260,7 @@ __device__ __forceinline__ void block_partial_store(double v, double* partial) {
     if (threadIdx.x == 0) {
         double tot = 0.0;
         for (int w = 0; w < (int)blockDim.x / kWave; ++w) tot += wsum[w];
-        partial[blockIdx.x] = tot;
+        partial[blockIdx.x] = (int)blockIdx.x < n_before ? partial[blockIdx.x] + tot : tot;
     }
 }
 
@@ -629,7 +630,7 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
     block_partial_store(ll, ll_partial);
 }
 
-// The same for documents of fewer than 2^16 tokens, without a dense row.  One bit per topic marks the topics
+// The same for documents of up to kRankedTokens tokens, without a dense row.  One bit per topic marks the topics
 // of the document; a prefix sum over the mark words tells every marked topic its place among them
 // (its rank); the tokens then add to a cell per rank, {topic, count}, and the cells leave as the row,
 // one per lane in whole consecutive stores.  Against compacting a dense row of K counters: LDS of K / 4 bytes and a cell per
@@ -641,7 +642,16 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
 // topics of the tokens beyond those in registers are kept in LDS, the rest is read again.
 // Tokens per lane whose topics are in registers: 128 of each document (256 with one document per wave
 // took 6 to 9 % longer on 1e8 tokens in documents of 330: more lines of z in use at once).
+// A document much longer than that is read again for every 1,024 of its topics, by one wave: beside 3e6 tokens in documents
+// of 300, one of 30,000 took 0.21 ms at K = 500, 0.73 at K = 5,000 and 2.05 at K = 40,000, one of 60,000 0.43, 1.5 and
+// 6.7.  Those beyond kRankedTokens are theta_rows_kernel's, in a launch before: 0.04, 0.05 and 0.15 ms, and 0.07, 0.08, 0.2.
+// Where the line lies, rebuild with all ranked / with that launch, us (K = 500, 5,000, 40,000):
+//   one document of 3,000 beside 3e6 tokens   42/57  51/56   67/100      300 of 3,000 beside 3e7   239/221  260/223
+//                   4,100                     51/47  71/51   92/90       300 of 4,000              270/218  301/232
+// n_before: an earlier launch left the sums of other documents in so many of the partials; they are added to.
 __host__ __device__ constexpr int rank_keep(int docs) { return docs == 1 ? 2 : 4; }
+constexpr int kRankStage = 2048;
+constexpr int kRankedTokens = 3072;
 constexpr int kPairMaxK = 1024;
 __host__ __device__ inline int theta_rank_words(int32_t K) { return ((K + 31) / 32 + 3) & ~3; }
 __host__ __device__ inline int theta_rank_cells(int32_t K, int64_t longest, int docs) {
@@ -649,7 +659,7 @@ __host__ __device__ inline int theta_rank_cells(int32_t K, int64_t longest, int 
     return (int)(((n < most ? n : most) + 3) & ~(int64_t)3);
 }
 __host__ __device__ inline int theta_rank_stage(int64_t longest, int docs) {
-    const int64_t most = docs == 1 ? 2048 : 256, n = longest - rank_keep(docs) * (kWave / docs);
+    const int64_t most = docs == 1 ? kRankStage : 256, n = longest - rank_keep(docs) * (kWave / docs);
     return n <= 0 ? 0 : (int)(((n < most ? n : most) + 3) & ~(int64_t)3);
 }
 __host__ __device__ inline size_t theta_rank_lds_bytes(int32_t K, int64_t longest, int docs) {
@@ -664,7 +674,7 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
                                                              int32_t K, double alpha, const double* lg_table,
                                                              unsigned long long* visited_partial,
                                                              double* ll_partial, int32_t* old_n_k,
-                                                             int32_t n_cells, int32_t n_stage) {
+                                                             int32_t n_cells, int32_t n_stage, int32_t n_before) {
     typedef typename Layout::Entry Entry;
     constexpr int W = kWave / kDocs, kKeep = rank_keep(kDocs);      // lanes per document
     clear_old_totals(old_n_k, K);
@@ -891,8 +901,8 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
         }
     }
     if (kDocs == 2) visited += __shfl_xor(visited, W, kWave);       // the other part's documents
-    if (lane == 0) visited_partial[blockIdx.x] = visited;
-    block_partial_store(ll, ll_partial);
+    if (lane == 0) visited_partial[blockIdx.x] = (int)blockIdx.x < n_before ? visited_partial[blockIdx.x] + visited : visited;
+    block_partial_store(ll, ll_partial, n_before);
 }
 
 // The two per-token index arrays that follow from tok_id and the document records are built

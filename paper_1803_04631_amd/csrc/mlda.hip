@@ -405,6 +405,7 @@ struct HostChunk {
     RowKind rows = RowKind::packed;     // layout of the theta rows
     bool wide_counters = false;         // some document has 2^16 tokens or more
     int64_t longest_doc = 0;            // tokens
+    int64_t n_unranked = 0, unranked_tokens = 0;        // documents beyond kRankedTokens (they come first), and their tokens
     bool short_docs = true;             // no document has more tokens than a 4-byte entry counts
     size_t slots_bytes = 0;
     int32_t n_tiles = 0, n_segs = 0, n_split = 0;
@@ -469,6 +470,8 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
         order_tokens[0] = 0;
         for (int64_t i = 0; i < D; ++i)
             order_tokens[(size_t)i + 1] = order_tokens[(size_t)i] + len_of(doc_order[(size_t)i]);
+        for (h.n_unranked = 0; h.n_unranked < D && len_of(doc_order[(size_t)h.n_unranked]) > mlda::kRankedTokens;) ++h.n_unranked;
+        h.unranked_tokens = order_tokens[(size_t)h.n_unranked];
         // theta row slots: fixed capacity, so rows never move; laid out in the
         // order the documents are worked on, so that rows in use together are neighbours.
         // The buffer starts with 64 bytes of padding entries.
@@ -719,10 +722,16 @@ struct mlda_ctx {
     int32_t *tok_id = nullptr, *doc_map = nullptr, *doc_ptr = nullptr;
     uint2* doc_pairs = nullptr;          // streamed: {slot of the token's document, its topic}, document order
     mlda::DocRec* doc_order = nullptr;   // documents by falling length, as the theta rebuild walks them
-    int32_t theta_grid = 0;
-    int theta_ranked = 0;                // documents per wave of theta_ranked_kernel, 0: theta_rows_kernel
-    bool theta_long_docs = false;
-    size_t theta_lds = 0;
+    // a launch of the theta rebuild: D documents of doc_order from `first` on
+    struct ThetaLaunch {
+        int64_t first = 0, D = 0;
+        int ranked = 0;                  // documents per wave of theta_ranked_kernel, 0: theta_rows_kernel
+        bool long_docs = false;
+        size_t lds = 0;
+        int32_t grid = 0;
+    };
+    ThetaLaunch theta[2];                // documents too long to be ranked, all others (either may have none)
+    int32_t theta_grid = 0;              // partials that they leave
     RowKind rows = RowKind::packed;
     bool wide_counters = false, short_docs = true;
     int32_t* split_words = nullptr;
@@ -800,6 +809,9 @@ const int32_t* current_n_k(const mlda_ctx* c) { return c->n_k[c->streamed ? c->m
 
 int blocks_for(int64_t n, int per) { return (int)((n + per - 1) / per); }
 
+// Tokens of the longest document that is rebuilt by ranks.
+int64_t ranked_longest(const HostChunk& h) { return std::min<int64_t>(h.longest_doc, mlda::kRankedTokens); }
+
 // Point the context at chunk h in workspace part `base` (no data moves).
 void point_at(mlda_ctx* c, const HostChunk& h, unsigned char* base) {
     c->at = &h;
@@ -829,24 +841,34 @@ void point_at(mlda_ctx* c, const HostChunk& h, unsigned char* base) {
     c->z[1] = (uint16_t*)(base + h.L.z1);
     c->slots = base + h.L.slots;
     c->cur = 0;
-    c->theta_long_docs = long_docs_for(h.D, h.T, h.longest_doc, c->n_cus);
-    // Ranks, but for 32-bit counters and documents so long that reading their topics twice costs more than
-    // the dense row does; two documents per wave where a half-wave suits them: few topics, short documents.
+    // Ranks, but for 32-bit counters and documents beyond kRankedTokens: few of those are rebuilt with a dense row in a
+    // launch of their own, and where documents are long on the whole all of them are.  Two documents per wave where
+    // a half-wave suits them: few topics, short documents.
     // Ranks / dense row, rebuild of 3e6 tokens from random topics (trained: alike), us:
     //   tokens       10         40        100       400      1,000     3,000
     //   K = 100   86 / 145   35 / 94    28 / 73   25 / 65   37 / 52   70 / 51
     //     1,000   86 / 128   35 / 82    29 / 72   28 / 66   42 / 61   79 / 57
     //     5,000  150 / 284   47 / 123   30 / 84   28 / 60   54 / 52  155 / 59
     //    30,000  295 / 2753  89 / 1142  49 / 568  38 / 228  65 / 154 203 / 125
-    c->theta_ranked = h.wide_counters || c->theta_long_docs || h.T > 1500 * h.D ? 0
-                      : c->K <= mlda::kPairMaxK && h.T <= 160 * h.D ? 2 : 1;
-    const size_t theta_lds = c->theta_ranked ? mlda::theta_rank_lds_bytes(c->K, h.longest_doc, c->theta_ranked)
-                                             : mlda::theta_lds_bytes(c->K, h.wide_counters);
-    c->theta_lds = theta_lds;
-    // 16 one-wave workgroups per CU: enough to hide the gathers' latency; more of them
-    // touch more lines of z at once than an XCD's L2 holds, and neighbours stop sharing
-    const int per_cu = std::max(1, std::min(16, (int)(144 * 1024 / theta_lds)));
-    c->theta_grid = (int32_t)std::min<int64_t>({h.D, (int64_t)c->n_cus * per_cu, (int64_t)kMaxThetaGrid});
+    const bool all_long = long_docs_for(h.D, h.T, h.longest_doc, c->n_cus);
+    const bool dense = h.wide_counters || all_long || h.T > 1500 * h.D;
+    const int64_t n_dense = dense ? h.D : h.n_unranked;
+    c->theta[0] = c->theta[1] = mlda_ctx::ThetaLaunch();
+    c->theta[0].D = n_dense;
+    c->theta[0].long_docs = dense ? all_long : long_docs_for(n_dense, h.unranked_tokens, h.longest_doc, c->n_cus);
+    c->theta[0].lds = mlda::theta_lds_bytes(c->K, h.wide_counters);
+    c->theta[1].first = n_dense;
+    c->theta[1].D = h.D - n_dense;
+    c->theta[1].ranked = c->K <= mlda::kPairMaxK && h.T <= 160 * h.D ? 2 : 1;
+    c->theta[1].lds = mlda::theta_rank_lds_bytes(c->K, ranked_longest(h), c->theta[1].ranked);
+    c->theta_grid = 0;
+    for (mlda_ctx::ThetaLaunch& l : c->theta) {
+        // 16 one-wave workgroups per CU: enough to hide the gathers' latency; more of them
+        // touch more lines of z at once than an XCD's L2 holds, and neighbours stop sharing
+        const int per_cu = std::max(1, std::min(16, (int)(144 * 1024 / l.lds)));
+        l.grid = (int32_t)std::min<int64_t>({l.D, (int64_t)c->n_cus * per_cu, (int64_t)kMaxThetaGrid});
+        c->theta_grid = std::max(c->theta_grid, l.grid);
+    }
 }
 
 // After the static part of a chunk has arrived: the index arrays that follow from it
@@ -1018,24 +1040,30 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
     using namespace mlda;
     const int32_t* doc_map = c->streamed ? nullptr : c->doc_map;
     if (c->D > 0) {
-        const void* kernel = c->theta_ranked ? theta_ranked_kernel_for(c->rows, c->theta_ranked)
-                                             : theta_kernel_for(c->rows, c->wide_counters, c->theta_long_docs);
-        int32_t n_cells = theta_rank_cells(c->K, c->at->longest_doc, c->theta_ranked);
-        int32_t n_stage = theta_rank_stage(c->at->longest_doc, std::max(c->theta_ranked, 1));
-        const DocRec* docs = c->doc_order;
         uint2* row_rec = c->row_rec;
         unsigned char* slots = c->slots;
-        int64_t D = c->D, T = c->T;
+        int64_t T = c->T;
         int32_t K = c->K;
         double alpha = c->alpha;
         const double* lg_table = c->lg_table;
         double* ll_partial = c->ll_partial + 2 * kLoglikBlocks;
         unsigned long long* visited = c->visited;
         int32_t* old_n_k = !c->streamed && c->n_k[0] != c->n_k[1] ? c->n_k[c->n_k_cur ^ 1] : nullptr;
-        void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &visited, &ll_partial, &old_n_k,
-                        &n_cells, &n_stage};        // (the last two: theta_ranked_kernel's)
-        HIP_TRY(hipLaunchKernel(kernel, dim3((unsigned)c->theta_grid), dim3((unsigned)(c->theta_long_docs ? kWave * kLongDocWaves : kWave)),
-                                args, c->theta_lds, c->stream));
+        int32_t n_before = 0;
+        for (const mlda_ctx::ThetaLaunch& l : c->theta) {
+            if (l.D == 0) continue;
+            const DocRec* docs = c->doc_order + l.first;
+            int64_t D = l.D;
+            int32_t n_cells = theta_rank_cells(c->K, ranked_longest(*c->at), l.ranked);
+            int32_t n_stage = theta_rank_stage(ranked_longest(*c->at), std::max(l.ranked, 1));
+            void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &visited, &ll_partial, &old_n_k,
+                            &n_cells, &n_stage, &n_before};         // (the last three: theta_ranked_kernel's)
+            HIP_TRY(hipLaunchKernel(l.ranked ? theta_ranked_kernel_for(c->rows, l.ranked)
+                                             : theta_kernel_for(c->rows, c->wide_counters, l.long_docs),
+                                    dim3((unsigned)l.grid), dim3((unsigned)(l.long_docs ? kWave * kLongDocWaves : kWave)),
+                                    args, l.lds, c->stream));
+            n_before = l.grid;
+        }
         c->spare_n_k_cleared = old_n_k != nullptr;
         // (one chunk: the next rebuild_phi adds the counts up; sampler bytes are asked of earlier ones only)
         if (c->streamed)

@@ -776,6 +776,63 @@ def test_rows_by_ranks(mlda, case):
         model.close()
 
 
+# (topics, lengths of the long documents, how many others and their tokens, empty documents): documents of more than 3,072
+# tokens are rebuilt in a launch of their own (of one or sixteen waves each), which leaves fewer or more partial sums
+# than the launch of the others that adds to them
+UNEVEN_CASES = [("two_per_wave", 500, [3073, 3072, 3071, 9000, 30000], 300, 60, 3),
+                ("one_per_wave", 5000, [3073, 3072, 2177, 2176, 5000, 30000], 100, 200, 5),
+                ("one_per_wave_many_rounds", 40000, [30000, 60000, 3073], 300, 300, 0),
+                ("counts_of_many_entries", 3, [3073, 60000], 200, 30, 1),
+                ("few_others", 700, [3100] * 40, 3, 100, 80)]
+
+
+@pytest.mark.parametrize("case", UNEVEN_CASES, ids=[c[0] for c in UNEVEN_CASES])
+def test_rows_of_uneven_documents(mlda, case):
+    name, K, long_docs, others, length, empty = case
+    rng = np.random.default_rng(K)
+    lens = rng.permutation(np.array(long_docs + [length] * others + [0] * empty, dtype=np.int64))
+
+    class C:
+        pass
+    c = C(); V = 50
+    c.doc_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    c.T = int(lens.sum())
+    c.word_ids = rng.integers(V, size=c.T).astype(np.int32)
+    z = rng.integers(K, size=c.T).astype(np.uint16)
+    for chunks in (1, 2):
+        say(name, "chunks", chunks)
+        model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, 50.0 / K, 0.01, SEED, chunks=chunks)
+        model.set_assignments(z)
+        check_counts(model, c, z, V, K)
+        check_step(model, c, z, V, K, 50.0 / K, 0.01, SEED, 1)
+        if chunks == 1 and K < 1024:        # the sums of row entries, in the bytes
+            row_ptr, _, counts = oracle.doc_topic_csr(c.doc_ptr, z, K)
+            entries = np.array([(-(-counts[a:b] // 15)).sum() for a, b in zip(row_ptr[:-1], row_ptr[1:])])
+            tiles = np.ceil(np.bincount(c.word_ids, minlength=V) / 1024).sum()
+            assert model.sampler_bytes()[-1] == 16.0 * c.T + 2.0 * float((lens * entries).sum()) + K * 2.0 * tiles
+        model.close()
+
+
+@pytest.mark.parametrize("K", [5000, 40000])
+def test_one_long_document_costs_what_its_tokens_do(mlda, K):
+    """The theta rebuild of 3e6 tokens in documents of 300 takes longer with one document of 60,000 among them, but by
+    no more than one wave that reads each of its tokens once: 4.7 ns a token, and as much again to spare."""
+    V, longest = 500, 60000
+
+    def rebuild_ms(lens):
+        doc_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        words = np.random.default_rng(1).integers(V, size=int(doc_ptr[-1])).astype(np.int32)
+        model = mlda.Mlda(doc_ptr, words, V, K, 50.0 / K, 0.01, SEED)
+        model.init_random(); model.step(3)
+        ms = model.timing()[:, 2].min()
+        model.close()
+        return ms
+    even = rebuild_ms(np.full(10000, 300))
+    uneven = rebuild_ms(np.concatenate([np.full(5000, 300), [longest], np.full(4800, 300)]))
+    say(K, "theta rebuild", even, "ms even,", uneven, "ms uneven")
+    assert uneven <= even + 2 * 4.7e-6 * longest
+
+
 @pytest.mark.parametrize("how", ["own_stream", "stream_per_thread", "streamed"])
 def test_large_transfers(mlda, how):
     """Transfers of 8 MB and more go through eight pinned pieces of 2 MB, each with a thread of its own:
