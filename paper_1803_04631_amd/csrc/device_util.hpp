@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace mlda {
 
@@ -80,6 +81,20 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
+// The last lane gets the least of all lanes' values.  Every lane must be active.
+__device__ __forceinline__ uint32_t wave_min_at_last(uint32_t v) {
+    auto with = [&](auto ctrl, auto rows) {      // (lanes without a source, and the other rows, see the largest number)
+        v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false));
+    };
+    with(std::integral_constant<int, 0x111>(), std::integral_constant<int, 0xf>());
+    with(std::integral_constant<int, 0x112>(), std::integral_constant<int, 0xf>());
+    with(std::integral_constant<int, 0x114>(), std::integral_constant<int, 0xf>());
+    with(std::integral_constant<int, 0x118>(), std::integral_constant<int, 0xf>());
+    with(std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xa>());
+    with(std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xc>());
     return v;
 }
 

@@ -44,6 +44,7 @@
 #pragma once
 #include <type_traits>
 #include "device_util.hpp"
+#include "row_sums.hpp"
 
 namespace mlda {
 
@@ -94,6 +95,7 @@ struct SampleArgs {
     // Tokens that share the walks over their rows: how many passes, and (fp64 weights) units of them, a wave keeps
     // the sums of at a time.  (fp32 weights: a sum per lane and pass)
     int32_t kept_passes, kept_sums;
+    uint32_t sum_slack;         // shared walks, fp64 weights: see kNearlyAll (bits of a double's exponent, in its upper dword)
 };
 
 constexpr int kRowHeader = 16;  // bytes before a theta row's entries
@@ -132,9 +134,11 @@ __host__ __device__ constexpr int sample_wave_bytes(int kept_passes, int kept_su
     const int shared = kept_sums * 8 + kept_passes * kWave * 2 + kWave * 5, records = kWave * (int)sizeof(TokenRec);
     return shared > records ? shared : records;
 }
+// Slots for the waves' least weights, filled up to 16 bytes.
+__host__ __device__ constexpr int least_slots(int waves) { return (waves + 3) & ~3; }
 // LDS bytes of sample_kernel<kWaves> for a given Kpad and bytes of a staged weight.
 __host__ __device__ constexpr size_t sample_lds_bytes(int Kpad, int waves, int weight_bytes, int kept_passes = 0, int kept_sums = 0) {
-    return (size_t)Kpad * weight_bytes + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 +
+    return (size_t)Kpad * weight_bytes + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 + (size_t)least_slots(waves) * 4 +
            (size_t)waves * sample_wave_bytes(kept_passes, kept_sums);
 }
 // The same when p* stays in device memory: the prefix sums and the waves' records only.
@@ -155,11 +159,16 @@ constexpr int kRunTileTokens = 1024;    // a tile of a run holds a whole word of
 constexpr double kWeightScale = 0x1p1000;
 constexpr double kCountUnit = 0x1p-1042;
 constexpr double kSumScale = kWeightScale * kCountUnit;
+constexpr int kSumScaleLog2 = 1000 - 1042;
+// Shared walks, fp64 weights: sums of up to 2^sum_slack times what is exact round in a last bit or three where sub-lanes are
+// added up, as they do in a walk of the token's own, and are let where the row's sum with all of the own topic in it is at
+// most so many times the token's total.  Where the row's units end, error against __float128 in 2^-53 of the total, of such
+// tokens in books late in training (7 % of the tokens there, at beta = 0.01): root mean square 0.3949, at most 2.55, both as in a
+// walk of their own.  At beta = 1e-3 0.4846 against 0.4844; at 1e-5, where none are let, up to 2 % more or less.
+constexpr double kNearlyAll = 1.02;
 // Q' times kSumScale is a normal number from here on.  A smaller one (alpha below 1e-290 or so) decides
 // draws of tokens that are alone in their document only; their place in p2 is worked out without the scale.
 constexpr double kSmallestScaled = 0x1p-900;
-// Shared walks: how many times a token's total a row's sum may be in which its own topic still counts in full.
-constexpr double kMostTakenOff = 2.0;
 
 // A staged weight of either form without its scale.
 __device__ __forceinline__ double plain_weight(float w) { return (double)w; }
@@ -764,8 +773,9 @@ __device__ __forceinline__ void row_pass_double(TokenRec* rec, int sl, const uin
 }
 
 // The walk over a row for all the tokens that share it: what the row's sub-lanes have summed up at the end
-// of each of their units, every entry with p*, goes to LDS (`sums`, the row's units one after the other),
-// with the topic of each sub-lane's first entry.  Three instructions per entry and no draw.
+// of each of their units, every entry with p*, goes to LDS (`sums`, the row's units one after the other; the last one of
+// a sub-lane with the sub-lanes before it), with the topic of each sub-lane's first entry.  Three instructions per
+// entry and no draw.
 template <class Layout, int kLanes, int kUnits>
 __device__ __forceinline__ void row_pass_shared(double* sums, uint16_t* first_topic, int rel, int sl, const uint4* raw) {
     double at_end[kUnits];
@@ -776,10 +786,9 @@ __device__ __forceinline__ void row_pass_shared(double* sums, uint16_t* first_to
         at_end[c] = acc;
     }
     const double incl = group_inclusive_sum<kLanes>(acc);
-    const double excl = group_previous<kLanes>(incl, sl);
     const int lane_at = rel * kLanes + sl;
 #pragma unroll
-    for (int c = 0; c + 1 < kUnits; ++c) sums[lane_at * kUnits + c] = excl + at_end[c];
+    for (int c = 0; c + 1 < kUnits; ++c) sums[lane_at * kUnits + c] = at_end[c];
     sums[lane_at * kUnits + kUnits - 1] = incl;
     first_topic[lane_at] = (uint16_t)Layout::entry_topic((typename Layout::Entry)raw[0].x);
 }
@@ -998,8 +1007,8 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     double* cp = reinterpret_cast<double*>(lds + pstar_lds);
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);      // wave-uniform, in an SGPR
-    unsigned char* wave_base = lds + pstar_lds + (size_t)((ng + 1) & ~1) * 8;
     constexpr bool kShares = Layout::kShares;
+    unsigned char* wave_base = lds + pstar_lds + (size_t)((ng + 1) & ~1) * 8 + (kShares ? least_slots(kWaves) * 4 : 0);
     const int wave_bytes = kShares ? sample_wave_bytes(a.kept_passes, a.kept_sums) : kWave * (int)sizeof(TokenRec);
     TokenRec* my_rec = reinterpret_cast<TokenRec*>(wave_base + wave * wave_bytes);
     typedef typename std::conditional<kFar, FarWeights, LdsWeights>::type Weights;
@@ -1028,6 +1037,15 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     if (in_run()) {
         for (int w = tid; w < (ng + 31) / 32; w += kWaves * kWave) changed[w] = 0u;
     }
+    // Shared walks: no weight of the tile's word is less than the least of the fp32 numbers with these bits, one per wave (see
+    // row_sums.hpp; bits of numbers that are not negative are in the numbers' order).
+    [[maybe_unused]] uint32_t* least = reinterpret_cast<uint32_t*>(wave_base) - least_slots(kWaves);
+    auto note_least = [&](uint32_t v, bool beside) {        // (beside what the wave has noted before)
+        if constexpr (kShares) {
+            v = wave_min_at_last(v);
+            if (lane == kWave - 1) least[wave] = beside ? min(v, least[wave]) : v;
+        }
+    };
     for (int ti = kFar ? (int)blockIdx.x : first_tile();;) {
     Tile tl = a.tiles[ti];                 // the same for every lane: keep it in SGPRs
     tl.word = __builtin_amdgcn_readfirstlane(tl.word);
@@ -1050,19 +1068,25 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         // tile's tokens: only those cells differ from beta / (n_k + beta V).  Every changed cell
         // gets the value a fresh staging would give it, and the sums of the groups that hold
         // one are added up again in the same order, so the result is the fresh staging's, bit
-        // for bit.
+        // for bit.  (The least weight so far stays a bound: a cell that changes counts with every value it is given.)
+        uint32_t my_least = 0xffffffffu;
         for (int idx = tid; idx < prev_count; idx += kWaves * kWave) {
             const int k = (int)a.z_cur[prev_begin + idx];
-            pstar[k] = (float)((0.0 + a.beta) / ((double)a.n_k[k] + a.beta_V));
+            const float w = (float)((0.0 + a.beta) / ((double)a.n_k[k] + a.beta_V));
+            pstar[k] = w;
+            my_least = min(my_least, __float_as_uint(w));
             atomicOr(&changed[(k / kGroup) >> 5], 1u << ((k / kGroup) & 31));
         }
         __syncthreads();
         const uint16_t* phi_v = reinterpret_cast<const uint16_t*>(phi_cells) + phi_cell0;   // (never a wide row)
         for (int idx = tid; idx < tl.count; idx += kWaves * kWave) {
             const int k = (int)a.z_cur[tl.begin + idx];
-            pstar[k] = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
+            const float w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
+            pstar[k] = w;
+            my_least = min(my_least, __float_as_uint(w));
             atomicOr(&changed[(k / kGroup) >> 5], 1u << ((k / kGroup) & 31));
         }
+        note_least(my_least, true);
         __syncthreads();
         for (int g = tid; g < ng; g += kWaves * kWave)
             if ((changed[g >> 5] >> (g & 31)) & 1u) {
@@ -1086,21 +1110,29 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         __syncthreads();
     } else {
     // ---- stage p*(k) = (phi_kv + beta)/(n_k + beta V) as fp32 (Eq. 8)
+    uint32_t my_least = 0xffffffffu;
     if (wide) {
         const int32_t* phi_v = reinterpret_cast<const int32_t*>(phi_cells) + phi_cell0;
         for (int k = tid; k < Kpad; k += kWaves * kWave) {
             float w = 0.f;
-            if (k < K) w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
+            if (k < K) {
+                w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
+                my_least = min(my_least, __float_as_uint(w));
+            }
             pstar[k] = (Weight)(kStagedScale * (double)w);
         }
     } else {
         const uint16_t* phi_v = reinterpret_cast<const uint16_t*>(phi_cells) + phi_cell0;
         for (int k = tid; k < Kpad; k += kWaves * kWave) {
             float w = 0.f;
-            if (k < K) w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
+            if (k < K) {
+                w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
+                my_least = min(my_least, __float_as_uint(w));
+            }
             pstar[k] = (Weight)(kStagedScale * (double)w);
         }
     }
+    note_least(my_least, false);
     __syncthreads();
     for (int g = tid; g < ng; g += kWaves * kWave) {
         double s = 0.0;
@@ -1134,6 +1166,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     const int batch = min(kWave, max(kWaves <= 4 ? a.min_batch : kMinBatch,
                                      ((tl.count + kWaves - 1) / kWaves + 3) & ~3));
     const int n_batches = (tl.count + batch - 1) / batch;
+    [[maybe_unused]] int kept_own = 0;     // tokens of the wave's last shared batch that walked by themselves: with many, the rest do not share in vain
     for (int b = wave; b < n_batches; b += kWaves) {
         // ---- one token per lane: token, uniform, own-count correction
         const int idx = b * batch + lane;
@@ -1239,13 +1272,31 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         // p*: where rows are shared, a row is walked once for all its tokens of the batch.  The sums at the
         // ends of its units go to LDS, and each token, one per lane, then finds its topic among the row's
         // sub-lanes, counts it, corrects the sums from there on and looks its draw up among them.
-        // A correction that takes off more than it leaves would cost bits: such tokens, and those
-        // with their topic spread over several units, take the walk of their own below.
+        // Sums that hold no rounding are what a walk of the token's own would have found, to the last bit, and so is the
+        // draw.  Tokens whose row's sum is too large for that (weights of the row far apart; at beta = 0.01 next to none), and those
+        // with their topic spread over several units, take that walk below.
         bool in_rest = valid, shared = false;
         // (lane 0 is given slot 0, which no document has)
         const bool head = valid && mine.off != (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine.off, 0x138, 0xf, 0xf, true);
         const uint64_t heads = kShares ? __ballot(head) : 0;
         const int n_rows = __popcll(heads);
+        // Sums whose upper dword is less are exact (with w_o in the place of p*(o), too)
+        auto exact_below = [&]() {
+            uint32_t smallest = __float_as_uint(mine.w_o);
+            // (the address is made here, every time: hoisted, it would hold a register for good)
+            int at = (int)(reinterpret_cast<unsigned char*>(least) - lds);
+            asm volatile("" : "+v"(at));
+            if constexpr (kWaves == 1) {
+                smallest = min(smallest, *reinterpret_cast<const uint32_t*>(lds + at));
+            } else {
+#pragma unroll
+                for (int w = 0; w < kWaves; w += 4) {
+                    const uint4 four = *reinterpret_cast<const uint4*>(lds + at + 4 * w);
+                    smallest = min(min(min(smallest, four.x), min(four.y, four.z)), four.w);
+                }
+            }
+            return exact_sums_below(smallest, kDouble ? kSumScaleLog2 : 0);
+        };
         // Sharing costs a search per token among its row's sums and a wait for units of the row, once for every
         // time that the kept sums fill up; it saves the walks that are not made, and a quarter of each that
         // is.  So: at most two rows for three tokens, and two passes saved.  Sampling
@@ -1256,7 +1307,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         //   1.2e7, documents of 4,000, K = 2,000 5.76  5.36   3.93   3.87
         auto share_walks = [&]() {
             const int n = min(batch, tl.count - b * batch);
-            if (3 * n_rows > 2 * n || (kDouble && __ballot(mine.nnz > kMostKeptUnits) != 0)) return false;
+            if (4 * kept_own > kWave || 3 * n_rows > 2 * n || (kDouble && __ballot(mine.nnz > kMostKeptUnits) != 0)) return false;
             const int rows_per_pass = __ballot(mine.nnz > 12) == 0 ? 16 : __ballot(mine.nnz > 24) == 0 ? 8 : __ballot(mine.nnz > 48) == 0 ? 4 : 1;
             return 4 * n - 3 * n_rows >= 8 * rows_per_pass;
         };
@@ -1273,14 +1324,16 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                 row_slot[row] = mine.off;
                 row_units[row] = (unsigned char)mine.nnz;
             }
-            if (lane >= n_rows) {
-                row_slot[lane] = 0;
-                row_units[lane] = 0;
+            int at = lane;              // (addresses made here, every time: hoisted, they would hold registers for good)
+            asm volatile("" : "+v"(at));
+            if (at >= n_rows) {
+                row_slot[at] = 0;
+                row_units[at] = 0;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            learn_shapes((int)row_units[lane]);
+            learn_shapes((int)row_units[at]);
             auto request = [&](int t0, int shape, uint4* raw, bool live) {
                 place_lanes(shape);
                 const int r = min(t0 + geo_rel, kWave - 1);
@@ -1300,7 +1353,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             request(0, shape_next, raw_next, true);
             do {                // as many passes as there is room for, then the tokens of their rows
                 const int row0 = t_next;
-                int n_passes = 0, n_sums = 0, most_lanes = 4, most_units = 1;
+                int n_passes = 0, n_sums = 0, most_lanes = 4;
                 do {
                     const int shape = shape_next, rel = geo_rel, sl = geo_sl, t0 = t_next;
                     uint4 raw[kKeptUnits];
@@ -1309,7 +1362,6 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                     const int lanes = 1 << lanes_log2(shape), nu = units_of(shape);
                     t_next += kWave / lanes;
                     most_lanes = max(most_lanes, lanes);
-                    most_units = max(most_units, lanes * nu);
                     const int t_req = min(t_next, kWave - 1);
                     shape_next = shape_at(t_req);
                     request(t_req, shape_next, raw_next, t_next < n_rows);
@@ -1360,7 +1412,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                         Layout::count_own(held[c], o, n_o);
                         n_to[c] = n_o;
                     }
-                    const int c_o = n_to[0] > 0 ? 0 : n_to[1] > 0 ? 1 : 2, q_o = q0 + c_o;
+                    const int c_o = n_to[0] > 0 ? 0 : n_to[1] > 0 ? 1 : 2;
                     if ((n_to[0] > 0 ? n_to[0] : n_to[1] > 0 ? n_to[1] : n_to[2]) != n_o) in_rest = true;
                     if (holder > 0 && (int)first_topic[lane0 + holder] == o &&
                         key_before_unit<Layout>(a.slots + ((size_t)mine.off + 1u + (size_t)q0) * 16u) == Layout::key_of_topic(o))
@@ -1368,24 +1420,43 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                     const double w_o = kWeightScale * (double)mine.w_o;
                     const double shift = fma(__hiloint2double((int)n_o - 1, 0), w_o,
                                              -(__hiloint2double((int)n_o, 0) * (double)pstar[o]));
-                    const double S_all = row_sums[n_units - 1];
+                    const double S_all = row_sums[lanes * nu - 1];
                     const double S = S_all + shift, total = fma(mine.Qp, kSumScale, S);
-                    if (!(S_all <= kMostTakenOff * total) || !(mine.Qp >= kSmallestScaled)) in_rest = true;
+                    const uint32_t below = exact_below(), sum_hi = (uint32_t)__double2hiint(S_all);
+                    const bool exact = sum_hi < below;
+                    if (!exact && !(sum_hi < below + a.sum_slack && S_all <= kNearlyAll * total)) in_rest = true;
+                    if (!(mine.Qp >= kSmallestScaled)) in_rest = true;
                     const double x = mine.u * total;
-                    int unit = 0;           // units known to lie before the draw
+                    int sub = 0;            // sub-lanes known to lie before the draw
                     double before = 0.0;
-                    for (int step = 1 << (31 - __builtin_clz(most_units)); step > 0; step >>= 1) {
-                        const int upto = unit + step;
-                        if (upto <= n_units) {
-                            const double e = row_sums[upto - 1] + (upto > q_o ? shift : 0.0);
-                            if (!(e > x)) { unit = upto; before = e; }
+                    for (int step = most_lanes; step > 0; step >>= 1) {
+                        const int upto = sub + step;
+                        if (upto <= lanes) {
+                            const double e = row_sums[upto * nu - 1] + (upto > holder ? shift : 0.0);
+                            if (!(e > x)) { sub = upto; before = e; }
                         }
                     }
+                    sub = min(sub, lanes - 1);      // (the last sum is S: above x, if the draw is in the row)
+                    const double y = x - before;
+                    int c_x = 0;
+                    double base = 0.0;
+                    const int c_shift = sub == holder ? c_o : kKeptUnits;       // its units from here on have the correction in their sums
+                    const double* unit_sums = row_sums + sub * nu;
+#pragma unroll
+                    for (int c = 0; c + 1 < kKeptUnits; ++c) {
+                        if (c_x == c && c + 1 < nu) {
+                            const double e = unit_sums[c] + (c >= c_shift ? shift : 0.0);
+                            if (!(e > y)) { c_x = c + 1; base = e; }
+                        }
+                    }
+                    // (sums that round may leave the draw a last unit without weight)
+                    if (!exact && c_x + 1 == nu && !(row_sums[sub * nu + nu - 1] + (sub >= holder ? shift : 0.0) - before > base))
+                        in_rest = true;
                     if (!in_rest) {
                         const bool sparse = x < S;
                         mine.nnz = sparse ? kDrawInUnit : kDrawDense;
-                        mine.off += 1u + (uint32_t)min(unit, n_units - 1);      // (the last unit's sum is S: above x)
-                        mine.u = x - (sparse ? before : S);
+                        mine.off += 1u + (uint32_t)min(sub * nu + c_x, n_units - 1);
+                        mine.u = sparse ? y - base : x - S;
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1411,14 +1482,16 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                 row_slot[row] = mine.off;
                 row_units[row] = (uint16_t)mine.nnz;
             }
-            if (lane >= n_rows) {
-                row_slot[lane] = 0;
-                row_units[lane] = 0;
+            int at = lane;              // (addresses made here, every time: hoisted, they would hold registers for good)
+            asm volatile("" : "+v"(at));
+            if (at >= n_rows) {
+                row_slot[at] = 0;
+                row_units[at] = 0;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            learn_shapes((int)row_units[lane]);
+            learn_shapes((int)row_units[at]);
             int t_next = 0, scan_units = 0;
             do {                // as many passes as there is room for, then the tokens of their rows
                 const int row0 = t_next;
@@ -1504,7 +1577,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                     const double shift = fma((double)(n_o - 1), (double)mine.w_o, -((double)n_o * (double)pstar[o]));
                     const double S_all = sums[lane0 + n_lanes - 1];
                     const double S = S_all + shift, total = mine.Qp + S;
-                    if (!(S_all <= kMostTakenOff * total)) in_rest = true;
+                    if (!((uint32_t)__double2hiint(S_all) < exact_below())) in_rest = true;
                     const double x = mine.u * total;
                     int sub = 0;                // sub-lanes known to lie before the draw
                     double before = 0.0;
@@ -1536,7 +1609,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         int n_here = min(batch, tl.count - b * batch), my_place = lane;
         if (kShares && shared) {
             const uint64_t rest = __ballot(in_rest);
-            n_here = __popcll(rest);
+            kept_own = n_here = __popcll(rest);
             if (n_here == 0) continue;
             my_place = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(rest >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)rest, 0u));
             if (!in_rest) {             // (behind the records in use)

@@ -337,6 +337,28 @@ def test_walks_shared_by_tokens(mlda, case, shape, monkeypatch):
     model.close()
 
 
+@pytest.mark.parametrize("beta", [1e-3, 1e-5, 1e-9])
+@pytest.mark.parametrize("case", [(2000, 4000, 8, 4), (300, 500, 40, 5), (24, 200, 150, 4), (299, 30000, 4, 40),
+                                  (2500, 1100, 30, 3), (40000, 300, 30, 3)], ids=lambda c: "k%d_n%d" % c[:2])
+def test_walks_shared_where_sums_round(mlda, case, beta):
+    """Some topics hold most tokens of some words and none of others: of the rows' sums some are exact, some too long by a
+    bit or two, and some by many (those tokens' walks are their own)."""
+    K, length, D, V = case
+    rng = np.random.default_rng(K)
+
+    class C:  # minimal corpus record
+        pass
+    c = C(); c.T = D * length; c.doc_ptr = np.arange(D + 1, dtype=np.int64) * length
+    c.word_ids = rng.integers(V, size=c.T).astype(np.int32)
+    group = (c.word_ids.astype(np.int64) * K // V + rng.integers(max(1, K // V), size=c.T)) % K       # topics of the word's own
+    z = np.where(rng.random(c.T) < 0.9, group, rng.integers(K, size=c.T)).astype(np.uint16)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, 50.0 / K, beta, SEED)
+    model.set_assignments(z)
+    for it in (1, 2):
+        z = check_step(model, c, z, V, K, 50.0 / K, beta, SEED, it)
+    model.close()
+
+
 @pytest.mark.parametrize("beta", [0.01, 1e-14, 1e-30])
 @pytest.mark.parametrize("K", [30, 500, 3000])
 def test_shared_walks_with_little_left(mlda, K, beta):
