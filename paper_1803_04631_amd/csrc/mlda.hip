@@ -27,6 +27,7 @@
 
 #include "kernels_rebuild.hpp"
 #include "kernels_sample.hpp"
+#include "switches.hpp"
 
 namespace {
 
@@ -1371,15 +1372,14 @@ int device_limits(mlda_ctx* c) {
     // (a switch for tests: the 64-bit form is otherwise only reached by theta slots beyond 4 GiB)
     const char* wide = std::getenv("MLDA_WIDE_SLOT_OFFSETS");
     c->wide_slot_offsets = wide && wide[0] != '\0' && wide[0] != '0';
-    if (const char* from = std::getenv("MLDA_REORDER_BY_TILES")) c->reorder_by_tiles = std::atoll(from);
+    (void)mlda::switch_numbers(std::getenv("MLDA_REORDER_BY_TILES"), 1, 0, INT64_MAX, &c->reorder_by_tiles);
     // (likewise: small corpora have no runs)
-    if (const char* run = std::getenv("MLDA_RUN_TILES")) c->forced_run = std::max(0, std::min(kRunTiles, std::atoi(run)));
+    int64_t numbers[2];
+    if (mlda::switch_numbers(std::getenv("MLDA_RUN_TILES"), 1, 1, kRunTiles, numbers)) c->forced_run = (int32_t)numbers[0];
     // (likewise: most shapes are otherwise only reached by corpora of millions of tokens)
-    const char* shape = std::getenv("MLDA_TILE_SHAPE");
-    int tokens = 0, alone = 0;
-    if (shape && c->K <= 2048 && std::sscanf(shape, "%d,%d", &tokens, &alone) == 2 && tokens >= 16 && tokens <= 1024 &&
-        alone >= 0 && alone <= tokens)
-        c->shape = {tokens, alone};
+    if (c->K <= 2048 && mlda::switch_numbers(std::getenv("MLDA_TILE_SHAPE"), 2, 0, 1024, numbers) && numbers[0] >= 16 &&
+        numbers[1] <= numbers[0])
+        c->shape = {(int32_t)numbers[0], (int32_t)numbers[1]};
     c->sample_lds = c->far_weights ? mlda::sample_far_lds_bytes(c->Kpad, sample_waves_for(c->K))
                                    : mlda::sample_lds_bytes(c->Kpad, sample_waves_for(c->K), sample_waves_for(c->K) == 4 ? 8 : 4);
     if (c->sample_lds > (size_t)c->lds_limit)
