@@ -362,17 +362,19 @@ def test_walks_shared_where_sums_round(mlda, case, beta):
 @pytest.mark.parametrize("beta", [0.01, 1e-14, 1e-30])
 @pytest.mark.parametrize("K", [30, 500, 3000])
 def test_shared_walks_with_little_left(mlda, K, beta):
-    """Documents with one token of a word, its only one of its topic, among documents with forty: without the
-    token nothing of the row's sum is left but beta, and alpha is too small to matter."""
-    V, pairs = 3, 11
+    """Documents with one token of a word, its only one of its topic, among documents of that word alone: without the
+    token nothing of the row's sum is left but beta, and alpha is too small to matter.  (Documents of fewer than 90 tokens
+    do not share walks beyond K = 2,048.)"""
+    V, pairs, length = 3, 11, 40 if K <= 2048 else 100
+    half = length // 2
     words, z = [], []
     for i in range(pairs):
-        words += [0] * 40 + [0] + [1] * 39
-        z += [0] * 40 + [2 + i] + [K - 1] * 20 + [K - 2] * 19
+        words += [0] * length + [0] + [1] * (length - 1)
+        z += [0] * length + [2 + i] + [K - 1] * half + [K - 2] * (length - 1 - half)
 
     class C:  # minimal corpus record
         pass
-    c = C(); c.doc_ptr = np.arange(2 * pairs + 1, dtype=np.int64) * 40; c.T = 80 * pairs
+    c = C(); c.doc_ptr = np.arange(2 * pairs + 1, dtype=np.int64) * length; c.T = 2 * length * pairs
     c.word_ids = np.array(words, dtype=np.int32)
     z = np.array(z, dtype=np.uint16)
     model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, 1e-30, beta, SEED)
