@@ -498,13 +498,12 @@ struct FarWeights {
 // its first entry counts one less: the token itself.  `prev_own`: the lanes whose entry before
 // this unit belongs to their o; on return: those whose last entry of the unit does.  ("Own and
 // first" is worked out on these lane masks, by the scalar unit.)
-// This form leaves the sum at the unit's end only: every entry is added with its whole count,
-// and the lanes whose first own entry lies in the unit give w_o back once, at the end.
+// This form leaves the sum at the unit's end only.  (Every entry added with its whole count, and w_o given back at the
+// end, takes an instruction less per entry; but w_o may be 1 / beta times all the rest, of which nothing is then left.)
 template <class Layout, class Weights>
 __device__ __forceinline__ void unit_sum(const Weights& weight_at, const uint4& raw, int o_key, float w_o,
                                          uint64_t& prev_own, double& acc) {
     constexpr int n = Layout::kUnitEntries;
-    uint64_t first_here = 0;
 #pragma unroll
     for (int h = 0; h < n; h += 4) {       // four gathers of p* on their way at a time
         int key[4];
@@ -518,16 +517,14 @@ __device__ __forceinline__ void unit_sum(const Weights& weight_at, const uint4& 
         for (int j = 0; j < 4; ++j) {
             const bool own = key[j] == o_key;
             const uint64_t own_lanes = __ballot(own);
-            first_here |= own_lanes & ~prev_own;
+            const bool first = __builtin_amdgcn_inverse_ballot_w64(own_lanes & ~prev_own);
             prev_own = own_lanes;
-            acc = fma((double)Layout::count(raw, h + j), (double)(own ? w_o : w[j]), acc);
+            acc = fma((double)(Layout::count(raw, h + j) - (first ? 1 : 0)), (double)(own ? w_o : w[j]), acc);
         }
     }
-    acc -= __builtin_amdgcn_inverse_ballot_w64(first_here) ? (double)w_o : 0.0;
 }
 
-// The same with the running sum after every entry and the entries' keys kept (the first own
-// entry counts one less where it stands).
+// The same with the running sum after every entry and the entries' keys kept.
 template <class Layout, class Weights>
 __device__ __forceinline__ void unit_prefix_sums(const Weights& weight_at, const uint4& raw, int o_key, float w_o,
                                                  uint64_t& prev_own, double& acc, double* sums, int* keys) {

@@ -360,11 +360,11 @@ def test_walks_shared_where_sums_round(mlda, case, beta):
 
 
 @pytest.mark.parametrize("beta", [0.01, 1e-14, 1e-30])
-@pytest.mark.parametrize("K", [30, 500, 3000])
+@pytest.mark.parametrize("K", [30, 500, 3000, 31000])
 def test_shared_walks_with_little_left(mlda, K, beta):
     """Documents with one token of a word, its only one of its topic, among documents of that word alone: without the
     token nothing of the row's sum is left but beta, and alpha is too small to matter.  (Documents of fewer than 90 tokens
-    do not share walks beyond K = 2,048.)"""
+    do not share walks beyond K = 2,048; K = 31,000 has its weights in device memory.)"""
     V, pairs, length = 3, 11, 40 if K <= 2048 else 100
     half = length // 2
     words, z = [], []
