@@ -134,11 +134,10 @@ __host__ __device__ constexpr int sample_wave_bytes(int kept_passes, int kept_su
     const int shared = kept_sums * 8 + kept_passes * kWave * 2 + kWave * 5, records = kWave * (int)sizeof(TokenRec);
     return shared > records ? shared : records;
 }
-// Slots for the waves' least weights, filled up to 16 bytes.
-__host__ __device__ constexpr int least_slots(int waves) { return (waves + 3) & ~3; }
-// LDS bytes of sample_kernel<kWaves> for a given Kpad and bytes of a staged weight.
+// LDS bytes of sample_kernel<kWaves> for a given Kpad and bytes of a staged weight: p*, the prefix sums, the word's least
+// weight (in 16 bytes), the waves' own.
 __host__ __device__ constexpr size_t sample_lds_bytes(int Kpad, int waves, int weight_bytes, int kept_passes = 0, int kept_sums = 0) {
-    return (size_t)Kpad * weight_bytes + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 + (size_t)least_slots(waves) * 4 +
+    return (size_t)Kpad * weight_bytes + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 + 16 +
            (size_t)waves * sample_wave_bytes(kept_passes, kept_sums);
 }
 // The same when p* stays in device memory: the prefix sums and the waves' records only.
@@ -1005,7 +1004,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);      // wave-uniform, in an SGPR
     constexpr bool kShares = Layout::kShares;
-    unsigned char* wave_base = lds + pstar_lds + (size_t)((ng + 1) & ~1) * 8 + (kShares ? least_slots(kWaves) * 4 : 0);
+    unsigned char* wave_base = lds + pstar_lds + (size_t)((ng + 1) & ~1) * 8 + (kShares ? 16 : 0);
     const int wave_bytes = kShares ? sample_wave_bytes(a.kept_passes, a.kept_sums) : kWave * (int)sizeof(TokenRec);
     TokenRec* my_rec = reinterpret_cast<TokenRec*>(wave_base + wave * wave_bytes);
     typedef typename std::conditional<kFar, FarWeights, LdsWeights>::type Weights;
@@ -1034,13 +1033,22 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     if (in_run()) {
         for (int w = tid; w < (ng + 31) / 32; w += kWaves * kWave) changed[w] = 0u;
     }
-    // Shared walks: no weight of the tile's word is less than the least of the fp32 numbers with these bits, one per wave (see
-    // row_sums.hpp; bits of numbers that are not negative are in the numbers' order).
-    [[maybe_unused]] uint32_t* least = reinterpret_cast<uint32_t*>(wave_base) - least_slots(kWaves);
-    auto note_least = [&](uint32_t v, bool beside) {        // (beside what the wave has noted before)
+    // Shared walks: no weight of the tile's word is less than the fp32 number with these bits (see row_sums.hpp; bits of
+    // numbers that are not negative are in the numbers' order).  Every wave notes its own least in the LDS of its records;
+    // the second one collects them while the first adds up the groups' sums.
+    [[maybe_unused]] uint32_t* least = reinterpret_cast<uint32_t*>(wave_base) - 4;
+    auto note_least = [&](uint32_t v) {
         if constexpr (kShares) {
             v = wave_min_at_last(v);
-            if (lane == kWave - 1) least[wave] = beside ? min(v, least[wave]) : v;
+            if (lane == kWave - 1) *(kWaves == 1 ? least : reinterpret_cast<uint32_t*>(my_rec)) = v;
+        }
+    };
+    auto collect_least = [&](bool beside) {         // (beside: of the words before in the run, too)
+        if constexpr (kShares && kWaves > 1) {
+            uint32_t v = 0xffffffffu;
+            if (lane < kWaves) v = *reinterpret_cast<const uint32_t*>(wave_base + lane * wave_bytes);
+            v = wave_min_at_last(v);
+            if (lane == kWave - 1) *least = beside ? min(v, *least) : v;
         }
     };
     for (int ti = kFar ? (int)blockIdx.x : first_tile();;) {
@@ -1083,7 +1091,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             my_least = min(my_least, __float_as_uint(w));
             atomicOr(&changed[(k / kGroup) >> 5], 1u << ((k / kGroup) & 31));
         }
-        note_least(my_least, true);
+        note_least(my_least);
         __syncthreads();
         for (int g = tid; g < ng; g += kWaves * kWave)
             if ((changed[g >> 5] >> (g & 31)) & 1u) {
@@ -1103,6 +1111,8 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                 if (g < ng) cp[g] = x;
                 carry = read_lane(x, kWave - 1);
             }
+        } else if (wave == 1) {
+            collect_least(true);
         }
         __syncthreads();
     } else {
@@ -1129,7 +1139,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             pstar[k] = (Weight)(kStagedScale * (double)w);
         }
     }
-    note_least(my_least, false);
+    note_least(my_least);
     __syncthreads();
     for (int g = tid; g < ng; g += kWaves * kWave) {
         double s = 0.0;
@@ -1148,6 +1158,8 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             if (g < ng) cp[g] = x;
             carry = read_lane(x, kWave - 1);
         }
+    } else if (wave == 1) {
+        collect_least(false);
     }
     __syncthreads();
     }
@@ -1279,19 +1291,10 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         const int n_rows = __popcll(heads);
         // Sums whose upper dword is less are exact (with w_o in the place of p*(o), too)
         auto exact_below = [&]() {
-            uint32_t smallest = __float_as_uint(mine.w_o);
             // (the address is made here, every time: hoisted, it would hold a register for good)
             int at = (int)(reinterpret_cast<unsigned char*>(least) - lds);
             asm volatile("" : "+v"(at));
-            if constexpr (kWaves == 1) {
-                smallest = min(smallest, *reinterpret_cast<const uint32_t*>(lds + at));
-            } else {
-#pragma unroll
-                for (int w = 0; w < kWaves; w += 4) {
-                    const uint4 four = *reinterpret_cast<const uint4*>(lds + at + 4 * w);
-                    smallest = min(min(min(smallest, four.x), min(four.y, four.z)), four.w);
-                }
-            }
+            const uint32_t smallest = min(*reinterpret_cast<const uint32_t*>(lds + at), __float_as_uint(mine.w_o));
             return exact_sums_below(smallest, kDouble ? kSumScaleLog2 : 0);
         };
         // Sharing costs a search per token among its row's sums and a wait for units of the row, once for every
