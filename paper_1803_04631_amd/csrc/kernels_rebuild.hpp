@@ -1172,7 +1172,7 @@ __global__ __launch_bounds__(256) void loglik_value_kernel(const double* partial
 }
 
 // The per-document term lgG(K alpha) - lgG(N_d + K alpha), one thread per document (the
-// entries of the theta rows are summed by theta_rows_kernel).  A constant of the corpus.
+// entries of the theta rows are summed by the theta rebuild).  A constant of the corpus.
 __global__ __launch_bounds__(256) void loglik_doc_term_kernel(const int32_t* doc_ptr, int64_t D,
                                                               double k_alpha, double* partial) {
     const double lg_ka = lgamma(k_alpha);

@@ -436,9 +436,12 @@ struct HostChunk {
 
 // Word-first order (Section 6.1.2), document->token map (Section 6.2), theta row slots, tiles.
 // Inside a word the tokens are put in order of falling document length, so that the theta
-// rows a wave walks together have similar lengths; any order inside a word gives the same
-// result, because the uniforms are keyed by the caller's token index.  `accumulate`: the
-// chunk's counts will be added to phi (several chunks) instead of stored.
+// rows a wave walks together have similar lengths.  Any order inside a word, and any cut into chunks and tiles,
+// draws with the same uniforms (they are keyed by the caller's token index) from the same row sums, added
+// up in an order that depends on the other tokens of the batch: those sums that round (row_sums.hpp has the rule for
+// those that do not) may differ in their last bit.  So the result is the same but for draws that lie
+// within such a rounding; none was seen in any test.
+// `accumulate`: the chunk's counts will be added to phi (several chunks) instead of stored.
 int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64_t d_begin,
                   int64_t d_end, int32_t V, int32_t K, bool accumulate, bool pinned, bool runs, const TileShape* forced, HostChunk& h) {
     const int64_t D = d_end - d_begin;
@@ -880,11 +883,9 @@ void point_at(mlda_ctx* c, const HostChunk& h, unsigned char* base) {
 // reads when it has no entries of its own: padding entries (count 0, topic K) in the 64 bytes
 // before the first slot.  A streamed chunk arrives with its assignments in document order
 // and hands them back so: its theta rebuilds read them directly and it needs no map (building
-// one costs as much as a theta rebuild); the tokens' slots are then found by bisection.
+// one costs as much as a theta rebuild); the tokens' slots come with its assignments (see attach).
 void derive_chunk_arrays(mlda_ctx* c) {
-    if (c->streamed) {
-        // (the slots of a streamed chunk's tokens come with its assignments, see attach)
-    } else if (c->T > 0) {
+    if (!c->streamed && c->T > 0) {
         hipLaunchKernelGGL(mlda::derive_doc_map_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0, c->stream,
                            c->tok_id, c->T, c->at->tok_begin, c->doc_map);
         const int grid = (int)std::min<int64_t>(c->D, (int64_t)c->n_cus * 32);
