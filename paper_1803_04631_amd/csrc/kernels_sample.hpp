@@ -93,7 +93,7 @@ struct SampleArgs {
     float* far_pstar;
     int32_t min_batch;          // K <= 2048: tokens a wave takes at a time at least
     // Tokens that share the walks over their rows: how many passes, and (fp64 weights) units of them, a wave keeps
-    // the sums of at a time.  (fp32 weights: a sum per lane and pass)
+    // the sums of at a time; none: every token walks by itself.  (fp32 weights: a sum per lane and pass)
     int32_t kept_passes, kept_sums;
     uint32_t sum_slack;         // shared walks, fp64 weights: see kNearlyAll (bits of a double's exponent, in its upper dword)
 };
@@ -1307,6 +1307,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         //   1.2e7, documents of 4,000, K = 2,000 5.76  5.36   3.93   3.87
         auto share_walks = [&]() {
             const int n = min(batch, tl.count - b * batch);
+            if (kDouble && a.kept_passes == 0) return false;
             if (4 * kept_own > kWave || 3 * n_rows > 2 * n || (kDouble && __ballot(mine.nnz > kMostKeptUnits) != 0)) return false;
             const int rows_per_pass = __ballot(mine.nnz > 12) == 0 ? 16 : __ballot(mine.nnz > 24) == 0 ? 8 : __ballot(mine.nnz > 48) == 0 ? 4 : 1;
             return 4 * n - 3 * n_rows >= 8 * rows_per_pass;

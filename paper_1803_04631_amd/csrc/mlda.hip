@@ -157,6 +157,14 @@ const void* theta_ranked_kernel_for(RowKind rows, int docs) {
 //   K = 1,000, 3.3e7 tokens       2.63   2.46   2.47   2.69   (four workgroups a CU)
 //   K = 1,537, 6.3e6             0.549  0.557  0.630  0.783   (four from 448 on)
 //   K = 2,000, 1.1e7             0.960  1.053  1.279  1.258   (four from 320 on)
+// None for few topics of many tokens: the topics' totals are then so large, and a word's least weight so small, that most sums
+// are too long to be exact, and rows of so few topics are walked in a pass or two anyway.  Sampling launch, us, by T
+// (words 5,000, the generator's topics), shared in tiles of 128 / not shared in tiles of 128 / not shared in tiles of 1,024:
+//                       1e6          5e6           1e7           1.5e7         3e7
+//   K = 11, n = 150     33 33 41     116 117 123   216 220 219   320 320 315   682 636 614
+//           n = 4,800   30 32 39     105 110 113   200 204 203   303 299 296   631 602 578     (8.2e7: 1,750 1,586 1,505)
+//   K = 15, n = 4,800   30 32 40     106 111 116   206 209 207   302 304 296   644 603 586
+bool few_topics_of_many_tokens(int32_t K, int64_t T) { return K <= 16 && T > 10000000; }
 struct KeptSums { int32_t passes, sums; };
 KeptSums kept_sums_for(int32_t Kpad, int waves) {
     const size_t budget = (size_t)(128 * waves / 20) * 1280;
@@ -214,6 +222,7 @@ struct TileShape { int32_t tokens, alone; };
 TileShape tile_shape_for(int32_t K, int64_t T) {
     if (K > 2048) return {4096, 0};
     if (T <= (K <= 512 ? 2000000 : K <= 1024 ? 200000 : 100000)) return {64, 64};
+    if (few_topics_of_many_tokens(K, T)) return {1024, 0};
     if (K <= 256 && T <= 100000000) return {128, 128};
     if (K <= 512) return {1024, 128};
     if (K <= 1024) return {T <= 4000000 ? 256 : 1024, 64};
@@ -1132,7 +1141,9 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
                                         : a.n_single + (a.n_tiles - a.n_single + a.run_tiles - 1) / a.run_tiles;
     const bool near = slots_near(c->slots_bytes) && !c->wide_slot_offsets;
     const int weight_bytes = c->rows == RowKind::packed ? 4 : 8;
-    const KeptSums kept = kept_sums_for(c->Kpad, 4), kept_solo = kept_sums_for(c->Kpad, 1);
+    const bool shares = !few_topics_of_many_tokens(c->K, c->T);
+    const KeptSums kept = shares ? kept_sums_for(c->Kpad, 4) : KeptSums{0, 0};
+    const KeptSums kept_solo = shares ? kept_sums_for(c->Kpad, 1) : KeptSums{0, 0};
     a.kept_passes = kept.passes;
     a.kept_sums = kept.sums;
     a.sum_slack = c->beta >= kSlackBeta ? 3u << 20 : 0u;

@@ -337,6 +337,23 @@ def test_walks_shared_by_tokens(mlda, case, shape, monkeypatch):
     model.close()
 
 
+@pytest.mark.parametrize("K", [1, 11, 16, 17])
+def test_few_topics_of_many_tokens(mlda, K):
+    """Up to 16 topics of more than 10 million tokens: no walks are shared, though every document has its words many times."""
+    D, length, V = 2501, 4000, 300
+    rng = np.random.default_rng(K)
+
+    class C:  # minimal corpus record
+        pass
+    c = C(); c.T = D * length; c.doc_ptr = np.arange(D + 1, dtype=np.int64) * length
+    c.word_ids = rng.integers(V, size=c.T).astype(np.int32)
+    z = ((c.word_ids * K // V + (rng.random(c.T) < 0.1) * rng.integers(K, size=c.T)) % K).astype(np.uint16)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, 50.0 / K, 0.01, SEED)
+    model.set_assignments(z)
+    check_step(model, c, z, V, K, 50.0 / K, 0.01, SEED, 1)
+    model.close()
+
+
 @pytest.mark.parametrize("beta", [1e-3, 1e-5, 1e-9])
 @pytest.mark.parametrize("case", [(2000, 4000, 8, 4), (300, 500, 40, 5), (24, 200, 150, 4), (299, 30000, 4, 40),
                                   (2500, 1100, 30, 3), (40000, 300, 30, 3)], ids=lambda c: "k%d_n%d" % c[:2])
