@@ -28,13 +28,13 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E peak
 # this chip, WRITE_SIZE by 1.000 (same summaries).
 FETCH_SCALE, WRITE_SCALE = 2.000, 1.000
 MEASURED_TRAFFIC_KIB = {
-    ("C4", "init"): (7.05941e7, 1.71133e6, "profiles/sample_kernel_C4.md"),
-    ("C3", "init"): (1.22510e7, 2.28277e5, "profiles/sample_kernel_C3_C5.md"),
-    ("C5", "init"): (2.94472e7, 1.47728e6, "profiles/sample_kernel_C3_C5.md"),
+    ("C4", "init"): (7.05334e7, 1.70854e6, "profiles/sample_kernel_C4.md"),
+    ("C3", "init"): (1.22362e7, 2.28200e5, "profiles/sample_kernel_C3_C5.md"),
+    ("C5", "init"): (2.94770e7, 1.56570e6, "profiles/sample_kernel_C3_C5.md"),
 }
 # VALU wave-instructions per sampling launch (SQ_INSTS_VALU, same summaries): the sampler's other
 # limit is instruction issue, 1024 SIMDs x 2.4 GHz / 4 cycles per wave-instruction
-MEASURED_VALU_INSTS = {("C4", "init"): 1.41003e10, ("C3", "init"): 3.07680e9, ("C5", "init"): 4.99308e9}
+MEASURED_VALU_INSTS = {("C4", "init"): 1.42844e10, ("C3", "init"): 3.11411e9, ("C5", "init"): 5.04840e9}
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0
 
 
@@ -195,6 +195,7 @@ def main():
         traffic = (measured[0] * FETCH_SCALE + measured[1] * WRITE_SCALE) * 1024.0
         traffic_source = measured[2]
         hbm_gbs = traffic / (sample_ms * 1e-3) / 1e9
+    valu_issue_frac = valu_insts / VALU_ISSUE_PEAK / (sample_ms * 1e-3) if valu_insts else None
     value = T * args.steps / elapsed
     log("per iteration: sample %.2f ms, phi %.2f ms, theta %.2f ms, loglik %.2f ms; wall %.2f ms"
         % (*mean_ms, elapsed / args.steps * 1e3))
@@ -247,18 +248,21 @@ def main():
             "avg_launch_ms": sample_ms,
             "algorithmic_bytes_per_launch": float(algo_bytes.mean()),
             # the two rates side by side: `useful` moves the bytes the method needs (one walk of
-            # its theta row per token, so rows that co-resident tiles share in cache count once
-            # per token), `hbm` the bytes the memory counters saw per launch in the committed
+            # its theta row per token, so rows that co-resident tiles share in cache, and rows that
+            # tokens of one document and word walk together, count once per token: a measure of the work,
+            # which may exceed what memory delivers), `hbm` the bytes the memory counters saw per launch in the committed
             # profile of this command, over this run's launch time
             "useful_gbs": achieved,
             "useful_frac": achieved / HBM_PEAK_GBS,
             "hbm_gbs": hbm_gbs,
             "hbm_frac": hbm_gbs / HBM_PEAK_GBS if hbm_gbs else None,
             "traffic_source": traffic_source,
-            # the unit that is busiest: VALU issue (instructions from the same committed profile
-            # over this run's launch time, against the chip's issue rate)
+            # VALU issue: instructions from the same committed profile over this run's launch
+            # time, against the chip's issue rate
             "valu_insts_per_launch": valu_insts,
-            "valu_issue_frac": valu_insts / VALU_ISSUE_PEAK / (sample_ms * 1e-3) if valu_insts else None,
+            "valu_issue_frac": valu_issue_frac,
+            # which of the two the launch keeps busier
+            "busier": ("valu_issue" if valu_issue_frac > hbm_gbs / HBM_PEAK_GBS else "hbm") if hbm_gbs and valu_insts else None,
         },
     }
     model.close()
