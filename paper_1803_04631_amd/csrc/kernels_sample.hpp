@@ -1305,12 +1305,17 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         //   6.3e6, K = 1,537                    0.62   0.78   0.55   0.55      1e6, K = 128      0.058  0.071  0.056  0.056
         //   8.6e6, documents of 30,000, K = 299 1.42   0.53   0.47   0.47      1e5, K = 32       12.3us 16.0   12.4   12.4
         //   1.2e7, documents of 4,000, K = 2,000 5.76  5.36   3.93   3.87
+        // Rows of up to 8 units (late in training, or few topics) take so short a pass that the search is the larger part: only
+        // where one pass stands for four.  2e7 tokens late in training, us, two passes saved / with this:
+        //   K = 80, documents of 92, 769 words   860  757 (684 without sharing, in tiles of 1,024)       20,000 words  629  604
+        //   K = 200, documents of 92, 800 words  626  603     K = 80, documents of 300  546  548     K = 24, of 2,000  432  433
         auto share_walks = [&]() {
             const int n = min(batch, tl.count - b * batch);
             if (kDouble && a.kept_passes == 0) return false;
             if (4 * kept_own > kWave || 3 * n_rows > 2 * n || (kDouble && __ballot(mine.nnz > kMostKeptUnits) != 0)) return false;
             const int rows_per_pass = __ballot(mine.nnz > 12) == 0 ? 16 : __ballot(mine.nnz > 24) == 0 ? 8 : __ballot(mine.nnz > 48) == 0 ? 4 : 1;
-            return 4 * n - 3 * n_rows >= 8 * rows_per_pass;
+            const int least_saved = kDouble && __ballot(mine.nnz > 8) == 0 ? 13 : 8;
+            return 4 * n - 3 * n_rows >= least_saved * rows_per_pass;
         };
         if constexpr (kDouble) if (share_walks()) {
             in_rest = false;
