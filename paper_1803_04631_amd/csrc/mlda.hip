@@ -206,7 +206,7 @@ int tile_tokens_for(int32_t K) { return K <= 2048 ? 1024 : 4096; }
 //                       1024/0  1024/64  256/64  128/128  64/64
 //   K = 16,     1e5       24      28       17      15       11
 //               3e6      110      99       94      85       86
-//               4e7      926     911      961     865      961
+//               4e7      926     911      961     865      961     (beyond 1e7 see few_topics_of_many_tokens)
 //   K = 128,    1e5       34      41       25      22       16
 //               1e6      106      92       76      73       67
 //               4e7     1538    1439     1507    1427     1518
