@@ -181,7 +181,7 @@ def main():
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
 
-    ms = model.timing()                       # [steps, 4] HIP-event times on the library's stream
+    ms = model.timing()                       # [steps, 4] kernel times on the library's stream
     algo_bytes = model.sampler_bytes()        # [steps] algorithmic bytes of each sampling launch
     ll = model.loglik()
     nnz = model.doc_topic_nnz()

@@ -193,9 +193,10 @@ int mlda_get_doc_topic_csr(mlda_ctx* ctx, int64_t* row_ptr, uint16_t* topics, in
 int mlda_get_loglik(mlda_ctx* ctx, double* ll);
 
 /*
- * Kernel times of the iterations of the most recent mlda_step, from HIP events on
- * the context's stream.  ms: host, capacity_iters rows of 4 doubles (sampling, rebuild
- * phi and n_k, rebuild theta, log-likelihood), out; n_iters: host, out, rows filled
+ * Kernel times of the iterations of the most recent mlda_step: each phase from its start to the
+ * next one's, by the device's clock (chunks that take turns: from HIP events on the context's stream).
+ * ms: host, capacity_iters rows of 4 doubles (sampling, rebuild phi and n_k, rebuild theta,
+ * log-likelihood; 0 where the step did not evaluate it), out; n_iters: host, out, rows filled
  * (the last min(n, capacity_iters, 1024) iterations of that step).
  */
 int mlda_get_timing(mlda_ctx* ctx, double* ms, int32_t capacity_iters, int32_t* n_iters);

@@ -9,6 +9,9 @@ namespace mlda {
 
 __global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
 
+// (where no launch of the phase itself stores it)
+__global__ void stamp_kernel(unsigned long long* at) { stamp_start(at); }
+
 __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -33,7 +36,9 @@ __global__ __launch_bounds__(256) void visited_sum_kernel(const unsigned long lo
 // What the rebuilds of one state add to must start at zero: the rows of words whose tokens span
 // several segments, and the topic totals where the theta rebuild before has not cleared them
 // (n_k null: it has).  grid = (#split words + 1, ceil(K / blockDim)).
-__global__ void zero_sums_kernel(const int32_t* split_words, PhiView phi, int32_t K, int32_t* n_k) {
+__global__ void zero_sums_kernel(const int32_t* split_words, PhiView phi, int32_t K, int32_t* n_k,
+                                 unsigned long long* started) {
+    stamp_start(started);
     const int k = (int)(blockIdx.y * blockDim.x + threadIdx.x);
     if (k >= K) return;
     if (blockIdx.x == 0) {
@@ -105,8 +110,9 @@ template <bool kPacked>
 __global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t n_segs, const uint16_t* z,
                                                        PhiView phi, int32_t K, int64_t T, int32_t n_totals, int32_t* n_k,
                                                        const unsigned long long* visited, int n_visited,
-                                                       unsigned long long* visited_sum) {
+                                                       unsigned long long* visited_sum, unsigned long long* started) {
     extern __shared__ __align__(16) unsigned char lds[];
+    stamp_start(started);
     const int tid = (int)threadIdx.x;
     if ((int)blockIdx.x >= n_segs) {
         const int part = (int)blockIdx.x - n_segs;
@@ -428,8 +434,10 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
                                                            int32_t K, double alpha,
                                                            const double* lg_table,
                                                            unsigned long long* visited_partial,
-                                                           double* ll_partial, int32_t* old_n_k) {
+                                                           double* ll_partial, int32_t* old_n_k,
+                                                           unsigned long long* started) {
     typedef typename Layout::Entry Entry;
+    stamp_start(started);
     clear_old_totals(old_n_k, K);
     if (T == 0) {       // no token anywhere: the loads "past a document's end" still need a place that exists
         doc_map = nullptr;
@@ -674,8 +682,10 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
                                                              int32_t K, double alpha, const double* lg_table,
                                                              unsigned long long* visited_partial,
                                                              double* ll_partial, int32_t* old_n_k,
-                                                             int32_t n_cells, int32_t n_stage, int32_t n_before) {
+                                                             unsigned long long* started, int32_t n_cells,
+                                                             int32_t n_stage, int32_t n_before) {
     typedef typename Layout::Entry Entry;
+    stamp_start(started);
     constexpr int W = kWave / kDocs, kKeep = rank_keep(kDocs);      // lanes per document
     clear_old_totals(old_n_k, K);
     if (T == 0) {       // no token anywhere: the loads "past a document's end" still need a place that exists
@@ -1091,8 +1101,10 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
                                                                const double* lg_table, double* partial,
                                                                const double* theta_partial, int n_theta,
                                                                const double* theta_sum, const double* doc_term,
-                                                               unsigned int* ticket, double* out) {
+                                                               unsigned int* ticket, double* out,
+                                                               unsigned long long* started) {
     // (ticket: null if loglik_value_kernel follows)
+    stamp_start(started);
     __shared__ double table[kLgTable];
     for (int c = (int)threadIdx.x; c < kLgTable; c += 256) table[c] = lg_table[c];
     const double lg_beta = lg_table[kLgTable];

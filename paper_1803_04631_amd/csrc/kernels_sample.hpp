@@ -96,6 +96,7 @@ struct SampleArgs {
     // the sums of at a time; none: every token walks by itself.  (fp32 weights: a sum per lane and pass)
     int32_t kept_passes, kept_sums;
     uint32_t sum_slack;         // shared walks, fp64 weights: see kNearlyAll (bits of a double's exponent, in its upper dword)
+    unsigned long long* started;    // see stamp_start
 };
 
 constexpr int kRowHeader = 16;  // bytes before a theta row's entries
@@ -991,6 +992,7 @@ __attribute__((amdgpu_waves_per_eu(Layout::kWavesPerSimd)))
 __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int kGroup = dense_group(kWaves);
+    stamp_start(a.started);
     const int K = a.K, Kpad = a.Kpad, ng = Kpad / kGroup;
     constexpr bool kDouble = Layout::kDoubleWeights;
     static_assert(!(kDouble && (kFar || kWaves > 4)), "fp64 weights: workgroups of up to four waves, in LDS");

@@ -305,6 +305,9 @@ constexpr int kMaxThetaGrid = 4096;    // workgroups of the theta rebuild (each 
 constexpr int32_t kSpareTotals = 2 * kLoglikBlocks;
 static_assert(kSpareTotals <= mlda::kPhiDwordTopics, "phi and the totals share a launch's LDS");
 constexpr int kEntryRing = 2048;      // per-rebuild counters of theta row entries (> kMaxTimedIters)
+// resident: when the four phases of every timed iteration started, and when the last one had ended
+constexpr int kPhases = 4;
+constexpr size_t kStampBytes = ((size_t)kMaxTimedIters * kPhases + 1) * 8;
 
 // Where the buffers of one chunk of documents lie inside its part of the workspace (byte
 // offsets).  The static part (up to static_bytes) is the preprocessed corpus and is copied
@@ -356,7 +359,7 @@ ChunkLayout chunk_layout_bound(int64_t D, int64_t T, int32_t V, int32_t K, bool 
 // the words with 2^16 tokens or more, of which a corpus of T tokens has at most T / 2^16.
 struct ModelLayout {
     size_t phi[2] = {0, 0}, phi_wide = 0, phi_bytes = 0, wide_row = 0, n_k[2] = {0, 0}, ll_partial = 0,
-           ll_scalars = 0, lg_table = 0, row_entries = 0, far_pstar = 0, total = 0;
+           ll_scalars = 0, lg_table = 0, row_entries = 0, stamps = 0, far_pstar = 0, total = 0;
 };
 
 int64_t wide_rows_bound(int32_t V, int64_t T) {
@@ -378,6 +381,7 @@ ModelLayout model_layout(int32_t V, int32_t K, int64_t T, bool two_phi) {
     L.ll_scalars = put(4 * 8);                            // value, theta sum, document term, the word side's ticket
     L.lg_table = put((size_t)(mlda::kLgTable + 1) * 8 * 2);   // one for alpha, one for beta
     L.row_entries = put((size_t)kEntryRing * 8);
+    L.stamps = put((size_t)kStampBytes);
     L.far_pstar = put(far_weights_for(K) ? (size_t)kFarStrips * (size_t)kpad_for(K) * 4 : 0);
     L.total = at;
     return L;
@@ -705,10 +709,13 @@ struct mlda_ctx {
     unsigned long long* row_entries = nullptr;   // ring: [r % kEntryRing] belongs to rebuild r
     unsigned long long* visited = nullptr;       // the last theta rebuild's row entries, one value per workgroup
     int64_t rebuilds = 0;                        // rebuilds launched so far
+    unsigned long long* stamps = nullptr;        // resident: [4 i + phase] of timed iteration i, see stamp_start
+    int clock_khz = 0;                           // the rate they count at
     int32_t last_step_iters = 0;
+    bool last_step_loglik = false;
     bool has_state = false, ll_fresh = false;
-    std::vector<hipEvent_t> events;     // 5 per timed iteration (streamed: kVisitEvents per timed visit)
-    int32_t timed_iters = 0;            // iterations of the last step that carry events
+    std::vector<hipEvent_t> events;     // streamed: kVisitEvents per timed visit
+    int32_t timed_iters = 0;            // iterations of the last step that carry events or stamps
     // streamed: what mlda_get_timing and mlda_get_sampler_bytes need of every timed chunk visit
     struct Visit {
         int32_t iter_row;               // row of the step's timed iterations
@@ -978,7 +985,7 @@ int store_z_and_release(mlda_ctx* c, int32_t m, bool store) {
 // phi (into n_wk[which]) from the attached chunk's assignments z (word-major).  One chunk:
 // rows are stored and n_k follows; several: the chunk's counts are added to a phi that was
 // zeroed before the first chunk, and n_k is formed after the last (finish_model).
-int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which) {
+int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which, unsigned long long* started = nullptr) {
     using namespace mlda;
     int32_t* n_k = nullptr;
     int32_t n_totals = 0;           // workgroups of the phi launch that count the topic totals
@@ -991,7 +998,8 @@ int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which) {
         if (c->n_split > 0 || !cleared) {
             const dim3 grid((unsigned)c->n_split + 1u, (unsigned)blocks_for(c->K, 256));
             hipLaunchKernelGGL(zero_sums_kernel, grid, dim3(256), 0, c->stream, c->split_words, c->phi[which], c->K,
-                               cleared ? (int32_t*)nullptr : n_k);
+                               cleared ? (int32_t*)nullptr : n_k, started);
+            started = nullptr;
         }
         // n_k comes from the fresh n_wk where that is fewer bytes than z (and no LDS atomics); else from z, beside
         // phi while the counters of both leave room for many workgroups per CU
@@ -1000,11 +1008,12 @@ int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which) {
     unsigned long long* visited_sum =
         !c->streamed && c->rebuilds > 0 ? c->row_entries + ((c->rebuilds - 1) % kEntryRing) : nullptr;
     const unsigned blocks = (unsigned)(c->n_segs + n_totals + (visited_sum ? 1 : 0));
+    if (blocks == 0 && started) hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
     if (blocks > 0)
         hipLaunchKernelGGL((c->K <= kPhiDwordTopics ? phi_tile_kernel<false> : phi_tile_kernel<true>), dim3(blocks),
                            dim3(256), phi_tile_lds_bytes(c->K), c->stream,
                            c->segs, c->n_segs, z, c->phi[which], c->K, c->T, n_totals, n_k, c->visited, c->theta_grid,
-                           visited_sum);
+                           visited_sum, started);
     if (!c->streamed && c->T > 0 && n_totals == 0) {        // (streamed: after the last chunk)
         if (from_rows) {
             const int words_per_slice = 64;
@@ -1050,8 +1059,9 @@ int finish_model(mlda_ctx* c, int which) {
 // theta rows of the attached chunk from its assignments: z word-major, reached through the
 // document->token map; streamed: z = z_doc, read directly.  Leaves the rows' part of the
 // log-likelihood as one partial per workgroup in ll_partial[2 kLoglikBlocks ..].
-int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
+int rebuild_theta(mlda_ctx* c, const uint16_t* z, unsigned long long* started = nullptr) {
     using namespace mlda;
+    if (c->D == 0 && started) hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
     const int32_t* doc_map = c->streamed ? nullptr : c->doc_map;
     if (c->D > 0) {
         uint2* row_rec = c->row_rec;
@@ -1071,12 +1081,13 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z) {
             int32_t n_cells = theta_rank_cells(c->K, ranked_longest(*c->at), l.ranked);
             int32_t n_stage = theta_rank_stage(ranked_longest(*c->at), std::max(l.ranked, 1));
             void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &visited, &ll_partial, &old_n_k,
-                            &n_cells, &n_stage, &n_before};         // (the last three: theta_ranked_kernel's)
+                            &started, &n_cells, &n_stage, &n_before};         // (the last three: theta_ranked_kernel's)
             HIP_TRY(hipLaunchKernel(l.ranked ? theta_ranked_kernel_for(c->rows, l.ranked)
                                              : theta_kernel_for(c->rows, c->wide_counters, l.long_docs),
                                     dim3((unsigned)l.grid), dim3((unsigned)(l.long_docs ? kWave * kLongDocWaves : kWave)),
                                     args, l.lds, c->stream));
             n_before = l.grid;
+            started = nullptr;
         }
         c->spare_n_k_cleared = old_n_k != nullptr;
         // (one chunk: the next rebuild_phi adds the counts up; sampler bytes are asked of earlier ones only)
@@ -1104,9 +1115,13 @@ int run_length(const mlda_ctx* c, int32_t n_small) {
     return std::max(1, std::min(c->run_tiles, (n_small + want - 1) / want));
 }
 
-int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
-    if (c->n_tiles == 0) return MLDA_OK;
+int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next, unsigned long long* started = nullptr) {
+    if (c->n_tiles == 0) {
+        if (started) hipLaunchKernelGGL(mlda::stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
+        return launch_check("stamp_kernel");
+    }
     mlda::SampleArgs a;
+    a.started = started;
     a.tiles = c->tiles;
     a.tok_slot = c->tok_slot;
     a.tok_id = c->tok_id;
@@ -1161,6 +1176,7 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
                                 dim3((unsigned)(waves * mlda::kWave)), kernel_args, lds, c->stream));
     const int32_t n_solo = c->n_tiles - c->n_shared;
     if (n_solo > 0) {
+        if (grid > 0) a.started = nullptr;
         a.tiles += c->n_shared;
         if (weight_bytes == 8) {
             a.kept_passes = kept_solo.passes;
@@ -1176,7 +1192,7 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next) {
 
 // The word side of the log-likelihood and the value: with the theta partials that the last
 // rebuild_theta left (one chunk), or their sum over all chunks (streamed), and the documents' term.
-int launch_loglik(mlda_ctx* c) {
+int launch_loglik(mlda_ctx* c, unsigned long long* started = nullptr) {
     using namespace mlda;
     const int64_t cells = (int64_t)c->V * c->K, wide_cells = (int64_t)c->n_wide * c->K;
     // a thread reads 16 bytes at a time
@@ -1190,7 +1206,7 @@ int launch_loglik(mlda_ctx* c) {
     hipLaunchKernelGGL(loglik_word_side_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream,
                        c->phi[c->model_cur], cells, wide_cells, current_n_k(c), c->K, c->beta,
                        (double)c->V * c->beta, c->lg_table_beta, c->ll_partial, theta_partial, n_theta, theta_sum,
-                       doc_term, small ? (unsigned int*)(c->ll_scalars + 3) : (unsigned int*)nullptr, c->ll_scalars);
+                       doc_term, small ? (unsigned int*)(c->ll_scalars + 3) : (unsigned int*)nullptr, c->ll_scalars, started);
     if (!small)
         hipLaunchKernelGGL(loglik_value_kernel, dim3(1), dim3(256), 0, c->stream, c->ll_partial, blocks, theta_partial,
                            n_theta, theta_sum, doc_term, c->ll_scalars);
@@ -1277,6 +1293,7 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     c->lg_table_beta = c->lg_table + (mlda::kLgTable + 1);
     c->row_entries = (unsigned long long*)(base + ML.row_entries);
     c->visited = (unsigned long long*)(c->ll_partial + 2 * kLoglikBlocks + kMaxThetaGrid);
+    c->stamps = (unsigned long long*)(base + ML.stamps);
     c->far_pstar = (float*)(base + ML.far_pstar);
 
     hipLaunchKernelGGL(mlda::lg_table_kernel, dim3(blocks_for(mlda::kLgTable + 1, 256)), dim3(256), 0,
@@ -1379,6 +1396,8 @@ int device_limits(mlda_ctx* c) {
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&c->n_cus, hipDeviceAttributeMultiprocessorCount, dev));
     HIP_TRY(hipDeviceGetAttribute(&c->lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    HIP_TRY(hipDeviceGetAttribute(&c->clock_khz, hipDeviceAttributeWallClockRate, dev));
+    if (c->clock_khz <= 0) return fail(MLDA_EHIP, "the device names no rate for its clock");
     c->Kpad = kpad_for(c->K);
     c->far_weights = far_weights_for(c->K);
     // (a switch for tests: the 64-bit form is otherwise only reached by theta slots beyond 4 GiB)
@@ -2013,30 +2032,26 @@ int mlda_step(mlda_ctx* c, int32_t n_iters, uint32_t flags) {
         return MLDA_OK;
     }
     const int32_t timed = std::min(n_iters, kMaxTimedIters);
-    while ((int32_t)c->events.size() < timed * 5) {
-        hipEvent_t ev;
-        HIP_TRY(hipEventCreate(&ev));
-        c->events.push_back(ev);
-    }
-    c->timed_iters = timed;
+    c->timed_iters = 0;
     c->last_step_iters = n_iters;
+    c->last_step_loglik = (flags & MLDA_STEP_LOGLIK) != 0;
     for (int32_t i = 0; i < n_iters; ++i) {
-        const int32_t slot = i - (n_iters - timed);
-        hipEvent_t* ev = slot >= 0 ? &c->events[(size_t)slot * 5] : nullptr;
-        if (slot == 0) HIP_TRY(hipEventRecord(ev[0], c->stream));   // (later ones start where the one before ended)
+        const int32_t row = i - (n_iters - timed);
+        auto phase = [&](int p) { return row >= 0 ? c->stamps + (size_t)row * kPhases + p : nullptr; };
         uint16_t* z_next = c->z[c->cur ^ 1];
-        RC_TRY(launch_sampler(c, c->z[c->cur], z_next));
-        if (ev) HIP_TRY(hipEventRecord(ev[1], c->stream));
-        RC_TRY(rebuild_phi(c, z_next, 0));
-        if (ev) HIP_TRY(hipEventRecord(ev[2], c->stream));
-        RC_TRY(rebuild_theta(c, z_next));
-        if (ev) HIP_TRY(hipEventRecord(ev[3], c->stream));
+        RC_TRY(launch_sampler(c, c->z[c->cur], z_next, phase(0)));
+        RC_TRY(rebuild_phi(c, z_next, 0, phase(1)));
+        RC_TRY(rebuild_theta(c, z_next, phase(2)));
         c->cur ^= 1;
         c->iter += 1;
         c->ll_fresh = false;
-        if (flags & MLDA_STEP_LOGLIK) RC_TRY(launch_loglik(c));
-        if (ev) HIP_TRY(hipEventRecord(ev[4], c->stream));
+        if (c->last_step_loglik) RC_TRY(launch_loglik(c, phase(3)));
     }
+    if (timed > 0) {        // when the last phase had ended
+        hipLaunchKernelGGL(mlda::stamp_kernel, dim3(1), dim3(1), 0, c->stream, c->stamps + (size_t)timed * kPhases);
+        RC_TRY(launch_check("stamp_kernel"));
+    }
+    c->timed_iters = timed;
     return MLDA_OK;
 }
 
@@ -2194,15 +2209,15 @@ int mlda_get_timing(mlda_ctx* c, double* ms, int32_t capacity_iters, int32_t* n_
         *n_iters = n;
         return MLDA_OK;
     }
-    for (int32_t i = 0; i < n; ++i) {
-        hipEvent_t* ev = &c->events[(size_t)(first + i) * 5];
-        for (int j = 0; j < 4; ++j) {
-            float t = 0.f;
-            const hipEvent_t start = j == 0 && first + i > 0 ? ev[-1] : ev[j];
-            HIP_TRY(hipEventElapsedTime(&t, start, ev[j + 1]));
-            ms[(size_t)i * 4 + j] = (double)t;
+    // a phase lasts until the next one that was launched starts
+    std::vector<unsigned long long> at;
+    try { at.resize((size_t)n * kPhases + 1); } catch (const std::bad_alloc&) { return fail(MLDA_ENOMEM, "out of host memory"); }
+    if (n > 0) RC_TRY(fetch(c, at.data(), c->stamps + (size_t)first * kPhases, at.size() * 8));
+    for (int32_t i = 0; i < n; ++i)
+        for (int j = 0; j < kPhases; ++j) {
+            const size_t p = (size_t)i * kPhases + j, next = j == 2 && !c->last_step_loglik ? p + 2 : p + 1;
+            ms[p] = j == 3 && !c->last_step_loglik ? 0.0 : (double)(at[next] - at[p]) / c->clock_khz;
         }
-    }
     *n_iters = n;
     return MLDA_OK;
 }
