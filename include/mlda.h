@@ -86,7 +86,7 @@ int mlda_workspace_bytes(int64_t D, int64_t T, int32_t V, int32_t K, size_t* byt
  * topics are assigned yet: call mlda_init_random or mlda_set_assignments next.
  * K: 1 .. 65,535 (MLDA_EINVAL outside).  A K whose column of p* does not fit the 160 KB of LDS
  * of a workgroup (beyond about 30,900) is sampled with p* in device memory: same results, several
- * times slower per token; the workspace then holds 512 such columns more.
+ * times slower per token; the workspace then holds 256 such columns more.
  * Environment, read here and by the other two ways to create a context, for tests: it takes forms that are
  * otherwise left to other sizes, with the same results, and slower.  A value that is not as said, and an empty one,
  * counts as none.
@@ -94,7 +94,7 @@ int mlda_workspace_bytes(int64_t D, int64_t T, int32_t V, int32_t K, size_t* byt
  *                                  only when the rows of a chunk fill more than 4 GiB (any value but 0)
  *   MLDA_TILE_SHAPE=tokens,alone   K <= 2048: sampling tiles of so many tokens (16 .. 1024), those of up to `alone`
  *                                  (0 .. tokens) taken by one wave each
- *   MLDA_RUN_TILES=n               K > 2048, where a workgroup takes words of few tokens one after the other: n (1 .. 16) of them
+ *   MLDA_RUN_TILES=n               K > 2048, where a workgroup takes tiles one after the other: n (1 .. 16) of them on the whole
  *   MLDA_REORDER_BY_TILES=tokens   resident: assignments of so many tokens and more change their order tile by tile
  */
 int mlda_create(mlda_ctx** out, const int64_t* doc_ptr, const int32_t* word_ids,

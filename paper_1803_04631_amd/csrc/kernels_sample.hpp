@@ -84,13 +84,14 @@ struct SampleArgs {
     double alpha, beta, beta_V;
     uint64_t seed;
     uint32_t iter;
-    // Workgroup b < n_single takes tile b.  The tiles from n_single on each hold a whole word of
-    // few tokens; a workgroup takes a run of run_tiles of them, one after the other, and turns
-    // p* of one word into p* of the next instead of staging it afresh (run_tiles <= 1: no runs).
-    int32_t n_tiles, n_single, run_tiles;
-    // K too large for p* to fit a workgroup's LDS (sample_kernel<12, .., true>): workgroup b keeps
-    // p* of its current tile in far_pstar[b * Kpad ..] and takes the tiles b, b + grid, ...
+    // The tiles from n_single on each hold a whole word of few tokens (see Form)
+    int32_t n_tiles, n_single;
+    // Form::queued and split: workgroup b takes tile b, then those that next_tile (zero before and after the launch)
+    // hands out from the grid's size on.
+    uint32_t* next_tile;
+    // Form::split: workgroup b keeps p* of the topics near_topics (a multiple of 16) and on in far_pstar[b * Kpad ..]
     float* far_pstar;
+    int32_t near_topics;
     int32_t min_batch;          // K <= 2048: tokens a wave takes at a time at least
     // Tokens that share the walks over their rows: how many passes, and (fp64 weights) units of them, a wave keeps
     // the sums of at a time; none: every token walks by itself.  (fp32 weights: a sum per lane and pass)
@@ -101,8 +102,8 @@ struct SampleArgs {
 
 constexpr int kRowHeader = 16;  // bytes before a theta row's entries
 // Topics per fp64 prefix group of the dense bucket: 4 where LDS has room (workgroups of up to four
-// waves, K <= 2048), 16 for the large-K workgroups of twelve waves.
-__host__ __device__ constexpr int dense_group(int waves) { return waves <= 4 ? 4 : 16; }
+// waves, K <= 2048), 16 for the large-K workgroups, 32 where p* does not fit beside the groups' sums.
+__host__ __device__ constexpr int dense_group(int waves, bool far = false) { return waves <= 4 ? 4 : far ? 32 : 16; }
 constexpr int kKeptUnits = 3;   // 16-byte units of entries a lane keeps in registers at most
 constexpr int kMostKeptUnits = kWave * kKeptUnits;  // of a row that is walked once
 constexpr int kMinBatch = 8;    // tokens a wave takes at a time at least
@@ -141,13 +142,16 @@ __host__ __device__ constexpr size_t sample_lds_bytes(int Kpad, int waves, int w
     return (size_t)Kpad * weight_bytes + (size_t)((Kpad / dense_group(waves) + 1) & ~1) * 8 + 16 +
            (size_t)waves * sample_wave_bytes(kept_passes, kept_sums);
 }
-// The same when p* stays in device memory: the prefix sums and the waves' records only.
-__host__ __device__ constexpr size_t sample_far_lds_bytes(int Kpad, int waves) { return sample_lds_bytes(Kpad, waves, 0, kLeastKeptPasses, lane_sums_for(kLeastKeptPasses)); }
 // What runs of small tiles keep in LDS besides: the groups' own sums (the prefix sums are made
 // from them again after every change) and one bit per group for "changed".
-__host__ __device__ constexpr size_t sample_run_lds_bytes(int Kpad, int waves) {
-    const size_t ng = (size_t)(Kpad / dense_group(waves));
+__host__ __device__ constexpr size_t sample_run_lds_bytes(int Kpad, int waves, bool far = false) {
+    const size_t ng = (size_t)(Kpad / dense_group(waves, far));
     return ((ng + 1) & ~(size_t)1) * 8 + ((ng + 31) / 32 * 4 + 15 & ~(size_t)15);
+}
+// The same when p* of the topics from `near` on stays in device memory (four cells of 0 stand for those).
+__host__ __device__ constexpr size_t sample_far_lds_bytes(int Kpad, int waves, int near) {
+    return (size_t)(near + 4) * 4 + (size_t)((Kpad / dense_group(waves, true) + 1) & ~1) * 8 + 16 +
+           (size_t)waves * sample_wave_bytes(kLeastKeptPasses, lane_sums_for(kLeastKeptPasses)) + sample_run_lds_bytes(Kpad, waves, true);
 }
 constexpr int kRunTileTokens = 1024;    // a tile of a run holds a whole word of at most this many tokens
 
@@ -177,8 +181,9 @@ __device__ __forceinline__ double plain_weight(double w) { return w * (1.0 / kWe
 // Dense bucket (p2 = alpha p*', Eq. 6): smallest k with alpha * prefix'(k) > y, where
 // prefix' is the prefix sum of p* with the entry of the token's own topic o replaced by
 // w_o (delta = w_o - p*(o)).  One lane per token.
-template <int kGroup, class Weight>
-__device__ __forceinline__ int dense_bucket_search(const Weight* pstar, const double* cp, int K,
+// four(k): the weights of the topics k .. k + 3 without their scale, k a multiple of 4.
+template <int kGroup, class Four>
+__device__ __forceinline__ int dense_bucket_search(const Four& four, const double* cp, int K,
                                                    int ng, double alpha, double y, int o,
                                                    float w_o, double delta) {
     // Bisection with steps of falling powers of two: `lo` counts the groups known to lie
@@ -196,26 +201,20 @@ __device__ __forceinline__ int dense_bucket_search(const Weight* pstar, const do
     if (lo >= ng) return K - 1;
     const int k0 = lo * kGroup;
     const double before = (lo > 0 ? cp[lo - 1] : 0.0) + (k0 > o ? delta : 0.0);
-    if (kGroup == 4) {
-        // the four topics of group `lo`, taken in one read (p* beyond K is 0 and adds nothing)
-        const double a0 = before + (k0 == o ? (double)w_o : plain_weight(pstar[k0]));
-        const double a1 = a0 + (k0 + 1 == o ? (double)w_o : plain_weight(pstar[k0 + 1]));
-        const double a2 = a1 + (k0 + 2 == o ? (double)w_o : plain_weight(pstar[k0 + 2]));
-        int found = k0 + 3;
-        if (alpha * a2 > y) found = k0 + 2;
-        if (alpha * a1 > y) found = k0 + 1;
-        if (alpha * a0 > y) found = k0;
-        return min(found, K - 1);
-    }
+    // the group's topics, four in a read (p* beyond K is 0 and adds nothing)
     double acc = before;
-    int found = min(k0 + kGroup - 1, K - 1);
-    for (int j = 0; j < kGroup; ++j) {
-        const int k = k0 + j;
-        if (k >= K) break;
-        acc += (k == o) ? (double)w_o : plain_weight(pstar[k]);
-        if (alpha * acc > y) { found = k; break; }
+    int found = k0 + kGroup - 1;
+#pragma unroll 1
+    for (int j = k0; j < k0 + kGroup; j += 4) {
+        const double4 w = four(j);
+        const double a0 = acc + (j == o ? (double)w_o : w.x);
+        const double a1 = a0 + (j + 1 == o ? (double)w_o : w.y);
+        const double a2 = a1 + (j + 2 == o ? (double)w_o : w.z);
+        acc = a2 + (j + 3 == o ? (double)w_o : w.w);
+        const int k = alpha * a0 > y ? j : alpha * a1 > y ? j + 1 : alpha * a2 > y ? j + 2 : j + 3;
+        if (kGroup == 4 || alpha * acc > y) { found = k; break; }
     }
-    return found;
+    return min(found, K - 1);
 }
 
 // DPP move of a double with full row and bank masks; lanes without a source read 0.
@@ -484,12 +483,15 @@ __device__ __forceinline__ double lds_double_at(uint32_t byte_address) {
 struct LdsWeights {
     __device__ __forceinline__ float operator()(uint32_t key) const { return lds_float_at(key); }
 };
-// ... or, when K is too large for that, in the workgroup's own strip of device memory (written by
-// the workgroup itself before a barrier, and read through the CU's own cache).
-struct FarWeights {
-    const unsigned char* base;
+// ... or, when K is too large for that, there up to near_key (where a 0 lies) and from there on in the workgroup's
+// own strip of device memory (written by the workgroup itself before a barrier, and read through the CU's own cache;
+// in front of its first cell lies a 0).  Every lane reads both places: those whose topic is near all read the
+// strip's one 0, so that a gather from it costs what its far topics do.
+struct SplitWeights {
+    const unsigned char* strip;
+    uint32_t near_key;
     __device__ __forceinline__ float operator()(uint32_t key) const {
-        return *reinterpret_cast<const float*>(base + key);
+        return lds_float_at(min(key, near_key)) + *reinterpret_cast<const float*>(strip + max(key, near_key - 4u));
     }
 };
 
@@ -980,18 +982,23 @@ __device__ __forceinline__ void row_pass_long(const Weights& weight_at, const un
 
 template <int kValue> using Int = std::integral_constant<int, kValue>;
 
-// kFar: K is too large for p* to fit a workgroup's LDS.  p* of the workgroup's tile then lives in
-// the workgroup's own strip of device memory (the prefix sums and the records stay in LDS), and
-// the launch has as many workgroups as there are strips, each taking every grid-th tile.
+// How a launch's workgroups meet its tiles.  once: a workgroup per tile.  queued: as many workgroups as the chip holds, each
+// of which takes tiles until there are none left; the small ones (from n_single on) come last, and p* of a small one is made
+// from that of the small one before.  split: the same where K is too large for p* to fit a workgroup's LDS: p* of the topics
+// that do not fit then lives in the workgroup's own strip of device memory.
+enum class Form { once, queued, split };
+
 // kNear: every byte of the slot buffer has a 32-bit offset; a pass then finds its units with
 // 32-bit arithmetic (one offset per lane, the unit's place in the load's own offset field).
-template <int kWaves, class Layout, bool kFar = false, bool kNear = false>
+template <int kWaves, class Layout, Form kForm = Form::once, bool kNear = false>
 // Six waves per SIMD (80 VGPRs), five (96) with fp64 weights: the walk hides HBM latency by occupancy as
 // well as by the early loads.
-__attribute__((amdgpu_waves_per_eu(Layout::kWavesPerSimd)))
+// (A workgroup of sixteen waves has a CU for itself.)
+__attribute__((amdgpu_waves_per_eu(kWaves == 16 ? 4 : Layout::kWavesPerSimd)))
 __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
-    constexpr int kGroup = dense_group(kWaves);
+    constexpr bool kFar = kForm == Form::split, kQueue = kForm != Form::once;
+    constexpr int kGroup = dense_group(kWaves, kFar);
     stamp_start(a.started);
     const int K = a.K, Kpad = a.Kpad, ng = Kpad / kGroup;
     constexpr bool kDouble = Layout::kDoubleWeights;
@@ -999,40 +1006,60 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     typedef typename std::conditional<kDouble, double, float>::type Weight;
     // (what a staged weight, and a sum over a row, carry as a factor)
     constexpr double kStagedScale = kDouble ? kWeightScale : 1.0, kRowScale = kDouble ? kSumScale : 1.0;
-    const size_t pstar_lds = kFar ? 0 : (size_t)Kpad * sizeof(Weight);
+    const size_t pstar_lds = kFar ? (size_t)(a.near_topics + 4) * 4 : (size_t)Kpad * sizeof(Weight);
     Weight* pstar = reinterpret_cast<Weight*>(lds);
-    if constexpr (kFar) pstar = a.far_pstar + (size_t)blockIdx.x * (size_t)Kpad;
+    [[maybe_unused]] float* strip = kFar ? a.far_pstar + (size_t)blockIdx.x * (size_t)Kpad : nullptr;
     double* cp = reinterpret_cast<double*>(lds + pstar_lds);
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);      // wave-uniform, in an SGPR
     constexpr bool kShares = Layout::kShares;
-    unsigned char* wave_base = lds + pstar_lds + (size_t)((ng + 1) & ~1) * 8 + (kShares ? 16 : 0);
+    unsigned char* wave_base = lds + pstar_lds + (size_t)((ng + 1) & ~1) * 8 + (kShares || kQueue ? 16 : 0);
     const int wave_bytes = kShares ? sample_wave_bytes(a.kept_passes, a.kept_sums) : kWave * (int)sizeof(TokenRec);
     TokenRec* my_rec = reinterpret_cast<TokenRec*>(wave_base + wave * wave_bytes);
-    typedef typename std::conditional<kFar, FarWeights, LdsWeights>::type Weights;
+    typedef typename std::conditional<kFar, SplitWeights, LdsWeights>::type Weights;
     [[maybe_unused]] Weights weight_at;
-    if constexpr (kFar) weight_at.base = reinterpret_cast<const unsigned char*>(pstar);
+    if constexpr (kFar) {
+        weight_at.strip = reinterpret_cast<const unsigned char*>(strip);
+        weight_at.near_key = (uint32_t)a.near_topics << 2;
+        if (tid < 4) {                  // (no topic is staged in these places)
+            pstar[a.near_topics + tid] = 0.f;
+            strip[a.near_topics - 4 + tid] = 0.f;
+        }
+    }
+    // p*(k) of the tile's word: put, read, and read four at a time without its scale (k a multiple of 4)
+    auto put_cell = [&](int k, Weight w) {
+        if (kFar && k >= a.near_topics) strip[k] = (float)w;
+        else pstar[k] = w;
+    };
+    auto cell = [&](int k) -> Weight {
+        if constexpr (kFar) return weight_at((uint32_t)k << 2);
+        else return pstar[k];
+    };
+    auto four_cells = [&](int k) {
+        if constexpr (kDouble) {
+            return make_double4(plain_weight(pstar[k]), plain_weight(pstar[k + 1]), plain_weight(pstar[k + 2]), plain_weight(pstar[k + 3]));
+        } else {
+            float4 w = *reinterpret_cast<const float4*>(pstar + (kFar ? min(k, a.near_topics) : k));
+            if constexpr (kFar) {
+                const float4 f = *reinterpret_cast<const float4*>(strip + max(k, a.near_topics - 4));
+                w.x += f.x; w.y += f.y; w.z += f.z; w.w += f.w;
+            }
+            return make_double4((double)w.x, (double)w.y, (double)w.z, (double)w.w);
+        }
+    };
+    auto group_total = [&](int g) {
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < kGroup; j += 4) {
+            const double4 w = four_cells(g * kGroup + j);
+            s += w.x; s += w.y; s += w.z; s += w.w;
+        }
+        return s;
+    };
 
-    // The workgroup's tiles: one, or (large K only) a run of small ones.  What says where the
-    // run starts and ends is worked out again where it is needed rather than kept through the
-    // token phase, whose registers are all taken.
-    // Runs are dealt evenly among the other workgroups in launch order (the runs wait for memory
-    // most of the time, the large tiles keep the arithmetic units busy: side by side on a CU they
-    // fill each other's gaps): of the workgroups before b, floor(b * n_runs / grid) take a run.
-    constexpr bool kRuns = kWaves == 12 && !kFar;
-    auto runs_before = [&](int b) {
-        const int n_runs = (int)gridDim.x - a.n_single;
-        return (int)((int64_t)b * n_runs / (int64_t)gridDim.x);
-    };
-    auto in_run = [&]() { return kRuns && runs_before((int)blockIdx.x + 1) > runs_before((int)blockIdx.x); };
-    auto first_tile = [&]() {
-        const int before = kRuns ? runs_before((int)blockIdx.x) : 0;
-        return in_run() ? a.n_single + before * a.run_tiles : (int)blockIdx.x - before;
-    };
-    auto last_tile = [&]() { return in_run() ? min(first_tile() + a.run_tiles, a.n_tiles) : first_tile() + 1; };
     double* group_sum = reinterpret_cast<double*>(wave_base + (size_t)kWaves * wave_bytes);
     uint32_t* changed = reinterpret_cast<uint32_t*>(group_sum + ((ng + 1) & ~1));
-    if (in_run()) {
+    if (kQueue) {
         for (int w = tid; w < (ng + 31) / 32; w += kWaves * kWave) changed[w] = 0u;
     }
     // Shared walks: no weight of the tile's word is less than the fp32 number with these bits (see row_sums.hpp; bits of
@@ -1053,7 +1080,19 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             if (lane == kWave - 1) *least = beside ? min(v, *least) : v;
         }
     };
-    for (int ti = kFar ? (int)blockIdx.x : first_tile();;) {
+    [[maybe_unused]] int last_ti = -1;          // kQueue: the tile before
+    for (int ti = (int)blockIdx.x;;) {
+    const bool small = kQueue && ti >= a.n_single, follows = small && last_ti >= a.n_single;
+    // kQueue: the next tile, asked for by a wave that has nothing else to do
+    auto ask_next = [&]() {
+        if constexpr (kQueue)
+            if (lane == 0) {
+                const uint32_t taken = atomicAdd(a.next_tile, 1u);
+                least[1] = taken + gridDim.x;
+                // (every workgroup asks until there is no tile left: n_tiles times in all)
+                if (taken + 1u == (uint32_t)a.n_tiles) atomicExch(a.next_tile, 0u);
+            }
+    };
     Tile tl = a.tiles[ti];                 // the same for every lane: keep it in SGPRs
     tl.word = __builtin_amdgcn_readfirstlane(tl.word);
     tl.begin = __builtin_amdgcn_readfirstlane(tl.begin);
@@ -1066,11 +1105,11 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     const size_t phi_cell0 = (size_t)(wide ? wide_row : tl.word) * (size_t)K;
     const uint32_t phi_shift = wide ? 2u : 1u, phi_mask = wide ? 0xffffffffu : 0xffffu;
 
-    if (kRuns && ti > first_tile()) {
-        const Tile prev = a.tiles[ti - 1];
+    if (kQueue && follows) {
+        const Tile prev = a.tiles[last_ti];
         const int prev_begin = __builtin_amdgcn_readfirstlane(prev.begin);
         const int prev_count = __builtin_amdgcn_readfirstlane(prev.count);
-        // ---- p* of the run's previous word becomes p* of this one.  Both words have all their
+        // ---- p* of the previous word becomes p* of this one.  Both words have all their
         // tokens in their tile, so a cell of phi is non-zero exactly for the topics of the
         // tile's tokens: only those cells differ from beta / (n_k + beta V).  Every changed cell
         // gets the value a fresh staging would give it, and the sums of the groups that hold
@@ -1080,7 +1119,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         for (int idx = tid; idx < prev_count; idx += kWaves * kWave) {
             const int k = (int)a.z_cur[prev_begin + idx];
             const float w = (float)((0.0 + a.beta) / ((double)a.n_k[k] + a.beta_V));
-            pstar[k] = w;
+            put_cell(k, w);
             my_least = min(my_least, __float_as_uint(w));
             atomicOr(&changed[(k / kGroup) >> 5], 1u << ((k / kGroup) & 31));
         }
@@ -1089,19 +1128,14 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         for (int idx = tid; idx < tl.count; idx += kWaves * kWave) {
             const int k = (int)a.z_cur[tl.begin + idx];
             const float w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
-            pstar[k] = w;
+            put_cell(k, w);
             my_least = min(my_least, __float_as_uint(w));
             atomicOr(&changed[(k / kGroup) >> 5], 1u << ((k / kGroup) & 31));
         }
         note_least(my_least);
         __syncthreads();
         for (int g = tid; g < ng; g += kWaves * kWave)
-            if ((changed[g >> 5] >> (g & 31)) & 1u) {
-                double s = 0.0;
-#pragma unroll
-                for (int j = 0; j < kGroup; ++j) s += (double)pstar[g * kGroup + j];
-                group_sum[g] = s;
-            }
+            if ((changed[g >> 5] >> (g & 31)) & 1u) group_sum[g] = group_total(g);
         __syncthreads();
         if (wave == 0) {
             for (int w = lane; w < (ng + 31) / 32; w += kWave) changed[w] = 0u;
@@ -1115,6 +1149,8 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             }
         } else if (wave == 1) {
             collect_least(true);
+        } else if (wave == 2) {
+            ask_next();
         }
         __syncthreads();
     } else {
@@ -1128,7 +1164,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                 w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
                 my_least = min(my_least, __float_as_uint(w));
             }
-            pstar[k] = (Weight)(kStagedScale * (double)w);
+            put_cell(k, (Weight)(kStagedScale * (double)w));
         }
     } else {
         const uint16_t* phi_v = reinterpret_cast<const uint16_t*>(phi_cells) + phi_cell0;
@@ -1138,17 +1174,15 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                 w = (float)(((double)phi_v[k] + a.beta) / ((double)a.n_k[k] + a.beta_V));
                 my_least = min(my_least, __float_as_uint(w));
             }
-            pstar[k] = (Weight)(kStagedScale * (double)w);
+            put_cell(k, (Weight)(kStagedScale * (double)w));
         }
     }
     note_least(my_least);
     __syncthreads();
     for (int g = tid; g < ng; g += kWaves * kWave) {
-        double s = 0.0;
-#pragma unroll
-        for (int j = 0; j < kGroup; ++j) s += plain_weight(pstar[g * kGroup + j]);
+        const double s = group_total(g);
         cp[g] = s;
-        if (in_run()) group_sum[g] = s;
+        if (small) group_sum[g] = s;
     }
     __syncthreads();
     if (wave == 0) {                       // inclusive prefix over the group sums
@@ -1162,6 +1196,8 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         }
     } else if (wave == 1) {
         collect_least(false);
+    } else if (wave == 2) {
+        ask_next();
     }
     __syncthreads();
     }
@@ -1214,7 +1250,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             const int32_t phi_own = (int32_t)((own_dword >> ((own_byte & 2u) << 3)) & phi_mask);
             mine.w_o = (float)(((double)(phi_own - 1) + ka->beta) /
                                ((double)(ka->n_k[mine.o] - 1) + ka->beta_V));
-            delta = (double)mine.w_o - plain_weight(pstar[mine.o]);
+            delta = (double)mine.w_o - plain_weight(cell(mine.o));
             // cp[ng - 1] = sum_k p*(k), read from LDS where it is needed; Q = alpha sum (Eq. 7)
             mine.Qp = ka->alpha * (cp[ng - 1] + delta);
         }
@@ -1273,8 +1309,8 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                 if (kDouble && __builtin_expect(Qp < kSmallestScaled, 0))
                     y = Qp * token_uniform(ka->seed, ka->iter,
                                            (uint64_t)load_at<uint32_t>(ka->tok_id + tl.begin, (uint32_t)(b * batch + lane) << 2));
-                z_new = dense_bucket_search<kGroup>(pstar, cp, K, ng, ka->alpha, y, o,
-                                                    w_o, (double)w_o - plain_weight(pstar[o]));
+                z_new = dense_bucket_search<kGroup>(four_cells, cp, K, ng, ka->alpha, y, o,
+                                                    w_o, (double)w_o - plain_weight(cell(o)));
             }
             store_at<uint16_t>(ka->z_next + tl.begin, (uint32_t)(b * batch + lane) << 1, (uint16_t)z_new);
         };
@@ -1582,7 +1618,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                     if (!Layout::kOneEntryPerTopic && holder > 0 && (int)first_topic[lane0 + holder] == o &&
                         key_before_unit<Layout>(a.slots + ((size_t)mine.off + 1u + (size_t)q0) * 16u) == o_key)
                         in_rest = true;         // the sub-lane before has some of o's entries, too
-                    const double shift = fma((double)(n_o - 1), (double)mine.w_o, -((double)n_o * (double)pstar[o]));
+                    const double shift = fma((double)(n_o - 1), (double)mine.w_o, -((double)n_o * (double)cell(o)));
                     const double S_all = sums[lane0 + n_lanes - 1];
                     const double S = S_all + shift, total = mine.Qp + S;
                     if (!((uint32_t)__double2hiint(S_all) < exact_below())) in_rest = true;
@@ -1731,8 +1767,10 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
-    ti += kFar ? (int)gridDim.x : 1;
-    if (kFar ? ti >= a.n_tiles : (!kRuns || ti >= last_tile())) break;
+    if constexpr (!kQueue) break;
+    last_ti = ti;
+    ti = __builtin_amdgcn_readfirstlane((int)least[1]);
+    if (ti >= a.n_tiles) break;
     __syncthreads();                // every wave is done with this word's p*
     }
 }

@@ -53,9 +53,15 @@ int fail(int code, const std::string& msg) {
 
 constexpr size_t kAlign = 256;        // workspace sub-buffer alignment
 constexpr size_t kSlotAlign = 64;     // theta row slot alignment (bytes)
+constexpr size_t kLdsPerWorkgroup = 160 * 1024;
 // waves per sampling workgroup: more of them share one staged p* column when K is large
-// (twelve: two such workgroups fill a CU's six waves per SIMD, and their LDS fits twice)
-int sample_waves_for(int32_t K) { return K <= 2048 ? 4 : 12; }
+// (twelve: two such workgroups fill a CU's six waves per SIMD, and their LDS fits twice; sixteen
+// where it does not, K beyond 11,300: 4e6 tokens at K = 13,000 608 us against 697, 2e6 at 29,000 910 against 1,085)
+size_t queued_lds_bytes(int32_t K, int waves) {
+    const int32_t g = mlda::dense_group(waves), Kpad = (K + g) / g * g;
+    return mlda::sample_lds_bytes(Kpad, waves, 4) + mlda::sample_run_lds_bytes(Kpad, waves);
+}
+int sample_waves_for(int32_t K) { return K <= 2048 ? 4 : 2 * queued_lds_bytes(K, 12) <= kLdsPerWorkgroup ? 12 : 16; }
 
 // How a chunk's theta rows are laid out: 4-byte entries of any K for the workgroups of twelve waves,
 // and for those of four (K <= 2048) where rows are shortest; else for these 2-byte entries with 3, 5 or
@@ -77,30 +83,39 @@ auto with_layout(RowKind rows, F&& f) {
 // What the sampler's LDS holds besides p* itself belongs to K as well: Kpad = K + 1 rounded up to
 // a multiple of the dense bucket's group (one zero entry of p* past the last topic: padding
 // entries of theta rows point at it).
+//
+// p* of one word beside the prefix sums and the waves' records: where that exceeds the LDS a
+// workgroup can have on this chip (K beyond about 26,100), p* of the topics that do not fit lives in device memory
+// instead, one strip per workgroup of a launch of at most kFarStrips workgroups.
+constexpr int kFarStrips = 256;
+bool far_weights_for(int32_t K) { return sample_waves_for(K) == 16 && queued_lds_bytes(K, 16) > kLdsPerWorkgroup; }
 int32_t kpad_for(int32_t K) {
-    const int32_t g = mlda::dense_group(sample_waves_for(K));
+    const int32_t g = mlda::dense_group(sample_waves_for(K), far_weights_for(K));
     return (K + g) / g * g;
 }
-// p* of one word beside the prefix sums and the waves' records: where that exceeds the LDS a
-// workgroup can have on this chip (K beyond about 30,900), p* lives in device memory instead,
-// one strip per workgroup of a launch of at most kFarStrips workgroups.
-constexpr size_t kLdsPerWorkgroup = 160 * 1024;
-constexpr int kFarStrips = 512;
-bool far_weights_for(int32_t K) {
-    return mlda::sample_lds_bytes(kpad_for(K), sample_waves_for(K), 4) > kLdsPerWorkgroup;
+// The topics whose p* stays in LDS then: as many as have room (0: none do).
+int32_t near_topics_for(int32_t K, size_t lds_limit) {
+    const size_t rest = mlda::sample_far_lds_bytes(kpad_for(K), sample_waves_for(K), 0);
+    return rest >= lds_limit ? 0 : (int32_t)std::min<size_t>((lds_limit - rest) / 4, (size_t)kpad_for(K)) & ~15;
 }
 
 // short_docs: no document has more tokens than a 4-byte entry counts; near: the theta slots of
 // the chunk end below 4 GiB, so that 32-bit byte offsets reach them
 template <bool kNear>
 const void* sample_kernel_of(int32_t K, RowKind rows, bool short_docs, bool alone) {
-    if (far_weights_for(K)) return (const void*)mlda::sample_kernel<12, mlda::PackedRows, true, kNear>;
-    if (rows == RowKind::packed && sample_waves_for(K) == 4) return (const void*)mlda::sample_kernel<4, mlda::PackedRowsAlone, false, kNear>;
-    if (rows == RowKind::packed && short_docs && alone) return (const void*)mlda::sample_kernel<12, mlda::PackedRowsAlone, false, kNear>;
-    if (rows == RowKind::packed && short_docs) return (const void*)mlda::sample_kernel<12, mlda::PackedRowsShort, false, kNear>;
+    if (far_weights_for(K)) return (const void*)mlda::sample_kernel<16, mlda::PackedRows, mlda::Form::split, kNear>;
+    if (rows == RowKind::packed && sample_waves_for(K) == 4) return (const void*)mlda::sample_kernel<4, mlda::PackedRowsAlone, mlda::Form::once, kNear>;
+    if (rows == RowKind::packed) {
+        auto of_waves = [&](auto waves) {
+            if (short_docs && alone) return (const void*)mlda::sample_kernel<waves.value, mlda::PackedRowsAlone, mlda::Form::queued, kNear>;
+            if (short_docs) return (const void*)mlda::sample_kernel<waves.value, mlda::PackedRowsShort, mlda::Form::queued, kNear>;
+            return (const void*)mlda::sample_kernel<waves.value, mlda::PackedRows, mlda::Form::queued, kNear>;
+        };
+        return sample_waves_for(K) == 12 ? of_waves(mlda::Int<12>()) : of_waves(mlda::Int<16>());
+    }
     return with_layout(rows, [](auto layout) {
         typedef decltype(layout) Layout;
-        return (const void*)mlda::sample_kernel<Layout::kDoubleWeights ? 4 : 12, Layout, false, kNear>;
+        return (const void*)mlda::sample_kernel<4, Layout, mlda::Form::once, kNear>;
     });
 }
 const void* sample_kernel_for(int32_t K, RowKind rows, bool short_docs, bool alone, bool near) {
@@ -109,11 +124,11 @@ const void* sample_kernel_for(int32_t K, RowKind rows, bool short_docs, bool alo
 // (a wave per tile, K <= 2048)
 template <bool kNear>
 const void* sample_solo_kernel_of(RowKind rows) {
-    if (rows == RowKind::packed) return (const void*)mlda::sample_kernel<1, mlda::PackedRowsAlone, false, kNear>;
+    if (rows == RowKind::packed) return (const void*)mlda::sample_kernel<1, mlda::PackedRowsAlone, mlda::Form::once, kNear>;
     return with_layout(rows, [](auto layout) {
         typedef decltype(layout) Layout;
         typedef typename std::conditional<Layout::kDoubleWeights, Layout, mlda::PackedRowsAlone>::type Rows;
-        return (const void*)mlda::sample_kernel<1, Rows, false, kNear>;
+        return (const void*)mlda::sample_kernel<1, Rows, mlda::Form::once, kNear>;
     });
 }
 bool slots_near(size_t slots_bytes) { return slots_bytes <= 0xffffffffull; }
@@ -189,7 +204,9 @@ constexpr int kMostKeptPasses = 8;
 // (7.4e8: the scatter itself 24.05 / 11.2, the gather of the setter 12.55 / 7.5; 9.9e7: 1.00 / 1.95 and 1.36 / 1.15.)
 constexpr int64_t kReorderByTiles = 200000000;
 constexpr int kMaxTimedIters = 1024;
-constexpr int kRunTiles = 16;           // small tiles a workgroup of the large-K sampler takes one after the other
+// Words of few tokens whose p* is made from one another's (K > 2048) count in the sampler's bytes as if every
+// kRunTiles-th were staged afresh.
+constexpr int kRunTiles = 16;
 // events of a streamed chunk visit: its uploads have arrived | topics and slots in word-major
 // order | theta rebuilt | sampled | phi added to | new topics in document order | theta of the
 // new topics (log-likelihood)
@@ -378,7 +395,7 @@ ModelLayout model_layout(int32_t V, int32_t K, int64_t T, bool two_phi) {
     L.n_k[0] = put((size_t)K * 4);
     L.n_k[1] = two_phi ? put((size_t)K * 4) : L.n_k[0];
     L.ll_partial = put((size_t)(2 * kLoglikBlocks + 2 * kMaxThetaGrid) * 8);
-    L.ll_scalars = put(4 * 8);                            // value, theta sum, document term, the word side's ticket
+    L.ll_scalars = put(5 * 8);      // value, theta sum, document term, the word side's ticket, the sampler's next tile
     L.lg_table = put((size_t)(mlda::kLgTable + 1) * 8 * 2);   // one for alpha, one for beta
     L.row_entries = put((size_t)kEntryRing * 8);
     L.stamps = put((size_t)kStampBytes);
@@ -685,12 +702,14 @@ struct mlda_ctx {
     int32_t iter = 0;
     hipStream_t stream = nullptr;
     int n_cus = 0, lds_limit = 0;
-    bool far_weights = false;           // p* of the sampler's tiles in device memory (large K)
+    bool queued = false;                // the sampler's workgroups take tile after tile (large K)
+    bool far_weights = false;           // part of p* in device memory (larger K)
     int64_t reorder_by_tiles = kReorderByTiles;         // MLDA_REORDER_BY_TILES: other tokens than these
     bool wide_slot_offsets = false;     // MLDA_WIDE_SLOT_OFFSETS: 64-bit unit addresses whatever the buffer's size
     TileShape shape = {0, 0};           // MLDA_TILE_SHAPE="tokens,alone": this one whatever the sizes
     const TileShape* forced_shape() const { return shape.tokens > 0 ? &shape : nullptr; }
     float* far_pstar = nullptr;
+    int32_t near_topics = 0;            // those of them in LDS
     size_t sample_lds = 0;
     int32_t kept_passes = mlda::kLeastKeptPasses;       // K > 2048: of shared walks, see device_limits
     mlda::PhiView phi[2];                // [model_cur] is the current phi; two copies when streamed
@@ -767,12 +786,11 @@ struct mlda_ctx {
     mlda::Tile* tiles = nullptr;         // sampling tiles
     mlda::Tile* segs = nullptr;          // phi rebuild segments
     int32_t n_tiles = 0, n_segs = 0, n_split = 0, n_wide_tiles = 0;
-    int32_t n_single = 0;                // tiles taken one per workgroup; the rest in runs of run_tiles
+    int32_t n_single = 0;                // the tiles from this one on hold whole small words
     int32_t n_shared = 0;                // tiles taken by workgroups of several waves, the rest by a wave each
     int32_t counted_tiles = 0;           // see HostChunk
-    int32_t run_tiles = 1;
-    int32_t forced_run = 0;             // MLDA_RUN_TILES: runs of so many whatever the number of tiles
-    int64_t run_tokens = 0;              // tokens of the tiles taken in runs
+    int32_t forced_run = 0;             // MLDA_RUN_TILES: so few workgroups that each takes so many tiles on the whole
+    int64_t run_tokens = 0;              // tokens of the tiles that hold whole small words
 
     // large transfers between the device and the caller's memory (see through_ring): pinned pieces,
     // made by the first of them, one per worker thread
@@ -1099,22 +1117,6 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z, unsigned long long* started = 
     return launch_check("theta rebuild kernel");
 }
 
-// Small tiles that a workgroup takes one after the other: kRunTiles, fewer where that leaves the chip less than three
-// workgroups a CU.  Sampling launch, us, by run length:
-//                                              1     2     4     8     16
-//   2.4e4 tokens, 580 words, K = 9,819        53    52    52    82    150
-//   1.5e5, 890 words, K = 4,983              185   193   284   515    955
-//   4.9e5, 1,000 words, K = 12,736           126   107   102   112    192
-//   1.0e6, 3,000 words, K = 5,000            142   126   111   130    191
-//   5.0e5, 20,000 words, K = 3,000           395   332   303   290    312
-//   5.0e5, 20,000 words, K = 20,000         1848  1292   995   868    797
-int run_length(const mlda_ctx* c, int32_t n_small) {
-    if (c->run_tiles <= 1) return c->run_tiles;
-    if (c->forced_run > 0) return c->forced_run;
-    const int32_t want = 3 * c->n_cus;
-    return std::max(1, std::min(c->run_tiles, (n_small + want - 1) / want));
-}
-
 int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next, unsigned long long* started = nullptr) {
     if (c->n_tiles == 0) {
         if (started) hipLaunchKernelGGL(mlda::stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
@@ -1138,9 +1140,10 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next, unsigne
     a.seed = c->seed;
     a.iter = (uint32_t)(c->iter + 1);
     a.n_tiles = c->n_shared;
-    a.n_single = c->run_tiles > 1 ? c->n_single : c->n_shared;
-    a.run_tiles = run_length(c, a.n_tiles - a.n_single);
+    a.n_single = c->queued ? c->n_single : c->n_shared;
     a.far_pstar = c->far_pstar;
+    a.near_topics = c->near_topics;
+    a.next_tile = (uint32_t*)(c->ll_scalars + 4);
     // With few tiles the launch takes the time of one tile, and a small tile is done sooner by four waves side
     // by side than by one with a full batch; with more it is the work in all that counts, and later so where
     // rows are long and a pass takes few of a batch's tokens anyway.  Batches of at least 16 / 64 tokens,
@@ -1152,8 +1155,9 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next, unsigne
     const bool long_rows = c->K >= 200 && c->T >= 200 * c->D;
     a.min_batch = c->n_shared <= (long_rows ? 8 : 4) * c->n_cus ? mlda::kMinBatch * 2 : mlda::kWave;
     const int waves = sample_waves_for(c->K);
-    const int32_t grid = c->far_weights ? std::min<int32_t>(a.n_tiles, kFarStrips)
-                                        : a.n_single + (a.n_tiles - a.n_single + a.run_tiles - 1) / a.run_tiles;
+    int32_t grid = a.n_tiles;
+    if (c->queued) grid = std::min({grid, (waves == 12 ? 2 : 1) * c->n_cus, c->far_weights ? kFarStrips : INT32_MAX});
+    if (c->queued && c->forced_run > 0) grid = std::min(grid, (a.n_tiles + c->forced_run - 1) / c->forced_run);
     const bool near = slots_near(c->slots_bytes) && !c->wide_slot_offsets;
     const int weight_bytes = c->rows == RowKind::packed ? 4 : 8;
     const bool shares = !few_topics_of_many_tokens(c->K, c->T);
@@ -1163,7 +1167,7 @@ int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next, unsigne
     a.kept_sums = kept.sums;
     a.sum_slack = c->beta >= kSlackBeta ? 3u << 20 : 0u;
     const bool alone = c->T < kAloneDocs * c->D;
-    if (waves == 12) {
+    if (waves > 4) {
         a.kept_passes = c->kept_passes;
         a.kept_sums = mlda::lane_sums_for(c->kept_passes);
     } else if (weight_bytes != 8) {
@@ -1304,10 +1308,10 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     const int64_t dwords = (int64_t)(c->phi_bytes / 4);
     hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(blocks_for(dwords, 256)), dim3(256), 0, c->stream,
                        (int32_t*)c->phi[0].narrow, dwords, 0);
-    hipLaunchKernelGGL(mlda::zero_u64_kernel, dim3(1), dim3(1), 0, c->stream,
-                       (unsigned long long*)(c->ll_scalars + 3));     // launch_loglik's ticket
+    for (int i : {3, 4})        // launch_loglik's ticket, launch_sampler's next tile
+        hipLaunchKernelGGL(mlda::zero_u64_kernel, dim3(1), dim3(1), 0, c->stream, (unsigned long long*)(c->ll_scalars + i));
     RC_TRY(launch_check("model set-up kernels"));
-    if (c->sample_lds > 48 * 1024)          // (the workgroups of twelve waves only)
+    if (c->sample_lds > 48 * 1024)          // (the workgroups of twelve and sixteen waves only)
         for (bool short_docs : {false, true})
             for (int form = 0; form < 4; ++form)
                 // (the attribute belongs to the kernel, not to this context: contexts of different
@@ -1399,40 +1403,32 @@ int device_limits(mlda_ctx* c) {
     HIP_TRY(hipDeviceGetAttribute(&c->clock_khz, hipDeviceAttributeWallClockRate, dev));
     if (c->clock_khz <= 0) return fail(MLDA_EHIP, "the device names no rate for its clock");
     c->Kpad = kpad_for(c->K);
+    c->queued = sample_waves_for(c->K) > 4;
     c->far_weights = far_weights_for(c->K);
     // (a switch for tests: the 64-bit form is otherwise only reached by theta slots beyond 4 GiB)
     const char* wide = std::getenv("MLDA_WIDE_SLOT_OFFSETS");
     c->wide_slot_offsets = wide && wide[0] != '\0' && wide[0] != '0';
     (void)mlda::switch_numbers(std::getenv("MLDA_REORDER_BY_TILES"), 1, 0, INT64_MAX, &c->reorder_by_tiles);
-    // (likewise: small corpora have no runs)
+    // (likewise: in small corpora no workgroup takes a second tile)
     int64_t numbers[2];
     if (mlda::switch_numbers(std::getenv("MLDA_RUN_TILES"), 1, 1, kRunTiles, numbers)) c->forced_run = (int32_t)numbers[0];
     // (likewise: most shapes are otherwise only reached by corpora of millions of tokens)
     if (c->K <= 2048 && mlda::switch_numbers(std::getenv("MLDA_TILE_SHAPE"), 2, 0, 1024, numbers) && numbers[0] >= 16 &&
         numbers[1] <= numbers[0])
         c->shape = {(int32_t)numbers[0], (int32_t)numbers[1]};
-    c->sample_lds = c->far_weights ? mlda::sample_far_lds_bytes(c->Kpad, sample_waves_for(c->K))
-                                   : mlda::sample_lds_bytes(c->Kpad, sample_waves_for(c->K), sample_waves_for(c->K) == 4 ? 8 : 4);
+    c->near_topics = c->far_weights ? near_topics_for(c->K, std::min(kLdsPerWorkgroup, (size_t)c->lds_limit)) : 0;
+    const int waves = sample_waves_for(c->K);
+    c->sample_lds = c->far_weights ? mlda::sample_far_lds_bytes(c->Kpad, waves, std::max(c->near_topics, 16))
+                                   : c->queued ? queued_lds_bytes(c->K, waves) : mlda::sample_lds_bytes(c->Kpad, waves, 8);
     if (c->sample_lds > (size_t)c->lds_limit)
         return fail(MLDA_ENOTSUP, "K = " + std::to_string(c->K) + " needs " + std::to_string(c->sample_lds) +
                                       " bytes of LDS per workgroup, the device allows " +
                                       std::to_string(c->lds_limit));
-    // Large K, corpus resident (so that phi holds exactly the attached tokens): the many words
-    // of few tokens are sampled in runs, one workgroup turning p* of one word into p* of the
-    // next.  That takes a little more LDS; not if it would cost the CU its second workgroup.
-    c->run_tiles = 1;
-    const size_t with_runs = c->sample_lds + mlda::sample_run_lds_bytes(c->Kpad, sample_waves_for(c->K));
-    const size_t cu_lds = 160 * 1024;
-    if (sample_waves_for(c->K) == 12 && !c->far_weights && !c->streamed && with_runs <= (size_t)c->lds_limit &&
-        (2 * with_runs <= cu_lds || 2 * c->sample_lds > cu_lds)) {
-        c->sample_lds = with_runs;
-        c->run_tiles = kRunTiles;
-    }
     // the sums of more passes where that leaves a CU as many workgroups
-    if (sample_waves_for(c->K) == 12) {
-        const size_t room = 2 * c->sample_lds <= cu_lds ? cu_lds / 2 : (size_t)c->lds_limit;
+    if (c->queued && !c->far_weights) {
+        const size_t room = waves == 12 ? kLdsPerWorkgroup / 2 : (size_t)c->lds_limit;
         for (int passes = kMostKeptPasses; passes > mlda::kLeastKeptPasses; --passes) {
-            const size_t more = 12 * (size_t)(mlda::sample_wave_bytes(passes, mlda::lane_sums_for(passes)) -
+            const size_t more = (size_t)waves * (size_t)(mlda::sample_wave_bytes(passes, mlda::lane_sums_for(passes)) -
                                               mlda::sample_wave_bytes(mlda::kLeastKeptPasses, mlda::lane_sums_for(mlda::kLeastKeptPasses)));
             if (c->sample_lds + more > room) continue;
             c->sample_lds += more;
@@ -1773,7 +1769,7 @@ static int create_resident(mlda_ctx** out, const int64_t* doc_ptr, const int32_t
     if (rc == MLDA_OK) {
         try { c->chunks = std::vector<HostChunk>(1); } catch (const std::bad_alloc&) { rc = fail(MLDA_ENOMEM, "out of host memory"); }
     }
-    if (rc == MLDA_OK) rc = prepare_chunk(doc_ptr, word_ids, 0, D, V, K, false, false, c->run_tiles > 1, c->forced_shape(), c->chunks[0]);
+    if (rc == MLDA_OK) rc = prepare_chunk(doc_ptr, word_ids, 0, D, V, K, false, false, c->queued, c->forced_shape(), c->chunks[0]);
     if (rc == MLDA_OK) rc = check_theta_lds(c, c->chunks[0]);
     if (rc == MLDA_OK) rc = mark_wide_tiles(c, c->chunks[0]);
     const ModelLayout ML = model_layout(V, K, T, false);
@@ -2251,15 +2247,16 @@ int mlda_get_sampler_bytes(mlda_ctx* c, double* bytes, int32_t capacity_iters, i
         const double row_entries = c->D > 0 ? (double)ring[(size_t)(r % kEntryRing)] : 0.0;
         // per token: row slot 4, token id 4, old topic 2, new topic 2, row length 4
         // per tile: the word's row of phi, 2 K bytes, or 4 K for a word with 2^16 tokens or more;
-        // a tile that follows another in a run reads, instead of a row of phi, the topics of
+        // a tile that follows another one (small words, p* in LDS) reads, instead of a row of phi, the topics of
         // the previous tile's tokens and, for its own tokens, topic and cell of phi: 6 bytes
         // per token, counted as if both tiles had this tile's tokens (and as runs of kRunTiles)
-        const int32_t n_run_tiles = c->run_tiles > 1 ? c->n_tiles - c->n_single : 0;
-        const int32_t n_runs = n_run_tiles > 0 ? (n_run_tiles + c->run_tiles - 1) / c->run_tiles : 0;
+        const bool in_runs = c->queued && !c->far_weights;
+        const int32_t n_run_tiles = in_runs ? c->n_tiles - c->n_single : 0;
+        const int32_t n_runs = (n_run_tiles + kRunTiles - 1) / kRunTiles;
         const double staged_rows = (double)(c->counted_tiles - n_run_tiles + n_runs);
         bytes[i] = 16.0 * (double)c->T + entry_bytes * row_entries +
                    (double)c->K * (2.0 * staged_rows + 2.0 * (double)c->n_wide_tiles) +
-                   6.0 * (double)c->run_tokens;
+                   (in_runs ? 6.0 * (double)c->run_tokens : 0.0);
     }
     *n_iters = n;
     return MLDA_OK;

@@ -782,6 +782,23 @@ def test_large_k_in_runs(mlda, case, run, monkeypatch):
     test_edge_shapes(mlda, case)
 
 
+@pytest.mark.parametrize("chunks", [1, 2])
+@pytest.mark.parametrize("K,mean_len", [(11439, 40), (11440, 40), (11440, 120), (26159, 40), (26159, 120), (26160, 120)])
+def test_queued_tiles_at_the_edges_of_the_workgroups(mlda, K, mean_len, chunks, monkeypatch):
+    """The last K of twelve waves and the first of sixteen, the last whose p* fits LDS and the first that is split; a word
+    of more than 1,024 tokens, then small ones, sixteen tiles to a workgroup, so that p* is made from the word before's."""
+    monkeypatch.setenv("MLDA_RUN_TILES", "16")
+    V, alpha, beta = 400, 50.0 / K, 0.01
+    c = corpus_synth.tiny(D=9600 // mean_len, V=V, K=K, mean_len=mean_len, seed=K)
+    c.word_ids[: len(c.word_ids) // 6] = 7
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, beta, SEED, chunks=chunks)
+    model.init_random()
+    z = oracle.init_topics(c.T, K, SEED)
+    for it in (1, 2):
+        z = check_step(model, c, z, V, K, alpha, beta, SEED, it)
+    model.close()
+
+
 # (topics, lengths of the first documents, further documents of 3 tokens each)
 RANKED_CASES = [("two_per_wave", 1000, [0, 1, 31, 32, 33, 127, 128, 129, 383, 384, 385, 1500, 4000, 0, 700], 60),
                 ("two_per_wave_33", 33, [0, 1, 127, 128, 129, 383, 384, 385, 3000], 60),
