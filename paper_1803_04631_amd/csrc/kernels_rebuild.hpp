@@ -256,7 +256,9 @@ __device__ __forceinline__ void store_loglik(const double* partial, int n, const
     if (threadIdx.x == 0) *out = sum;
 }
 
-// (n_before: so many of the partials are there already, and are added to)
+// (n_before: so many of the partials are there already, and are added to.  kShared: written past the caches, and there when
+// the call returns to the first thread)
+template <bool kShared = false>
 __device__ __forceinline__ void block_partial_store(double v, double* partial, int n_before = 0) {
     __shared__ double wsum[16];
     const int lane = lane_id(), wave = (int)threadIdx.x / kWave;
@@ -266,20 +268,26 @@ __device__ __forceinline__ void block_partial_store(double v, double* partial, i
     if (threadIdx.x == 0) {
         double tot = 0.0;
         for (int w = 0; w < (int)blockDim.x / kWave; ++w) tot += wsum[w];
-        partial[blockIdx.x] = (int)blockIdx.x < n_before ? partial[blockIdx.x] + tot : tot;
+        if constexpr (kShared) {
+            __hip_atomic_store(partial + blockIdx.x, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        } else {
+            partial[blockIdx.x] = (int)blockIdx.x < n_before ? partial[blockIdx.x] + tot : tot;
+        }
     }
 }
 
 // lgG(c + a) - lgG(a) for the small integer counts c < kLgTable that make up almost all
 // cells comes from a table, filled once per context in global memory (kLgTable entries, then
-// lgG(a) itself): the kernels that use it call no lgamma and stay register-lean.
-constexpr int kLgTable = 1024;
+// lgG(a) itself, and lgG(b) of another number b): the kernels that use it call no lgamma and stay register-lean.
+constexpr int kLgTable = 1024, kLgTableSize = kLgTable + 2;
 
-__global__ void lg_table_kernel(double* table, double a) {
+__global__ void lg_table_kernel(double* table, double a, double b) {
     const double lg_a = lgamma(a);
     const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (c < kLgTable) table[c] = lgamma((double)c + a) - lg_a;
     if (c == kLgTable) table[c] = lg_a;
+    if (c == kLgTable + 1) table[c] = lgamma(b);
 }
 
 // lgG(x) for x >= 1024 by Stirling's series; the first omitted term is below 1e-24.
@@ -1093,7 +1101,7 @@ __global__ __launch_bounds__(kWave) void export_rows_kernel(const uint2* row_rec
 // The 16-bit cells are read eight at a time, the 32-bit cells of the wide rows four at a time
 // (empty cells add nothing, so the unused 16-bit rows of the wide words do not matter); the
 // table of small counts comes ready-made from global memory (lg_table: kLgTable entries, then
-// lgG(beta)), larger counts use Stirling's series.
+// lgG(beta) and lgG(V beta)), larger counts use Stirling's series.
 __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int64_t n_narrow_cells,
                                                                int64_t n_wide_cells,
                                                                const int32_t* n_k, int32_t K,
@@ -1106,6 +1114,13 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
     // (ticket: null if loglik_value_kernel follows)
     stamp_start(started);
     __shared__ double table[kLgTable];
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t n_octs = n_narrow_cells / 8;
+    const uint4* octs = reinterpret_cast<const uint4*>(phi.narrow);
+    // (on its way while the table is staged: a small launch has no other)
+    uint4 first_oct = make_uint4(0u, 0u, 0u, 0u);
+    if (first < n_octs) first_oct = octs[first];
     for (int c = (int)threadIdx.x; c < kLgTable; c += 256) table[c] = lg_table[c];
     const double lg_beta = lg_table[kLgTable];
     __syncthreads();
@@ -1117,12 +1132,13 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
         }
     };
     auto add_pair = [&](uint32_t two) { add_cell((int)(two & 0xffffu)); add_cell((int)(two >> 16)); };
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    auto add_oct = [&](const uint4& v) {
+        if (__ballot((v.x | v.y | v.z | v.w) != 0) == 0) return;
+        add_pair(v.x); add_pair(v.y); add_pair(v.z); add_pair(v.w);
+    };
     {
-        const int64_t n_octs = n_narrow_cells / 8;
-        const uint4* octs = reinterpret_cast<const uint4*>(phi.narrow);
-        int64_t i = first;
+        add_oct(first_oct);
+        int64_t i = first + stride;
         for (; i + 3 * stride < n_octs; i += 4 * stride) {     // four loads in flight per thread
             const uint4 v0 = octs[i], v1 = octs[i + stride], v2 = octs[i + 2 * stride],
                         v3 = octs[i + 3 * stride];
@@ -1134,11 +1150,7 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
             add_pair(v2.x); add_pair(v2.y); add_pair(v2.z); add_pair(v2.w);
             add_pair(v3.x); add_pair(v3.y); add_pair(v3.z); add_pair(v3.w);
         }
-        for (; i < n_octs; i += stride) {
-            const uint4 v = octs[i];
-            if (__ballot((v.x | v.y | v.z | v.w) != 0) == 0) continue;
-            add_pair(v.x); add_pair(v.y); add_pair(v.z); add_pair(v.w);
-        }
+        for (; i < n_octs; i += stride) add_oct(octs[i]);
     }
     {
         const int64_t n_quads = n_wide_cells / 4;
@@ -1155,23 +1167,24 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
         add_cell(i < n_narrow_cells ? (int)phi.narrow[i] : 0);
         const int64_t j = n_wide_cells / 4 * 4 + (int64_t)threadIdx.x;
         add_cell(j < n_wide_cells ? phi.wide[j] : 0);
-        const double lg_vb = lgamma(v_beta);
-        for (int k = (int)threadIdx.x; k < K; k += (int)blockDim.x)
-            acc += lg_vb - lgamma((double)n_k[k] + v_beta);
+        const double lg_vb = lg_table[kLgTable + 1];
+        for (int k = (int)threadIdx.x; k < K; k += (int)blockDim.x) {
+            const double x = (double)n_k[k] + v_beta;
+            acc += lg_vb - (x >= 1024.0 ? lgamma_large(x) : lgamma(x));
+        }
     }
-    block_partial_store(acc, partial);
-    // A small launch needs no other: the workgroup that finishes last adds up.  (Its fences take
-    // longer than a launch once there are many workgroups: 2,048 of them 52 us against 26 with
-    // loglik_value_kernel; 50 of them 12 against 19.)
-    if (!ticket) return;
+    if (!ticket) {
+        block_partial_store(acc, partial);
+        return;
+    }
+    // A small launch needs no other: the workgroup that finishes last adds up, from partials written and read past
+    // the caches.  With fences, which write the caches back, 1.6e5 cells took 9.7 us, now 8.8.  Tickets take their turns at
+    // one address: 489 workgroups 13.1 us, with loglik_value_kernel 12.3; 977 19.5 and 12.2.
+    block_partial_store<true>(acc, partial);
     __shared__ bool last;
-    if (threadIdx.x == 0) {
-        __threadfence();
-        last = atomicAdd(ticket, 1u) == gridDim.x - 1;
-    }
+    if (threadIdx.x == 0) last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     __syncthreads();
     if (!last) return;
-    __threadfence();
     if (threadIdx.x == 0) *ticket = 0u;               // for the next launch
     store_loglik<true>(partial, (int)gridDim.x, theta_partial, n_theta, theta_sum, doc_term, out);
 }

@@ -396,7 +396,7 @@ ModelLayout model_layout(int32_t V, int32_t K, int64_t T, bool two_phi) {
     L.n_k[1] = two_phi ? put((size_t)K * 4) : L.n_k[0];
     L.ll_partial = put((size_t)(2 * kLoglikBlocks + 2 * kMaxThetaGrid) * 8);
     L.ll_scalars = put(5 * 8);      // value, theta sum, document term, the word side's ticket, the sampler's next tile
-    L.lg_table = put((size_t)(mlda::kLgTable + 1) * 8 * 2);   // one for alpha, one for beta
+    L.lg_table = put((size_t)mlda::kLgTableSize * 8 * 2);   // one for alpha, one for beta
     L.row_entries = put((size_t)kEntryRing * 8);
     L.stamps = put((size_t)kStampBytes);
     L.far_pstar = put(far_weights_for(K) ? (size_t)kFarStrips * (size_t)kpad_for(K) * 4 : 0);
@@ -1314,16 +1314,16 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     if (!c->streamed && c->K <= kSpareTotals) c->n_k[1] = (int32_t*)(c->ll_partial + kLoglikBlocks);
     c->ll_scalars = (double*)(base + ML.ll_scalars);
     c->lg_table = (double*)(base + ML.lg_table);
-    c->lg_table_beta = c->lg_table + (mlda::kLgTable + 1);
+    c->lg_table_beta = c->lg_table + mlda::kLgTableSize;
     c->row_entries = (unsigned long long*)(base + ML.row_entries);
     c->visited = (unsigned long long*)(c->ll_partial + 2 * kLoglikBlocks + kMaxThetaGrid);
     c->stamps = (unsigned long long*)(base + ML.stamps);
     c->far_pstar = (float*)(base + ML.far_pstar);
 
-    hipLaunchKernelGGL(mlda::lg_table_kernel, dim3(blocks_for(mlda::kLgTable + 1, 256)), dim3(256), 0,
-                       c->stream, c->lg_table, c->alpha);
-    hipLaunchKernelGGL(mlda::lg_table_kernel, dim3(blocks_for(mlda::kLgTable + 1, 256)), dim3(256), 0,
-                       c->stream, c->lg_table_beta, c->beta);
+    hipLaunchKernelGGL(mlda::lg_table_kernel, dim3(blocks_for(mlda::kLgTableSize, 256)), dim3(256), 0,
+                       c->stream, c->lg_table, c->alpha, (double)c->K * c->alpha);
+    hipLaunchKernelGGL(mlda::lg_table_kernel, dim3(blocks_for(mlda::kLgTableSize, 256)), dim3(256), 0,
+                       c->stream, c->lg_table_beta, c->beta, (double)c->V * c->beta);
     // rows of words without tokens are never written again: start phi at zero
     const int64_t dwords = (int64_t)(c->phi_bytes / 4);
     hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(blocks_for(dwords, 256)), dim3(256), 0, c->stream,
