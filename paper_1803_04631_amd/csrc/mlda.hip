@@ -371,6 +371,13 @@ ChunkLayout chunk_layout_bound(int64_t D, int64_t T, int32_t V, int32_t K, bool 
     return chunk_layout(D, T, slots, n_tiles, n_segs, (size_t)V, streamed);
 }
 
+// Large transfers between the device and the caller's memory, see on_workers.
+constexpr int kRingWorkers = 8;
+constexpr size_t kRingPiece = (size_t)2 << 20;
+constexpr size_t kRingFrom = (size_t)8 << 20;
+constexpr int kCopyBlocks = 64;         // workgroups of copy_to_host_kernel (32 to 128: the same)
+constexpr size_t kRingFlag = 64;        // bytes from one flag to the next, behind the pieces
+
 // The model and the scratch of the reductions.
 // phi[i] is one copy of the model: the 16-bit matrix [V][K], then room for the int32 rows of
 // the words with 2^16 tokens or more, of which a corpus of T tokens has at most T / 2^16.
@@ -395,7 +402,8 @@ ModelLayout model_layout(int32_t V, int32_t K, int64_t T, bool two_phi) {
     L.n_k[0] = put((size_t)K * 4);
     L.n_k[1] = two_phi ? put((size_t)K * 4) : L.n_k[0];
     L.ll_partial = put((size_t)(2 * kLoglikBlocks + 2 * kMaxThetaGrid) * 8);
-    L.ll_scalars = put(5 * 8);      // value, theta sum, document term, the word side's ticket, the sampler's next tile
+    // value, theta sum, document term, the word side's ticket, the sampler's next tile; the workers' counters (copy_to_host_kernel)
+    L.ll_scalars = put((size_t)(5 + kRingWorkers) * 8);
     L.lg_table = put((size_t)mlda::kLgTableSize * 8 * 2);   // one for alpha, one for beta
     L.row_entries = put((size_t)kEntryRing * 8);
     L.stamps = put((size_t)kStampBytes);
@@ -796,7 +804,7 @@ struct mlda_ctx {
     int32_t forced_run = 0;             // MLDA_RUN_TILES: so few workgroups that each takes so many tiles on the whole
     int64_t run_tokens = 0;              // tokens of the tiles that hold whole small words
 
-    // large transfers between the device and the caller's memory (see through_ring): pinned pieces,
+    // large transfers between the device and the caller's memory (see on_workers): pinned pieces,
     // made by the first of them, one per worker thread
     unsigned char* ring = nullptr;
     std::vector<hipEvent_t> ring_events;
@@ -1328,8 +1336,9 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     const int64_t dwords = (int64_t)(c->phi_bytes / 4);
     hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(blocks_for(dwords, 256)), dim3(256), 0, c->stream,
                        (int32_t*)c->phi[0].narrow, dwords, 0);
-    for (int i : {3, 4})        // launch_loglik's ticket, launch_sampler's next tile
-        hipLaunchKernelGGL(mlda::zero_u64_kernel, dim3(1), dim3(1), 0, c->stream, (unsigned long long*)(c->ll_scalars + i));
+    // launch_loglik's ticket, launch_sampler's next tile, copy_to_host_kernel's counters
+    hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(1), dim3(256), 0, c->stream, (int32_t*)(c->ll_scalars + 3),
+                       (int64_t)(2 + kRingWorkers) * 2, 0);
     RC_TRY(launch_check("model set-up kernels"));
     if (c->sample_lds > 48 * 1024)          // (the workgroups of twelve and sixteen waves only)
         for (bool short_docs : {false, true})
@@ -1487,25 +1496,25 @@ void destroy(mlda_ctx* c) {
 // 50.  Here kRingWorkers threads each own a pinned piece of kRingPiece bytes and take every
 // kRingWorkers-th piece of the transfer: the copies queue up on the context's stream, and what a
 // piece needs on the host (a copy, a widening) is done by its thread while the others' are on
-// their way.  From kRingFrom bytes on (four pieces: below, too few
+// their way.  What comes from the device comes by halves of a piece, through a kernel that sets a flag, each worker's next
+// half on its way while it takes this one: 198 MB of assignments 6.7 -> 5.7 ms, 1.5 GB 51.4 -> 46.8, 12.6 MB 0.52 -> 0.41
+// (pieces of 4 MB: 5.4, 44.9, 0.44, and twice the pinned memory to be made by the first).  From kRingFrom bytes on (four pieces: below, too few
 // threads have work; with 32 MB as the line, five iterations on 6.3e6 tokens and their 12.6 MB took 4.42 ms,
 // now 4.12, the first time on a new context 5.36 and 5.17).  Ten iterations on 7.4e8 tokens and their assignments fetched: 535 -> 432 ms; five on
 // 9.9e7: 59.5 -> 45.2 ms (first time on a new context 58 -> 45 ms).  A context on the static workspace, and one for which no pinned memory is left,
 // does without.
-constexpr int kRingWorkers = 8;
-constexpr size_t kRingPiece = (size_t)2 << 20;
-constexpr size_t kRingFrom = (size_t)8 << 20;
 
 bool ring_ready(mlda_ctx* c) {
     if (c->ring) return true;
     if (c->ring_failed || c->static_device >= 0) return false;
     c->ring_failed = true;
     void* p = nullptr;
-    if (hipHostMalloc(&p, kRingWorkers * kRingPiece, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&p, kRingWorkers * (kRingPiece + 2 * kRingFlag), hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
     c->ring = (unsigned char*)p;
+    std::memset(c->ring + kRingWorkers * kRingPiece, 0, kRingWorkers * 2 * kRingFlag);
     try { c->ring_events.reserve(kRingWorkers); } catch (const std::bad_alloc&) {}
     while (c->ring_events.capacity() >= (size_t)kRingWorkers && c->ring_events.size() < (size_t)kRingWorkers) {
         hipEvent_t ev;
@@ -1521,9 +1530,15 @@ bool ring_ready(mlda_ctx* c) {
     return true;
 }
 
-// per_piece(pinned piece, event, offset, bytes) -> hipError_t for every piece, on the worker threads.
+unsigned char* ring_piece(const mlda_ctx* c, int w) { return c->ring + (size_t)w * kRingPiece; }
+// What copy_to_host_kernel sets: a flag for each half of a piece.
+volatile uint32_t* ring_flag(const mlda_ctx* c, int w, int half) {
+    return (volatile uint32_t*)(c->ring + kRingWorkers * kRingPiece + (size_t)(2 * w + half) * kRingFlag);
+}
+
+// work(worker) -> hipError_t on the worker threads.
 template <class F>
-int through_ring(mlda_ctx* c, size_t bytes, F&& per_piece) {
+int on_workers(mlda_ctx* c, F&& work) {
     int device = 0;
     HIP_TRY(hipGetDevice(&device));
     // This handle names another stream in every thread: what the caller's has queued must be done
@@ -1533,8 +1548,7 @@ int through_ring(mlda_ctx* c, size_t bytes, F&& per_piece) {
     for (hipError_t& e : first_error) e = hipSuccess;
     const bool ran = parallel_chunks(kRingWorkers, [&](int w) {
         hipError_t e = hipSetDevice(device);
-        for (size_t at = (size_t)w * kRingPiece; e == hipSuccess && at < bytes; at += kRingWorkers * kRingPiece)
-            e = per_piece(c->ring + (size_t)w * kRingPiece, c->ring_events[(size_t)w], at, std::min(kRingPiece, bytes - at));
+        if (e == hipSuccess) e = work(w);
         if (e != hipSuccess) (void)hipStreamSynchronize(c->stream);     // (no copy into the piece is left)
         first_error[w] = e;
     });
@@ -1545,23 +1559,64 @@ int through_ring(mlda_ctx* c, size_t bytes, F&& per_piece) {
     return MLDA_OK;
 }
 
+// Device memory into the caller's by one copy, done on return.  (One call: with hipMemcpyAsync and a wait behind it the
+// 8 bytes of the likelihood took 21 us, now 13.)
+int fetch_now(mlda_ctx* c, void* host, const void* dev, size_t bytes) {
+    if (bytes > 0) HIP_TRY(hipMemcpyWithStream(host, dev, bytes, hipMemcpyDeviceToHost, c->stream));
+    else HIP_TRY(hipStreamSynchronize(c->stream));
+    return MLDA_OK;
+}
+
+// A copy of `n` bytes of device memory (at a multiple of 16 bytes) into half `half` of worker w's piece is queued ...
+hipError_t queue_copy(mlda_ctx* c, int w, int half, const unsigned char* dev, size_t n, uint32_t value) {
+    void *piece = nullptr, *flag = nullptr;
+    hipError_t e = hipHostGetDevicePointer(&piece, ring_piece(c, w) + half * (kRingPiece / 2), 0);
+    if (e == hipSuccess) e = hipHostGetDevicePointer(&flag, (void*)ring_flag(c, w, half), 0);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(mlda::copy_to_host_kernel, dim3(kCopyBlocks), dim3(256), 0, c->stream, dev, (unsigned char*)piece, (int64_t)n,
+                       (uint32_t*)(c->ll_scalars + 5 + w), (uint32_t*)flag, value);
+    return hipGetLastError();
+}
+// ... and has arrived.
+hipError_t await_copy(mlda_ctx* c, int w, int half, uint32_t value) {
+    volatile uint32_t* flag = ring_flag(c, w, half);
+    // (what the stream holds in front of it may take long, and a launch that failed never sets the flag)
+    for (int spins = 0; *flag != value; ++spins) {
+        if (spins < 20000) { for (int i = 0; i < 16; ++i) __builtin_ia32_pause(); continue; }
+        const hipError_t e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return e;
+        if (*flag != value) return hipErrorLaunchFailure;
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    return hipSuccess;
+}
+
 // Device memory, handed to take(offset, piece, bytes) piece by piece: on several threads at once, or
 // as a whole through `whole`, which then must hold all of it (made here).
 template <class F>
 int fetch_pieces(mlda_ctx* c, const void* dev, size_t bytes, F&& take) {
     if (bytes == 0) return MLDA_OK;
     if (bytes >= kRingFrom && ring_ready(c))
-        return through_ring(c, bytes, [&](unsigned char* piece, hipEvent_t ev, size_t at, size_t n) {
-            hipError_t e = hipMemcpyAsync(piece, (const unsigned char*)dev + at, n, hipMemcpyDeviceToHost, c->stream);
-            if (e == hipSuccess) e = hipEventRecord(ev, c->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(ev);
-            if (e == hipSuccess) take(at, (const unsigned char*)piece, n);
+        // each worker's next half piece is on its way while this one is taken
+        return on_workers(c, [&](int w) {
+            constexpr size_t kHalf = kRingPiece / 2;
+            uint32_t value[2] = {*ring_flag(c, w, 0), *ring_flag(c, w, 1)};
+            auto queue = [&](size_t at, int half) {
+                return at < bytes ? queue_copy(c, w, half, (const unsigned char*)dev + at, std::min(kHalf, bytes - at), ++value[half])
+                                  : hipSuccess;
+            };
+            size_t at = (size_t)w * kHalf;
+            hipError_t e = queue(at, 0);
+            for (int half = 0; e == hipSuccess && at < bytes; half ^= 1, at += kRingWorkers * kHalf) {
+                e = queue(at + kRingWorkers * kHalf, half ^ 1);
+                if (e == hipSuccess) e = await_copy(c, w, half, value[half]);
+                if (e == hipSuccess) take(at, (const unsigned char*)ring_piece(c, w) + half * kHalf, std::min(kHalf, bytes - at));
+            }
             return e;
         });
     std::vector<unsigned char> whole;
     try { whole.resize(bytes); } catch (const std::bad_alloc&) { return fail(MLDA_ENOMEM, "out of host memory"); }
-    HIP_TRY(hipMemcpyAsync(whole.data(), dev, bytes, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    RC_TRY(fetch_now(c, whole.data(), dev, bytes));
     take(0, (const unsigned char*)whole.data(), bytes);
     return MLDA_OK;
 }
@@ -1572,17 +1627,19 @@ int fetch(mlda_ctx* c, void* host, const void* dev, size_t bytes) {
         return fetch_pieces(c, dev, bytes, [&](size_t at, const unsigned char* piece, size_t n) {
             std::memcpy((unsigned char*)host + at, piece, n);
         });
-    if (bytes > 0) HIP_TRY(hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return MLDA_OK;
+    return fetch_now(c, host, dev, bytes);
 }
 int send(mlda_ctx* c, void* dev, const void* host, size_t bytes) {
     if (bytes >= kRingFrom && ring_ready(c))
-        return through_ring(c, bytes, [&](unsigned char* piece, hipEvent_t ev, size_t at, size_t n) {
-            std::memcpy(piece, (const unsigned char*)host + at, n);
-            hipError_t e = hipMemcpyAsync((unsigned char*)dev + at, piece, n, hipMemcpyHostToDevice, c->stream);
-            if (e == hipSuccess) e = hipEventRecord(ev, c->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(ev);
+        return on_workers(c, [&](int w) {
+            hipError_t e = hipSuccess;
+            for (size_t at = (size_t)w * kRingPiece; e == hipSuccess && at < bytes; at += kRingWorkers * kRingPiece) {
+                const size_t n = std::min(kRingPiece, bytes - at);
+                std::memcpy(ring_piece(c, w), (const unsigned char*)host + at, n);
+                e = hipMemcpyAsync((unsigned char*)dev + at, ring_piece(c, w), n, hipMemcpyHostToDevice, c->stream);
+                if (e == hipSuccess) e = hipEventRecord(c->ring_events[(size_t)w], c->stream);
+                if (e == hipSuccess) e = hipEventSynchronize(c->ring_events[(size_t)w]);
+            }
             return e;
         });
     if (bytes > 0) HIP_TRY(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, c->stream));
@@ -2134,9 +2191,7 @@ int mlda_get_word_topic(mlda_ctx* c, int32_t* n_wk) {
 int mlda_get_topic_totals(mlda_ctx* c, int32_t* n_k) {
     RC_TRY(need_state(c));
     if (!n_k) return fail(MLDA_EINVAL, "n_k is null");
-    HIP_TRY(hipMemcpyAsync(n_k, current_n_k(c), (size_t)c->K * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return MLDA_OK;
+    return fetch_now(c, n_k, current_n_k(c), (size_t)c->K * 4);
 }
 
 int mlda_get_doc_topic_nnz(mlda_ctx* c, int64_t* nnz) {
@@ -2201,9 +2256,7 @@ int mlda_get_loglik(mlda_ctx* c, double* ll) {
             RC_TRY(launch_loglik(c));
         }
     }
-    HIP_TRY(hipMemcpyAsync(ll, c->ll_scalars, 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return MLDA_OK;
+    return fetch_now(c, ll, c->ll_scalars, 8);
 }
 
 int mlda_get_timing(mlda_ctx* c, double* ms, int32_t capacity_iters, int32_t* n_iters) {
