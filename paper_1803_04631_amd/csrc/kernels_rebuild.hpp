@@ -50,25 +50,24 @@ __global__ void zero_sums_kernel(const int32_t* split_words, PhiView phi, int32_
     else phi.narrow[(size_t)v * (size_t)K + k] = 0;
 }
 
-// f(topic) for the tokens [lo, hi) of z, by 256 threads: 16 bytes (eight tokens) per load, four loads
-// in flight per thread, single tokens only before the first and after the last aligned eight.
-template <class F>
-__device__ __forceinline__ void for_topics(const uint16_t* z, int64_t lo, int64_t hi, F&& f) {
-    const int tid = (int)threadIdx.x;
+// f(topic) for the tokens [lo, hi) of z, by kThreads threads of which this is number `me`: 16 bytes (eight tokens) per load,
+// four loads in flight per thread, single tokens only before the first and after the last aligned eight.
+template <int kThreads, class F>
+__device__ __forceinline__ void for_topics(const uint16_t* z, int64_t lo, int64_t hi, int me, F&& f) {
     const int64_t lo8 = min((lo + 7) & ~(int64_t)7, hi), hi8 = max(hi & ~(int64_t)7, lo8);
     const int n_head = (int)(lo8 - lo), n_ends = n_head + (int)(hi - hi8);      // at most 14
     int end_topic = -1;
-    if (tid < n_ends) end_topic = (int)z[tid < n_head ? lo + tid : hi8 + (tid - n_head)];
+    if (me < n_ends) end_topic = (int)z[me < n_head ? lo + me : hi8 + (me - n_head)];
     auto add_pair = [&](uint32_t two) { f((int)(two & 0xffffu)); f((int)(two >> 16)); };
     auto add_eight = [&](const uint4& v) { add_pair(v.x); add_pair(v.y); add_pair(v.z); add_pair(v.w); };
     const uint4* eights = reinterpret_cast<const uint4*>(z + lo8);
     const int64_t n8 = (hi8 - lo8) / 8;
-    int64_t i = tid;
-    for (; i + 768 < n8; i += 1024) {
-        const uint4 v0 = eights[i], v1 = eights[i + 256], v2 = eights[i + 512], v3 = eights[i + 768];
+    int64_t i = me;
+    for (; i + 3 * kThreads < n8; i += 4 * kThreads) {
+        const uint4 v0 = eights[i], v1 = eights[i + kThreads], v2 = eights[i + 2 * kThreads], v3 = eights[i + 3 * kThreads];
         add_eight(v0); add_eight(v1); add_eight(v2); add_eight(v3);
     }
-    for (; i < n8; i += 256) add_eight(eights[i]);
+    for (; i < n8; i += kThreads) add_eight(eights[i]);
     if (end_topic >= 0) f(end_topic);
 }
 
@@ -81,7 +80,7 @@ __device__ __forceinline__ void add_topic_totals(int32_t* hist, const uint16_t* 
     const int tid = (int)threadIdx.x;
     for (int k = tid; k < n; k += 256) hist[k] = 0;
     __syncthreads();
-    for_topics(z, lo, hi, [&](int k) {
+    for_topics<256>(z, lo, hi, tid, [&](int k) {
         if (kRange) k -= k_lo;
         if (!kRange || (unsigned)k < (unsigned)n) atomicAdd(&hist[k], 1);
     });
@@ -97,52 +96,43 @@ __device__ __forceinline__ void add_topic_totals(int32_t* hist, const uint16_t* 
 // the word's row outright if the segment is the whole word, else adds its non-zero bins
 // to the row.  A narrow row is written by dwords of two cells and more, and added to by dwords; the word
 // has fewer than 2^16 tokens, so no sum carries into the neighbouring cell.
-// Bound by the LDS atomics, 33 to 50 cycles of a CU for a wave's 64 tokens: 7.4e8 tokens at K = 1,000
-// take 0.52 ms, 3.4 TB/s (0.62 with 2-byte loads and stores; 0.79 with a wide row's cells added in pairs).
+// Bound by the LDS atomics, 33 to 50 cycles of a CU for a wave's 64 tokens, and small corpora by how fast workgroups
+// start: 7.4e8 tokens at K = 1,000 take 0.60 ms with their totals, 1e6 at 128 14 us (0.71 and 21 with a workgroup per segment).
 // kPacked: two topics share a dword of LDS (a segment's counts fit 16 bits), so that every K fits at once.
 // More atomics then meet at one address: 1e6 to 1e7 tokens at K = 128 ... 1,537 take 3 to 9 % longer than
 // with a dword per topic.  Where that takes so much LDS that fewer workgroups fit a CU it is the slower one:
 // 2e7 tokens at K = 4,200 90 us (packed 92), 8,000 131 (123), 16,000 158 (147), 30,000 290 (250).
-// The workgroups from n_segs on do what else one launch can (each launch costs a small corpus 5 us):
+// The segments from n_shared on are counted by a wave each, four of them to a workgroup.
+// The workgroups behind those do what else one launch can (each launch costs a small corpus 5 us):
 // n_totals of them add the topic totals of a share of the tokens to n_k (which is zero on entry), and the
 // last one adds up the counts that the theta rebuild before left (`visited`, to visited_sum; null: none).
-template <bool kPacked>
-__global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t n_segs, const uint16_t* z,
-                                                       PhiView phi, int32_t K, int64_t T, int32_t n_totals, int32_t* n_k,
-                                                       const unsigned long long* visited, int n_visited,
-                                                       unsigned long long* visited_sum, unsigned long long* started) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    stamp_start(started);
-    const int tid = (int)threadIdx.x;
-    if ((int)blockIdx.x >= n_segs) {
-        const int part = (int)blockIdx.x - n_segs;
-        if (part < n_totals) {
-            const int64_t per = ((T + n_totals - 1) / n_totals + 7) & ~(int64_t)7;
-            const int64_t lo = min(per * part, T);
-            add_topic_totals<false>(reinterpret_cast<int32_t*>(lds), z, lo, min(lo + per, T), n_k, 0, K);
-        } else if (visited_sum) {
-            store_visited_sum(visited, n_visited, visited_sum);
-        }
-        return;
-    }
+
+// Up to which K a topic has a dword, and the LDS bytes of a segment's counters (the totals' counters are dwords).
+constexpr int32_t kPhiDwordTopics = 4096;
+__host__ __device__ inline size_t phi_counter_bytes(int32_t K) {
+    return ((K <= kPhiDwordTopics ? (size_t)K * 4 : (size_t)((K + 1) / 2) * 4) + 15) & ~(size_t)15;
+}
+// One segment by kThreads threads, of which this is number `me`; `lds` is theirs, `sync` makes them wait for each other.
+template <bool kPacked, int kThreads, class Sync>
+__device__ __forceinline__ void phi_segment(unsigned char* lds, const Tile& tl, const uint16_t* z, const PhiView& phi, int32_t K,
+                                            int me, Sync&& sync) {
     uint32_t* hist = reinterpret_cast<uint32_t*>(lds);
-    const Tile tl = segs[blockIdx.x];
     const int wide_row = phi.wide_row[tl.word];
     const int n_counters = kPacked ? (K + 1) / 2 : K;
-    for (int i = tid; i < (n_counters + 3) / 4; i += 256) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-    for_topics(z, tl.begin, (int64_t)tl.begin + tl.count, [&](int k) {
+    for (int i = me; i < (n_counters + 3) / 4; i += kThreads) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+    sync();
+    for_topics<kThreads>(z, tl.begin, (int64_t)tl.begin + tl.count, me, [&](int k) {
         if (kPacked) atomicAdd(&hist[k >> 1], 1u << ((k & 1) << 4));
         else atomicAdd(&hist[k], 1u);
     });
-    __syncthreads();
+    sync();
     auto count_of = [&](int k) -> uint32_t {        // (0 outside the row)
         if ((unsigned)k >= (unsigned)K) return 0u;
         return kPacked ? (hist[k >> 1] >> ((k & 1) << 4)) & 0xffffu : hist[k];
     };
     if (wide_row >= 0) {                // (2^16 tokens or more: never a whole word)
         int32_t* row = phi.wide + (size_t)wide_row * (size_t)K;
-        for (int k = tid; k < K; k += 256) {
+        for (int k = me; k < K; k += kThreads) {
             const int c = (int)count_of(k);
             if (c != 0) atomicAdd(&row[k], c);
         }
@@ -152,7 +142,7 @@ __global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t
     if (tl.whole && (K & 7) == 0) {     // (every row starts at a multiple of 16 bytes)
         uint4* row = reinterpret_cast<uint4*>(phi.narrow + cell0);
         const uint4* counts = reinterpret_cast<const uint4*>(lds);
-        for (int i = tid; i < K / 8; i += 256) {
+        for (int i = me; i < K / 8; i += kThreads) {
             if (kPacked) {
                 row[i] = counts[i];
             } else {
@@ -166,7 +156,7 @@ __global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t
     // the row's first cell only (as the last may hold its last only; the other half is another row's).
     const int odd = (int)(cell0 & 1);
     uint32_t* dwords = reinterpret_cast<uint32_t*>(phi.narrow) + (cell0 >> 1);
-    for (int i = tid; i < (K + odd + 1) / 2; i += 256) {
+    for (int i = me; i < (K + odd + 1) / 2; i += kThreads) {
         const int k = 2 * i - odd;
         const uint32_t two = count_of(k) | count_of(k + 1) << 16;
         if (!tl.whole) {
@@ -180,12 +170,39 @@ __global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t
         }
     }
 }
-// Up to which K a topic has a dword, and the LDS bytes of a launch (the totals' counters are dwords).
-constexpr int32_t kPhiDwordTopics = 4096;
-__host__ __device__ inline size_t phi_tile_lds_bytes(int32_t K) {
-    return ((K <= kPhiDwordTopics ? (size_t)K * 4 : (size_t)((K + 1) / 2) * 4) + 15) & ~(size_t)15;
+// What the lanes of a wave wrote to LDS is there for all of them.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-
+constexpr int kPhiWaves = 4;        // waves of a workgroup
+template <bool kPacked>
+__global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t n_segs, int32_t n_shared, const uint16_t* z,
+                                                       PhiView phi, int32_t K, int64_t T, int32_t n_totals, int32_t* n_k,
+                                                       const unsigned long long* visited, int n_visited,
+                                                       unsigned long long* visited_sum, unsigned long long* started) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    stamp_start(started);
+    const int tid = (int)threadIdx.x, n_solo_groups = (n_segs - n_shared + kPhiWaves - 1) / kPhiWaves;
+    const int block = (int)blockIdx.x;
+    if (block < n_shared) {
+        phi_segment<kPacked, 256>(lds, segs[block], z, phi, K, tid, [] { __syncthreads(); });
+    } else if (block < n_shared + n_solo_groups) {
+        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), i = n_shared + (block - n_shared) * kPhiWaves + wave;
+        if (i < n_segs)
+            phi_segment<kPacked, kWave>(lds + (size_t)wave * phi_counter_bytes(K), segs[i], z, phi, K, tid & (kWave - 1), [] { wave_sync(); });
+    } else {
+        const int part = block - n_shared - n_solo_groups;
+        if (part < n_totals) {
+            const int64_t per = ((T + n_totals - 1) / n_totals + 7) & ~(int64_t)7;
+            const int64_t lo = min(per * part, T);
+            add_topic_totals<false>(reinterpret_cast<int32_t*>(lds), z, lo, min(lo + per, T), n_k, 0, K);
+        } else if (visited_sum) {
+            store_visited_sum(visited, n_visited, visited_sum);
+        }
+    }
+}
 // n_k[k] = number of tokens with topic k, as a launch of its own: each workgroup over a contiguous
 // share of the tokens; n_k must be zero on entry.
 // kRange: K counters do not fit a workgroup's LDS; the launch then covers the topics

@@ -246,6 +246,17 @@ TileShape tile_shape_for(int32_t K, int64_t T) {
     return {1024, 0};
 }
 constexpr int kPhiSegment = 16384;    // tokens one workgroup histograms for the phi rebuild
+// Up to how many tokens a wave counts a segment by itself: workgroups are started one in 1.3 ns, and most words have fewer
+// tokens than four waves lanes.  All segments where they are so many that the longest does not matter, none where the
+// counters of four take a CU's LDS.  Rebuild of phi, us, segments up to 0 / 64 / 256 / 1,024 / 16,384 tokens by a wave each:
+//   1e5 tokens, K = 32        5.2   5.1   5.2   5.2   8.5      2e6, K = 2,000        89    70    68    67    66
+//   1e6, K = 16, 60,000 words  16    12    11    11    15      2e7, K = 500         131    88    78    74    72
+//   1e6, K = 128               21    14    13    12    14      9.9e7, K = 1,000     316   312   296   271   264
+//   6.3e6, K = 1,537           59    50    46    45    47      7.4e8, K = 1,000     708   702   682   648   598
+//   2e6, K = 4,000            133   119   117   116   115      2e6, K = 8,000       213   213   213   212   212
+int solo_segment_for(int32_t K, int64_t T, int64_t n_segs) {
+    return K > mlda::kPhiDwordTopics ? 0 : T > 10000000 && n_segs >= 16384 ? kPhiSegment : 1024;
+}
 constexpr int32_t kHistTopics = 32768; // 32-bit counters of the n_k histogram that share a workgroup's LDS
 
 // A theta row's slot: a header of kRowHeader bytes (the row's number of entries), then the
@@ -451,6 +462,7 @@ struct HostChunk {
     bool short_docs = true;             // no document has more tokens than a 4-byte entry counts
     size_t slots_bytes = 0;
     int32_t n_tiles = 0, n_segs = 0, n_split = 0;
+    int32_t n_shared_segs = 0;          // the segments from this one on are counted by a wave each
     int32_t n_single = 0;               // the tiles from this one on hold whole small words: taken in runs
     int32_t n_shared = 0;               // K <= 2048: the tiles from this one on are taken by a wave each
     int32_t counted_tiles = 0;          // tiles of tile_tokens_for(K) tokens that the words have, as the sampler's bytes count them
@@ -669,6 +681,8 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
         });
         std::stable_sort(segs, segs + n_segs,
                          [](const mlda::Tile& a, const mlda::Tile& b) { return a.count > b.count; });
+        h.n_shared_segs = h.n_segs;
+        while (h.n_shared_segs > 0 && segs[h.n_shared_segs - 1].count <= solo_segment_for(K, T, h.n_segs)) --h.n_shared_segs;
         // tiles that hold a whole word of few tokens go last, to be taken in runs by one
         // workgroup each (their order among themselves stays)
         h.n_single = h.n_shared = h.n_tiles;
@@ -797,7 +811,7 @@ struct mlda_ctx {
     size_t slots_bytes = 0;
     mlda::Tile* tiles = nullptr;         // sampling tiles
     mlda::Tile* segs = nullptr;          // phi rebuild segments
-    int32_t n_tiles = 0, n_segs = 0, n_split = 0, n_wide_tiles = 0;
+    int32_t n_tiles = 0, n_segs = 0, n_shared_segs = 0, n_split = 0, n_wide_tiles = 0;
     int32_t n_single = 0;                // the tiles from this one on hold whole small words
     int32_t n_shared = 0;                // tiles taken by workgroups of several waves, the rest by a wave each
     int32_t counted_tiles = 0;           // see HostChunk
@@ -873,7 +887,7 @@ void point_at(mlda_ctx* c, const HostChunk& h, unsigned char* base) {
     c->wide_counters = h.wide_counters;
     c->short_docs = h.short_docs;
     c->slots_bytes = h.slots_bytes;
-    c->n_tiles = h.n_tiles; c->n_segs = h.n_segs; c->n_split = h.n_split;
+    c->n_tiles = h.n_tiles; c->n_segs = h.n_segs; c->n_shared_segs = h.n_shared_segs; c->n_split = h.n_split;
     c->n_wide_tiles = h.n_wide_tiles;
     c->n_single = h.n_single;
     c->n_shared = h.n_shared;
@@ -1053,12 +1067,13 @@ int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which, unsigned long long* s
     }
     unsigned long long* visited_sum =
         !c->streamed && c->rebuilds > 0 ? c->row_entries + ((c->rebuilds - 1) % kEntryRing) : nullptr;
-    const unsigned blocks = (unsigned)(c->n_segs + n_totals + (visited_sum ? 1 : 0));
+    const int32_t solo_groups = (c->n_segs - c->n_shared_segs + kPhiWaves - 1) / kPhiWaves;
+    const unsigned blocks = (unsigned)(c->n_shared_segs + solo_groups + n_totals + (visited_sum ? 1 : 0));
     if (blocks == 0 && started) hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
     if (blocks > 0)
         hipLaunchKernelGGL((c->K <= kPhiDwordTopics ? phi_tile_kernel<false> : phi_tile_kernel<true>), dim3(blocks),
-                           dim3(256), phi_tile_lds_bytes(c->K), c->stream,
-                           c->segs, c->n_segs, z, c->phi[which], c->K, c->T, n_totals, n_k, c->visited, c->theta_grid,
+                           dim3(256), phi_counter_bytes(c->K) * (solo_groups > 0 ? kPhiWaves : 1), c->stream,
+                           c->segs, c->n_segs, c->n_shared_segs, z, c->phi[which], c->K, c->T, n_totals, n_k, c->visited, c->theta_grid,
                            visited_sum, started);
     if (!c->streamed && c->T > 0 && n_totals == 0) {        // (streamed: after the last chunk)
         if (from_rows) {
@@ -1353,9 +1368,12 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
                                    (const void*)mlda::topic_totals_kernel<true>})
             HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, hist_bytes));
     }
-    if (mlda::phi_tile_lds_bytes(c->K) > 48 * 1024)
+    if (c->K <= mlda::kPhiDwordTopics && mlda::kPhiWaves * mlda::phi_counter_bytes(c->K) > 48 * 1024)
+        HIP_TRY(hipFuncSetAttribute((const void*)mlda::phi_tile_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)(mlda::kPhiWaves * mlda::phi_counter_bytes(mlda::kPhiDwordTopics))));
+    if (mlda::phi_counter_bytes(c->K) > 48 * 1024)
         HIP_TRY(hipFuncSetAttribute((const void*)mlda::phi_tile_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)mlda::phi_tile_lds_bytes(65535)));
+                                    (int)mlda::phi_counter_bytes(65535)));
     // (large K only: 4-byte rows of any K; the forms with a dense row)
     auto raise_theta = [&](bool wide, bool long_docs) {
         const size_t bytes = mlda::theta_lds_bytes(c->K, wide);
