@@ -235,6 +235,15 @@ int tile_tokens_for(int32_t K) { return K <= 2048 ? 1024 : 4096; }
 //               4e7     2251    2184     2358    3136     3852
 //   K = 2,000,  1e5       66      90       64      62       55
 //               1e6      272     338      315     388      415
+// Where a wave per tile of 64 leaves the chip room, tiles are cut smaller, to 16 or 32 tokens, as long as there are no more than
+// kFewestTiles (16 a CU) of them: the launch takes the time of one tile, and its passes follow one another.  us by tile size
+// 16 / 32 / 64:
+//   8e3 tokens, K = 24                6.4   6.4   8.4 (580 tiles of 16)      5e4, K = 32, 3,000 words    8.8   8.1   8.6 (4,600)
+//   2e4, K = 100                      7.7   8.1   9.5 (2,300)                5e4, K = 1,500             43.6  38.6  40.3 (4,600)
+//   3e4, K = 900, 3,000 words        17.2  21.1  25.2 (3,400)                1e5, K = 32                13.1   9.6  10.1 (8,800)
+//   5e4, K = 200, 2,000 words        12.0  14.3  16.2 (4,100)                1e5, K = 900               35.7  27.7  25.1 (7,800)
+constexpr int32_t kLeastTile = 16;
+constexpr int64_t kFewestTiles = 4096;
 struct TileShape { int32_t tokens, alone; };
 TileShape tile_shape_for(int32_t K, int64_t T) {
     if (K > 2048) return {4096, 0};
@@ -586,13 +595,21 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
         if (!accumulate && n > kPhiSegment) ++n_split;
     }
     TileShape shape = forced ? *forced : tile_shape_for(K, T);
+    auto tiles_of = [&](int32_t tokens) {
+        size_t n = 0;
+        for (int32_t v = 0; v < V; ++v) n += (size_t)((word_ptr[v + 1] - word_ptr[v] + tokens - 1) / tokens);
+        return n;
+    };
+    if (!forced && shape.alone >= shape.tokens && T <= kFewestTiles * kLeastTile * 4)
+        for (int32_t tokens = kLeastTile; tokens < shape.tokens; tokens *= 2)
+            if ((int64_t)tiles_of(tokens) <= kFewestTiles) shape = {tokens, tokens};
     for (;;) {
-        n_tiles = 0;
-        for (int32_t v = 0; v < V; ++v) n_tiles += (size_t)((word_ptr[v + 1] - word_ptr[v] + shape.tokens - 1) / shape.tokens);
+        n_tiles = tiles_of(shape.tokens);
         h.L = chunk_layout(D, T, h.slots_bytes, n_tiles, n_segs, n_split, accumulate);
         // (the bound that a workspace is sized by knows tiles of tile_tokens_for(K))
         if (shape.tokens >= tile_tokens_for(K) || h.L.total <= chunk_layout_bound(D, T, V, K, accumulate).total) break;
-        shape.tokens = tile_tokens_for(K);
+        if (shape.tokens < 64) shape = {64, 64};
+        else shape.tokens = tile_tokens_for(K);
     }
     const int32_t tile = shape.tokens;
     h.n_tiles = (int32_t)n_tiles; h.n_segs = (int32_t)n_segs; h.n_split = (int32_t)n_split;
