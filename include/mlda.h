@@ -194,7 +194,8 @@ int mlda_get_loglik(mlda_ctx* ctx, double* ll);
 
 /*
  * Kernel times of the iterations of the most recent mlda_step: each phase from its start to the
- * next one's, by the device's clock (chunks that take turns: from HIP events on the context's stream).
+ * next one's, by the device's clock (chunks that take turns: from HIP events on the context's stream; small
+ * corpora rebuild phi and theta side by side: theta's time is what is left once phi is done).
  * ms: host, capacity_iters rows of 4 doubles (sampling, rebuild phi and n_k, rebuild theta,
  * log-likelihood; 0 where the step did not evaluate it), out; n_iters: host, out, rows filled
  * (the last min(n, capacity_iters, 1024) iterations of that step).

@@ -177,32 +177,49 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 constexpr int kPhiWaves = 4;        // waves of a workgroup
+struct PhiArgs {
+    const Tile* segs;
+    int32_t n_segs, n_shared;
+    const uint16_t* z;
+    PhiView phi;
+    int32_t K;
+    int64_t T;
+    int32_t n_totals;
+    int32_t* n_k;
+    const unsigned long long* visited;
+    int32_t n_visited;
+    unsigned long long* visited_sum;
+    unsigned long long* started;
+};
+// What workgroup `block` of a phi rebuild does.
 template <bool kPacked>
-__global__ __launch_bounds__(256) void phi_tile_kernel(const Tile* segs, int32_t n_segs, int32_t n_shared, const uint16_t* z,
-                                                       PhiView phi, int32_t K, int64_t T, int32_t n_totals, int32_t* n_k,
-                                                       const unsigned long long* visited, int n_visited,
-                                                       unsigned long long* visited_sum, unsigned long long* started) {
-    extern __shared__ __align__(16) unsigned char lds[];
-    stamp_start(started);
-    const int tid = (int)threadIdx.x, n_solo_groups = (n_segs - n_shared + kPhiWaves - 1) / kPhiWaves;
-    const int block = (int)blockIdx.x;
-    if (block < n_shared) {
-        phi_segment<kPacked, 256>(lds, segs[block], z, phi, K, tid, [] { __syncthreads(); });
-    } else if (block < n_shared + n_solo_groups) {
-        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), i = n_shared + (block - n_shared) * kPhiWaves + wave;
-        if (i < n_segs)
-            phi_segment<kPacked, kWave>(lds + (size_t)wave * phi_counter_bytes(K), segs[i], z, phi, K, tid & (kWave - 1), [] { wave_sync(); });
+__device__ __forceinline__ void phi_work(unsigned char* lds, const PhiArgs& a, int block) {
+    const int tid = (int)threadIdx.x, n_solo_groups = (a.n_segs - a.n_shared + kPhiWaves - 1) / kPhiWaves;
+    if (block < a.n_shared) {
+        phi_segment<kPacked, 256>(lds, a.segs[block], a.z, a.phi, a.K, tid, [] { __syncthreads(); });
+    } else if (block < a.n_shared + n_solo_groups) {
+        const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), i = a.n_shared + (block - a.n_shared) * kPhiWaves + wave;
+        if (i < a.n_segs)
+            phi_segment<kPacked, kWave>(lds + (size_t)wave * phi_counter_bytes(a.K), a.segs[i], a.z, a.phi, a.K, tid & (kWave - 1),
+                                        [] { wave_sync(); });
     } else {
-        const int part = block - n_shared - n_solo_groups;
-        if (part < n_totals) {
-            const int64_t per = ((T + n_totals - 1) / n_totals + 7) & ~(int64_t)7;
-            const int64_t lo = min(per * part, T);
-            add_topic_totals<false>(reinterpret_cast<int32_t*>(lds), z, lo, min(lo + per, T), n_k, 0, K);
-        } else if (visited_sum) {
-            store_visited_sum(visited, n_visited, visited_sum);
+        const int part = block - a.n_shared - n_solo_groups;
+        if (part < a.n_totals) {
+            const int64_t per = ((a.T + a.n_totals - 1) / a.n_totals + 7) & ~(int64_t)7;
+            const int64_t lo = min(per * part, a.T);
+            add_topic_totals<false>(reinterpret_cast<int32_t*>(lds), a.z, lo, min(lo + per, a.T), a.n_k, 0, a.K);
+        } else if (a.visited_sum) {
+            store_visited_sum(a.visited, a.n_visited, a.visited_sum);
         }
     }
 }
+template <bool kPacked>
+__global__ __launch_bounds__(256) void phi_tile_kernel(const PhiArgs a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    stamp_start(a.started);
+    phi_work<kPacked>(lds, a, (int)blockIdx.x);
+}
+
 // n_k[k] = number of tokens with topic k, as a launch of its own: each workgroup over a contiguous
 // share of the tokens; n_k must be zero on entry.
 // kRange: K counters do not fit a workgroup's LDS; the launch then covers the topics
@@ -428,9 +445,10 @@ __device__ __forceinline__ void close_row(unsigned char* head, int n_entries, in
 }
 
 // The topic totals that nobody reads any more (null: there are none), for the next phi rebuild to add to.
-__device__ __forceinline__ void clear_old_totals(int32_t* old_n_k, int32_t K) {
+// (by `threads` threads, of which this is number `me`)
+__device__ __forceinline__ void clear_old_totals(int32_t* old_n_k, int32_t K, int me, int threads) {
     if (old_n_k)
-        for (int k = (int)(blockIdx.x * blockDim.x + threadIdx.x); k < K; k += (int)(gridDim.x * blockDim.x)) old_n_k[k] = 0;
+        for (int k = me; k < K; k += threads) old_n_k[k] = 0;
 }
 
 // Update theta (Section 6.2): document by document, (1) a dense K-long histogram of the
@@ -463,7 +481,7 @@ __global__ __launch_bounds__(kWave * kDocWaves) void theta_rows_kernel(const Doc
                                                            unsigned long long* started) {
     typedef typename Layout::Entry Entry;
     stamp_start(started);
-    clear_old_totals(old_n_k, K);
+    clear_old_totals(old_n_k, K, (int)(blockIdx.x * blockDim.x + threadIdx.x), (int)(gridDim.x * blockDim.x));
     if (T == 0) {       // no token anywhere: the loads "past a document's end" still need a place that exists
         doc_map = nullptr;
         z = reinterpret_cast<const uint16_t*>(docs);
@@ -695,40 +713,57 @@ __host__ __device__ inline int theta_rank_stage(int64_t longest, int docs) {
     const int64_t most = docs == 1 ? kRankStage : 256, n = longest - rank_keep(docs) * (kWave / docs);
     return n <= 0 ? 0 : (int)(((n < most ? n : most) + 3) & ~(int64_t)3);
 }
-__host__ __device__ inline size_t theta_rank_lds_bytes(int32_t K, int64_t longest, int docs) {
+// (a wave's own, and of a workgroup of so many waves with the table)
+__host__ __device__ inline size_t theta_rank_wave_bytes(int32_t K, int64_t longest, int docs) {
     return (size_t)docs * ((size_t)theta_rank_words(K) * 8 + (size_t)theta_rank_cells(K, longest, docs) * 4 +
-                           (size_t)theta_rank_stage(longest, docs) * 2) + (size_t)kThetaLgTable * 8;
+                           (size_t)theta_rank_stage(longest, docs) * 2);
+}
+__host__ __device__ inline size_t theta_rank_lds_bytes(int32_t K, int64_t longest, int docs, int waves = 1) {
+    return (size_t)waves * theta_rank_wave_bytes(K, longest, docs) + (size_t)kThetaLgTable * 8;
 }
 
+struct ThetaRankedArgs {
+    const DocRec* docs;
+    const int32_t* doc_map;
+    const uint16_t* z;
+    uint2* row_rec;
+    unsigned char* slots;
+    int64_t D, T;
+    int32_t K;
+    double alpha;
+    const double* lg_table;
+    unsigned long long* visited_partial;    // of every worker
+    double* ll_partial;
+    int32_t* old_n_k;
+    unsigned long long* started;
+    int32_t n_cells, n_stage, n_before, wave_bytes;
+};
+// What worker `worker` of `n_workers`, a wave, does; `lds` is its own, `table` the workgroup's.
 template <class Layout, int kDocs>
-__global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs, const int32_t* doc_map,
-                                                             const uint16_t* z, uint2* row_rec,
-                                                             unsigned char* slots, int64_t D, int64_t T,
-                                                             int32_t K, double alpha, const double* lg_table,
-                                                             unsigned long long* visited_partial,
-                                                             double* ll_partial, int32_t* old_n_k,
-                                                             unsigned long long* started, int32_t n_cells,
-                                                             int32_t n_stage, int32_t n_before) {
+__device__ __forceinline__ void theta_ranked(unsigned char* lds, const double* table, const ThetaRankedArgs& a, int worker, int n_workers) {
     typedef typename Layout::Entry Entry;
-    stamp_start(started);
     constexpr int W = kWave / kDocs, kKeep = rank_keep(kDocs);      // lanes per document
-    clear_old_totals(old_n_k, K);
+    const DocRec* docs = a.docs;
+    const int32_t* doc_map = a.doc_map;
+    const uint16_t* z = a.z;
+    const int64_t D = a.D, T = a.T;
+    const int32_t K = a.K, n_cells = a.n_cells, n_stage = a.n_stage;
+    const double alpha = a.alpha;
+    const double* lg_table = a.lg_table;
+    const int lane = (int)threadIdx.x & (kWave - 1), part = lane / W, hl = lane % W;
+    clear_old_totals(a.old_n_k, K, worker * kWave + lane, n_workers * kWave);
     if (T == 0) {       // no token anywhere: the loads "past a document's end" still need a place that exists
         doc_map = nullptr;
         z = reinterpret_cast<const uint16_t*>(docs);
     }
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int lane = (int)threadIdx.x, part = lane / W, hl = lane % W;
     const int n_words = theta_rank_words(K);
     // per document: {marks of 32 topics, topics marked before them}, the cells, the topics of further tokens
     uint2* words = reinterpret_cast<uint2*>(lds) + part * n_words;
     uint32_t* cells = reinterpret_cast<uint32_t*>(lds + (size_t)kDocs * n_words * 8) + part * n_cells;
     uint16_t* stage = reinterpret_cast<uint16_t*>(lds + (size_t)kDocs * (n_words * 8 + n_cells * 4)) + part * n_stage;
-    double* table = reinterpret_cast<double*>(lds + (size_t)kDocs * (n_words * 8 + n_cells * 4 + n_stage * 2));
     const double lg_alpha = lg_table[kLgTable];
     for (int i = lane; i < kDocs * n_words / 2; i += kWave) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
-    for (int c = lane; c < kThetaLgTable; c += kWave) table[c] = lg_table[c];
-    __syncthreads();
+    wave_sync();
     unsigned long long visited = 0;      // sum of N_d * (nominal entries of row d) over this part's documents
     double ll = 0.0;
     auto add_ll = [&](int c) {
@@ -761,18 +796,14 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
     constexpr bool kNominal = Layout::kDoubleWeights;
     const int plain = min(Layout::kMaxCount, kNominal && K < 1024 ? 15 : 16383);
 
-    const int64_t n_rounds = (D + kDocs - 1) / kDocs, step = gridDim.x;
+    const int64_t n_rounds = (D + kDocs - 1) / kDocs, step = n_workers;
     const DocRec none = {0, 0, 0u, 0};
     auto record = [&](int64_t r) {      // (the load is made for every r, from the last record if need be)
         const int64_t d = r * kDocs + part;
         const DocRec rec = docs[d < D ? d : D - 1];
         return d < D ? rec : none;
     };
-    // each XCD takes a contiguous run of documents (see theta_rows_kernel)
-    const int per_xcd = (int)gridDim.x / kXcds;
-    int64_t i = (int)blockIdx.x < per_xcd * kXcds
-                    ? (int64_t)((int)blockIdx.x % kXcds) * per_xcd + (int)blockIdx.x / kXcds
-                    : (int64_t)blockIdx.x;
+    int64_t i = worker;
     // One document per wave: three loads deep, as in theta_rows_kernel, every lane making every load.  Two
     // per wave: the topics of the next two documents are on their way while these are counted (positions and
     // topics of one token after the other: many gathers of a wave in flight at once measured slower).
@@ -823,7 +854,7 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
                 if (s + t * W < n_stage) stage[s + t * W] = (uint16_t)k[t];
             }
         }
-        __syncthreads();
+        wave_sync();
         // ---- topics marked before every word
         int n_topics;
         if constexpr (kDocs == 2) {
@@ -848,7 +879,7 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
                 n_topics += part_last(upto);
             }
         }
-        __syncthreads();
+        wave_sync();
         auto rank_of = [&](int k) {         // k >= 0, marked
             const uint2 w = words[k >> 5];
             return (int)(w.y + (uint32_t)__popc(w.x & ((1u << (k & 31)) - 1u)));
@@ -857,7 +888,7 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
 #pragma unroll
         for (int t = 0; t < kKeep; ++t) rank[t] = topic[t] >= 0 ? rank_of(topic[t]) : -1;
         // ---- the row, n_cells topics at a time
-        unsigned char* head = slots + (size_t)cur.slot * 16u;
+        unsigned char* head = a.slots + (size_t)cur.slot * 16u;
         Entry* ent = reinterpret_cast<Entry*>(head + kRowHeader);
         int filled = 0, further = 0;        // entries so far; nominal entries beyond one per topic (this lane's)
         bool any_further = false;
@@ -872,7 +903,7 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
                     atomicAdd(&cells[at], 1u);
                 }
             };
-            __syncthreads();
+            wave_sync();
 #pragma unroll
             for (int t = 0; t < kKeep; ++t) add_token(topic[t], rank[t] < 0 ? -1 : rank[t] - first);
             // the tokens beyond those in registers, four per lane at a time
@@ -896,7 +927,7 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
 #pragma unroll
                 for (int t = 0; t < 4; ++t) add_token(k[t], at[t]);
             }
-            __syncthreads();
+            wave_sync();
             const int here = min(n_topics - first, n_cells), most_here = min(most_topics - first, n_cells);
             for (int e0 = 0; e0 < most_here; e0 += W) {
                 const uint32_t cell = e0 + hl < here ? cells[e0 + hl] : 0u;
@@ -916,7 +947,7 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
                 }
                 add_ll(c);
             }
-            __syncthreads();
+            wave_sync();
         }
         for (int w = 2 * hl; w < n_words; w += 2 * W) *reinterpret_cast<uint4*>(words + w) = make_uint4(0u, 0u, 0u, 0u);
         const bool real = i * kDocs + part < D;          // the last round may lack its second document
@@ -924,10 +955,10 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
         int nominal = filled;
         if (kNominal && any_further) nominal = n_topics + part_last(part_sums(further));
         if (real && hl == 0) {
-            row_rec[cur.doc].y = (uint32_t)n_topics;     // distinct topics, for the getters
+            a.row_rec[cur.doc].y = (uint32_t)n_topics;     // distinct topics, for the getters
             visited += (unsigned long long)cur.n * (unsigned long long)nominal;
         }
-        __syncthreads();
+        wave_sync();
         cur = nxt; nxt = after; after = later;
 #pragma unroll
         for (int t = 0; t < kKeep; ++t) {
@@ -936,8 +967,53 @@ __global__ __launch_bounds__(kWave) void theta_ranked_kernel(const DocRec* docs,
         }
     }
     if (kDocs == 2) visited += __shfl_xor(visited, W, kWave);       // the other part's documents
-    if (lane == 0) visited_partial[blockIdx.x] = (int)blockIdx.x < n_before ? visited_partial[blockIdx.x] + visited : visited;
-    block_partial_store(ll, ll_partial, n_before);
+    ll = wave_sum(ll);
+    if (lane == 0) {
+        const bool more = worker < a.n_before;
+        a.visited_partial[worker] = more ? a.visited_partial[worker] + visited : visited;
+        a.ll_partial[worker] = more ? a.ll_partial[worker] + ll : ll;
+    }
+}
+
+// The log-gamma terms of small counts, for the workgroup's waves.
+__device__ __forceinline__ void stage_theta_table(double* table, const double* lg_table) {
+    for (int c = (int)threadIdx.x; c < kThetaLgTable; c += (int)blockDim.x) table[c] = lg_table[c];
+    __syncthreads();
+}
+// Number of the worker that workgroup `block` of `blocks` is first: workgroups are dealt to the XCDs round-robin, each XCD
+// takes a contiguous run of documents (see theta_rows_kernel).
+__device__ __forceinline__ int first_worker(int block, int blocks, int waves) {
+    const int per_xcd = blocks / kXcds;
+    return (block < per_xcd * kXcds ? block % kXcds * per_xcd + block / kXcds : block) * waves;
+}
+
+template <class Layout, int kDocs>
+__global__ __launch_bounds__(kWave) void theta_ranked_kernel(const ThetaRankedArgs a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    stamp_start(a.started);
+    stage_theta_table(reinterpret_cast<double*>(lds), a.lg_table);
+    theta_ranked<Layout, kDocs>(lds + kThetaLgTable * 8, reinterpret_cast<const double*>(lds), a,
+                                first_worker((int)blockIdx.x, (int)gridDim.x, 1), (int)gridDim.x);
+}
+
+// Both rebuilds of a corpus that neither of them fills the chip with, in one launch: the workgroups of phi, then those of
+// theta, four waves each, to each its documents.  Bound by the longest chain of waits, which two launches meet one after
+// the other: 1e5 tokens, K = 32, 11.5 us in two, 6.8 in one (kBothTokens has the line).
+template <class Layout, int kDocs>
+__global__ __launch_bounds__(256) void rebuild_kernel(const PhiArgs p, const ThetaRankedArgs t, int32_t n_phi, int32_t n_theta) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    stamp_start(p.started);
+    if ((int)blockIdx.x < n_phi) {
+        phi_work<false>(lds, p, (int)blockIdx.x);
+        // (theta's time starts when phi's is over, which some of its workgroups tell; earlier steps left earlier times)
+        if (t.started && threadIdx.x == 0 && (blockIdx.x % 64 == 0 || (int)blockIdx.x == n_phi - 1))
+            atomicMax(t.started, (unsigned long long)wall_clock64());
+        return;
+    }
+    const int block = (int)blockIdx.x - n_phi, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    stage_theta_table(reinterpret_cast<double*>(lds), t.lg_table);
+    theta_ranked<Layout, kDocs>(lds + kThetaLgTable * 8 + (size_t)wave * t.wave_bytes, reinterpret_cast<const double*>(lds), t,
+                                first_worker(block, n_theta, 4) + wave, 4 * n_theta);
 }
 
 // The two per-token index arrays that follow from tok_id and the document records are built

@@ -335,6 +335,14 @@ RowKind row_kind_for(const int64_t* doc_ptr, int64_t D, int32_t V, int32_t K) {
     return wider > (tiny == RowKind::tiny6 ? kTinyGrowth : kTinyGrowth5) * counted ? RowKind::counted : tiny;
 }
 
+// Resident corpora of up to so many tokens and topics: one launch rebuilds phi and theta (the counters of four segments then fit
+// 48 KB).  Both rebuilds, us, two launches / one:
+//   8e3 tokens, K = 24    8.7/ 5.3     5e5, K = 900    24.8/20.4     5e6, K = 2,000   56/50       2e7, K = 500     163/178
+//   1e5, K = 32          11.5/ 6.8     1e6, K = 128    26.2/25.2     6.3e6, K = 1,537 95/96       9.9e7, K = 1,000 922/1063
+constexpr int64_t kBothTokens = 5000000;
+constexpr int32_t kBothTopics = 3072;
+static_assert(kBothTopics <= mlda::kPhiDwordTopics, "a topic has a dword");
+
 constexpr int kLoglikBlocks = 2048;
 constexpr int kSmallLoglikBlocks = 256;     // up to so many, the word side's last workgroup adds up
 constexpr int kMaxThetaGrid = 4096;    // workgroups of the theta rebuild (each leaves one likelihood partial and one count)
@@ -421,7 +429,7 @@ ModelLayout model_layout(int32_t V, int32_t K, int64_t T, bool two_phi) {
     L.wide_row = put((size_t)V * 4);
     L.n_k[0] = put((size_t)K * 4);
     L.n_k[1] = two_phi ? put((size_t)K * 4) : L.n_k[0];
-    L.ll_partial = put((size_t)(2 * kLoglikBlocks + 2 * kMaxThetaGrid) * 8);
+    L.ll_partial = put((size_t)(2 * kLoglikBlocks + 3 * kMaxThetaGrid) * 8);
     // value, theta sum, document term, the word side's ticket, the sampler's next tile; the workers' counters (copy_to_host_kernel)
     L.ll_scalars = put((size_t)(5 + kRingWorkers) * 8);
     L.lg_table = put((size_t)mlda::kLgTableSize * 8 * 2);   // one for alpha, one for beta
@@ -765,7 +773,7 @@ struct mlda_ctx {
     double* lg_table = nullptr;          // lgG(c + alpha) - lgG(alpha), c < 1024, then lgG(alpha)
     double* lg_table_beta = nullptr;     // the same for beta
     unsigned long long* row_entries = nullptr;   // ring: [r % kEntryRing] belongs to rebuild r
-    unsigned long long* visited = nullptr;       // the last theta rebuild's row entries, one value per workgroup
+    unsigned long long* visited = nullptr;       // theta rebuilds' row entries, one value per workgroup; see visited_of
     int64_t rebuilds = 0;                        // rebuilds launched so far
     unsigned long long* stamps = nullptr;        // resident: [4 i + phase] of timed iteration i, see stamp_start
     int clock_khz = 0;                           // the rate they count at
@@ -816,7 +824,8 @@ struct mlda_ctx {
         int32_t grid = 0;
     };
     ThetaLaunch theta[2];                // documents too long to be ranked, all others (either may have none)
-    int32_t theta_grid = 0;              // partials that they leave
+    int32_t theta_grid = 0;              // partials that the last rebuild left
+    size_t both_lds = 0;                 // LDS of theta's workgroups where one launch rebuilds phi, too; 0: it does not
     RowKind rows = RowKind::packed;
     bool wide_counters = false, short_docs = true;
     int32_t* split_words = nullptr;
@@ -945,14 +954,14 @@ void point_at(mlda_ctx* c, const HostChunk& h, unsigned char* base) {
     c->theta[1].D = h.D - n_dense;
     c->theta[1].ranked = c->K <= mlda::kPairMaxK && h.T <= 160 * h.D ? 2 : 1;
     c->theta[1].lds = mlda::theta_rank_lds_bytes(c->K, ranked_longest(h), c->theta[1].ranked);
-    c->theta_grid = 0;
     for (mlda_ctx::ThetaLaunch& l : c->theta) {
         // 16 one-wave workgroups per CU: enough to hide the gathers' latency; more of them
         // touch more lines of z at once than an XCD's L2 holds, and neighbours stop sharing
         const int per_cu = std::max(1, std::min(16, (int)(144 * 1024 / l.lds)));
         l.grid = (int32_t)std::min<int64_t>({l.D, (int64_t)c->n_cus * per_cu, (int64_t)kMaxThetaGrid});
-        c->theta_grid = std::max(c->theta_grid, l.grid);
     }
+    const size_t both = mlda::theta_rank_lds_bytes(c->K, ranked_longest(h), c->theta[1].ranked, 4);
+    c->both_lds = !c->streamed && n_dense == 0 && h.T > 0 && h.T <= kBothTokens && c->K <= kBothTopics && both <= 40 * 1024 ? both : 0;
 }
 
 // After the static part of a chunk has arrived: the index arrays that follow from it
@@ -1059,10 +1068,30 @@ int store_z_and_release(mlda_ctx* c, int32_t m, bool store) {
     return MLDA_OK;
 }
 
+// The topic totals that a theta rebuild clears.
+int32_t* old_totals(const mlda_ctx* c) { return !c->streamed && c->n_k[0] != c->n_k[1] ? c->n_k[c->n_k_cur ^ 1] : nullptr; }
+
+// The counts that theta rebuild number `rebuild` leaves (the next phi rebuild reads them while the next theta rebuild
+// may already leave its own).
+unsigned long long* visited_of(const mlda_ctx* c, int64_t rebuild) { return c->visited + (rebuild & 1) * kMaxThetaGrid; }
+
+mlda::ThetaRankedArgs ranked_args(const mlda_ctx* c, const mlda_ctx::ThetaLaunch& l, const uint16_t* z, unsigned long long* started,
+                                  int32_t n_before) {
+    using namespace mlda;
+    const int64_t longest = ranked_longest(*c->at);
+    const int docs = std::max(l.ranked, 1);         // (0: not ranked, what the ranks need is not read)
+    return {c->doc_order + l.first, c->streamed ? nullptr : c->doc_map, z, c->row_rec, c->slots, l.D, c->T, c->K, c->alpha,
+            c->lg_table, visited_of(c, c->rebuilds), c->ll_partial + 2 * kLoglikBlocks, old_totals(c), started,
+            theta_rank_cells(c->K, longest, docs), theta_rank_stage(longest, docs), n_before,
+            (int32_t)theta_rank_wave_bytes(c->K, longest, docs)};
+}
+
 // phi (into n_wk[which]) from the attached chunk's assignments z (word-major).  One chunk:
 // rows are stored and n_k follows; several: the chunk's counts are added to a phi that was
 // zeroed before the first chunk, and n_k is formed after the last (finish_model).
-int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which, unsigned long long* started = nullptr) {
+// `with_theta`: theta's rows, too, in the same launch.
+int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which, unsigned long long* started = nullptr, bool with_theta = false,
+                unsigned long long* theta_started = nullptr) {
     using namespace mlda;
     int32_t* n_k = nullptr;
     int32_t n_totals = 0;           // workgroups of the phi launch that count the topic totals
@@ -1086,12 +1115,28 @@ int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which, unsigned long long* s
         !c->streamed && c->rebuilds > 0 ? c->row_entries + ((c->rebuilds - 1) % kEntryRing) : nullptr;
     const int32_t solo_groups = (c->n_segs - c->n_shared_segs + kPhiWaves - 1) / kPhiWaves;
     const unsigned blocks = (unsigned)(c->n_shared_segs + solo_groups + n_totals + (visited_sum ? 1 : 0));
-    if (blocks == 0 && started) hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
-    if (blocks > 0)
-        hipLaunchKernelGGL((c->K <= kPhiDwordTopics ? phi_tile_kernel<false> : phi_tile_kernel<true>), dim3(blocks),
-                           dim3(256), phi_counter_bytes(c->K) * (solo_groups > 0 ? kPhiWaves : 1), c->stream,
-                           c->segs, c->n_segs, c->n_shared_segs, z, c->phi[which], c->K, c->T, n_totals, n_k, c->visited, c->theta_grid,
-                           visited_sum, started);
+    const PhiArgs p = {c->segs, c->n_segs, c->n_shared_segs, z, c->phi[which], c->K, c->T, n_totals, n_k,
+                       visited_of(c, c->rebuilds - 1), c->theta_grid, visited_sum, started};
+    const size_t phi_lds = phi_counter_bytes(c->K) * (solo_groups > 0 ? kPhiWaves : 1);
+    if (with_theta) {
+        const mlda_ctx::ThetaLaunch& l = c->theta[1];
+        const ThetaRankedArgs t = ranked_args(c, l, z, theta_started, 0);
+        const int32_t n_theta = (l.grid + 3) / 4;
+        with_layout(c->rows, [&](auto layout) {
+            typedef decltype(layout) Layout;
+            hipLaunchKernelGGL((l.ranked == 2 ? rebuild_kernel<Layout, 2> : rebuild_kernel<Layout, 1>), dim3(blocks + (unsigned)n_theta),
+                               dim3(256), std::max(phi_lds, c->both_lds), c->stream, p, t, (int32_t)blocks, n_theta);
+            return 0;
+        });
+        c->spare_n_k_cleared = t.old_n_k != nullptr;
+        c->theta_grid = 4 * n_theta;
+        c->rebuilds += 1;
+    } else if (blocks > 0) {
+        hipLaunchKernelGGL((c->K <= kPhiDwordTopics ? phi_tile_kernel<false> : phi_tile_kernel<true>), dim3(blocks), dim3(256),
+                           phi_lds, c->stream, p);
+    } else if (started) {
+        hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
+    }
     if (!c->streamed && c->T > 0 && n_totals == 0) {        // (streamed: after the last chunk)
         if (from_rows) {
             const int words_per_slice = 64;
@@ -1140,37 +1185,28 @@ int finish_model(mlda_ctx* c, int which) {
 int rebuild_theta(mlda_ctx* c, const uint16_t* z, unsigned long long* started = nullptr) {
     using namespace mlda;
     if (c->D == 0 && started) hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
-    const int32_t* doc_map = c->streamed ? nullptr : c->doc_map;
     if (c->D > 0) {
-        uint2* row_rec = c->row_rec;
-        unsigned char* slots = c->slots;
-        int64_t T = c->T;
-        int32_t K = c->K;
-        double alpha = c->alpha;
-        const double* lg_table = c->lg_table;
-        double* ll_partial = c->ll_partial + 2 * kLoglikBlocks;
-        unsigned long long* visited = c->visited;
-        int32_t* old_n_k = !c->streamed && c->n_k[0] != c->n_k[1] ? c->n_k[c->n_k_cur ^ 1] : nullptr;
+        int32_t* old_n_k = old_totals(c);
         int32_t n_before = 0;
+        c->theta_grid = 0;
         for (const mlda_ctx::ThetaLaunch& l : c->theta) {
             if (l.D == 0) continue;
-            const DocRec* docs = c->doc_order + l.first;
-            int64_t D = l.D;
-            int32_t n_cells = theta_rank_cells(c->K, ranked_longest(*c->at), l.ranked);
-            int32_t n_stage = theta_rank_stage(ranked_longest(*c->at), std::max(l.ranked, 1));
-            void* args[] = {&docs, &doc_map, &z, &row_rec, &slots, &D, &T, &K, &alpha, &lg_table, &visited, &ll_partial, &old_n_k,
-                            &started, &n_cells, &n_stage, &n_before};         // (the last three: theta_ranked_kernel's)
+            ThetaRankedArgs a = ranked_args(c, l, z, started, n_before);
+            void* dense[] = {&a.docs, &a.doc_map, &a.z, &a.row_rec, &a.slots, &a.D, &a.T, &a.K, &a.alpha, &a.lg_table,
+                             &a.visited_partial, &a.ll_partial, &a.old_n_k, &a.started};
+            void* ranked[] = {&a};
             HIP_TRY(hipLaunchKernel(l.ranked ? theta_ranked_kernel_for(c->rows, l.ranked)
                                              : theta_kernel_for(c->rows, c->wide_counters, l.long_docs),
                                     dim3((unsigned)l.grid), dim3((unsigned)(l.long_docs ? kWave * kLongDocWaves : kWave)),
-                                    args, l.lds, c->stream));
+                                    l.ranked ? ranked : dense, l.lds, c->stream));
             n_before = l.grid;
+            c->theta_grid = std::max(c->theta_grid, l.grid);
             started = nullptr;
         }
         c->spare_n_k_cleared = old_n_k != nullptr;
         // (one chunk: the next rebuild_phi adds the counts up; sampler bytes are asked of earlier ones only)
         if (c->streamed)
-            hipLaunchKernelGGL(visited_sum_kernel, dim3(1), dim3(256), 0, c->stream, c->visited, c->theta_grid,
+            hipLaunchKernelGGL(visited_sum_kernel, dim3(1), dim3(256), 0, c->stream, visited_of(c, c->rebuilds), c->theta_grid,
                                c->row_entries + (c->rebuilds % kEntryRing));
     }
     c->rebuilds += 1;
@@ -1371,6 +1407,8 @@ int finish_create(mlda_ctx* c, unsigned char* base, const ModelLayout& ML) {
     // launch_loglik's ticket, launch_sampler's next tile, copy_to_host_kernel's counters
     hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(1), dim3(256), 0, c->stream, (int32_t*)(c->ll_scalars + 3),
                        (int64_t)(2 + kRingWorkers) * 2, 0);
+    hipLaunchKernelGGL(mlda::fill_i32_kernel, dim3(blocks_for((int64_t)(kStampBytes / 4), 256)), dim3(256), 0, c->stream,
+                       (int32_t*)c->stamps, (int64_t)(kStampBytes / 4), 0);
     RC_TRY(launch_check("model set-up kernels"));
     if (c->sample_lds > 48 * 1024)          // (the workgroups of twelve and sixteen waves only)
         for (bool short_docs : {false, true})
@@ -2153,8 +2191,12 @@ int mlda_step(mlda_ctx* c, int32_t n_iters, uint32_t flags) {
         auto phase = [&](int p) { return row >= 0 ? c->stamps + (size_t)row * kPhases + p : nullptr; };
         uint16_t* z_next = c->z[c->cur ^ 1];
         RC_TRY(launch_sampler(c, c->z[c->cur], z_next, phase(0)));
-        RC_TRY(rebuild_phi(c, z_next, 0, phase(1)));
-        RC_TRY(rebuild_theta(c, z_next, phase(2)));
+        if (c->both_lds > 0) {
+            RC_TRY(rebuild_phi(c, z_next, 0, phase(1), true, phase(2)));
+        } else {
+            RC_TRY(rebuild_phi(c, z_next, 0, phase(1)));
+            RC_TRY(rebuild_theta(c, z_next, phase(2)));
+        }
         c->cur ^= 1;
         c->iter += 1;
         c->ll_fresh = false;
