@@ -1083,15 +1083,65 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     [[maybe_unused]] int last_ti = -1;          // kQueue: the tile before
     for (int ti = (int)blockIdx.x;;) {
     const bool small = kQueue && ti >= a.n_single, follows = small && last_ti >= a.n_single;
-    // kQueue: the next tile, asked for by a wave that has nothing else to do
+    // kQueue: the next tile is asked for by one thread while the groups' sums are added up, and told the others.  (Asked for
+    // any earlier it holds up that wave's loads, which come back in order: 4 % slower where tiles have few tokens.)
+    [[maybe_unused]] uint32_t taken = 0;
     auto ask_next = [&]() {
         if constexpr (kQueue)
+            if (lane == 0) taken = atomicAdd(a.next_tile, 1u);
+    };
+    auto tell_next = [&]() {
+        if constexpr (kQueue)
             if (lane == 0) {
-                const uint32_t taken = atomicAdd(a.next_tile, 1u);
                 least[1] = taken + gridDim.x;
                 // (every workgroup asks until there is no tile left: n_tiles times in all)
                 if (taken + 1u == (uint32_t)a.n_tiles) atomicExch(a.next_tile, 0u);
             }
+    };
+    // The inclusive prefix over the groups' sums, 64 at a time (chunks of a wave's lanes, then the chunks before).  Where there are
+    // more than four chunks the waves scan them side by side, with the same additions in the same order: a tile of few
+    // tokens waits for little else.  One wave / all, sampling launch: 5e5 tokens, 20,000 words, K = 20,000 584 / 503 us, 3e6,
+    // K = 12,000 1,232 / 1,131; with two or three chunks (K < 4,096) the second barrier costs what it saves.
+    auto add_up_groups = [&](const double* sums, bool beside) {
+        const int n_chunks = (ng + kWave - 1) / kWave;
+        if (!kQueue || n_chunks <= 4) {
+            if (wave == 0) {
+                double carry = 0.0;
+                for (int base = 0; base < ng; base += kWave) {
+                    const int g = base + lane;
+                    double x = (g < ng) ? sums[g] : 0.0;
+                    x = wave_inclusive_sum(x) + carry;
+                    if (g < ng) cp[g] = x;
+                    carry = read_lane(x, kWave - 1);
+                }
+            } else if (wave == 1) {
+                collect_least(beside);
+            } else if (wave == 2) {
+                ask_next();
+                tell_next();
+            }
+            __syncthreads();
+            return;
+        }
+        // (in the records of a wave that are not in use yet, behind its least weight)
+        double* totals = reinterpret_cast<double*>(wave_base + 3 * wave_bytes + 64);
+        if (wave == kWaves - 1) ask_next();
+        for (int c = wave; c < n_chunks; c += kWaves) {
+            const int g = c * kWave + lane;
+            const double x = wave_inclusive_sum((g < ng) ? sums[g] : 0.0);
+            if (g < ng) cp[g] = x;
+            if (lane == kWave - 1) totals[c] = x;
+        }
+        if (wave == 1) collect_least(beside);
+        __syncthreads();
+        for (int c = wave; c < n_chunks; c += kWaves) {
+            double carry = 0.0;
+            for (int i = 0; i < c; ++i) carry = totals[i] + carry;
+            const int g = c * kWave + lane;
+            if (g < ng) cp[g] = cp[g] + carry;
+        }
+        if (wave == kWaves - 1) tell_next();
+        __syncthreads();
     };
     Tile tl = a.tiles[ti];                 // the same for every lane: keep it in SGPRs
     tl.word = __builtin_amdgcn_readfirstlane(tl.word);
@@ -1137,22 +1187,9 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         for (int g = tid; g < ng; g += kWaves * kWave)
             if ((changed[g >> 5] >> (g & 31)) & 1u) group_sum[g] = group_total(g);
         __syncthreads();
-        if (wave == 0) {
+        if (wave == 3)
             for (int w = lane; w < (ng + 31) / 32; w += kWave) changed[w] = 0u;
-            double carry = 0.0;
-            for (int base = 0; base < ng; base += kWave) {
-                const int g = base + lane;
-                double x = (g < ng) ? group_sum[g] : 0.0;
-                x = wave_inclusive_sum(x) + carry;
-                if (g < ng) cp[g] = x;
-                carry = read_lane(x, kWave - 1);
-            }
-        } else if (wave == 1) {
-            collect_least(true);
-        } else if (wave == 2) {
-            ask_next();
-        }
-        __syncthreads();
+        add_up_groups(group_sum, true);
     } else {
     // ---- stage p*(k) = (phi_kv + beta)/(n_k + beta V) as fp32 (Eq. 8)
     uint32_t my_least = 0xffffffffu;
@@ -1185,21 +1222,7 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
         if (small) group_sum[g] = s;
     }
     __syncthreads();
-    if (wave == 0) {                       // inclusive prefix over the group sums
-        double carry = 0.0;
-        for (int base = 0; base < ng; base += kWave) {
-            const int g = base + lane;
-            double x = (g < ng) ? cp[g] : 0.0;
-            x = wave_inclusive_sum(x) + carry;
-            if (g < ng) cp[g] = x;
-            carry = read_lane(x, kWave - 1);
-        }
-    } else if (wave == 1) {
-        collect_least(false);
-    } else if (wave == 2) {
-        ask_next();
-    }
-    __syncthreads();
+    add_up_groups(cp, false);
     }
 
     // a pass shape's lane geometry: token of the lane relative to the pass's first, the lane's
