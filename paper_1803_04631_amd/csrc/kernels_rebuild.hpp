@@ -177,9 +177,54 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 constexpr int kPhiWaves = 4;        // waves of a workgroup
+// Words of few tokens over many topics (kPacked): their rows hold the counts of z_old, and only the cells of the old and the new topics
+// are written.  A workgroup takes every `blocks`-th of the n segments; its counters are zero between them.
+// Bound by waiting for each word's topics (the next one's are on their way): 4e6 tokens of 60,000 words at K = 9,000 took 263 us
+// with every row written anew, 91 so (changed_cells_for has the line).
+__device__ __forceinline__ void phi_changed_cells(unsigned char* lds, const Tile* segs, int32_t n, const uint16_t* z_old,
+                                                  const uint16_t* z, const PhiView& phi, int32_t K, int block, int blocks) {
+    uint32_t* hist = reinterpret_cast<uint32_t*>(lds);
+    const int tid = (int)threadIdx.x;
+    for (int i = tid; i < ((K + 1) / 2 + 3) / 4; i += 256) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+    auto count_of = [&](int k) { return (hist[k >> 1] >> ((k & 1) << 4)) & 0xffffu; };
+    auto add = [&](int k) { atomicAdd(&hist[k >> 1], 1u << ((k & 1) << 4)); };
+    int i = block;
+    Tile tl = {0, 0, 0, 0};
+    int was = 0, is = 0;            // topics of the thread's first token
+    auto ask = [&](int at) {
+        if (at < n) tl = segs[at]; else tl.count = 0;
+        if (tid < tl.count) { was = (int)z_old[tl.begin + tid]; is = (int)z[tl.begin + tid]; }
+    };
+    ask(i);
+    __syncthreads();
+    while (i < n) {
+        const Tile cur = tl;
+        const int my_was = was, my_is = is;
+        uint16_t* row = phi.narrow + (size_t)cur.word * (size_t)K;
+        i += blocks;
+        ask(i);
+        const bool mine = tid < cur.count;
+        if (mine) add(my_is);
+        for (int t = tid + 256; t < cur.count; t += 256) add((int)z[cur.begin + t]);
+        __syncthreads();
+        auto write = [&](int before, int now) {
+            if (count_of(before) == 0u) row[before] = 0;
+            row[now] = (uint16_t)count_of(now);
+        };
+        if (mine) write(my_was, my_is);
+        for (int t = tid + 256; t < cur.count; t += 256) write((int)z_old[cur.begin + t], (int)z[cur.begin + t]);
+        __syncthreads();
+        if (mine) hist[my_is >> 1] = 0u;
+        for (int t = tid + 256; t < cur.count; t += 256) hist[(int)z[cur.begin + t] >> 1] = 0u;
+        __syncthreads();
+    }
+}
 struct PhiArgs {
     const Tile* segs;
     int32_t n_segs, n_shared;
+    // kPacked: the n_changed segments behind those n_segs are phi_changed_cells's, by this many workgroups
+    int32_t n_changed, changed_blocks;
+    const uint16_t* z_old;
     const uint16_t* z;
     PhiView phi;
     int32_t K;
@@ -194,6 +239,13 @@ struct PhiArgs {
 // What workgroup `block` of a phi rebuild does.
 template <bool kPacked>
 __device__ __forceinline__ void phi_work(unsigned char* lds, const PhiArgs& a, int block) {
+    if constexpr (kPacked) {        // (first: they take longest)
+        if (block < a.changed_blocks) {
+            phi_changed_cells(lds, a.segs + a.n_segs, a.n_changed, a.z_old, a.z, a.phi, a.K, block, a.changed_blocks);
+            return;
+        }
+        block -= a.changed_blocks;
+    }
     const int tid = (int)threadIdx.x, n_solo_groups = (a.n_segs - a.n_shared + kPhiWaves - 1) / kPhiWaves;
     if (block < a.n_shared) {
         phi_segment<kPacked, 256>(lds, a.segs[block], a.z, a.phi, a.K, tid, [] { __syncthreads(); });

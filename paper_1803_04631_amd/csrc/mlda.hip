@@ -255,6 +255,13 @@ TileShape tile_shape_for(int32_t K, int64_t T) {
     return {1024, 0};
 }
 constexpr int kPhiSegment = 16384;    // tokens one workgroup histograms for the phi rebuild
+// Up to how many tokens a word's row is changed rather than written anew, K > kPhiDwordTopics: a token costs two lines of memory, a row
+// K / 64.  Rebuild of phi and the totals, us, never / up to K / 256 / K / 64 / K / 16 tokens:
+//   5e5 tokens, 20,000 words, K = 5,000    40  26  26  26      3e6, 20,000 words, K = 20,000    192  85  86  87
+//   4e6, 60,000 words, K = 9,000          263  99  91  92      2e6, 6,000 words, K = 40,000     138  99  99  98
+//   2e7, 60,000 words, K = 8,000          289 206 149 145      2e6, 6,000 words, K = 60,000     200 120 123 125
+//   9.9e7, 102,000 words, K = 10,000      722 712 618 670      2e4, 100 words, K = 60,000        47  43  42  46
+int changed_cells_for(int32_t K) { return K > mlda::kPhiDwordTopics ? K / 64 : 0; }
 // Up to how many tokens a wave counts a segment by itself: workgroups are started one in 1.3 ns, and most words have fewer
 // tokens than four waves lanes.  All segments where they are so many that the longest does not matter, none where the
 // counters of four take a CU's LDS.  Rebuild of phi, us, segments up to 0 / 64 / 256 / 1,024 / 16,384 tokens by a wave each:
@@ -480,6 +487,7 @@ struct HostChunk {
     size_t slots_bytes = 0;
     int32_t n_tiles = 0, n_segs = 0, n_split = 0;
     int32_t n_shared_segs = 0;          // the segments from this one on are counted by a wave each
+    int32_t n_dense_segs = 0;           // from this one on a step writes only the cells of their tokens' topics
     int32_t n_single = 0;               // the tiles from this one on hold whole small words: taken in runs
     int32_t n_shared = 0;               // K <= 2048: the tiles from this one on are taken by a wave each
     int32_t counted_tiles = 0;          // tiles of tile_tokens_for(K) tokens that the words have, as the sampler's bytes count them
@@ -708,6 +716,9 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
                          [](const mlda::Tile& a, const mlda::Tile& b) { return a.count > b.count; });
         h.n_shared_segs = h.n_segs;
         while (h.n_shared_segs > 0 && segs[h.n_shared_segs - 1].count <= solo_segment_for(K, T, h.n_segs)) --h.n_shared_segs;
+        const int most_changed = changed_cells_for(K);
+        h.n_dense_segs = most_changed == 0 ? h.n_segs
+            : (int32_t)(std::stable_partition(segs, segs + n_segs, [&](const mlda::Tile& s) { return !(s.whole && s.count <= most_changed); }) - segs);
         // tiles that hold a whole word of few tokens go last, to be taken in runs by one
         // workgroup each (their order among themselves stays)
         h.n_single = h.n_shared = h.n_tiles;
@@ -1090,8 +1101,9 @@ mlda::ThetaRankedArgs ranked_args(const mlda_ctx* c, const mlda_ctx::ThetaLaunch
 // rows are stored and n_k follows; several: the chunk's counts are added to a phi that was
 // zeroed before the first chunk, and n_k is formed after the last (finish_model).
 // `with_theta`: theta's rows, too, in the same launch.
-int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which, unsigned long long* started = nullptr, bool with_theta = false,
-                unsigned long long* theta_started = nullptr) {
+// `z_old`: the assignments whose counts phi holds, if it does.
+int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which, const uint16_t* z_old = nullptr, unsigned long long* started = nullptr,
+                bool with_theta = false, unsigned long long* theta_started = nullptr) {
     using namespace mlda;
     int32_t* n_k = nullptr;
     int32_t n_totals = 0;           // workgroups of the phi launch that count the topic totals
@@ -1113,11 +1125,13 @@ int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which, unsigned long long* s
     }
     unsigned long long* visited_sum =
         !c->streamed && c->rebuilds > 0 ? c->row_entries + ((c->rebuilds - 1) % kEntryRing) : nullptr;
-    const int32_t solo_groups = (c->n_segs - c->n_shared_segs + kPhiWaves - 1) / kPhiWaves;
-    const unsigned blocks = (unsigned)(c->n_shared_segs + solo_groups + n_totals + (visited_sum ? 1 : 0));
-    const PhiArgs p = {c->segs, c->n_segs, c->n_shared_segs, z, c->phi[which], c->K, c->T, n_totals, n_k,
-                       visited_of(c, c->rebuilds - 1), c->theta_grid, visited_sum, started};
+    const int32_t n_segs = z_old ? c->at->n_dense_segs : c->n_segs, n_shared = std::min(c->n_shared_segs, n_segs);
+    const int32_t solo_groups = (n_segs - n_shared + kPhiWaves - 1) / kPhiWaves;
     const size_t phi_lds = phi_counter_bytes(c->K) * (solo_groups > 0 ? kPhiWaves : 1);
+    const int32_t changed_blocks = std::min(c->n_segs - n_segs, c->n_cus * (int32_t)std::max<size_t>(1, std::min<size_t>(8, kLdsPerWorkgroup / phi_lds)));
+    const unsigned blocks = (unsigned)(changed_blocks + n_shared + solo_groups + n_totals + (visited_sum ? 1 : 0));
+    const PhiArgs p = {c->segs, n_segs, n_shared, c->n_segs - n_segs, changed_blocks, z_old, z, c->phi[which], c->K, c->T, n_totals, n_k,
+                       visited_of(c, c->rebuilds - 1), c->theta_grid, visited_sum, started};
     if (with_theta) {
         const mlda_ctx::ThetaLaunch& l = c->theta[1];
         const ThetaRankedArgs t = ranked_args(c, l, z, theta_started, 0);
@@ -2189,12 +2203,12 @@ int mlda_step(mlda_ctx* c, int32_t n_iters, uint32_t flags) {
     for (int32_t i = 0; i < n_iters; ++i) {
         const int32_t row = i - (n_iters - timed);
         auto phase = [&](int p) { return row >= 0 ? c->stamps + (size_t)row * kPhases + p : nullptr; };
-        uint16_t* z_next = c->z[c->cur ^ 1];
-        RC_TRY(launch_sampler(c, c->z[c->cur], z_next, phase(0)));
+        uint16_t *z_old = c->z[c->cur], *z_next = c->z[c->cur ^ 1];
+        RC_TRY(launch_sampler(c, z_old, z_next, phase(0)));
         if (c->both_lds > 0) {
-            RC_TRY(rebuild_phi(c, z_next, 0, phase(1), true, phase(2)));
+            RC_TRY(rebuild_phi(c, z_next, 0, z_old, phase(1), true, phase(2)));
         } else {
-            RC_TRY(rebuild_phi(c, z_next, 0, phase(1)));
+            RC_TRY(rebuild_phi(c, z_next, 0, z_old, phase(1)));
             RC_TRY(rebuild_theta(c, z_next, phase(2)));
         }
         c->cur ^= 1;

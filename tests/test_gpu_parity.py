@@ -754,6 +754,28 @@ def test_phi_segment_edges(mlda, K):
         model.close()
 
 
+@pytest.mark.parametrize("K", [4097, 17000, 65535])
+def test_phi_cells_of_changed_topics(mlda, K):
+    """Rows of words of few tokens over many topics after a step and after assignments are installed: words of 1, 255, 256, 257
+    and K / 64 tokens, one more, and one of two segments whose last has few; topics that stay, leave and come back."""
+    most = K // 64
+    word_counts = np.array([1, 0, 2, 64, min(most, 255), min(most, 256), min(most, 257), most, most + 1, 2 * 16384 + 3, 5])
+    V, alpha, beta = len(word_counts), 50.0 / K, 0.01
+    rng = np.random.default_rng(K)
+
+    class C:
+        pass
+    c = C(); c.word_ids = rng.permutation(np.repeat(np.arange(V, dtype=np.int32), word_counts)); c.T = len(c.word_ids)
+    c.doc_ptr = np.concatenate([[0], np.cumsum(rng.multinomial(c.T, np.ones(200) / 200))]).astype(np.int64)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, beta, SEED)
+    for it, few in enumerate((3, K)):
+        z = rng.integers(few, size=c.T).astype(np.uint16)
+        model.set_assignments(z, it=2 * it)
+        for step in (1, 2):
+            z = check_step(model, c, z, V, K, alpha, beta, SEED, 2 * it + step)
+    model.close()
+
+
 @pytest.mark.parametrize("K", [40, 3000])
 def test_assignments_change_order_tile_by_tile(mlda, K, monkeypatch):
     """Both directions, tiles of every size up to the largest and one more, and a number of them that eight does not divide."""
