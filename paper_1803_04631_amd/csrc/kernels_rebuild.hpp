@@ -139,7 +139,7 @@ __device__ __forceinline__ void phi_segment(unsigned char* lds, const Tile& tl, 
         return;
     }
     const size_t cell0 = (size_t)tl.word * (size_t)K;
-    if (tl.whole && (K & 7) == 0) {     // (every row starts at a multiple of 16 bytes)
+    if (tl.whole > 0 && (K & 7) == 0) {     // (every row starts at a multiple of 16 bytes)
         uint4* row = reinterpret_cast<uint4*>(phi.narrow + cell0);
         const uint4* counts = reinterpret_cast<const uint4*>(lds);
         for (int i = me; i < K / 8; i += kThreads) {
@@ -159,7 +159,7 @@ __device__ __forceinline__ void phi_segment(unsigned char* lds, const Tile& tl, 
     for (int i = me; i < (K + odd + 1) / 2; i += kThreads) {
         const int k = 2 * i - odd;
         const uint32_t two = count_of(k) | count_of(k + 1) << 16;
-        if (!tl.whole) {
+        if (tl.whole <= 0) {
             if (two != 0u) atomicAdd(&dwords[i], two);
         } else if (k < 0) {
             phi.narrow[cell0] = (uint16_t)(two >> 16);
@@ -1267,6 +1267,15 @@ __global__ __launch_bounds__(kWave) void export_rows_kernel(const uint2* row_rec
 
 // ------------------------------------------------------------------ log-likelihood kernels
 
+// The topic totals' term, lgG(V beta) - lgG(n_k + V beta), over all threads of the launch.  (One workgroup took 0.2 ms for it
+// at K = 60,000.)
+__device__ __forceinline__ void add_totals_terms(const int32_t* n_k, int32_t K, double v_beta, double lg_vb, double& acc) {
+    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < K; k += (int64_t)gridDim.x * blockDim.x) {
+        const double x = (double)n_k[k] + v_beta;
+        acc += lg_vb - (x >= 1024.0 ? lgamma_large(x) : lgamma(x));
+    }
+}
+
 // Word side: sum over all cells of lgG(n_wk + beta) - lgG(beta), plus the topic totals' term.
 // The 16-bit cells are read eight at a time, the 32-bit cells of the wide rows four at a time
 // (empty cells add nothing, so the unused 16-bit rows of the wide words do not matter); the
@@ -1337,12 +1346,8 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
         add_cell(i < n_narrow_cells ? (int)phi.narrow[i] : 0);
         const int64_t j = n_wide_cells / 4 * 4 + (int64_t)threadIdx.x;
         add_cell(j < n_wide_cells ? phi.wide[j] : 0);
-        const double lg_vb = lg_table[kLgTable + 1];
-        for (int k = (int)threadIdx.x; k < K; k += (int)blockDim.x) {
-            const double x = (double)n_k[k] + v_beta;
-            acc += lg_vb - (x >= 1024.0 ? lgamma_large(x) : lgamma(x));
-        }
     }
+    add_totals_terms(n_k, K, v_beta, lg_table[kLgTable + 1], acc);
     if (!ticket) {
         block_partial_store(acc, partial);
         return;
@@ -1357,6 +1362,67 @@ __global__ __launch_bounds__(256) void loglik_word_side_kernel(PhiView phi, int6
     if (!last) return;
     if (threadIdx.x == 0) *ticket = 0u;               // for the next launch
     store_loglik<true>(partial, (int)gridDim.x, theta_partial, n_theta, theta_sum, doc_term, out);
+}
+
+// The same by words, where most of them have few tokens over many topics: rows of the n_dense segments in front (a word's first
+// or only one), and of the words behind them the cells that their tokens' topics z name, each of them for as many of its
+// tokens as it counts.  A value per workgroup; bound by the rows' bytes.  All cells / this, us: 4e6 tokens, 60,000 words, K = 9,000
+// 282/69, 5e5, 20,000 words, K = 20,000 183/47, 2e6, 6,000 words, K = 40,000 197/79, 9.9e7, 102,000 words, K = 10,000 564/491.
+__global__ __launch_bounds__(256) void loglik_word_rows_kernel(const Tile* segs, int32_t n_dense, int32_t n_segs, const uint16_t* z,
+                                                               PhiView phi, const int32_t* n_k, int32_t K, double beta,
+                                                               double v_beta, const double* lg_table, double* partial,
+                                                               unsigned long long* started) {
+    stamp_start(started);
+    __shared__ double table[kLgTable];
+    for (int c = (int)threadIdx.x; c < kLgTable; c += 256) table[c] = lg_table[c];
+    const double lg_beta = lg_table[kLgTable];
+    __syncthreads();
+    double acc = 0.0;
+    auto term = [&](int c) { return c < kLgTable ? table[c] : lgamma_large((double)c + beta) - lg_beta; };
+    auto add_cell = [&](int c) {
+        if (c > 0 && c < kLgTable) acc += table[c];
+        if (__ballot(c >= kLgTable) != 0) {
+            if (c >= kLgTable) acc += term(c);
+        }
+    };
+    auto add_pair = [&](uint32_t two) { add_cell((int)(two & 0xffffu)); add_cell((int)(two >> 16)); };
+    const int tid = (int)threadIdx.x;
+    for (int s = (int)blockIdx.x; s < n_dense; s += (int)gridDim.x) {
+        const Tile tl = segs[s];
+        if (tl.whole == 0) continue;
+        const int wide_row = phi.wide_row[tl.word];
+        if (wide_row >= 0) {
+            const int32_t* row = phi.wide + (size_t)wide_row * (size_t)K;
+            for (int i = tid; i - tid < K; i += 256) add_cell(i < K ? row[i] : 0);
+            continue;
+        }
+        const uint16_t* row = phi.narrow + (size_t)tl.word * (size_t)K;
+        const int head = min((int)((16 - ((uintptr_t)row & 15)) & 15) / 2, K), n8 = (K - head) / 8, rest = K - head - 8 * n8;
+        const uint4* octs = reinterpret_cast<const uint4*>(row + head);
+        for (int i = tid; i - tid < n8; i += 512) {
+            uint4 a = make_uint4(0u, 0u, 0u, 0u), b = a;
+            if (i < n8) a = octs[i];
+            if (i + 256 < n8) b = octs[i + 256];
+            if (__ballot((a.x | a.y | a.z | a.w | b.x | b.y | b.z | b.w) != 0) == 0) continue;
+            add_pair(a.x); add_pair(a.y); add_pair(a.z); add_pair(a.w);
+            add_pair(b.x); add_pair(b.y); add_pair(b.z); add_pair(b.w);
+        }
+        int c = 0;                      // (at most seven cells on either side)
+        if (tid < head) c = (int)row[tid];
+        else if (tid >= 8 && tid < 8 + rest) c = (int)row[head + 8 * n8 + tid - 8];
+        if (tid < kWave) add_cell(c);
+    }
+    const int waves = (int)gridDim.x * 4, lane = tid & (kWave - 1);
+    for (int s = n_dense + (int)blockIdx.x * 4 + tid / kWave; s < n_segs; s += waves) {
+        const Tile tl = segs[s];
+        const uint16_t* row = phi.narrow + (size_t)tl.word * (size_t)K;
+        for (int t = lane; t < tl.count; t += kWave) {
+            const int c = (int)row[z[tl.begin + t]];
+            if (c > 0) acc += term(c) / (double)c;
+        }
+    }
+    add_totals_terms(n_k, K, v_beta, lg_table[kLgTable + 1], acc);
+    block_partial_store(acc, partial);
 }
 
 // The value after a large loglik_word_side_kernel.  One workgroup.

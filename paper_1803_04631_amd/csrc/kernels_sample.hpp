@@ -52,7 +52,7 @@ struct Tile {          // consecutive word-major tokens of one word
     int32_t word;
     int32_t begin;     // first word-major token position
     int32_t count;     // 1 .. tile size
-    int32_t whole;     // phi segments: 1 if the segment holds every token of its word;
+    int32_t whole;     // phi segments: 1 if the segment holds every token of its word, -1 if it is the first of several;
                        // sampling tiles: the word's row in PhiView::wide, or -1
 };
 

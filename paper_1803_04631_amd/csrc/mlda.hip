@@ -700,7 +700,7 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
         if (!accumulate && n > kPhiSegment) split_words[ip++] = v;
         for (int32_t b = 0; b < n; b += kPhiSegment)
             segs[is++] = mlda::Tile{v, word_ptr[v] + b, std::min(kPhiSegment, n - b),
-                                    (!accumulate && n <= kPhiSegment) ? 1 : 0};
+                                    accumulate ? 0 : n <= kPhiSegment ? 1 : b == 0 ? -1 : 0};
     }
     try {
         // Sampling tiles run in the order of their middle document (longest documents first;
@@ -718,7 +718,7 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
         while (h.n_shared_segs > 0 && segs[h.n_shared_segs - 1].count <= solo_segment_for(K, T, h.n_segs)) --h.n_shared_segs;
         const int most_changed = changed_cells_for(K);
         h.n_dense_segs = most_changed == 0 ? h.n_segs
-            : (int32_t)(std::stable_partition(segs, segs + n_segs, [&](const mlda::Tile& s) { return !(s.whole && s.count <= most_changed); }) - segs);
+            : (int32_t)(std::stable_partition(segs, segs + n_segs, [&](const mlda::Tile& s) { return !(s.whole > 0 && s.count <= most_changed); }) - segs);
         // tiles that hold a whole word of few tokens go last, to be taken in runs by one
         // workgroup each (their order among themselves stays)
         h.n_single = h.n_shared = h.n_tiles;
@@ -1311,13 +1311,18 @@ int launch_loglik(mlda_ctx* c, unsigned long long* started = nullptr) {
     const int64_t cells = (int64_t)c->V * c->K, wide_cells = (int64_t)c->n_wide * c->K;
     // a thread reads 16 bytes at a time
     const int64_t wanted = std::max(cells / 8, wide_cells / 4) / 256 + 1;
-    const bool small = wanted <= kSmallLoglikBlocks;
+    const bool by_words = !c->streamed && c->at->n_dense_segs < c->n_segs, small = !by_words && wanted <= kSmallLoglikBlocks;
     const int blocks = small ? (int)wanted : kLoglikBlocks;
     const double* theta_partial = c->ll_partial + 2 * kLoglikBlocks;
     const int n_theta = c->streamed ? 0 : c->theta_grid;
     const double* theta_sum = c->streamed ? c->ll_scalars + 1 : nullptr;
     const double* doc_term = c->ll_scalars + 2;
-    hipLaunchKernelGGL(loglik_word_side_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream,
+    if (by_words)
+        hipLaunchKernelGGL(loglik_word_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream, c->segs, c->at->n_dense_segs,
+                           c->n_segs, c->z[c->cur], c->phi[0], current_n_k(c), c->K, c->beta, (double)c->V * c->beta,
+                           c->lg_table_beta, c->ll_partial, started);
+    else
+        hipLaunchKernelGGL(loglik_word_side_kernel, dim3((unsigned)blocks), dim3(256), 0, c->stream,
                        c->phi[c->model_cur], cells, wide_cells, current_n_k(c), c->K, c->beta,
                        (double)c->V * c->beta, c->lg_table_beta, c->ll_partial, theta_partial, n_theta, theta_sum,
                        doc_term, small ? (unsigned int*)(c->ll_scalars + 3) : (unsigned int*)nullptr, c->ll_scalars, started);
