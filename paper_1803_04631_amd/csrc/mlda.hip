@@ -235,6 +235,8 @@ int tile_tokens_for(int32_t K) { return K <= 2048 ? 1024 : 4096; }
 //               4e7     2251    2184     2358    3136     3852
 //   K = 2,000,  1e5       66      90       64      62       55
 //               1e6      272     338      315     388      415
+// (256 < K <= 512, 1024/128 and 128/128: 1e7 tokens at K = 300 in documents of 300, 4,000 and 30,000 567/545, 577/555 and
+// 460/440, at K = 500 of 1,500 613/593; 1.2e7 at K = 455 of 20,000 696/711, 3e7 at K = 500 of 10,000 2743/2837.)
 // Where a wave per tile of 64 leaves the chip room, tiles are cut smaller, to 16 or 32 tokens, as long as there are no more than
 // kFewestTiles (16 a CU) of them: the launch takes the time of one tile, and its passes follow one another.  us by tile size
 // 16 / 32 / 64:
@@ -249,7 +251,7 @@ TileShape tile_shape_for(int32_t K, int64_t T) {
     if (K > 2048) return {4096, 0};
     if (T <= (K <= 512 ? 2000000 : K <= 1024 ? 200000 : 100000)) return {64, 64};
     if (few_topics_of_many_tokens(K, T)) return {1024, 0};
-    if (K <= 256 && T <= 100000000) return {128, 128};
+    if (T <= (K <= 256 ? 100000000 : K <= 512 ? 10000000 : 0)) return {128, 128};
     if (K <= 512) return {1024, 128};
     if (K <= 1024) return {T <= 4000000 ? 256 : 1024, 64};
     return {1024, 0};
@@ -1227,6 +1229,14 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z, unsigned long long* started = 
     return launch_check("theta rebuild kernel");
 }
 
+// Resident: phi, n_k and theta from z (see rebuild_phi), the starts of both where they are wanted.
+int rebuild_both(mlda_ctx* c, const uint16_t* z, const uint16_t* z_old = nullptr, unsigned long long* phi_started = nullptr,
+                 unsigned long long* theta_started = nullptr) {
+    if (c->both_lds > 0) return rebuild_phi(c, z, 0, z_old, phi_started, true, theta_started);
+    RC_TRY(rebuild_phi(c, z, 0, z_old, phi_started));
+    return rebuild_theta(c, z, theta_started);
+}
+
 int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next, unsigned long long* started = nullptr) {
     if (c->n_tiles == 0) {
         if (started) hipLaunchKernelGGL(mlda::stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
@@ -2075,8 +2085,7 @@ int mlda_init_random(mlda_ctx* c) {
             hipLaunchKernelGGL(mlda::init_topics_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0,
                                c->stream, c->tok_id, c->z[c->cur], c->T, c->K, c->seed);
         RC_TRY(launch_check("init_topics_kernel"));
-        RC_TRY(rebuild_phi(c, c->z[c->cur], 0));
-        RC_TRY(rebuild_theta(c, c->z[c->cur]));
+        RC_TRY(rebuild_both(c, c->z[c->cur]));
     }
     c->iter = 0;
     c->has_state = true;
@@ -2116,8 +2125,7 @@ int mlda_set_assignments(mlda_ctx* c, const uint16_t* z, int32_t iter) {
                 hipLaunchKernelGGL(mlda::to_word_major_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0,
                                    c->stream, tmp, c->tok_id, c->z[c->cur], c->T, (int64_t)0);
         }
-        RC_TRY(rebuild_phi(c, c->z[c->cur], 0));
-        RC_TRY(rebuild_theta(c, c->z[c->cur]));
+        RC_TRY(rebuild_both(c, c->z[c->cur]));
     }
     c->iter = iter;
     c->has_state = true;
@@ -2210,12 +2218,7 @@ int mlda_step(mlda_ctx* c, int32_t n_iters, uint32_t flags) {
         auto phase = [&](int p) { return row >= 0 ? c->stamps + (size_t)row * kPhases + p : nullptr; };
         uint16_t *z_old = c->z[c->cur], *z_next = c->z[c->cur ^ 1];
         RC_TRY(launch_sampler(c, z_old, z_next, phase(0)));
-        if (c->both_lds > 0) {
-            RC_TRY(rebuild_phi(c, z_next, 0, z_old, phase(1), true, phase(2)));
-        } else {
-            RC_TRY(rebuild_phi(c, z_next, 0, z_old, phase(1)));
-            RC_TRY(rebuild_theta(c, z_next, phase(2)));
-        }
+        RC_TRY(rebuild_both(c, z_next, z_old, phase(1), phase(2)));
         c->cur ^= 1;
         c->iter += 1;
         c->ll_fresh = false;
