@@ -1229,14 +1229,6 @@ int rebuild_theta(mlda_ctx* c, const uint16_t* z, unsigned long long* started = 
     return launch_check("theta rebuild kernel");
 }
 
-// Resident: phi, n_k and theta from z (see rebuild_phi), the starts of both where they are wanted.
-int rebuild_both(mlda_ctx* c, const uint16_t* z, const uint16_t* z_old = nullptr, unsigned long long* phi_started = nullptr,
-                 unsigned long long* theta_started = nullptr) {
-    if (c->both_lds > 0) return rebuild_phi(c, z, 0, z_old, phi_started, true, theta_started);
-    RC_TRY(rebuild_phi(c, z, 0, z_old, phi_started));
-    return rebuild_theta(c, z, theta_started);
-}
-
 int launch_sampler(mlda_ctx* c, const uint16_t* z_cur, uint16_t* z_next, unsigned long long* started = nullptr) {
     if (c->n_tiles == 0) {
         if (started) hipLaunchKernelGGL(mlda::stamp_kernel, dim3(1), dim3(1), 0, c->stream, started);
@@ -2085,7 +2077,8 @@ int mlda_init_random(mlda_ctx* c) {
             hipLaunchKernelGGL(mlda::init_topics_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0,
                                c->stream, c->tok_id, c->z[c->cur], c->T, c->K, c->seed);
         RC_TRY(launch_check("init_topics_kernel"));
-        RC_TRY(rebuild_both(c, c->z[c->cur]));
+        RC_TRY(rebuild_phi(c, c->z[c->cur], 0));
+        RC_TRY(rebuild_theta(c, c->z[c->cur]));
     }
     c->iter = 0;
     c->has_state = true;
@@ -2125,7 +2118,8 @@ int mlda_set_assignments(mlda_ctx* c, const uint16_t* z, int32_t iter) {
                 hipLaunchKernelGGL(mlda::to_word_major_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0,
                                    c->stream, tmp, c->tok_id, c->z[c->cur], c->T, (int64_t)0);
         }
-        RC_TRY(rebuild_both(c, c->z[c->cur]));
+        RC_TRY(rebuild_phi(c, c->z[c->cur], 0));
+        RC_TRY(rebuild_theta(c, c->z[c->cur]));
     }
     c->iter = iter;
     c->has_state = true;
@@ -2218,7 +2212,12 @@ int mlda_step(mlda_ctx* c, int32_t n_iters, uint32_t flags) {
         auto phase = [&](int p) { return row >= 0 ? c->stamps + (size_t)row * kPhases + p : nullptr; };
         uint16_t *z_old = c->z[c->cur], *z_next = c->z[c->cur ^ 1];
         RC_TRY(launch_sampler(c, z_old, z_next, phase(0)));
-        RC_TRY(rebuild_both(c, z_next, z_old, phase(1), phase(2)));
+        if (c->both_lds > 0) {
+            RC_TRY(rebuild_phi(c, z_next, 0, z_old, phase(1), true, phase(2)));
+        } else {
+            RC_TRY(rebuild_phi(c, z_next, 0, z_old, phase(1)));
+            RC_TRY(rebuild_theta(c, z_next, phase(2)));
+        }
         c->cur ^= 1;
         c->iter += 1;
         c->ll_fresh = false;
