@@ -1695,16 +1695,18 @@ int fetch_pieces(mlda_ctx* c, const void* dev, size_t bytes, F&& take) {
         return on_workers(c, [&](int w) {
             constexpr size_t kHalf = kRingPiece / 2;
             uint32_t value[2] = {*ring_flag(c, w, 0), *ring_flag(c, w, 1)};
+            // a worker's pieces follow one another: side by side, two workers' met in the caller's huge pages as they are made
+            const size_t per = (bytes + kRingWorkers * kHalf - 1) / (kRingWorkers * kHalf) * kHalf, end = std::min(bytes, (size_t)(w + 1) * per);
             auto queue = [&](size_t at, int half) {
-                return at < bytes ? queue_copy(c, w, half, (const unsigned char*)dev + at, std::min(kHalf, bytes - at), ++value[half])
-                                  : hipSuccess;
+                return at < end ? queue_copy(c, w, half, (const unsigned char*)dev + at, std::min(kHalf, end - at), ++value[half])
+                                : hipSuccess;
             };
-            size_t at = (size_t)w * kHalf;
+            size_t at = (size_t)w * per;
             hipError_t e = queue(at, 0);
-            for (int half = 0; e == hipSuccess && at < bytes; half ^= 1, at += kRingWorkers * kHalf) {
-                e = queue(at + kRingWorkers * kHalf, half ^ 1);
+            for (int half = 0; e == hipSuccess && at < end; half ^= 1, at += kHalf) {
+                e = queue(at + kHalf, half ^ 1);
                 if (e == hipSuccess) e = await_copy(c, w, half, value[half]);
-                if (e == hipSuccess) take(at, (const unsigned char*)ring_piece(c, w) + half * kHalf, std::min(kHalf, bytes - at));
+                if (e == hipSuccess) take(at, (const unsigned char*)ring_piece(c, w) + half * kHalf, std::min(kHalf, end - at));
             }
             return e;
         });
