@@ -1067,6 +1067,9 @@ int to_document_order(mlda_ctx* c, const uint16_t* z_word) {
 // starts later, beside the sampling of the next chunk.  (The copy is a kernel that waits for the link most of the time, and
 // while it runs every other launch takes until it is nearly done to end: started right away, the short launches at the
 // next visit's start took its 0.9 ms per 2.5e7 tokens; two iterations on 9.9e7 tokens in four chunks 41.7 ms, now 33.8.)
+// Where the chunks are many, it starts at once: the next upload but one waits for it.  An iteration, later / at once, ms:
+//   9.9e7 tokens in 4 chunks 15.3/15.6   8 17.0/16.8   16 21.1/20.8    7.4e8 in 4 84.5/84.9   8 89.8..101/88   16 115..125/109
+constexpr size_t kFewChunks = 6;
 int store_z_and_release(mlda_ctx* c, int32_t m, bool store) {
     const int s = (int)((c->visits - 1) % 2);
     HIP_TRY(hipEventRecord(c->slot_done[s], c->stream));
@@ -1075,6 +1078,7 @@ int store_z_and_release(mlda_ctx* c, int32_t m, bool store) {
         c->to_store = m;
         c->to_store_slot = s;
         c->to_store_z = c->z_doc;
+        if (c->chunks.size() > kFewChunks) RC_TRY(store_z(c));
     } else {
         HIP_TRY(hipEventRecord(c->slot_free[s], c->stream));
     }
