@@ -60,8 +60,8 @@ extern "C" {
 #define MLDA_EHIP     -3   /* a HIP call failed; the message names it */
 #define MLDA_ENOTSUP  -4   /* the device allows a workgroup less LDS than a kernel needs for this K (not on
                               MI355X, whose 160 KB serve every K up to 65,535, the range of the 16-bit topic
-                              index of Section 6.1.3: up to about 30,900 the sampler keeps the word's column
-                              of p* (Eq. 8) in LDS, beyond that in device memory, several times slower; the
+                              index of Section 6.1.3: up to about 26,100 the sampler keeps the word's column
+                              of p* (Eq. 8) in LDS, beyond that the part without room in device memory; the
                               paper's own range is 1,000 to 10,000, Section 2.1); also theta rows beyond
                               64 GiB in one chunk, and a device index beyond the library's table */
 
@@ -85,8 +85,8 @@ int mlda_workspace_bytes(int64_t D, int64_t T, int32_t V, int32_t K, size_t* byt
  * The corpus is copied; the host arrays may be released after the call.  No
  * topics are assigned yet: call mlda_init_random or mlda_set_assignments next.
  * K: 1 .. 65,535 (MLDA_EINVAL outside).  A K whose column of p* does not fit the 160 KB of LDS
- * of a workgroup (beyond about 30,900) is sampled with p* in device memory: same results, several
- * times slower per token; the workspace then holds 256 such columns more.
+ * of a workgroup (beyond about 26,100) is sampled with the rest of it in device memory: same results,
+ * slower per token; the workspace then holds room for it, and beyond 30,900 for 512 such columns more.
  * Environment, read here and by the other two ways to create a context, for tests: it takes forms that are
  * otherwise left to other sizes, with the same results, and slower.  A value that is not as said, and an empty one,
  * counts as none.
@@ -111,7 +111,7 @@ int mlda_create(mlda_ctx** out, const int64_t* doc_ptr, const int32_t* word_ids,
  * of default priority that the library creates, overlapping the kernels of the chunk
  * before), its theta rows are rebuilt from its assignments, it is sampled against the phi of
  * the iteration's start, its counts are added to the next phi, and its new assignments go
- * back to the host (on a second such stream).  Results are those of mlda_create: the counts of an iteration are frozen
+ * back to the host (on a second such stream, beside the sampling of the chunk after).  Results are those of mlda_create: the counts of an iteration are frozen
  * and the uniforms are keyed by the caller's token index.  (A draw that lies within the fp64 rounding of a sum over a
  * theta row may come out one topic off, as the sums' order depends on the tokens worked on together; none has been seen.)
  * The workspace (mlda_workspace_bytes_streamed: two copies of phi and two chunk buffers) and

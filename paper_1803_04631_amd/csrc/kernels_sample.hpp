@@ -89,7 +89,8 @@ struct SampleArgs {
     // Form::queued and split: workgroup b takes tile b, then those that next_tile (zero before and after the launch)
     // hands out from the grid's size on.
     uint32_t* next_tile;
-    // Form::split: workgroup b keeps p* of the topics near_topics (a multiple of 16) and on in far_pstar[b * Kpad ..]
+    // Form::split: workgroup b keeps p* of the topics near_topics (a multiple of 16) and on in its strip of
+    // far_strip_cells(Kpad, near_topics) from far_pstar on, from the kFarFirst-th of them
     float* far_pstar;
     int32_t near_topics;
     int32_t min_batch;          // K <= 2048: tokens a wave takes at a time at least
@@ -148,6 +149,9 @@ __host__ __device__ constexpr size_t sample_run_lds_bytes(int Kpad, int waves, b
     const size_t ng = (size_t)(Kpad / dense_group(waves, far));
     return ((ng + 1) & ~(size_t)1) * 8 + ((ng + 31) / 32 * 4 + 15 & ~(size_t)15);
 }
+// Cells of a workgroup's strip of device memory: those of the topics from `near` on, and four of 0 before them.
+constexpr int kFarFirst = 16;
+__host__ __device__ constexpr size_t far_strip_cells(int Kpad, int near) { return (size_t)(Kpad - near + kFarFirst); }
 // The same when p* of the topics from `near` on stays in device memory (four cells of 0 stand for those).
 __host__ __device__ constexpr size_t sample_far_lds_bytes(int Kpad, int waves, int near) {
     return (size_t)(near + 4) * 4 + (size_t)((Kpad / dense_group(waves, true) + 1) & ~1) * 8 + 16 +
@@ -1025,7 +1029,8 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     constexpr double kStagedScale = kDouble ? kWeightScale : 1.0, kRowScale = kDouble ? kSumScale : 1.0;
     const size_t pstar_lds = kFar ? (size_t)(a.near_topics + 4) * 4 : (size_t)Kpad * sizeof(Weight);
     Weight* pstar = reinterpret_cast<Weight*>(lds);
-    [[maybe_unused]] float* strip = kFar ? a.far_pstar + (size_t)blockIdx.x * (size_t)Kpad : nullptr;
+    // (by topic: strip[near_topics] is the first of its own)
+    [[maybe_unused]] float* strip = kFar ? a.far_pstar + (size_t)blockIdx.x * far_strip_cells(Kpad, a.near_topics) + kFarFirst - a.near_topics : nullptr;
     double* cp = reinterpret_cast<double*>(lds + pstar_lds);
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);      // wave-uniform, in an SGPR

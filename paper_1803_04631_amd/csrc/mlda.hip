@@ -93,10 +93,19 @@ int32_t kpad_for(int32_t K) {
     const int32_t g = mlda::dense_group(sample_waves_for(K), far_weights_for(K));
     return (K + g) / g * g;
 }
-// The topics whose p* stays in LDS then: as many as have room (0: none do).
-int32_t near_topics_for(int32_t K, size_t lds_limit) {
+// The topics whose p* stays in LDS then: as many as have room.
+int32_t near_topics_for(int32_t K) {
     const size_t rest = mlda::sample_far_lds_bytes(kpad_for(K), sample_waves_for(K), 0);
-    return rest >= lds_limit ? 0 : (int32_t)std::min<size_t>((lds_limit - rest) / 4, (size_t)kpad_for(K)) & ~15;
+    return (int32_t)std::min<size_t>((kLdsPerWorkgroup - rest) / 4, (size_t)kpad_for(K)) & ~15;
+}
+// What the others take of the workspace.  (Beyond kFarColumnsFrom topics, where little else fits LDS besides a whole
+// column, callers are told of kFarColumns whole ones on top: the bound that mlda.h has named from the start.)
+constexpr int32_t kFarColumnsFrom = 30900;
+constexpr int kFarColumns = 512;
+size_t far_bytes_for(int32_t K) {
+    if (!far_weights_for(K)) return 0;
+    return mlda::far_strip_cells(kpad_for(K), near_topics_for(K)) * kFarStrips * 4 +
+           (K > kFarColumnsFrom ? (size_t)kpad_for(K) * kFarColumns * 4 : 0);
 }
 
 // short_docs: no document has more tokens than a 4-byte entry counts; near: the theta slots of
@@ -444,7 +453,7 @@ ModelLayout model_layout(int32_t V, int32_t K, int64_t T, bool two_phi) {
     L.lg_table = put((size_t)mlda::kLgTableSize * 8 * 2);   // one for alpha, one for beta
     L.row_entries = put((size_t)kEntryRing * 8);
     L.stamps = put((size_t)kStampBytes);
-    L.far_pstar = put(far_weights_for(K) ? (size_t)kFarStrips * (size_t)kpad_for(K) * 4 : 0);
+    L.far_pstar = put(far_bytes_for(K));
     L.total = at;
     return L;
 }
@@ -1543,9 +1552,9 @@ int device_limits(mlda_ctx* c) {
     if (c->K <= 2048 && mlda::switch_numbers(std::getenv("MLDA_TILE_SHAPE"), 2, 0, 1024, numbers) && numbers[0] >= 16 &&
         numbers[1] <= numbers[0])
         c->shape = {(int32_t)numbers[0], (int32_t)numbers[1]};
-    c->near_topics = c->far_weights ? near_topics_for(c->K, std::min(kLdsPerWorkgroup, (size_t)c->lds_limit)) : 0;
+    c->near_topics = c->far_weights ? near_topics_for(c->K) : 0;
     const int waves = sample_waves_for(c->K);
-    c->sample_lds = c->far_weights ? mlda::sample_far_lds_bytes(c->Kpad, waves, std::max(c->near_topics, 16))
+    c->sample_lds = c->far_weights ? mlda::sample_far_lds_bytes(c->Kpad, waves, c->near_topics)
                                    : c->queued ? queued_lds_bytes(c->K, waves) : mlda::sample_lds_bytes(c->Kpad, waves, 8);
     if (c->sample_lds > (size_t)c->lds_limit)
         return fail(MLDA_ENOTSUP, "K = " + std::to_string(c->K) + " needs " + std::to_string(c->sample_lds) +
