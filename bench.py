@@ -28,13 +28,13 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E peak
 # this chip, WRITE_SIZE by 1.000 (same summaries).
 FETCH_SCALE, WRITE_SCALE = 2.000, 1.000
 MEASURED_TRAFFIC_KIB = {
-    ("C4", "init"): (7.05334e7, 1.70854e6, "profiles/sample_kernel_C4.md"),
-    ("C3", "init"): (1.22362e7, 2.28200e5, "profiles/sample_kernel_C3_C5.md"),
-    ("C5", "init"): (2.94770e7, 1.56570e6, "profiles/sample_kernel_C3_C5.md"),
+    ("C4", "init"): (7.03824e7, 1.70104e6, "profiles/sample_kernel_C4.md"),
+    ("C3", "init"): (1.22520e7, 2.27930e5, "profiles/sample_kernel_C3_C5.md"),
+    ("C5", "init"): (3.13090e7, 2.62790e5, "profiles/sample_kernel_C3_C5.md"),
 }
 # VALU wave-instructions per sampling launch (SQ_INSTS_VALU, same summaries): the sampler's other
 # limit is instruction issue, 1024 SIMDs x 2.4 GHz / 4 cycles per wave-instruction
-MEASURED_VALU_INSTS = {("C4", "init"): 1.42844e10, ("C3", "init"): 3.11411e9, ("C5", "init"): 5.04840e9}
+MEASURED_VALU_INSTS = {("C4", "init"): 1.41592e10, ("C3", "init"): 3.09143e9, ("C5", "init"): 5.04370e9}
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0
 
 
