@@ -388,14 +388,6 @@ __device__ __forceinline__ double lgamma_large(double x) {
 constexpr int kThetaLgTable = 128;
 constexpr int kXcds = 8;            // accelerator dies of an MI355X, each with its own L2
 
-// One document as the theta rebuild needs it, stored in processing order.
-struct __align__(16) DocRec {
-    int32_t begin;      // first document-major token
-    int32_t n;          // tokens
-    uint32_t slot;      // offset of the theta row's slot, 16-byte units
-    int32_t doc;        // document id
-};
-
 // Where the topic of the document's token `j` is found in z, or -1 past the document's end:
 // its word-major position, through the map; or, without a map (z in document order), the
 // token's own index.

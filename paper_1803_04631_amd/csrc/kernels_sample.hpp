@@ -43,18 +43,11 @@
 //     loads of the next pass are issued before the current pass is worked on.
 #pragma once
 #include <type_traits>
+#include "chunk_layout.hpp"
 #include "device_util.hpp"
 #include "row_sums.hpp"
 
 namespace mlda {
-
-struct Tile {          // consecutive word-major tokens of one word
-    int32_t word;
-    int32_t begin;     // first word-major token position
-    int32_t count;     // 1 .. tile size
-    int32_t whole;     // phi segments: 1 if the segment holds every token of its word, -1 if it is the first of several;
-                       // sampling tiles: the word's row in PhiView::wide, or -1
-};
 
 // phi (Section 6.1.3: short integers for the dense model).  A word with fewer than 2^16 tokens
 // can never overflow a 16-bit count: its row lives in `narrow`.  The few heavier words have an

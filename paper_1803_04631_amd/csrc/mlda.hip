@@ -25,6 +25,7 @@
 #include <thread>
 #include <vector>
 
+#include "chunk_layout.hpp"
 #include "kernels_rebuild.hpp"
 #include "kernels_sample.hpp"
 #include "switches.hpp"
@@ -51,7 +52,11 @@ int fail(int code, const std::string& msg) {
         if (rc_ != MLDA_OK) return rc_; \
     } while (0)
 
-constexpr size_t kAlign = 256;        // workspace sub-buffer alignment
+using mlda::kAlign;
+using mlda::align_up;
+using mlda::ChunkLayout;
+using mlda::chunk_first;
+using mlda::chunk_layout;
 constexpr size_t kSlotAlign = 64;     // theta row slot alignment (bytes)
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;
 // waves per sampling workgroup: more of them share one staged p* column when K is large
@@ -222,8 +227,6 @@ constexpr int kRunTiles = 16;
 constexpr int kVisitEvents = 7;
 constexpr int kMaxTimedVisits = 4096;
 
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
 int tile_tokens_for(int32_t K) { return K <= 2048 ? 1024 : 4096; }
 // K <= 2048: the tokens of a sampling tile, and up to how many of them a wave takes the tile alone.  A workgroup
 // of four waves keeps three of them idle over a word of few tokens, and on a small corpus the launch takes the time
@@ -372,42 +375,7 @@ constexpr int kEntryRing = 2048;      // per-rebuild counters of theta row entri
 constexpr int kPhases = 4;
 constexpr size_t kStampBytes = ((size_t)kMaxTimedIters * kPhases + 1) * 8;
 
-// Where the buffers of one chunk of documents lie inside its part of the workspace (byte
-// offsets).  The static part (up to static_bytes) is the preprocessed corpus and is copied
-// from the host as one block; two index arrays derived from it on the device, z and the theta
-// rows follow.
-struct ChunkLayout {
-    size_t tok_slot = 0, tok_id = 0, doc_map = 0, doc_ptr = 0, doc_order = 0, row_rec = 0, tiles = 0,
-           segs = 0, split = 0, static_bytes = 0, doc_pairs = 0, z0 = 0, z1 = 0, slots = 0, total = 0;
-};
-
-// `streamed`: the chunk takes turns on the device with others.  It then needs no
-// document->token map: its assignments arrive in document order (z_doc, in the map's place) and
-// are paired with their documents' slots there (doc_pairs) on their way to word-major order.
-ChunkLayout chunk_layout(int64_t D, int64_t T, size_t slots_bytes, size_t n_tiles, size_t n_segs,
-                         size_t n_split, bool streamed) {
-    ChunkLayout L;
-    size_t at = 0;
-    auto put = [&](size_t bytes) { const size_t o = at; at += align_up(bytes, kAlign); return o; };
-    L.tok_id = put((size_t)T * 4);
-    L.doc_ptr = put((size_t)(D + 1) * 4);
-    L.doc_order = put((size_t)D * sizeof(mlda::DocRec));
-    L.row_rec = put((size_t)D * 8);
-    L.tiles = put(n_tiles * sizeof(mlda::Tile));
-    L.segs = put(n_segs * sizeof(mlda::Tile));
-    L.split = put(n_split * 4);
-    L.static_bytes = at;
-    L.tok_slot = put((size_t)T * 4);       // derived on the device from the static part
-    L.doc_map = put((size_t)T * (streamed ? 2 : 4));
-    L.doc_pairs = put(streamed ? (size_t)T * 8 : 0);
-    L.z0 = put((size_t)T * 2);
-    L.z1 = put((size_t)T * 2);
-    L.slots = put(slots_bytes);
-    L.total = at;
-    return L;
-}
-
-// An upper bound of the same from the sizes alone.
+// An upper bound of a chunk's layout from the sizes alone.
 ChunkLayout chunk_layout_bound(int64_t D, int64_t T, int32_t V, int32_t K, bool streamed) {
     const size_t tile = (size_t)tile_tokens_for(K);
     // (at most one entry of at most 4 bytes per token, a header, a unit's and a slot's rounding)
@@ -752,14 +720,6 @@ int prepare_chunk(const int64_t* doc_ptr_all, const int32_t* word_ids_all, int64
     return MLDA_OK;
 }
 
-// Chunk m of M covers the documents [chunk_first(m), chunk_first(m + 1)): about T / M tokens each.
-int64_t chunk_first(const int64_t* doc_ptr, int64_t D, int32_t M, int32_t m) {
-    if (m <= 0) return 0;
-    if (m >= M) return D;
-    const int64_t want = doc_ptr[D] / M * m;
-    return std::lower_bound(doc_ptr, doc_ptr + D + 1, want) - doc_ptr;
-}
-
 }  // namespace
 
 struct mlda_ctx {
@@ -817,7 +777,8 @@ struct mlda_ctx {
     // ---- the chunks (one: attached for good; several: attached in turn, Algorithm 1 WorkSchedule2)
     std::vector<HostChunk> chunks;
     bool streamed = false;
-    unsigned char* slot_base[2] = {nullptr, nullptr};   // the workspace parts chunks are attached to
+    unsigned char* slot_base[2] = {nullptr, nullptr};   // where an attached chunk's layout begins
+    uint16_t* slot_z[2] = {nullptr, nullptr};           // streamed: the assignments in document order, see StreamedSlot
     uint16_t* z_host = nullptr;          // streamed: all assignments in the caller's order (pinned)
     hipStream_t copy_stream = nullptr;   // streamed: uploads run beside the kernels,
     hipStream_t down_stream = nullptr;   // and so do the downloads of new assignments
@@ -852,7 +813,7 @@ struct mlda_ctx {
     bool wide_counters = false, short_docs = true;
     int32_t* split_words = nullptr;
     uint16_t* z[2] = {nullptr, nullptr}; // word-major assignments
-    uint16_t* z_doc = nullptr;           // streamed: the same in document order (in doc_map's place)
+    uint16_t* z_doc = nullptr;           // streamed: the same in document order
     int cur = 0;
     uint2* row_rec = nullptr;
     unsigned char* slots = nullptr;
@@ -945,7 +906,6 @@ void point_at(mlda_ctx* c, const HostChunk& h, unsigned char* base) {
     c->tok_id = (int32_t*)(base + h.L.tok_id);
     c->doc_map = (int32_t*)(base + h.L.doc_map);
     c->doc_pairs = (uint2*)(base + h.L.doc_pairs);
-    c->z_doc = (uint16_t*)(base + h.L.doc_map);   // a streamed chunk needs no map, see derive_chunk_arrays
     c->doc_ptr = (int32_t*)(base + h.L.doc_ptr);
     c->doc_order = (mlda::DocRec*)(base + h.L.doc_order);
     c->row_rec = (uint2*)(base + h.L.row_rec);
@@ -1034,9 +994,10 @@ int attach(mlda_ctx* c, int32_t m, bool with_z, hipEvent_t* ev = nullptr) {
     const int s = (int)(c->visits % 2);
     c->visits += 1;
     point_at(c, h, c->slot_base[s]);
+    c->z_doc = c->slot_z[s];
     if (c->to_store >= 0 && (c->to_store == m || c->to_store_slot == s)) RC_TRY(store_z(c));
-    // the slot's previous user must be done (its assignments may still be on their way to the host: they
-    // are not in the static part), and this chunk's last assignments stored
+    // the slot's previous user must be done (its assignments may still be on their way to the host: no chunk's
+    // layout reaches them, see StreamedSlot), and this chunk's last assignments stored
     HIP_TRY(hipStreamWaitEvent(c->copy_stream, c->slot_done[s], 0));
     if (h.L.static_bytes > 0)
         HIP_TRY(hipMemcpyAsync(c->slot_base[s], h.arena, h.L.static_bytes, hipMemcpyHostToDevice,
@@ -1400,11 +1361,13 @@ int check_device_pointer(void* dev_workspace) {
 
 size_t streamed_workspace_bound(const int64_t* doc_ptr, int64_t D, int32_t V, int32_t K, int32_t M) {
     size_t chunk = 0;
+    int64_t tokens = 0;
     for (int32_t m = 0; m < M; ++m) {
         const int64_t a = chunk_first(doc_ptr, D, M, m), b = chunk_first(doc_ptr, D, M, m + 1);
+        tokens = std::max(tokens, doc_ptr[b] - doc_ptr[a]);
         chunk = std::max(chunk, chunk_layout_bound(b - a, doc_ptr[b] - doc_ptr[a], V, K, true).total);
     }
-    return model_layout(V, K, doc_ptr[D], true).total + 2 * chunk;
+    return model_layout(V, K, doc_ptr[D], true).total + 2 * mlda::streamed_slot(tokens, chunk).total;
 }
 
 // Everything mlda_create and mlda_create_streamed share: device limits, the model's buffers
@@ -2032,24 +1995,32 @@ int mlda_create_streamed(mlda_ctx** out, const int64_t* doc_ptr, const int32_t* 
         } catch (const std::bad_alloc&) { rc = fail(MLDA_ENOMEM, "out of host memory"); }
     }
     size_t chunk_bytes = 0;
+    int64_t chunk_tokens = 0;
     for (int32_t m = 0; rc == MLDA_OK && m < n_chunks; ++m) {
         rc = prepare_chunk(doc_ptr, word_ids, chunk_first(doc_ptr, D, n_chunks, m),
                            chunk_first(doc_ptr, D, n_chunks, m + 1), V, K, true, true, false, c->forced_shape(), c->chunks[(size_t)m]);
         if (rc == MLDA_OK) rc = check_theta_lds(c, c->chunks[(size_t)m]);
         if (rc == MLDA_OK) rc = mark_wide_tiles(c, c->chunks[(size_t)m]);
-        if (rc == MLDA_OK) chunk_bytes = std::max(chunk_bytes, c->chunks[(size_t)m].L.total);
+        if (rc == MLDA_OK) {
+            chunk_bytes = std::max(chunk_bytes, c->chunks[(size_t)m].L.total);
+            chunk_tokens = std::max(chunk_tokens, c->chunks[(size_t)m].T);
+        }
     }
+    const mlda::StreamedSlot slot = mlda::streamed_slot(chunk_tokens, chunk_bytes);
     const ModelLayout ML = model_layout(V, K, T, true);
-    if (rc == MLDA_OK && ML.total + 2 * chunk_bytes > workspace_bytes)
+    if (rc == MLDA_OK && ML.total + 2 * slot.total > workspace_bytes)
         rc = fail(MLDA_ENOMEM, "workspace has " + std::to_string(workspace_bytes) + " bytes, need " +
-                                   std::to_string(ML.total + 2 * chunk_bytes));
+                                   std::to_string(ML.total + 2 * slot.total));
     auto hip_ok = [&](hipError_t e, const char* what) {
         if (rc == MLDA_OK && e != hipSuccess) rc = fail(MLDA_EHIP, std::string(what) + ": " + hipGetErrorString(e));
     };
     if (rc == MLDA_OK) {
         unsigned char* base = (unsigned char*)dev_workspace;
-        c->slot_base[0] = base + ML.total;
-        c->slot_base[1] = c->slot_base[0] + chunk_bytes;
+        for (int s = 0; s < 2; ++s) {
+            unsigned char* at = base + ML.total + (size_t)s * slot.total;
+            c->slot_z[s] = (uint16_t*)(at + slot.z_doc);
+            c->slot_base[s] = at + slot.chunk;
+        }
         void* zh = nullptr;
         hip_ok(hipHostMalloc(&zh, std::max<size_t>((size_t)T * 2, 1), hipHostMallocDefault), "hipHostMalloc");
         c->z_host = (uint16_t*)zh;

@@ -636,6 +636,39 @@ def test_streamed_chunks_match_oracle(mlda, chunks):
     model.close()
 
 
+@pytest.mark.parametrize("chunks", [3, 4, 5, 8])
+@pytest.mark.parametrize("order", ["long_first", "short_first", "long_and_empty"])
+def test_streamed_chunks_of_different_shapes(mlda, order, chunks):
+    """Chunks of few long documents and chunks of many short or empty ones take turns in the same two buffers, an odd number
+    of them in the other one every iteration: one's records are copied in while another's assignments are copied out."""
+    V, K, alpha, beta = 3000, 100, 0.5, 0.01
+    lengths = np.repeat([300, 5], [1000, 60000])
+    if order == "short_first":
+        lengths = lengths[::-1]
+    elif order == "long_and_empty":
+        lengths = np.concatenate([np.full(1500, 200), np.zeros(150000, dtype=np.int64), np.full(1500, 200)])
+
+    class C:
+        pass
+    c = C(); c.T = int(lengths.sum())
+    c.doc_ptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    rng = np.random.default_rng(chunks)
+    c.word_ids = np.minimum(rng.zipf(1.3, c.T) - 1, V - 1).astype(np.int32)
+    say("different shapes", order, "chunks", chunks, "T", c.T)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, beta, SEED, chunks=chunks)
+    model.init_random()
+    z = oracle.init_topics(c.T, K, SEED)
+    assert np.array_equal(model.assignments(), z)
+    for it in (1, 2, 3):
+        z = check_step(model, c, z, V, K, alpha, beta, SEED, it)
+    model.step(2, loglik=True)
+    for it in (4, 5):
+        n_wk, n_k = oracle.count_word_topic(c.word_ids, z, V, K)
+        z = oracle.iteration(c.doc_ptr, c.word_ids, z, V, K, alpha, beta, SEED, it, n_wk, n_k)
+    assert int((model.assignments() != z).sum()) <= Z_MISMATCH_FRACTION * c.T
+    model.close()
+
+
 def test_streamed_with_weights_in_device_memory(mlda):
     """K beyond the LDS column, the corpus in three chunks: p* in device memory, phi counted in
     two ranges of topics and added to chunk by chunk."""
