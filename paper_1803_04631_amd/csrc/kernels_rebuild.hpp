@@ -757,10 +757,11 @@ __host__ __device__ inline int theta_rank_stage(int64_t longest, int docs) {
     const int64_t most = docs == 1 ? kRankStage : 256, n = longest - rank_keep(docs) * (kWave / docs);
     return n <= 0 ? 0 : (int)(((n < most ? n : most) + 3) & ~(int64_t)3);
 }
-// (a wave's own, and of a workgroup of so many waves with the table)
+// (a wave's own, and of a workgroup of so many waves with the table.  Whole 16 bytes: the next wave's words and cells are read and
+// written by so many, and one document's stage may end in the middle of them)
 __host__ __device__ inline size_t theta_rank_wave_bytes(int32_t K, int64_t longest, int docs) {
-    return (size_t)docs * ((size_t)theta_rank_words(K) * 8 + (size_t)theta_rank_cells(K, longest, docs) * 4 +
-                           (size_t)theta_rank_stage(longest, docs) * 2);
+    return ((size_t)docs * ((size_t)theta_rank_words(K) * 8 + (size_t)theta_rank_cells(K, longest, docs) * 4 +
+                            (size_t)theta_rank_stage(longest, docs) * 2) + 15) & ~(size_t)15;
 }
 __host__ __device__ inline size_t theta_rank_lds_bytes(int32_t K, int64_t longest, int docs, int waves = 1) {
     return (size_t)waves * theta_rank_wave_bytes(K, longest, docs) + (size_t)kThetaLgTable * 8;

@@ -809,6 +809,29 @@ def test_phi_cells_of_changed_topics(mlda, K):
     model.close()
 
 
+@pytest.mark.parametrize("K,longest", [(1500, 300), (453, 700), (1025, 132), (3072, 3071), (300, 500)])
+def test_one_launch_rebuild_with_one_document_per_wave(mlda, K, longest):
+    """phi and theta in one launch, four waves to a workgroup and a document to a wave, whose parts of LDS end in the middle of
+    16 bytes: documents of 0 tokens to the longest, whose tokens beyond those in registers are an odd number of times four."""
+    V, alpha, beta = 500, 50.0 / K, 0.01
+    rng = np.random.default_rng(longest)
+    lengths = rng.permutation(np.concatenate([np.full(20, longest), rng.integers(0, longest + 1, 60), np.full(60, longest // 4),
+                                              [0, 1, 2, 127, 128, 129]]))
+
+    class C:
+        pass
+    c = C(); c.T = int(lengths.sum())
+    c.doc_ptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    c.word_ids = rng.integers(V, size=c.T).astype(np.int32)
+    say("one document per wave", K, longest, "T", c.T)
+    model = mlda.Mlda(c.doc_ptr, c.word_ids, V, K, alpha, beta, SEED)
+    model.init_random()
+    z = oracle.init_topics(c.T, K, SEED)
+    for it in (1, 2):
+        z = check_step(model, c, z, V, K, alpha, beta, SEED, it)
+    model.close()
+
+
 @pytest.mark.parametrize("K", [40, 3000])
 def test_assignments_change_order_tile_by_tile(mlda, K, monkeypatch):
     """Both directions, tiles of every size up to the largest and one more, and a number of them that eight does not divide."""
