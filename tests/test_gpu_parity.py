@@ -1003,6 +1003,24 @@ def test_large_transfers(mlda, how):
         model.close()
 
 
+def test_getters_leave_nothing_on_the_stream(mlda):
+    """A getter synchronises the stream, whichever way its bytes take: of 16 MB and 9 MB, and of few."""
+    V, K = 70000, 64
+    rng = np.random.default_rng(5)
+    T = (8 << 20) + 4321
+    doc_ptr = np.append(np.arange(0, T, 100), T).astype(np.int64)
+    model = mlda.Mlda(doc_ptr, rng.integers(V, size=T).astype(np.int32), V, K, 0.5, 0.01, SEED)
+    model.init_random()
+    busy = {"assignments": 0, "word_topic": 0, "doc_topic_csr": 0, "topic_totals": 0, "loglik": 0}
+    for _ in range(20):
+        for name in busy:
+            getattr(model, name)()
+            busy[name] += not model.stream.query()
+    say(busy)
+    model.close()
+    assert not any(busy.values())
+
+
 def test_empty_corpus(mlda):
     doc_ptr = np.zeros(4, dtype=np.int64)
     model = mlda.Mlda(doc_ptr, np.zeros(0, dtype=np.int32), 5, 3, 0.5, 0.01, 1)
