@@ -1816,6 +1816,7 @@ int export_rows(mlda_ctx* c, const std::vector<uint2>& rec, const int64_t* row_p
 // Streamed: phi and n_k of the assignments in z_host (after init or set_assignments);
 // `init`: the assignments are drawn on the device first and stored.
 int rebuild_model_streamed(mlda_ctx* c, bool init) {
+    c->to_store = -1;       // (a step that failed may have left some: not into the assignments that are to be counted)
     RC_TRY(begin_model(c, c->model_cur));
     for (int32_t m = 0; m < (int32_t)c->chunks.size(); ++m) {
         if (c->chunks[(size_t)m].D == 0) continue;
