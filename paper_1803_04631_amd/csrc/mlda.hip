@@ -1118,6 +1118,7 @@ int rebuild_phi(mlda_ctx* c, const uint16_t* z, int which, const uint16_t* z_old
                                dim3(256), std::max(phi_lds, c->both_lds), c->stream, p, t, (int32_t)blocks, n_theta);
             return 0;
         });
+        RC_TRY(launch_check("rebuild kernel"));         // (a launch that failed has cleared no totals)
         c->spare_n_k_cleared = t.old_n_k != nullptr;
         c->theta_grid = 4 * n_theta;
         c->rebuilds += 1;

@@ -14,6 +14,12 @@ STAND_IN = r'''
 #include <hip/hip_runtime_api.h>
 #include <stdlib.h>
 #include <string.h>
+struct Launch { char name[64]; int failed; long long value; };
+static struct Launch launches[4096];
+static int n_launches = 0;
+static const void* kernels[1024];
+static const char* names[1024];
+static int n_kernels = 0;
 static int left = -1;                   // launches before the one that fails; negative: none does
 static hipError_t last = hipSuccess;
 static char somewhere[256];
@@ -21,8 +27,21 @@ extern "C" {
 char FATBIN[16];
 void fail_after(int launches) { left = launches; }
 int launches_left() { return left; }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
-    if (left >= 0 && left-- == 0) return last = hipErrorLaunchFailure;
+void forget_launches() { n_launches = 0; }
+int launched(int i, char* name, int* failed, long long* value) {
+    if (i >= n_launches) return 0;
+    strcpy(name, launches[i].name); *failed = launches[i].failed; *value = launches[i].value;
+    return 1;
+}
+hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void** args, size_t, hipStream_t) {
+    const int fails = left >= 0 && left-- == 0;
+    struct Launch* l = &launches[n_launches < 4095 ? n_launches++ : 4095];
+    l->name[0] = 0; l->failed = fails; l->value = 0;
+    for (int i = 0; i < n_kernels; ++i)
+        if (kernels[i] == kernel) strncpy(l->name, names[i], 63);
+    // whether the totals are cleared by it
+    if (strstr(l->name, "zero_sums_kernel")) l->value = *(void**)args[3] != 0;
+    if (fails) return last = hipErrorLaunchFailure;
     return hipSuccess;
 }
 hipError_t hipGetLastError(void) { const hipError_t e = last; last = hipSuccess; return e; }
@@ -30,7 +49,9 @@ const char* hipGetErrorString(hipError_t) { return "stand-in"; }
 hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
 void** __hipRegisterFatBinary(const void*) { static void* p; return &p; }
-void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
+void __hipRegisterFunction(void**, const void* host, char* name, const char*, unsigned, void*, void*, void*, void*, int*) {
+    kernels[n_kernels] = host; names[n_kernels++] = name;
+}
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 void __hipUnregisterFatBinary(void**) {}
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
@@ -72,6 +93,15 @@ def lib(tmp_path_factory):
     subprocess.check_call(["g++", "-O1", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", str(d / "hip.cpp"),
                            str(d / "mlda.o"), "-lpthread", "-Wl,-Bsymbolic", "-Wl,-z,defs", "-o", str(d / "mlda.so")])
     return ctypes.CDLL(str(d / "mlda.so"))
+
+
+def launches_of(lib):
+    """(kernel, whether its launch failed, value) of the launches since forget_launches."""
+    name, failed, value = ctypes.create_string_buffer(64), ctypes.c_int(), ctypes.c_longlong()
+    found = []
+    while lib.launched(len(found), name, ctypes.byref(failed), ctypes.byref(value)):
+        found.append((name.value.decode(), bool(failed.value), value.value))
+    return found
 
 
 class Model:
@@ -124,3 +154,41 @@ def test_assignments_installed_after_a_failed_step(lib, chunks, loglik):
         if not reached:
             break
     assert failed > 5 * chunks and rc == 0
+
+
+def corpus(seed, V, T_most=30):
+    rng = np.random.default_rng(seed)
+    doc_ptr = np.concatenate([[0], np.cumsum(rng.integers(1, T_most, 60))]).astype(np.int64)
+    return doc_ptr, rng.integers(V, size=doc_ptr[-1]).astype(np.int32)
+
+
+def test_totals_are_cleared_after_a_failed_step(lib):
+    """The topic totals are added to.  Where one launch rebuilds phi and theta it also clears the totals that nobody reads any more;
+    if it fails they are as they were, and the next rebuild has to clear those that it adds to."""
+    V, K = 40, 12
+    doc_ptr, words = corpus(7, V)
+    z = (np.arange(doc_ptr[-1]) % K).astype(np.uint16)
+    failed_rebuilds = 0
+    for launches in range(1000):
+        lib.forget_launches()
+        m = Model(lib, doc_ptr, words, V, K, 1)
+        lib.fail_after(launches)
+        rc = lib.mlda_step(m.ctx, 3, 1)
+        reached = lib.launches_left() < 0
+        lib.fail_after(-1)
+        lib.hipGetLastError()
+        cleared = False
+        for name, failed, _ in launches_of(lib):
+            if "phi_tile" in name:                  # takes what is cleared into use
+                cleared = False
+            elif "theta" in name or "rebuild_kernel" in name:
+                cleared = not failed
+                failed_rebuilds += failed
+        lib.forget_launches()
+        assert lib.mlda_set_assignments(m.ctx, ctypes.c_void_p(z.ctypes.data), 0) == 0
+        clears = [value for name, _, value in launches_of(lib) if "zero_sums" in name]
+        m.close()
+        assert clears == ([] if cleared else [1]), (launches, rc)
+        if not reached:
+            break
+    assert failed_rebuilds == 3 and rc == 0
