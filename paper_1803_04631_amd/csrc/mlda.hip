@@ -762,6 +762,7 @@ struct mlda_ctx {
     int32_t last_step_iters = 0;
     bool last_step_loglik = false;
     bool has_state = false, ll_fresh = false;
+    bool phi_of_z = false;              // resident: phi holds the counts of z[cur] (false while, and if, a rebuild has not gone through)
     std::vector<hipEvent_t> events;     // streamed: kVisitEvents per timed visit
     int32_t timed_iters = 0;            // iterations of the last step that carry events or stamps
     // streamed: what mlda_get_timing and mlda_get_sampler_bytes need of every timed chunk visit
@@ -2070,8 +2071,10 @@ int mlda_init_random(mlda_ctx* c) {
             hipLaunchKernelGGL(mlda::init_topics_kernel, dim3(blocks_for(c->T, 256)), dim3(256), 0,
                                c->stream, c->tok_id, c->z[c->cur], c->T, c->K, c->seed);
         RC_TRY(launch_check("init_topics_kernel"));
+        c->phi_of_z = false;
         RC_TRY(rebuild_phi(c, c->z[c->cur], 0));
         RC_TRY(rebuild_theta(c, c->z[c->cur]));
+        c->phi_of_z = true;
     }
     c->iter = 0;
     c->has_state = true;
@@ -2101,6 +2104,7 @@ int mlda_set_assignments(mlda_ctx* c, const uint16_t* z, int32_t iter) {
             return fail(MLDA_ENOMEM, "out of host memory");
         RC_TRY(rebuild_model_streamed(c, false));
     } else {
+        c->phi_of_z = false;
         if (c->T > 0) {
             uint16_t* tmp = c->z[c->cur ^ 1];
             RC_TRY(send(c, tmp, z, (size_t)c->T * 2));    // (done: the caller's z may go away)
@@ -2113,6 +2117,7 @@ int mlda_set_assignments(mlda_ctx* c, const uint16_t* z, int32_t iter) {
         }
         RC_TRY(rebuild_phi(c, c->z[c->cur], 0));
         RC_TRY(rebuild_theta(c, c->z[c->cur]));
+        c->phi_of_z = true;
     }
     c->iter = iter;
     c->has_state = true;
@@ -2205,13 +2210,16 @@ int mlda_step(mlda_ctx* c, int32_t n_iters, uint32_t flags) {
         auto phase = [&](int p) { return row >= 0 ? c->stamps + (size_t)row * kPhases + p : nullptr; };
         uint16_t *z_old = c->z[c->cur], *z_next = c->z[c->cur ^ 1];
         RC_TRY(launch_sampler(c, z_old, z_next, phase(0)));
+        const uint16_t* counted = c->phi_of_z ? z_old : nullptr;
+        c->phi_of_z = false;
         if (c->both_lds > 0) {
-            RC_TRY(rebuild_phi(c, z_next, 0, z_old, phase(1), true, phase(2)));
+            RC_TRY(rebuild_phi(c, z_next, 0, counted, phase(1), true, phase(2)));
         } else {
-            RC_TRY(rebuild_phi(c, z_next, 0, z_old, phase(1)));
+            RC_TRY(rebuild_phi(c, z_next, 0, counted, phase(1)));
             RC_TRY(rebuild_theta(c, z_next, phase(2)));
         }
         c->cur ^= 1;
+        c->phi_of_z = true;
         c->iter += 1;
         c->ll_fresh = false;
         if (c->last_step_loglik) RC_TRY(launch_loglik(c, phase(3)));

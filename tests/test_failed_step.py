@@ -39,8 +39,9 @@ hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void** args, size_t, 
     l->name[0] = 0; l->failed = fails; l->value = 0;
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i] == kernel) strncpy(l->name, names[i], 63);
-    // whether the totals are cleared by it
+    // whether the totals are cleared by it; PhiArgs::n_changed
     if (strstr(l->name, "zero_sums_kernel")) l->value = *(void**)args[3] != 0;
+    if (strstr(l->name, "phi_tile_kernel")) l->value = ((int*)args[0])[4];
     if (fails) return last = hipErrorLaunchFailure;
     return hipSuccess;
 }
@@ -192,3 +193,42 @@ def test_totals_are_cleared_after_a_failed_step(lib):
         if not reached:
             break
     assert failed_rebuilds == 3 and rc == 0
+
+
+@pytest.mark.parametrize("installed", [False, True])
+def test_rows_of_phi_are_written_anew_after_a_failed_call(lib, installed):
+    """Beyond 4,096 topics a step changes the cells of a word's old and new topics and leaves the rest of its row.  A rebuild
+    that has not gone through, a step's or that of an installed state, leaves rows of other assignments: the next one writes
+    them whole."""
+    V, K = 40, 5000
+    doc_ptr, words = corpus(7, V)
+    z = (np.arange(doc_ptr[-1]) % K).astype(np.uint16)
+    n_words = len(np.unique(words))
+    assert np.bincount(words).max() <= K // 64
+    anew = 0
+    for launches in range(1000):
+        lib.forget_launches()
+        m = Model(lib, doc_ptr, words, V, K, 1)
+        lib.fail_after(launches)
+        if installed:
+            rc = lib.mlda_set_assignments(m.ctx, ctypes.c_void_p(z.ctypes.data), 0)
+        else:
+            rc = lib.mlda_step(m.ctx, 3, 1)
+        reached = lib.launches_left() < 0
+        lib.fail_after(-1)
+        lib.hipGetLastError()
+        whole = True            # a rebuild of phi has been followed by one of theta
+        for name, failed, _ in launches_of(lib):
+            if "phi_tile" in name:
+                whole = False
+            elif "theta_r" in name and not failed:
+                whole = True
+        lib.forget_launches()
+        assert lib.mlda_step(m.ctx, 2, 0) == 0
+        changed = [value for name, _, value in launches_of(lib) if "phi_tile" in name]
+        m.close()
+        assert changed == ([n_words, n_words] if whole and not (installed and rc) else [0, n_words]), (launches, rc)
+        anew += changed[0] == 0
+        if not reached:
+            break
+    assert anew >= (2 if installed else 6) and rc == 0
