@@ -86,7 +86,7 @@ int mlda_workspace_bytes(int64_t D, int64_t T, int32_t V, int32_t K, size_t* byt
  * topics are assigned yet: call mlda_init_random or mlda_set_assignments next.
  * K: 1 .. 65,535 (MLDA_EINVAL outside).  A K whose column of p* does not fit the 160 KB of LDS
  * of a workgroup (beyond about 26,100) is sampled with the rest of it in device memory: same results,
- * slower per token; the workspace then holds room for it, and beyond 30,900 for 512 such columns more.
+ * slower per token; the workspace then holds room for it, and beyond 30,943 for 512 such columns more.
  * Environment, read here and by the other two ways to create a context, for tests: it takes forms that are
  * otherwise left to other sizes, with the same results, and slower.  A value that is not as said, and an empty one,
  * counts as none.
@@ -146,7 +146,7 @@ int mlda_create_streamed(mlda_ctx** out, const int64_t* doc_ptr, const int32_t* 
  *   - The array keeps what the previous context left there; the library initialises
  *     every part it reads, as it does for a caller's uninitialised workspace.
  */
-#define MLDA_STATIC_WORKSPACE_BYTES (64u << 20)
+#define MLDA_STATIC_WORKSPACE_BYTES (68u << 20)
 int mlda_create_static(mlda_ctx** out, const int64_t* doc_ptr, const int32_t* word_ids,
                        int64_t D, int32_t V, int32_t K, double alpha, double beta, uint64_t seed,
                        void* hip_stream);

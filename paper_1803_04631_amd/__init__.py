@@ -15,7 +15,7 @@ import numpy as np
 from ._build import LIB_PATH, build  # noqa: F401  (re-exported)
 
 STEP_LOGLIK = 1
-STATIC_WORKSPACE_BYTES = 64 << 20     # MLDA_STATIC_WORKSPACE_BYTES of include/mlda.h
+STATIC_WORKSPACE_BYTES = 68 << 20     # MLDA_STATIC_WORKSPACE_BYTES of include/mlda.h
 
 _lib = None
 

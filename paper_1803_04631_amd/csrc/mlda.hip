@@ -103,9 +103,10 @@ int32_t near_topics_for(int32_t K) {
     const size_t rest = mlda::sample_far_lds_bytes(kpad_for(K), sample_waves_for(K), 0);
     return (int32_t)std::min<size_t>((kLdsPerWorkgroup - rest) / 4, (size_t)kpad_for(K)) & ~15;
 }
-// What the others take of the workspace.  (Beyond kFarColumnsFrom topics, where little else fits LDS besides a whole
-// column, callers are told of kFarColumns whole ones on top: the bound that mlda.h has named from the start.)
-constexpr int32_t kFarColumnsFrom = 30900;
+// What the others take of the workspace.  (Beyond kFarColumnsFrom topics, where a whole column beside twelve waves' records
+// exceeds the LDS, callers are told of kFarColumns whole ones on top: the bound that mlda.h has named from the start.  The
+// strips need no more than 42 MB of it, at K = 65,535.)
+constexpr int32_t kFarColumnsFrom = 30943;
 constexpr int kFarColumns = 512;
 size_t far_bytes_for(int32_t K) {
     if (!far_weights_for(K)) return 0;

@@ -58,6 +58,24 @@ def test_workspace_bytes_validates_and_bounds(lib):
     assert sizes[65_535] >= 512 * 65_536 * 4
 
 
+# (documents, tokens, words, topics): the most words that have fitted 64 MiB with an earlier layout of the workspace
+FITTED = [(1, 1, 1594624, 1), (1000, 100000, 219083, 128), (1000, 100000, 31785, 1000), (1, 1, 8133, 4096), (1000, 100000, 2825, 11440),
+          (1, 1, 1277, 26159), (1, 1, 1277, 26160), (1000, 100000, 1076, 30000), (1, 1, 1081, 30900), (1000, 100000, 1044, 30901),
+          (1, 1, 1079, 30943), (1, 1, 55, 30944), (1000, 100000, 17, 31000), (1, 1, 19, 32000), (1, 1, 1, 32589)]
+
+
+@pytest.mark.parametrize("D,T,V,K", FITTED)
+def test_the_static_workspace_holds_what_it_held(lib, D, T, V, K):
+    """Device memory beside phi and the corpus (the phases' times, counts of two theta rebuilds, strips of p*) has grown: the
+    static array with it."""
+    n = ctypes.c_size_t()
+    assert lib.mlda_workspace_bytes(D, T, V, K, ctypes.addressof(n)) == 0
+    assert n.value <= mlda.STATIC_WORKSPACE_BYTES
+    # (512 columns of p* belong to the workspace from K = 30,944 on)
+    assert lib.mlda_workspace_bytes(10, 1000, 5, K, ctypes.addressof(n)) == 0
+    assert (n.value < 8 << 20) == (K < 30944)
+
+
 def test_create_rejects_bad_arguments_on_the_host(lib):
     ctx = ctypes.c_void_p()
     out = ctypes.addressof(ctx)
