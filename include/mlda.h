@@ -111,7 +111,7 @@ int mlda_create(mlda_ctx** out, const int64_t* doc_ptr, const int32_t* word_ids,
  * of default priority that the library creates, overlapping the kernels of the chunk
  * before), its theta rows are rebuilt from its assignments, it is sampled against the phi of
  * the iteration's start, its counts are added to the next phi, and its new assignments go
- * back to the host (on a second such stream, beside the sampling of the chunk after).  Results are those of mlda_create: the counts of an iteration are frozen
+ * back to the host (on a second such stream, beside the work on the chunk after).  Results are those of mlda_create: the counts of an iteration are frozen
  * and the uniforms are keyed by the caller's token index.  (A draw that lies within the fp64 rounding of a sum over a
  * theta row may come out one topic off, as the sums' order depends on the tokens worked on together; none has been seen.)
  * The workspace (mlda_workspace_bytes_streamed: two copies of phi and two chunk buffers) and

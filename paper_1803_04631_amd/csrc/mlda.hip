@@ -1035,13 +1035,21 @@ int to_document_order(mlda_ctx* c, const uint16_t* z_word) {
     return launch_check("to_doc_major_scatter_kernel");
 }
 
-// Streamed: the attached chunk's visit is over.  `store`: its assignments (z_doc) are to go to the host, which store_z
-// starts later, beside the sampling of the next chunk.  (The copy is a kernel that waits for the link most of the time, and
-// while it runs every other launch takes until it is nearly done to end: started right away, the short launches at the
-// next visit's start took its 0.9 ms per 2.5e7 tokens; two iterations on 9.9e7 tokens in four chunks 41.7 ms, now 33.8.)
-// Where the chunks are many, it starts at once: the next upload but one waits for it.  An iteration, later / at once, ms:
-//   9.9e7 tokens in 4 chunks 15.3/15.6   8 17.0/16.8   16 21.1/20.8    7.4e8 in 4 84.5/84.9   8 89.8..101/88   16 115..125/109
+// Streamed: the attached chunk's visit is over.  `store`: its assignments (z_doc) are to go to the host.  The copy starts at
+// once, or where chunks are few and small later, beside the sampling of the next chunk: a visit is then bound by its short launches,
+// and right after them the copy holds up the next visit's.  Large chunks have nothing to gain, and the next upload but one
+// waits for the copy's end.  An iteration that starts copies later as a share of one that starts them at once (in the mean over corpora of
+// 25 to 10,000 tokens a document, with and without their outputs fetched):
+//   tokens a chunk     1e4   5e4   1.5e5  3e5   4e5   5e5   6e5   1.2e6  2.5e6
+//   2 chunks           0.93  0.93  0.95   0.92  0.92  1.02  1.01  1.05   1.04
+//   3                  0.91  0.93  0.94   0.96              1.04  1.06   1.05
+//   6                  0.94  0.96  0.97   0.99  1.02  1.06  1.07  1.18   1.17
+//   7                  0.98  0.96  0.99   1.00  1.03
+//   12                 0.98  0.98  1.00   1.03  1.07
+//   20                 0.99  0.98  1.02   1.06  1.08
+// (9.9e7 tokens in 2 to 7 chunks 1.00 to 1.01, 7.4e8 in 2 to 8 chunks 1.00.)
 constexpr size_t kFewChunks = 6;
+constexpr int64_t kFewChunkTokens = 400000;
 int store_z_and_release(mlda_ctx* c, int32_t m, bool store) {
     const int s = (int)((c->visits - 1) % 2);
     HIP_TRY(hipEventRecord(c->slot_done[s], c->stream));
@@ -1050,7 +1058,7 @@ int store_z_and_release(mlda_ctx* c, int32_t m, bool store) {
         c->to_store = m;
         c->to_store_slot = s;
         c->to_store_z = c->z_doc;
-        if (c->chunks.size() > kFewChunks) RC_TRY(store_z(c));
+        if (c->chunks.size() > kFewChunks || c->T > kFewChunkTokens) RC_TRY(store_z(c));
     } else {
         HIP_TRY(hipEventRecord(c->slot_free[s], c->stream));
     }

@@ -72,7 +72,14 @@ hipError_t hipEventElapsedTime(float* t, hipEvent_t, hipEvent_t) { *t = 0.f; ret
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = calloc(n ? n : 1, 1); return hipSuccess; }
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return hipSuccess; }
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memmove(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind kind, hipStream_t) {
+    if (kind == hipMemcpyDeviceToHost && n_launches < 4095) {
+        struct Launch* l = &launches[n_launches++];
+        strcpy(l->name, "copy down"); l->failed = 0; l->value = (long long)n;
+    }
+    memmove(d, s, n);
+    return hipSuccess;
+}
 hipError_t hipMemcpyWithStream(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memmove(d, s, n); return hipSuccess; }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void*) { memset(a, 0, sizeof *a); a->type = hipMemoryTypeDevice; return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)somewhere; return hipSuccess; }
@@ -161,6 +168,25 @@ def corpus(seed, V, T_most=30):
     rng = np.random.default_rng(seed)
     doc_ptr = np.concatenate([[0], np.cumsum(rng.integers(1, T_most, 60))]).astype(np.int64)
     return doc_ptr, rng.integers(V, size=doc_ptr[-1]).astype(np.int32)
+
+
+@pytest.mark.parametrize("chunks,tokens,later", [(3, 400000, True), (6, 5000, True), (3, 400100, False), (6, 900000, False), (7, 5000, False)])
+def test_when_new_assignments_start_down(lib, chunks, tokens, later):
+    """Few small chunks: beside the sampling of the next one.  Large ones and many: right behind the launches that made them,
+    as the upload after the next waits for the copy."""
+    V, K = 40, 12
+    doc_ptr = np.arange(0, chunks * tokens + 1, 100, dtype=np.int64)
+    words = np.random.default_rng(0).integers(V, size=doc_ptr[-1]).astype(np.int32)
+    m = Model(lib, doc_ptr, words, V, K, chunks)
+    lib.forget_launches()
+    assert lib.mlda_step(m.ctx, 2, 0) == 0
+    found = launches_of(lib)
+    m.close()
+    copies = [i for i, (name, _, _) in enumerate(found) if name == "copy down"]
+    assert [found[i][2] for i in copies] == [2 * tokens] * (2 * chunks)
+    at_once = sum("to_doc_major" in found[i - 1][0] for i in copies)
+    beside_next = sum(i + 1 < len(found) and "sample_kernel" in found[i + 1][0] for i in copies)
+    assert (at_once, beside_next) == ((0, 2 * chunks - 1) if later else (2 * chunks, 0))
 
 
 def test_totals_are_cleared_after_a_failed_step(lib):
