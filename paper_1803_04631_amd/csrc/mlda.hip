@@ -973,12 +973,10 @@ void derive_chunk_arrays(mlda_ctx* c) {
                        (int64_t)(kSlotAlign / 4), (int32_t)pad);
 }
 
-// Streamed: the assignments that are yet to be downloaded start on their way, on a stream of their own, when the
-// context's stream gets here.
+// Streamed: the assignments that are yet to be downloaded are put on their way, on a stream of their own.
 int store_z(mlda_ctx* c) {
     if (c->to_store < 0) return MLDA_OK;
     const HostChunk& h = c->chunks[(size_t)c->to_store];
-    HIP_TRY(hipEventRecord(c->z_ready, c->stream));
     HIP_TRY(hipStreamWaitEvent(c->down_stream, c->z_ready, 0));
     HIP_TRY(hipMemcpyAsync(c->z_host + h.tok_begin, c->to_store_z, (size_t)h.T * 2, hipMemcpyDeviceToHost, c->down_stream));
     HIP_TRY(hipEventRecord(c->z_stored[(size_t)c->to_store], c->down_stream));
@@ -1011,6 +1009,7 @@ int attach(mlda_ctx* c, int32_t m, bool with_z, hipEvent_t* ev = nullptr) {
                                c->copy_stream));
     }
     HIP_TRY(hipEventRecord(c->slot_ready[s], c->copy_stream));
+    RC_TRY(store_z(c));         // (of the chunk before, see store_z_and_release)
     HIP_TRY(hipStreamWaitEvent(c->stream, c->slot_ready[s], 0));
     if (ev) HIP_TRY(hipEventRecord(ev[0], c->stream));
     derive_chunk_arrays(c);
@@ -1035,30 +1034,27 @@ int to_document_order(mlda_ctx* c, const uint16_t* z_word) {
     return launch_check("to_doc_major_scatter_kernel");
 }
 
-// Streamed: the attached chunk's visit is over.  `store`: its assignments (z_doc) are to go to the host.  The copy starts at
-// once, or where chunks are few and small later, beside the sampling of the next chunk: a visit is then bound by its short launches,
-// and right after them the copy holds up the next visit's.  Large chunks have nothing to gain, and the next upload but one
-// waits for the copy's end.  An iteration that starts copies later as a share of one that starts them at once (in the mean over corpora of
-// 25 to 10,000 tokens a document, with and without their outputs fetched):
-//   tokens a chunk     1e4   5e4   1.5e5  3e5   4e5   5e5   6e5   1.2e6  2.5e6
-//   2 chunks           0.93  0.93  0.95   0.92  0.92  1.02  1.01  1.05   1.04
-//   3                  0.91  0.93  0.94   0.96              1.04  1.06   1.05
-//   6                  0.94  0.96  0.97   0.99  1.02  1.06  1.07  1.18   1.17
-//   7                  0.98  0.96  0.99   1.00  1.03
-//   12                 0.98  0.98  1.00   1.03  1.07
-//   20                 0.99  0.98  1.02   1.06  1.08
-// (9.9e7 tokens in 2 to 7 chunks 1.00 to 1.01, 7.4e8 in 2 to 8 chunks 1.00.)
-constexpr size_t kFewChunks = 6;
-constexpr int64_t kFewChunkTokens = 400000;
+// Streamed: the attached chunk's visit is over.  `store`: its assignments (z_doc) are to go to the host as soon as they are made.  The
+// copy is put into its queue by store_z, behind the next chunk's uploads: streams share hardware queues (four in a process: those
+// of a second context already), and a copy in front of the uploads that waits for this chunk's kernels would make them wait, too.
+// Two iterations with their outputs fetched, ms, the copy queued before the next uploads / after them / after the next theta rebuild:
+//   9.9e7 tokens in 4 chunks, first context of a process 31.2/31.2/31.8, second 54.0/34.6/38.7, third 48.4/48.1/48.4
+// An iteration as a share of one with the copy queued before the next uploads, in the mean over corpora of 25 to 10,000 tokens a
+// document, after them / after the next theta rebuild:
+//   tokens a chunk   1e4        5e4        1.5e5      4e5        1.2e6      4e6
+//   2 chunks         0.91/0.95  0.90/0.93  0.92/0.95  0.88/0.91  1.00/1.03  1.00/1.04
+//   4                0.91/0.95  0.92/0.93  0.95/0.96  0.92/0.96  1.03/1.10  1.01/1.04
+//   6                0.92/0.97  0.93/0.95  0.97/0.98  0.94/1.01  1.03/1.17  1.01/1.03
+//   12               0.93/0.98  0.96/0.98  0.99/1.00  0.97/1.06  1.00/1.18  1.03/1.17
 int store_z_and_release(mlda_ctx* c, int32_t m, bool store) {
     const int s = (int)((c->visits - 1) % 2);
     HIP_TRY(hipEventRecord(c->slot_done[s], c->stream));
     if (store && c->T > 0) {
         RC_TRY(store_z(c));
+        HIP_TRY(hipEventRecord(c->z_ready, c->stream));
         c->to_store = m;
         c->to_store_slot = s;
         c->to_store_z = c->z_doc;
-        if (c->chunks.size() > kFewChunks || c->T > kFewChunkTokens) RC_TRY(store_z(c));
     } else {
         HIP_TRY(hipEventRecord(c->slot_free[s], c->stream));
     }
@@ -2163,7 +2159,6 @@ static int step_streamed(mlda_ctx* c, bool loglik, int32_t timed_row) {
         }
         RC_TRY(rebuild_theta(c, c->z_doc));            // theta is not kept between visits
         if (ev) HIP_TRY(hipEventRecord(ev[2], c->stream));
-        RC_TRY(store_z(c));                            // (of the chunk before, beside this launch)
         RC_TRY(launch_sampler(c, c->z[0], c->z[1]));
         if (ev) HIP_TRY(hipEventRecord(ev[3], c->stream));
         RC_TRY(rebuild_phi(c, c->z[1], next));
