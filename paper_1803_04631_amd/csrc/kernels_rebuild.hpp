@@ -7,8 +7,6 @@
 
 namespace mlda {
 
-__global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
-
 // (where no launch of the phase itself stores it)
 __global__ void stamp_kernel(unsigned long long* at) { stamp_start(at); }
 

@@ -61,7 +61,7 @@ constexpr size_t kSlotAlign = 64;     // theta row slot alignment (bytes)
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;
 // waves per sampling workgroup: more of them share one staged p* column when K is large
 // (twelve: two such workgroups fill a CU's six waves per SIMD, and their LDS fits twice; sixteen
-// where it does not, K beyond 11,300: 4e6 tokens at K = 13,000 608 us against 697, 2e6 at 29,000 910 against 1,085)
+// where it does not, from K = 11,440 on: 4e6 tokens at K = 13,000 608 us against 697, 2e6 at 29,000 910 against 1,085)
 size_t queued_lds_bytes(int32_t K, int waves) {
     const int32_t g = mlda::dense_group(waves), Kpad = (K + g) / g * g;
     return mlda::sample_lds_bytes(Kpad, waves, 4) + mlda::sample_run_lds_bytes(Kpad, waves);
