@@ -1098,21 +1098,6 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     [[maybe_unused]] int last_ti = -1;          // kQueue: the tile before
     for (int ti = (int)blockIdx.x;;) {
     const bool small = kQueue && ti >= a.n_single, follows = small && last_ti >= a.n_single;
-    // kQueue: the next tile is asked for by one thread while the groups' sums are added up, and told the others.  (Asked for
-    // any earlier it holds up that wave's loads, which come back in order: 4 % slower where tiles have few tokens.)
-    [[maybe_unused]] uint32_t taken = 0;
-    auto ask_next = [&]() {
-        if constexpr (kQueue)
-            if (lane == 0) taken = atomicAdd(a.next_tile, 1u);
-    };
-    auto tell_next = [&]() {
-        if constexpr (kQueue)
-            if (lane == 0) {
-                least[1] = taken + gridDim.x;
-                // (every workgroup asks until there is no tile left: n_tiles times in all)
-                if (taken + 1u == (uint32_t)a.n_tiles) atomicExch(a.next_tile, 0u);
-            }
-    };
     // The inclusive prefix over the groups' sums, 64 at a time (chunks of a wave's lanes, then the chunks before).  Where there are
     // more than four chunks the waves scan them side by side, with the same additions in the same order: a tile of few
     // tokens waits for little else.  One wave / all, sampling launch: 5e5 tokens, 20,000 words, K = 20,000 584 / 503 us, 3e6,
@@ -1131,16 +1116,12 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
                 }
             } else if (wave == 1) {
                 collect_least(beside);
-            } else if (wave == 2) {
-                ask_next();
-                tell_next();
             }
             __syncthreads();
             return;
         }
         // (in the records of a wave that are not in use yet, behind its least weight)
         double* totals = reinterpret_cast<double*>(wave_base + 3 * wave_bytes + 64);
-        if (wave == kWaves - 1) ask_next();
         for (int c = wave; c < n_chunks; c += kWaves) {
             const int g = c * kWave + lane;
             const double x = wave_inclusive_sum((g < ng) ? sums[g] : 0.0);
@@ -1155,7 +1136,6 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
             const int g = c * kWave + lane;
             if (g < ng) cp[g] = cp[g] + carry;
         }
-        if (wave == kWaves - 1) tell_next();
         __syncthreads();
     };
     Tile tl = a.tiles[ti];                 // the same for every lane: keep it in SGPRs
@@ -1807,9 +1787,21 @@ __global__ __launch_bounds__(kWaves * kWave) void sample_kernel(const SampleArgs
     }
     if constexpr (!kQueue) break;
     last_ti = ti;
+    // The next tile is asked for by the wave that has the fewest batches, when it is done with them.  (Asked for beside the groups'
+    // sums its time would not show, but a workgroup would hold it while it works on a long tile, and do long ones one after the
+    // other for which others are free.)  Sampling launch, us, a workgroup for every tile / asked for beside the sums / when done:
+    //   6.6e6 tokens in 300 documents, 139 words, K = 5,741       2,490 / 3,777 / 2,190     5,000 words   1,326 / 1,351 / 1,000
+    //   1.9e6 in 87, K = 3,000     669 / 810 / 670                9.9e7 in 3e5, 102,000 words, K = 10,000 10,362 / 8,977 / 8,900
+    //   3.8e6 in 15,000, 60,000 words, K = 9,000 1,108 / 849 / 828     2e6 in 8,009, K = 40,000 - / 455 / 449
+    if (wave == kWaves - 1 && lane == 0) {
+        const uint32_t taken = atomicAdd(a.next_tile, 1u);
+        least[1] = taken + gridDim.x;
+        // (every workgroup asks until there is no tile left: n_tiles times in all)
+        if (taken + 1u == (uint32_t)a.n_tiles) atomicExch(a.next_tile, 0u);
+    }
+    __syncthreads();                // (and every wave is done with this word's p*)
     ti = __builtin_amdgcn_readfirstlane((int)least[1]);
     if (ti >= a.n_tiles) break;
-    __syncthreads();                // every wave is done with this word's p*
     }
 }
 
