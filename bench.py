@@ -30,11 +30,11 @@ FETCH_SCALE, WRITE_SCALE = 2.000, 1.000
 MEASURED_TRAFFIC_KIB = {
     ("C4", "init"): (7.03824e7, 1.70104e6, "profiles/sample_kernel_C4.md"),
     ("C3", "init"): (1.22520e7, 2.27930e5, "profiles/sample_kernel_C3_C5.md"),
-    ("C5", "init"): (3.13090e7, 2.62790e5, "profiles/sample_kernel_C3_C5.md"),
+    ("C5", "init"): (3.01130e7, 2.64470e5, "profiles/sample_kernel_C3_C5.md"),
 }
 # VALU wave-instructions per sampling launch (SQ_INSTS_VALU, same summaries): the sampler's other
 # limit is instruction issue, 1024 SIMDs x 2.4 GHz / 4 cycles per wave-instruction
-MEASURED_VALU_INSTS = {("C4", "init"): 1.41592e10, ("C3", "init"): 3.09143e9, ("C5", "init"): 5.04370e9}
+MEASURED_VALU_INSTS = {("C4", "init"): 1.41592e10, ("C3", "init"): 3.09143e9, ("C5", "init"): 5.03510e9}
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0
 
 
